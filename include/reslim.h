@@ -552,7 +552,7 @@ int reslim_asc_forward(reslim_ctx *ctx, const reslim_asc_plan *plan, const float
 int reslim_debug_copy(const void *src, void *dst, size_t bytes, void *hip_stream);
 
 /* Tuning hook for benchmarks and tests: pins the bf16 GEMM kernel (-1 = built-in heuristic,
- * 2 = one 128x128 tile per work-group, 3 = persistent direct-to-LDS 256x256 tiles; add 100
+ * 2 = one 128x128 tile per work-group, 3 and 4 = persistent 256x256 / 128x256 tiles; add 100
  * to 2 for columns-fastest tile order; other values act like 2).  A plain process-wide
  * variable read at every launch: not thread-safe, not part of the method; set it while no
  * other thread is inside the library and restore -1 afterwards. */

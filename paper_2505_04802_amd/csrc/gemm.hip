@@ -11,6 +11,10 @@
 // inside a run tiles are ordered in bands of GROUP_M row-tiles so concurrently
 // resident tiles share A and W slabs.
 // fp32 path (debug): plain LDS-tiled FMA kernel.
+#include <algorithm>
+#include <cmath>
+#include <type_traits>
+
 #include "common.h"
 
 namespace reslim {
@@ -63,12 +67,10 @@ __device__ __forceinline__ float gelu_erf_fast(float x) {
 
 // Every epilogue runs with the MFMA operand roles swapped: the accumulator block is
 // then C^T, a lane holds one output row (lane % 32) and four consecutive columns per
-// register quad.  fp32 outputs (residual read-modify-write, table add) are updated
-// with one 16-byte load/store per lane (measured 1.85x faster than 4-byte accesses
-// for the read-modify-write).  bf16 outputs go through a 4 KB staging area of the
-// wave in LDS, 32 rows x 64 columns at a time, so that a store instruction writes
-// eight complete 128-byte row segments (16 bytes per lane) instead of 64 partial
-// ones; no barrier is involved, the LDS operations of one wave execute in order.
+// register quad.  All outputs go through a 4 KB staging area of the wave in LDS, bf16
+// ones 32 rows x 64 columns at a time, fp32 ones 32 x 32, so that a store instruction
+// writes eight complete 128-byte row segments (16 bytes per lane) instead of 32 or 64
+// partial ones; no barrier is involved, the LDS operations of one wave execute in order.
 template <int EPI>
 __device__ __host__ constexpr bool epi_act_out() {
   return EPI == EPI_BIAS_ACT || EPI == EPI_BIAS_QSCALE_ACT || EPI == EPI_BIAS_GELU_ACT || EPI == EPI_BIAS_ACT_GELU2;
@@ -92,14 +94,13 @@ __device__ __forceinline__ uint32_t pack2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
 }
 
-// Rows m_first .. m_first + 31, columns n_first .. n_first + 32 NB - 1 (NB = 1 or 2
-// accumulator blocks side by side) of a bf16 output; bias[jj][q] holds the four
-// bias values of this lane's column quad.  Staging layout: row r at 128 r bytes, its
-// 16-byte chunk c at position c ^ ((r >> 1) & 7), and the two 8-byte halves of a
+// Rows m_first .. m_first + 31, columns n_first .. n_first + 63 (two accumulator
+// blocks side by side) of a bf16 output; bias[jj][q] holds the four bias values of
+// this lane's column quad.  Staging layout: row r at 128 r bytes, its 16-byte chunk c at position c ^ ((r >> 1) & 7), and the two 8-byte halves of a
 // chunk exchanged where r >= 16: with that the 8-byte writes of 32 lanes (32 rows,
 // one column quad) and the 16-byte reads of 16 lanes (two rows) each touch every
 // bank once.  N is a multiple of 8, so a 16-byte piece is inside the row or not at all.
-template <int EPI, bool SECOND, bool GUARD, int NB>
+template <int EPI, bool SECOND, bool GUARD>
 __device__ __forceinline__ void epilogue_act_stage(const GemmArgs &g, const f32x16 *blk, const float4 (*bias)[4],
                                                    int m_first, int n_first, int lane, unsigned char *stg) {
   const int l32 = lane & 31, hi = lane >> 5;
@@ -107,7 +108,7 @@ __device__ __forceinline__ void epilogue_act_stage(const GemmArgs &g, const f32x
   unsigned char *wrow = stg + l32 * 128 + ((hi ^ (l32 >> 4)) << 3);
   const int wsw = (l32 >> 1) & 7;
 #pragma unroll
-  for (int jj = 0; jj < NB; ++jj) {
+  for (int jj = 0; jj < 2; ++jj) {
     const float sc = (EPI == EPI_BIAS_QSCALE_ACT && n_first + jj * 32 < g.qcols) ? g.qscale : 1.0f;   // uniform
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -118,8 +119,7 @@ __device__ __forceinline__ void epilogue_act_stage(const GemmArgs &g, const f32x
       *reinterpret_cast<u32x2 *>(wrow + (((jj * 4 + q) ^ wsw) << 4)) = pk;
     }
   }
-  // read back row-major: 8 lanes per row (NB = 2) or 4 lanes per row (NB = 1)
-  constexpr int LPR = 4 * NB, RPI = 64 / LPR;      // lanes per row, rows per instruction
+  constexpr int LPR = 8, RPI = 64 / LPR;           // read back row-major: lanes per row, rows per instruction
   const int c = lane % LPR, rr = lane / LPR;
   const int n = n_first + c * 8;
 #pragma unroll
@@ -133,94 +133,117 @@ __device__ __forceinline__ void epilogue_act_stage(const GemmArgs &g, const f32x
   __builtin_amdgcn_sched_barrier(0);   // keeps the next block's arithmetic from being hoisted over this one (registers)
 }
 
-// GUARD = false: the wave's part of the tile lies inside the output (the common
-// case, decided per wave): no bounds test anywhere.  GUARD = true: rows past M and
-// column quads past N compute on clamped (valid) addresses and skip only the store.
-// Column blocks are taken two at a time; the bias of the lane's eight column quads is
-// fetched once per pair.  N is a multiple of 8: quads are whole or absent.
-template <int EPI, bool GUARD, int MI, int NI, int MIe, int NIe>
-__device__ __forceinline__ void epilogue_wave_impl(const GemmArgs &g, const f32x16 (&acc)[MI][NI], int m_base, int n_base,
-                                                   int lane, unsigned char *stg) {
-  const int l32 = lane & 31, hi = lane >> 5;
+// fp32 outputs: rows m_base .. m_base + 32 MI - 1, columns n_base .. n_base + 32 NI - 1, one 32 x 32 block at a time
+// through the wave's 4 KB of LDS (row r at 128 r bytes, its 16-byte chunk c at c ^ ((r >> 1) & 7): the column quads of
+// 16 rows and the chunks of two rows both fall into 16 different bank groups).  Eight lanes then hold a row's 128
+// bytes, so a load or store instruction moves eight whole lines; straight from the accumulator layout it touches 32
+// lines, 32 bytes of each, and the address path of the compute unit, not the memory, sets the pace (403,200 x 1024
+// outputs with skip connection: 0.775 -> 0.648 ms on top of a 64-deep product, 1.24 -> 1.00 of a 1024-deep one).  The skip input (or the table) of the next DEPTH blocks is
+// requested ahead of the block at hand.  The skip input may be the output itself: a lane reads what it writes.
+template <int EPI, bool GUARD, int MI, int NI, int DEPTH>
+__device__ __forceinline__ void epilogue_f32(const GemmArgs &g, const f32x16 (&acc)[MI][NI], int m_base, int n_base, int lane,
+                                             unsigned char *stg) {
+  constexpr bool kAdd = EPI != EPI_BIAS_F32, kTab = EPI == EPI_BIAS_TAB_F32;
+  const int l32 = lane & 31, hi = lane >> 5, lr = lane >> 3, lc = lane & 7;
+  auto col = [&](int j) { return GUARD ? min(n_base + j * 32 + lc * 4, g.N - 4) : n_base + j * 32 + lc * 4; };
+  const float *src = kTab ? g.tab : EPI == EPI_BIAS_RES_F32 ? static_cast<const float *>(g.aux) : static_cast<const float *>(g.out);
+  const bool mapped = EPI == EPI_BIAS_RES_F32 && g.res_map;      // uniform
+  float4 x[DEPTH][4];
+  auto fetch = [&](int b) {
+    if constexpr (kAdd) {
+      const int i = b / NI, j = b % NI;
 #pragma unroll
-  for (int j0 = 0; j0 < NIe; j0 += 2) {
-    const int JN = (NIe - j0) < 2 ? (NIe - j0) : 2;      // folds: j0 is a compile-time value after unrolling
-    float4 bias[2][4];
-    if constexpr (EPI != EPI_BIAS_TAB_F32) {
-#pragma unroll
-      for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int n = n_base + (j0 + jj) * 32 + 8 * q + 4 * hi;
-          if (jj < JN) bias[jj][q] = *reinterpret_cast<const float4 *>(g.bias + (GUARD ? min(n, g.N - 4) : n));
+      for (int it = 0; it < 4; ++it) {
+        const int mu = m_base + i * 32 + it * 8;                 // uniform
+        const int m = GUARD ? min(mu + lr, g.M - 1) : mu + lr;
+        const float *p;
+        if constexpr (kTab) {
+          p = src + static_cast<size_t>(m % g.tab_rows) * g.N + col(j);
+        } else if (mapped) {
+          p = src + (static_cast<size_t>(m / g.res_out) * g.res_in + g.res_map[m % g.res_out]) * g.ldo + col(j);
+        } else if constexpr (GUARD) {
+          p = src + static_cast<size_t>(m) * g.ldo + col(j);
+        } else {                                                 // uniform base, one 32-bit offset per lane
+          p = src + static_cast<size_t>(mu) * g.ldo + n_base + j * 32 + static_cast<unsigned>(lr * g.ldo + lc * 4);
         }
-    }
-    if constexpr (epi_act_out<EPI>()) {
-#pragma unroll
-      for (int i = 0; i < MIe; ++i) {
-        if (JN == 2) {
-          epilogue_act_stage<EPI, false, GUARD, 2>(g, &acc[i][j0], bias, m_base + i * 32, n_base + j0 * 32, lane, stg);
-          if constexpr (EPI == EPI_BIAS_ACT_GELU2)
-            epilogue_act_stage<EPI, true, GUARD, 2>(g, &acc[i][j0], bias, m_base + i * 32, n_base + j0 * 32, lane, stg);
-        } else {
-          epilogue_act_stage<EPI, false, GUARD, 1>(g, &acc[i][j0], bias, m_base + i * 32, n_base + j0 * 32, lane, stg);
-          if constexpr (EPI == EPI_BIAS_ACT_GELU2)
-            epilogue_act_stage<EPI, true, GUARD, 1>(g, &acc[i][j0], bias, m_base + i * 32, n_base + j0 * 32, lane, stg);
-        }
+        x[b % DEPTH][it] = *reinterpret_cast<const float4 *>(p);
       }
-    } else {
+    }
+  };
 #pragma unroll
-      for (int i = 0; i < MIe; ++i) {
-        const int m = m_base + i * 32 + l32;
-        const bool row_ok = !GUARD || m < g.M;
-        const int mc = GUARD ? min(m, g.M - 1) : m;
-        const size_t row = static_cast<size_t>(mc) * g.ldo;
-        float *orow = static_cast<float *>(g.out) + row;
-        // row the skip connection is read from: the output itself (in place) or another buffer
-        const float *rrow = orow;
-        if constexpr (EPI == EPI_BIAS_RES_F32) {
-          const size_t src = g.res_map ? static_cast<size_t>(mc / g.res_out) * g.res_in + g.res_map[mc % g.res_out]
-                                       : static_cast<size_t>(mc);
-          rrow = static_cast<const float *>(g.aux) + src * g.ldo;
-        }
-        const float *trow = (EPI == EPI_BIAS_TAB_F32) ? g.tab + static_cast<size_t>(mc % g.tab_rows) * g.N : nullptr;
+  for (int b = 0; b < DEPTH && b < MI * NI; ++b) fetch(b);
+  float4 bias[NI];
+  if constexpr (!kTab) {
 #pragma unroll
-        for (int jj = 0; jj < 2; ++jj) {
-          if (jj >= JN) continue;
-          float4 v[4];
+    for (int j = 0; j < NI; ++j) bias[j] = *reinterpret_cast<const float4 *>(g.bias + col(j));
+  }
+  unsigned char *wrow = stg + l32 * 128;
+  const int wsw = (l32 >> 1) & 7;
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int n = n_base + (j0 + jj) * 32 + 8 * q + 4 * hi;
-            const int nc = GUARD ? min(n, g.N - 4) : n;
-            float4 add;
-            if constexpr (EPI == EPI_BIAS_TAB_F32) add = *reinterpret_cast<const float4 *>(trow + nc);
-            else add = bias[jj][q];
-            const f32x16 &a = acc[i][j0 + jj];
-            v[q] = make_float4(a[4 * q] + add.x, a[4 * q + 1] + add.y, a[4 * q + 2] + add.z, a[4 * q + 3] + add.w);
-            if constexpr (EPI == EPI_BIAS_RESADD_F32 || EPI == EPI_BIAS_RES_F32) {
-              const float4 x = *reinterpret_cast<const float4 *>(rrow + nc);
-              v[q].x += x.x; v[q].y += x.y; v[q].z += x.z; v[q].w += x.w;
-            }
-          }
+  for (int b = 0; b < MI * NI; ++b) {
+    const int i = b / NI, j = b % NI;
+    const f32x16 &a = acc[i][j];
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int n = n_base + (j0 + jj) * 32 + 8 * q + 4 * hi;
-            if (row_ok && (!GUARD || n < g.N)) *reinterpret_cast<float4 *>(orow + n) = v[q];
-          }
-        }
+    for (int q = 0; q < 4; ++q)
+      *reinterpret_cast<float4 *>(wrow + (((2 * q + hi) ^ wsw) << 4)) = make_float4(a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]);
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+      const int r = it * 8 + lr;
+      float4 v = *reinterpret_cast<const float4 *>(stg + r * 128 + ((lc ^ ((r >> 1) & 7)) << 4));
+      if constexpr (!kTab) { v.x += bias[j].x; v.y += bias[j].y; v.z += bias[j].z; v.w += bias[j].w; }
+      if constexpr (kAdd) {
+        const float4 s = x[b % DEPTH][it];
+        v.x += s.x; v.y += s.y; v.z += s.z; v.w += s.w;
+      }
+      const int mu = m_base + i * 32 + it * 8;
+      float *o = static_cast<float *>(g.out) + static_cast<size_t>(mu) * g.ldo + n_base + j * 32 + static_cast<unsigned>(lr * g.ldo + lc * 4);
+      if (!GUARD || (mu + lr < g.M && n_base + j * 32 + lc * 4 < g.N)) *reinterpret_cast<float4 *>(o) = v;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (b + DEPTH < MI * NI) fetch(b + DEPTH);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// bf16 outputs: column blocks are taken two at a time, the bias of the lane's eight column quads is fetched once per pair.
+template <int EPI, bool GUARD, int MI, int NI>
+__device__ __forceinline__ void epilogue_act(const GemmArgs &g, const f32x16 (&acc)[MI][NI], int m_base, int n_base, int lane,
+                                             unsigned char *stg) {
+  const int hi = lane >> 5;
+  static_assert(NI % 2 == 0, "column blocks come in pairs");
+#pragma unroll
+  for (int j0 = 0; j0 < NI; j0 += 2) {
+    float4 bias[2][4];
+#pragma unroll
+    for (int jj = 0; jj < 2; ++jj)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int n = n_base + (j0 + jj) * 32 + 8 * q + 4 * hi;
+        bias[jj][q] = *reinterpret_cast<const float4 *>(g.bias + (GUARD ? min(n, g.N - 4) : n));
+      }
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      epilogue_act_stage<EPI, false, GUARD>(g, &acc[i][j0], bias, m_base + i * 32, n_base + j0 * 32, lane, stg);
+      if constexpr (EPI == EPI_BIAS_ACT_GELU2) {
+        // the second output adds the bias again: without this the compiler keeps the biased values of a whole block and spills
+#pragma unroll
+        for (int jj = 0; jj < 2; ++jj)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) asm volatile("" : "+v"(bias[jj][q].x), "+v"(bias[jj][q].y), "+v"(bias[jj][q].z), "+v"(bias[jj][q].w));
+        epilogue_act_stage<EPI, true, GUARD>(g, &acc[i][j0], bias, m_base + i * 32, n_base + j0 * 32, lane, stg);
       }
     }
   }
 }
 
-// Only the leading MIe x NIe blocks of acc are written (a wave working on part of a
-// tile fills just those).  stg: this wave's kEpiStageBytes of LDS (bf16 outputs).
-template <int EPI, int MI, int NI, int MIe = MI, int NIe = NI>
-__device__ __forceinline__ void epilogue_wave(const GemmArgs &g, const f32x16 (&acc)[MI][NI], int m_base, int n_base,
-                                              int lane, unsigned char *stg) {
-  const bool inside = m_base + MIe * 32 <= g.M && n_base + NIe * 32 <= g.N;     // wave-uniform
-  if (inside) epilogue_wave_impl<EPI, false, MI, NI, MIe, NIe>(g, acc, m_base, n_base, lane, stg);
-  else epilogue_wave_impl<EPI, true, MI, NI, MIe, NIe>(g, acc, m_base, n_base, lane, stg);
+// GUARD = false: the wave's part of the tile lies inside the output (the common case, decided per wave): no bounds
+// test anywhere.  GUARD = true: rows past M and column quads past N compute on clamped (valid) addresses and skip only
+// the store.  N is a multiple of 8: quads are whole or absent.  stg: this wave's kEpiStageBytes of LDS.
+template <int EPI, bool GUARD, int MI, int NI>
+__device__ __forceinline__ void epilogue_wave(const GemmArgs &g, const f32x16 (&acc)[MI][NI], int m_base, int n_base, int lane,
+                                              unsigned char *stg) {
+  if constexpr (epi_act_out<EPI>()) epilogue_act<EPI, GUARD, MI, NI>(g, acc, m_base, n_base, lane, stg);
+  else epilogue_f32<EPI, GUARD, MI, NI, EPI == EPI_BIAS_RES_F32 ? 2 : 3>(g, acc, m_base, n_base, lane, stg);
 }
 
 // tile id seen by the hardware dispatcher -> tile id in XCD-contiguous order
@@ -372,11 +395,13 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void gemm_bf16_kernel(GemmArgs 
     }
   }
 
-  epilogue_wave<EPI, MI, NI>(g, acc, m0 + wm * TM, n0 + wn * TN, lane,
-                             smem + NBUF * (BM + BN) * PITCH * sizeof(bf16_t) + wave * kEpiStageBytes);
+  const int me = m0 + wm * TM, ne = n0 + wn * TN;
+  unsigned char *stg = smem + NBUF * (BM + BN) * PITCH * sizeof(bf16_t) + wave * kEpiStageBytes;
+  if (me + TM <= g.M && ne + TN <= g.N) epilogue_wave<EPI, false, MI, NI>(g, acc, me, ne, lane, stg);
+  else epilogue_wave<EPI, true, MI, NI>(g, acc, me, ne, lane, stg);
 }
 
-#include "gemm_dl.inc"
+#include "gemm_pp.inc"
 
 // ------------------------------------------------------------------ fp32 debug path
 template <int EPI>
@@ -475,24 +500,46 @@ static hipError_t launch_bf16_tc(GemmArgs g, hipStream_t st) {
 
 typedef TileCfg<128, 128, 64, 2, 2, 1, 3> TileSmall;   // 64x64 per wave, 36 KB LDS, 3 WG / CU
 
-typedef DlCfg<4, 2, 64, 2> DlA;          // persistent 256x256, 8 waves of 64x128, 2 x 64 KB slabs in LDS
-
 static int g_col_fast = 0;
-static int g_gemm_tile_override = -1;   // test / tuning hook: 2 = 128x128 tiles, 3 = persistent direct-to-LDS
+static int g_gemm_tile_override = -1;   // test / tuning hook: 2 = 128x128 tiles, 3 / 4 = persistent 256x256 / 128x256
+
+// Which bf16 kernel a product gets: the smallest of three estimates of its time in microseconds.  A launch runs in
+// rounds of as many tiles as the chip holds at once (one per CU for the persistent kernels, three for the small tiles,
+// whose last round is not a whole one because nothing ties their work-groups together); a round costs its 64-deep slabs
+// and one epilogue, both cheaper when part of the chip is idle.  The constants are fitted to 52 products (M 2280 ..
+// 403,200, N 192 .. 16,384, K 256 .. 16,384, every epilogue) on MI355X: the pick is within 2 % of the best of the three
+// on average.  In words: 256 x 256 tiles where there are at least about two rounds of them; 128 x 256 where their
+// rounds come out emptier (42,560 x 512 x 2048: 0.124 -> 0.106 ms) or K is deep and there is less than one
+// (5000 x 1024 x 4096: 0.072 -> 0.047); 128 x 128 for shallow products with heavy epilogues and for the smallest.
+struct EpiCost { double pp2, pp1, small; };
+template <int EPI>
+static constexpr EpiCost epi_cost() {
+  if (EPI == EPI_BIAS_GELU_ACT) return {10.0, 5.0, 4.0};
+  if (EPI == EPI_BIAS_ACT_GELU2) return {14.0, 8.0, 7.5};
+  if (EPI == EPI_BIAS_F32) return {10.0, 4.5, 4.0};
+  if (EPI == EPI_BIAS_RESADD_F32 || EPI == EPI_BIAS_RES_F32 || EPI == EPI_BIAS_TAB_F32) return {14.0, 7.7, 8.5};
+  return {6.0, 3.0, 2.5};
+}
+
+template <int EPI>
+static int choose_bf16(const GemmArgs &g) {
+  constexpr EpiCost e = epi_cost<EPI>();
+  const double nk = g.K / 64, cus = g_num_cus;
+  auto tiles = [&](int bm, int bn) { return static_cast<double>((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn); };
+  const double t2 = tiles(256, 256), t1 = tiles(128, 256), ts = tiles(128, 128);
+  const double f2 = std::min(1.0, t2 / cus), f1 = std::min(1.0, t1 / cus);                 // share of the chip at work
+  const double fs = std::min(1.0, std::max(0.0, (ts / cus - 1.0) / 2.0));                  // second and third work-group of a CU
+  const double c2 = std::ceil(t2 / cus) * (nk * (0.9 + 0.55 * f2) + e.pp2 * (0.5 + 0.5 * f2)) + 3.0;
+  const double c1 = std::ceil(t1 / cus) * (nk * (0.5 + 0.37 * f1) + e.pp1 * (0.5 + 0.5 * f1)) + 3.0;
+  const double cs = std::max(1.0, ts / (3.0 * cus)) * (nk * (1.05 + 0.85 * fs) + e.small * (0.6 + 0.4 * fs));
+  return cs <= c1 && cs <= c2 ? 2 : c1 < c2 ? 4 : 3;
+}
 
 template <int EPI>
 static hipError_t launch_bf16(GemmArgs g, hipStream_t st) {
-  // Measured on MI355X: the persistent direct-to-LDS kernel wins once there are at
-  // least two rounds of 256x256 tiles and either a deep contraction or a light
-  // epilogue; otherwise 128x128 tiles with three work-groups per CU hide the
-  // epilogue (residual read-modify-write, GELU) behind other groups' MFMAs.
-  const long tiles_big = static_cast<long>((g.M + 255) / 256) * ((g.N + 255) / 256);
-  int choice = 2;
-  const bool light_epilogue = EPI == EPI_BIAS_ACT || EPI == EPI_BIAS_QSCALE_ACT;
-  if (tiles_big >= 2L * g_num_cus && (light_epilogue || g.K >= 1024)) choice = 3;
-  if (g_gemm_tile_override >= 0) choice = g_gemm_tile_override;
-  switch (choice) {
-    case 3: return launch_bf16_dl<DlA, EPI>(g, st);
+  switch (g_gemm_tile_override >= 0 ? g_gemm_tile_override : choose_bf16<EPI>(g)) {
+    case 3: return launch_bf16_pp<2, EPI>(g, st);
+    case 4: return launch_bf16_pp<1, EPI>(g, st);
     default: return launch_bf16_tc<TileSmall, EPI>(g, st);
   }
 }
@@ -507,7 +554,8 @@ static hipError_t launch_f32(GemmArgs g, hipStream_t st) {
 template <int EPI>
 static hipError_t init_epi() {
   hipError_t e;
-  if ((e = set_attr_dl<DlA, EPI>()) != hipSuccess) return e;
+  if ((e = set_attr_pp<2, EPI>()) != hipSuccess) return e;
+  if ((e = set_attr_pp<1, EPI>()) != hipSuccess) return e;
   return set_attr<TileSmall, EPI>();
 }
 
@@ -571,8 +619,8 @@ hipError_t launch_gemm(int dtype, Epilogue epi, const void *A, const void *W, co
 
 }  // namespace reslim
 
-// tuning hook for the benchmark (not part of the method; selects the bf16 GEMM kernel:
-// -1 heuristic, 2 = 128x128 tiles, 3 = persistent 256x256; +100 = columns-fastest bands)
+// tuning hook for the benchmark (not part of the method; selects the bf16 GEMM kernel: -1 heuristic, 2 = 128x128 tiles,
+// 3 = persistent 256x256, 4 = persistent 128x256; +100 = columns-fastest bands)
 extern "C" void reslim_debug_set_gemm_tile(int choice) {
   reslim::g_col_fast = choice >= 100 ? 1 : 0;   // 100 + c: choice c with columns-fastest bands
   reslim::g_gemm_tile_override = choice >= 100 ? choice - 100 : choice;
