@@ -465,9 +465,9 @@ def reslim_asc_build(images: np.ndarray, patch: int, max_leaf: int, min_leaf: in
     images = np.ascontiguousarray(images, np.float32)
     B, H, W = images.shape
     cap = max(B * (H // max(patch, 1)) * (W // max(patch, 1)), 1)
-    ly, lx, ls = (np.zeros(cap, np.int32) for _ in range(3))
-    off = np.zeros(B + 1, np.int32)
-    pl = np.zeros(cap, np.int32)
+    ly, lx, ls = (np.empty(cap, np.int32) for _ in range(3))
+    off = np.empty(B + 1, np.int32)
+    pl = np.empty(cap, np.int32)
     n = C.c_int64(0)
     _check(load().reslim_asc_build(images.ctypes.data, B, H, W, patch, max_leaf, min_leaf, canny_low, canny_high, tau,
                                    ly.ctypes.data, lx.ctypes.data, ls.ctypes.data, off.ctypes.data, pl.ctypes.data,
@@ -489,9 +489,9 @@ def reslim_asc_build_tiles(images: np.ndarray, patch: int, tiles_y: int, tiles_x
     if Hp >= 1 and Wp >= 1 and tiles_y >= 1 and tiles_x >= 1:
         _check(load().tiles_partition(Hp, Wp, tiles_y, tiles_x, halo, (TileDesc * (tiles_y * tiles_x))(), None, None, C.byref(n_h)))
     cap = max(B * int(n_h.value), 1)
-    ly, lx, ls = (np.zeros(cap, np.int32) for _ in range(3))
-    off = np.zeros(B * max(tiles_y * tiles_x, 1) + 1, np.int32)
-    pl = np.zeros(max(B * Hp * Wp, 1), np.int32)
+    ly, lx, ls = (np.empty(cap, np.int32) for _ in range(3))
+    off = np.empty(B * max(tiles_y * tiles_x, 1) + 1, np.int32)
+    pl = np.empty(max(B * Hp * Wp, 1), np.int32)
     n = C.c_int64(0)
     _check(load().reslim_asc_build_tiles(images.ctypes.data, B, H, W, patch, tiles_y, tiles_x, halo, max_leaf, min_leaf,
                                          canny_low, canny_high, tau, ly.ctypes.data, lx.ctypes.data, ls.ctypes.data,

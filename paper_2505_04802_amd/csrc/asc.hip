@@ -3,6 +3,7 @@
 // one token per quad-tree leaf with attention inside each sample, decompression
 // folded into the final LayerNorm's row map, then the usual head and residual path.
 #include <algorithm>
+#include <cstring>
 #include <string>
 #include <vector>
 
@@ -76,18 +77,21 @@ __global__ __launch_bounds__(256) void asc_expand_kernel(const float *__restrict
 // Gradient of compression where tiles overlap: one wave per patch adds gradient / (side * side) of
 // every leaf that holds the patch (one per box whose haloed region contains it), in increasing
 // leaf order: a fixed order, deterministic.
-__global__ __launch_bounds__(256) void asc_cover_sum_kernel(const float *__restrict__ d_leaf_tok, const int32_t *__restrict__ cover_off,
-                                                            const int32_t *__restrict__ cover_leaf, const int32_t *__restrict__ leaf,
-                                                            float *__restrict__ dst, int64_t patches, int D) {
+__global__ __launch_bounds__(256) void asc_cover_sum_kernel(const float *__restrict__ d_leaf_tok, const int32_t *__restrict__ copy_off,
+                                                            const int32_t *__restrict__ copy_idx, const int32_t *__restrict__ owner,
+                                                            const int32_t *__restrict__ leaf, float *__restrict__ dst, int64_t patches,
+                                                            int N, int64_t n_h, int D) {
   const int lane = threadIdx.x & 63;
   const int64_t p = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
   if (p >= patches) return;
-  const int lo = cover_off[p], hi = cover_off[p + 1];
+  const int64_t b = p / N;
+  const int g = static_cast<int>(p % N), lo = copy_off[g], hi = copy_off[g + 1];
+  owner += b * n_h;                                    // leaves are numbered tile by tile: increasing copies, increasing leaves
   float4 *out = reinterpret_cast<float4 *>(dst + static_cast<size_t>(p) * D);
   for (int d = lane; d < D / 4; d += 64) {
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int k = lo; k < hi; ++k) {
-      const int l = cover_leaf[k], s = leaf[4 * static_cast<int64_t>(l) + 1];
+      const int l = owner[copy_idx[k]], s = leaf[4 * static_cast<int64_t>(l) + 1];
       const float f = 1.0f / static_cast<float>(s * s);
       const float4 v = reinterpret_cast<const float4 *>(d_leaf_tok + static_cast<size_t>(l) * D)[d];
       acc.x = fmaf(v.x, f, acc.x); acc.y = fmaf(v.y, f, acc.y); acc.z = fmaf(v.z, f, acc.z); acc.w = fmaf(v.w, f, acc.w);
@@ -149,15 +153,106 @@ __global__ __launch_bounds__(256) void asc_image_kernel(const float *__restrict_
   }
 }
 
-static void asc_free(reslim_asc_plan *pl) {
-  if (!pl) return;
-  if (pl->d_seq) (void)hipFree(pl->d_seq);
-  if (pl->d_seq_of_leaf) (void)hipFree(pl->d_seq_of_leaf);
-  if (pl->d_leaf) (void)hipFree(pl->d_leaf);
-  if (pl->d_patch_leaf) (void)hipFree(pl->d_patch_leaf);
-  if (pl->d_cover_off) (void)hipFree(pl->d_cover_off);
-  if (pl->d_cover_leaf) (void)hipFree(pl->d_cover_leaf);
-  delete pl;
+// ------------------------------------------------------------------ plan memory
+static void block_free(PlanBlock *b) {
+  if (!b) return;
+  (void)hipFree(b->dev);                               // waits for the device
+  (void)hipHostFree(b->host);
+  for (hipEvent_t e : b->ev)
+    if (e) (void)hipEventDestroy(e);
+  delete b;
+}
+
+void plan_pool_free(PlanPool &pool) {
+  for (PlanBlock *b : pool.idle) block_free(b);
+  pool.idle.clear();
+  if (pool.upload) (void)hipStreamDestroy(pool.upload);
+  pool.upload = nullptr;
+}
+
+void plan_used(const reslim_asc_plan *plan, hipStream_t st) {
+  reslim_asc_plan *pl = const_cast<reslim_asc_plan *>(plan);
+  PlanBlock *b = pl->block;
+  std::lock_guard<std::mutex> hold(pl->lock);
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    b->foreign = true;                                 // a graph may replay the reads at any later time
+    return;
+  }
+  int i = 0;
+  while (i < b->n_ev && b->stream[i] != st) ++i;
+  if (i == 4 || (!b->ev[i] && hipEventCreateWithFlags(&b->ev[i], hipEventDisableTiming) != hipSuccess) ||
+      hipEventRecord(b->ev[i], st) != hipSuccess) {
+    (void)hipGetLastError();
+    b->foreign = true;
+    return;
+  }
+  b->stream[i] = st;
+  b->n_ev = std::max(b->n_ev, i + 1);
+}
+
+// A block of at least `bytes`, idle on the device: a kept one, or a new one.  With kMost kept blocks that are all still
+// in use the oldest is waited for, so a host that runs ahead of the device cannot pile up memory.
+static hipError_t block_take(reslim_ctx *c, size_t bytes, PlanBlock **out) {
+  *out = nullptr;
+  PlanPool &pool = c->plans;
+  PlanBlock *b = nullptr;
+  {
+    std::lock_guard<std::mutex> hold(pool.lock);
+    if (!pool.upload) {
+      const hipError_t e = hipStreamCreateWithFlags(&pool.upload, hipStreamNonBlocking);
+      if (e != hipSuccess) return e;
+    }
+    for (size_t k = 0; k < pool.idle.size() && !b; ++k) {
+      bool done = true;
+      for (int i = 0; i < pool.idle[k]->n_ev && done; ++i) done = hipEventQuery(pool.idle[k]->ev[i]) == hipSuccess;
+      if (!done) (void)hipGetLastError();
+      if (done) {
+        b = pool.idle[k];
+        pool.idle.erase(pool.idle.begin() + k);
+      }
+    }
+    if (!b && pool.idle.size() == PlanPool::kMost) {
+      b = pool.idle.front();
+      pool.idle.erase(pool.idle.begin());
+    }
+  }
+  if (b)
+    for (int i = 0; i < b->n_ev; ++i)
+      if (hipEventSynchronize(b->ev[i]) != hipSuccess) b->foreign = true;
+  if (b && (b->cap < bytes || b->foreign)) {
+    block_free(b);
+    b = nullptr;
+  }
+  if (!b) {
+    b = new (std::nothrow) PlanBlock;
+    if (!b) return hipErrorOutOfMemory;
+    b->cap = (bytes + (bytes >> 2) + 65535) / 65536 * 65536;      // the next batch's tree may be somewhat larger
+    hipError_t e = hipMalloc(reinterpret_cast<void **>(&b->dev), b->cap);
+    if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void **>(&b->host), b->cap, hipHostMallocDefault);
+    if (e != hipSuccess) {
+      block_free(b);
+      return e;
+    }
+  }
+  b->n_ev = 0;
+  *out = b;
+  return hipSuccess;
+}
+
+static void block_give(reslim_ctx *c, PlanBlock *b) {
+  PlanBlock *drop = b;
+  if (!b->foreign) {
+    std::lock_guard<std::mutex> hold(c->plans.lock);
+    drop = nullptr;
+    if (c->plans.idle.size() == PlanPool::kMost) {
+      drop = c->plans.idle.front();
+      c->plans.idle.erase(c->plans.idle.begin());
+    }
+    c->plans.idle.push_back(b);
+  }
+  block_free(drop);
 }
 
 static int asc_check(reslim_ctx *c, const reslim_asc_plan *pl, const char *fn) {
@@ -190,9 +285,27 @@ extern "C" int reslim_asc_plan_create(reslim_ctx *c, int32_t batch, const int32_
   // aligned to the box, and patch_leaf must name, for every patch, its leaf in the tile that
   // owns it: the kernels trust the table.
   if (sample_off[0] != 0 || sample_off[n_seq] != n_leaves) return set_error(c, RESLIM_EINVAL, std::string(fn) + ": sample_off does not span the leaves");
-  std::vector<int32_t> leaf(static_cast<size_t>(n_leaves) * 4, 0), seq_of(static_cast<size_t>(n_leaves));
-  std::vector<tile_desc> seq(n_seq);
-  std::vector<int32_t> owner;                  // leaf of every box patch of the sequence at hand
+  // one block for all tables, filled in its pinned half and copied at once; the leaf of every tile-major token is needed
+  // for the check anyway and goes along where tiles overlap (with one tile it is patch_leaf itself)
+  const int64_t cells = batch * c->n_h;
+  size_t at = 0;
+  auto place = [&](size_t bytes) { const size_t o = at; at += align256(bytes); return o; };
+  const size_t o_seq = place(n_seq * sizeof(tile_desc)), o_seqof = place(n_leaves * 4), o_leaf = place(n_leaves * 16), o_patch = place(batch * N * 4);
+  const size_t o_owner = place(cells * 4), upload = T != 1 ? at : o_owner;
+  PlanBlock *blk = nullptr;
+  hipError_t e = block_take(c, at, &blk);
+  auto device_error = [&]() {
+    return set_error(c, e == hipErrorOutOfMemory ? RESLIM_ENOMEM : RESLIM_EHIP, std::string(fn) + ": " + hipGetErrorString(e));
+  };
+  if (e != hipSuccess) return device_error();
+  auto refuse = [&](const char *why) {
+    block_give(c, blk);
+    return set_error(c, RESLIM_EINVAL, std::string(fn) + ": " + why);
+  };
+  tile_desc *seq = reinterpret_cast<tile_desc *>(blk->host + o_seq);
+  int32_t *seq_of = reinterpret_cast<int32_t *>(blk->host + o_seqof), *leaf = reinterpret_cast<int32_t *>(blk->host + o_leaf);
+  int32_t *owner = reinterpret_cast<int32_t *>(blk->host + o_owner);
+  std::memset(owner, 0xff, cells * 4);
   int max_n = 0;
   double pairs = 0;
   for (int64_t q = 0; q < n_seq; ++q) {
@@ -200,70 +313,51 @@ extern "C" int reslim_asc_plan_create(reslim_ctx *c, int32_t batch, const int32_
     const tile_desc &td = c->tiles[q % T];
     const int hp = td.Y1 - td.Y0, wp = td.X1 - td.X0;
     const int64_t lo = sample_off[q], hi = sample_off[q + 1];
-    if (hi <= lo || hi > n_leaves) return set_error(c, RESLIM_EINVAL, std::string(fn) + ": sample_off not increasing");
-    owner.assign(static_cast<size_t>(hp) * wp, -1);
+    if (hi <= lo || hi > n_leaves) return refuse("sample_off not increasing");
+    int32_t *own = owner + b * c->n_h + td.tok_off;          // tokens of the box, row-major
+    int64_t area = 0;
     for (int64_t l = lo; l < hi; ++l) {
       const int y0 = leaf_y0[l], x0 = leaf_x0[l], s = leaf_s[l];
-      if (s < 1 || (s & (s - 1)) || y0 < td.Y0 || x0 < td.X0 || (y0 - td.Y0) % s || (x0 - td.X0) % s || y0 + s > td.Y1 || x0 + s > td.X1)
-        return set_error(c, RESLIM_EINVAL, std::string(fn) + ": leaf outside its box or not an aligned power-of-two square");
-      for (int yy = y0; yy < y0 + s; ++yy)
-        for (int xx = x0; xx < x0 + s; ++xx) {
-          int32_t &o = owner[static_cast<size_t>(yy - td.Y0) * wp + (xx - td.X0)];
-          if (o != -1) return set_error(c, RESLIM_EINVAL, std::string(fn) + ": two leaves of a sequence overlap");
-          o = static_cast<int32_t>(l);
-        }
+      if (s < 1 || (s & (s - 1)) || y0 < td.Y0 || x0 < td.X0 || ((y0 - td.Y0) & (s - 1)) || ((x0 - td.X0) & (s - 1)) || s > td.Y1 - y0 || s > td.X1 - x0)
+        return refuse("leaf outside its box or not an aligned power-of-two square");
+      int32_t *o = own + static_cast<int64_t>(y0 - td.Y0) * wp + (x0 - td.X0);
+      for (int yy = 0; yy < s; ++yy, o += wp)
+        for (int xx = 0; xx < s; ++xx) o[xx] = static_cast<int32_t>(l);
+      area += static_cast<int64_t>(s) * s;
       leaf[4 * l] = static_cast<int32_t>(b * N + static_cast<int64_t>(y0) * c->Wp + x0);
       leaf[4 * l + 1] = s;
+      leaf[4 * l + 2] = leaf[4 * l + 3] = 0;
       seq_of[l] = static_cast<int32_t>(q);
     }
-    for (int32_t o : owner)
-      if (o == -1) return set_error(c, RESLIM_EINVAL, std::string(fn) + ": leaves of a sequence do not cover its box");
+    // squares inside the box whose areas add up to the box's leave a cell free exactly where two of them overlap
+    int32_t least = 0;
+    for (int64_t k = 0, n = static_cast<int64_t>(hp) * wp; k < n; ++k) least = std::min(least, own[k]);
+    if (area != static_cast<int64_t>(hp) * wp || least < 0) return refuse("leaves of a sequence overlap or do not cover its box");
     for (int yy = td.y0; yy < td.y1; ++yy)
-      for (int xx = td.x0; xx < td.x1; ++xx)
-        if (patch_leaf[b * N + static_cast<int64_t>(yy) * c->Wp + xx] != owner[static_cast<size_t>(yy - td.Y0) * wp + (xx - td.X0)])
-          return set_error(c, RESLIM_EINVAL, std::string(fn) + ": patch_leaf disagrees with the leaf list");
+      if (std::memcmp(patch_leaf + b * N + static_cast<int64_t>(yy) * c->Wp + td.x0, own + static_cast<int64_t>(yy - td.Y0) * wp + (td.x0 - td.X0),
+                      static_cast<size_t>(td.x1 - td.x0) * 4))
+        return refuse("patch_leaf disagrees with the leaf list");
     seq[q] = tile_desc{};
     seq[q].tok_off = lo;
     seq[q].n_tok = static_cast<int32_t>(hi - lo);
     max_n = std::max(max_n, seq[q].n_tok);
     pairs += static_cast<double>(hi - lo) * static_cast<double>(hi - lo);
   }
-  // leaves of every patch (tiled contexts): counting pass, prefix sums, fill in increasing leaf order
-  std::vector<int32_t> cover_off, cover_leaf;
-  if (T != 1) {
-    cover_off.assign(static_cast<size_t>(batch) * N + 1, 0);
-    for (int64_t l = 0; l < n_leaves; ++l)
-      for (int dy = 0; dy < leaf[4 * l + 1]; ++dy)
-        for (int dx = 0; dx < leaf[4 * l + 1]; ++dx) ++cover_off[static_cast<size_t>(leaf[4 * l]) + static_cast<size_t>(dy) * c->Wp + dx + 1];
-    for (size_t i = 1; i < cover_off.size(); ++i) cover_off[i] += cover_off[i - 1];
-    cover_leaf.resize(static_cast<size_t>(cover_off.back()));
-    std::vector<int32_t> fill(cover_off.begin(), cover_off.end() - 1);
-    for (int64_t l = 0; l < n_leaves; ++l)
-      for (int dy = 0; dy < leaf[4 * l + 1]; ++dy)
-        for (int dx = 0; dx < leaf[4 * l + 1]; ++dx)
-          cover_leaf[static_cast<size_t>(fill[static_cast<size_t>(leaf[4 * l]) + static_cast<size_t>(dy) * c->Wp + dx]++)] = static_cast<int32_t>(l);
+  std::memcpy(blk->host + o_patch, patch_leaf, batch * N * 4);
+  e = hipMemcpyAsync(blk->dev, blk->host, upload, hipMemcpyHostToDevice, c->plans.upload);
+  if (e == hipSuccess) e = hipStreamSynchronize(c->plans.upload);      // the tables are there before any stream reads them
+  reslim_asc_plan *pl = e == hipSuccess ? new (std::nothrow) reslim_asc_plan : nullptr;
+  if (!pl) {
+    blk->foreign = true;
+    block_give(c, blk);
+    return e != hipSuccess ? device_error() : set_error(c, RESLIM_ENOMEM, std::string(fn) + ": host allocation failed");
   }
-  reslim_asc_plan *pl = new (std::nothrow) reslim_asc_plan;
-  if (!pl) return set_error(c, RESLIM_ENOMEM, std::string(fn) + ": host allocation failed");
-  pl->ctx = c; pl->batch = batch; pl->L = n_leaves; pl->seq = seq;
-  hipError_t e = hipMalloc(reinterpret_cast<void **>(&pl->d_seq), n_seq * sizeof(tile_desc));
-  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&pl->d_seq_of_leaf), n_leaves * 4);
-  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&pl->d_leaf), n_leaves * 16);
-  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&pl->d_patch_leaf), batch * N * 4);
-  if (e == hipSuccess) e = hipMemcpy(pl->d_seq, seq.data(), n_seq * sizeof(tile_desc), hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(pl->d_seq_of_leaf, seq_of.data(), n_leaves * 4, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(pl->d_leaf, leaf.data(), n_leaves * 16, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(pl->d_patch_leaf, patch_leaf, batch * N * 4, hipMemcpyHostToDevice);
-  if (e == hipSuccess && T != 1) {
-    e = hipMalloc(reinterpret_cast<void **>(&pl->d_cover_off), cover_off.size() * 4);
-    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&pl->d_cover_leaf), std::max<size_t>(cover_leaf.size() * 4, 256));
-    if (e == hipSuccess) e = hipMemcpy(pl->d_cover_off, cover_off.data(), cover_off.size() * 4, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(pl->d_cover_leaf, cover_leaf.data(), cover_leaf.size() * 4, hipMemcpyHostToDevice);
-  }
-  if (e != hipSuccess) {
-    asc_free(pl);
-    return set_error(c, e == hipErrorOutOfMemory ? RESLIM_ENOMEM : RESLIM_EHIP, std::string(fn) + ": " + hipGetErrorString(e));
-  }
+  pl->ctx = c; pl->batch = batch; pl->L = n_leaves; pl->block = blk;
+  pl->d_seq = reinterpret_cast<tile_desc *>(blk->dev + o_seq);
+  pl->d_seq_of_leaf = reinterpret_cast<int32_t *>(blk->dev + o_seqof);
+  pl->d_leaf = reinterpret_cast<int32_t *>(blk->dev + o_leaf);
+  pl->d_patch_leaf = reinterpret_cast<int32_t *>(blk->dev + o_patch);
+  pl->d_owner = T != 1 ? reinterpret_cast<int32_t *>(blk->dev + o_owner) : nullptr;
   pl->geom.d_tiles = pl->d_seq;
   pl->geom.d_tile_of_tok = pl->d_seq_of_leaf;
   pl->geom.T = static_cast<int>(n_seq);
@@ -275,7 +369,11 @@ extern "C" int reslim_asc_plan_create(reslim_ctx *c, int32_t batch, const int32_
   return RESLIM_OK;
 }
 
-extern "C" void reslim_asc_plan_destroy(reslim_asc_plan *plan) { asc_free(plan); }
+extern "C" void reslim_asc_plan_destroy(reslim_asc_plan *plan) {
+  if (!plan) return;
+  block_give(plan->ctx, plan->block);
+  delete plan;
+}
 
 extern "C" int reslim_asc_image(reslim_ctx *c, const float *tokens, const float *w_img, const float *b_img, float *image,
                                 int32_t batch, void *hip_stream) {
@@ -298,6 +396,7 @@ extern "C" int reslim_asc_compress(reslim_ctx *c, const reslim_asc_plan *plan, c
   if (rc != RESLIM_OK) return rc;
   if (!tokens || !tokens_c) return set_error(c, RESLIM_EINVAL, std::string(fn) + ": null buffer");
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
+  const PlanUse use{plan, st};
   asc_compress_kernel<true><<<dim3(static_cast<unsigned>(plan->L)), dim3(256), 0, st>>>(tokens, plan->d_leaf, tokens_c, c->Wp, c->cfg.embed_dim);
   RESLIM_TRY("asc_compress", hipGetLastError());
   return RESLIM_OK;
@@ -310,6 +409,7 @@ static int asc_move(reslim_ctx *c, const reslim_asc_plan *plan, const char *fn, 
   if (rc != RESLIM_OK) return rc;
   if (!src || !dst) return set_error(c, RESLIM_EINVAL, std::string(fn) + ": null buffer");
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
+  const PlanUse use{plan, st};
   const int D = c->cfg.embed_dim;
   const int64_t patches = static_cast<int64_t>(plan->batch) * c->N;
   const dim3 pg(static_cast<unsigned>((patches + 3) / 4));
@@ -319,7 +419,7 @@ static int asc_move(reslim_ctx *c, const reslim_asc_plan *plan, const char *fn, 
   const bool tiled = c->T != 1;
   if (mode == 0) asc_expand_kernel<false><<<pg, dim3(256), 0, st>>>(src, plan->d_patch_leaf, plan->d_leaf, dst, patches, D);
   else if (mode == 1 && !tiled) asc_expand_kernel<true><<<pg, dim3(256), 0, st>>>(src, plan->d_patch_leaf, plan->d_leaf, dst, patches, D);
-  else if (mode == 1) asc_cover_sum_kernel<<<pg, dim3(256), 0, st>>>(src, plan->d_cover_off, plan->d_cover_leaf, plan->d_leaf, dst, patches, D);
+  else if (mode == 1) asc_cover_sum_kernel<<<pg, dim3(256), 0, st>>>(src, c->d_copy_off, c->d_copy_idx, plan->d_owner, plan->d_leaf, dst, patches, c->N, c->n_h, D);
   else if (!tiled) asc_compress_kernel<false><<<dim3(static_cast<unsigned>(plan->L)), dim3(256), 0, st>>>(src, plan->d_leaf, dst, c->Wp, D);
   else asc_owned_sum_kernel<<<dim3(static_cast<unsigned>(plan->L)), dim3(256), 0, st>>>(src, plan->d_leaf, plan->d_patch_leaf, dst, c->Wp, D);
   RESLIM_TRY("launch", hipGetLastError());
@@ -353,6 +453,7 @@ extern "C" int reslim_asc_forward(reslim_ctx *c, const reslim_asc_plan *plan, co
   if (rc != RESLIM_OK) return rc;
   const Workspace w = plan_workspace(c, batch, workspace);
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
+  const PlanUse use{plan, st};
   const int D = c->cfg.embed_dim, dt = c->cfg.dtype;
   const int Mi = batch * c->N;
   const double es = static_cast<double>(act_size(c)), dMi = Mi, dD = D, dO = c->head_out, dL = static_cast<double>(plan->L);

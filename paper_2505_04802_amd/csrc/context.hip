@@ -100,6 +100,7 @@ extern "C" void reslim_destroy(reslim_ctx *ctx) {
   if (!ctx) return;
   for (void *p : ctx->allocs) (void)hipFree(p);
   for (hipEvent_t e : ctx->prof_ev) (void)hipEventDestroy(e);
+  plan_pool_free(ctx->plans);
   delete ctx;
 }
 
@@ -149,6 +150,15 @@ extern "C" int reslim_create(const reslim_config *cfg, const reslim_weights *w, 
     c->d_gather = static_cast<int32_t *>(up.raw(gather.data(), gather.size() * 4));
     c->d_interior_src = static_cast<int32_t *>(up.raw(isrc.data(), isrc.size() * 4));
     c->d_tile_of_tok = static_cast<int32_t *>(up.raw(tile_of.data(), tile_of.size() * 4));
+    {
+      std::vector<int32_t> off(static_cast<size_t>(c->N) + 1, 0), idx(c->n_h);
+      for (int64_t r = 0; r < c->n_h; ++r) ++off[gather[r] + 1];
+      for (int n = 0; n < c->N; ++n) off[n + 1] += off[n];
+      std::vector<int32_t> at(off.begin(), off.end() - 1);
+      for (int64_t r = 0; r < c->n_h; ++r) idx[at[gather[r]]++] = static_cast<int32_t>(r);
+      c->d_copy_off = static_cast<int32_t *>(up.raw(off.data(), off.size() * 4));
+      c->d_copy_idx = static_cast<int32_t *>(up.raw(idx.data(), idx.size() * 4));
+    }
 
     // ---- fold tokenisation into the aggregation (Sec. 4.1), in double
     // e_v = W_pe[v] x + base_v,  base_v = b_pe[v] + var_emb[v]

@@ -927,10 +927,10 @@ static int embed_bwd_impl(reslim_ctx *c, const char *fn, const float *x, const f
     const dim3 grid(static_cast<unsigned>((Mi + 3) / 4));
     if (dt == RESLIM_BF16)
       RESLIM_LAUNCH("gather_grad", 0, 4.0 * batch * static_cast<double>(c->n_h) * dD + (4.0 + es) * dMi * dD,
-                    (gather_transpose_kernel<bf16_t><<<grid, dim3(256), 0, st>>>(d_tokens, tm.copy_off, tm.copy_idx, w.dz, static_cast<bf16_t *>(w.dz_act), Mi, c->n_h, c->N, D), hipGetLastError()));
+                    (gather_transpose_kernel<bf16_t><<<grid, dim3(256), 0, st>>>(d_tokens, c->d_copy_off, c->d_copy_idx, w.dz, static_cast<bf16_t *>(w.dz_act), Mi, c->n_h, c->N, D), hipGetLastError()));
     else
       RESLIM_LAUNCH("gather_grad", 0, 4.0 * batch * static_cast<double>(c->n_h) * dD + 8.0 * dMi * dD,
-                    (gather_transpose_kernel<float><<<grid, dim3(256), 0, st>>>(d_tokens, tm.copy_off, tm.copy_idx, w.dz, static_cast<float *>(w.dz_act), Mi, c->n_h, c->N, D), hipGetLastError()));
+                    (gather_transpose_kernel<float><<<grid, dim3(256), 0, st>>>(d_tokens, c->d_copy_off, c->d_copy_idx, w.dz, static_cast<float *>(w.dz_act), Mi, c->n_h, c->N, D), hipGetLastError()));
   }
   // position rows (shared by the samples), aggregated values again, output map of the aggregation
   {
@@ -1125,24 +1125,6 @@ extern "C" int reslim_train_prepare_model(reslim_ctx *c, const reslim_weights *w
   };
   if (e == hipSuccess) e = transposed(c->d_w_head, c->head_out, D, &tm.wt_head);
   if (e == hipSuccess) e = transposed(c->d_agg_wo, D, D, &tm.wt_agg_wo);
-  // halo copies of every patch, in increasing tile-major index
-  if (e == hipSuccess) {
-    std::vector<int32_t> gather(c->n_h), off(static_cast<size_t>(c->N) + 1, 0), idx(c->n_h);
-    e = hipMemcpy(gather.data(), c->d_gather, gather.size() * 4, hipMemcpyDeviceToHost);
-    if (e == hipSuccess) {
-      for (int64_t r = 0; r < c->n_h; ++r) ++off[gather[r] + 1];
-      for (int n = 0; n < c->N; ++n) off[n + 1] += off[n];
-      std::vector<int32_t> fill(off.begin(), off.end() - 1);
-      for (int64_t r = 0; r < c->n_h; ++r) idx[fill[gather[r]]++] = static_cast<int32_t>(r);
-      void *d0 = nullptr, *d1 = nullptr;
-      e = hipMalloc(&d0, off.size() * 4);
-      if (e == hipSuccess) { c->allocs.push_back(d0); e = hipMalloc(&d1, std::max<size_t>(idx.size() * 4, 256)); }
-      if (e == hipSuccess) { c->allocs.push_back(d1); e = hipMemcpy(d0, off.data(), off.size() * 4, hipMemcpyHostToDevice); }
-      if (e == hipSuccess) e = hipMemcpy(d1, idx.data(), idx.size() * 4, hipMemcpyHostToDevice);
-      tm.copy_off = static_cast<int32_t *>(d0);
-      tm.copy_idx = static_cast<int32_t *>(d1);
-    }
-  }
   // the value table by (head, variable, pixel | offset) for the GEMM of the aggregation gradient
   if (e == hipSuccess) {
     const int rows = c->cfg.heads * V * (p2 + 1);

@@ -1,0 +1,59 @@
+"""Compression plans made and given back while the kernels that read the previous ones are still queued: the memory of
+a plan is kept for the next one, and a table must never be overwritten under a kernel."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2505_04802_amd import binding as B
+from paper_2505_04802_amd import workloads as WL
+
+pytestmark = pytest.mark.gpu
+CFG = WL.ReslimConfig("plans", batch=2, in_vars=3, out_vars=2, H=64, W=96, scale=4, patch=2, embed_dim=128, heads=2, mlp_ratio=2,
+                      depth=3, tiles_y=1, tiles_x=1, halo=0, dtype=1, seed=17)
+
+
+@pytest.mark.parametrize("tiled", [False, True], ids=["one_tile", "tiles"])
+def test_plans_in_flight(tiled):
+    cfg = CFG.with_(tiles_y=2, tiles_x=3, halo=2) if tiled else CFG
+    w = WL.make_weights(cfg)
+    fields = [WL.make_fields(cfg.with_(seed=s)) for s in range(3)]
+    trees = []
+    for f in fields:
+        for low in (20, 60):
+            img = np.ascontiguousarray(f[:, 0])
+            prm = (8, 1, low, 2 * low, 0.05)
+            trees.append(B.reslim_asc_build_tiles(img, 2, 2, 3, 2, *prm) if tiled else B.reslim_asc_build(img, 2, *prm))
+    xs = [torch.from_numpy(f).cuda() for f in fields]
+    shape = (cfg.batch, cfg.out_vars, cfg.H * cfg.scale, cfg.W * cfg.scale)
+    with B.Reslim(cfg, w) as m:
+        def one(i, y, ws, stream=None):
+            plan = B.reslim_asc_plan_create(m.ctx, cfg.batch, trees[i])
+            B.reslim_asc_forward(m.ctx, plan, xs[i // 2], y, ws, stream)
+            B.reslim_asc_plan_destroy(plan)
+        ref = []
+        for i in range(len(trees)):
+            y = torch.empty(shape, dtype=torch.float32, device="cuda")
+            one(i, y, m.ws)
+            torch.cuda.synchronize()
+            ref.append(y)
+        assert not torch.equal(ref[0], ref[1])
+        for round_ in range(4):
+            print(f"plans in flight: round {round_}", flush=True)
+            side = [torch.cuda.current_stream(), torch.cuda.Stream()]
+            side[1].wait_stream(side[0])
+            wss = [m.ws, torch.empty_like(m.ws)]
+            ys = [torch.full(shape, float("nan"), device="cuda") for _ in trees]
+            torch.cuda.synchronize()
+            for i in range(len(trees)):
+                one(i, ys[i], wss[i % 2], side[i % 2])
+            torch.cuda.synchronize()
+            assert all(torch.equal(a, b) for a, b in zip(ys, ref))
+        bad = dict(trees[0])
+        bad["patch_leaf"] = bad["patch_leaf"].copy()
+        bad["patch_leaf"].reshape(-1)[5] ^= 1
+        with pytest.raises(B.ReslimError):
+            B.reslim_asc_plan_create(m.ctx, cfg.batch, bad)
+        y = torch.empty(shape, dtype=torch.float32, device="cuda")
+        one(0, y, m.ws)
+        torch.cuda.synchronize()
+        assert torch.equal(y, ref[0])
