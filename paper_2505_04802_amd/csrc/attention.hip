@@ -528,63 +528,123 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
   }
 }
 
-// ------------------------------------------------------------------ fp32 debug path
-// One work-group per (sample, tile-major token, head): scores for all keys of the
-// tile in LDS, two block reductions, then one thread per feature accumulates P V.
-__global__ __launch_bounds__(128) void tiles_attention_f32_kernel(AttnArgs a, int dh, const int32_t *tile_of_tok) {
-  extern __shared__ float sm[];
-  float *sc = sm;              // [max_n_tok]
-  float *qv = sm + a.QB;       // [dh]   (QB carries max_n_tok here)
-  __shared__ float red[128];
-  const int64_t tok = blockIdx.x;
-  const int head = blockIdx.y, b = blockIdx.z;
-  const int tile = tile_of_tok[tok];
-  const int n_t = a.tiles[tile].n_tok;
-  const int64_t tok_off = a.tiles[tile].tok_off;
+// ------------------------------------------------------------------ fp32 path
+// 32 queries of one (sample, tile, head) per work-group, MFMA 32x32x2 in fp32 with operands straight from global memory.
+// The four waves take every fourth block of 32 keys, each with a softmax of its own (running maximum, sum and output);
+// the four are merged through LDS in wave order.  As in the bf16 kernel S^T = K Q^T is computed, so a lane owns a query
+// column, and the accumulator registers of S^T are the B operand of O^T = V^T P^T: register 4 q + j of lane half hi
+// holds key 8 q + 4 hi + j, so matrix step (q, j) multiplies keys 8 q + j and 8 q + 4 + j.  The tiny workload (128
+// tokens a tile, head dimension 32) takes 5 us; one work-group per query with a reduction over LDS took 20.
+// NB: 32-feature blocks of the output a work-group takes (wider heads: more work-groups, each with all the scores),
+// VEC4: the head's rows start on 16 bytes.
+template <int NB, bool VEC4>
+__global__ __launch_bounds__(256) void tiles_attention_f32_kernel(AttnArgs a, int dh) {
+  __shared__ float stat[4][2][32];
+  __shared__ float box[4][16][64];
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int l32 = lane & 31, hi = lane >> 5;
+  const int qb = blockIdx.x % a.QB, head = blockIdx.y, tile = (blockIdx.x / a.QB) % a.T, b = blockIdx.x / a.QB / a.T;
+  const int n_t = a.tiles[tile].n_tok, q0 = qb * 32;
+  if (q0 >= n_t) return;                                     // uniform
+  const int64_t row0 = static_cast<int64_t>(b) * a.n_h + a.tiles[tile].tok_off;
   const int ld = 3 * a.D;
-  const float *base = static_cast<const float *>(a.qkv) + (static_cast<size_t>(b) * a.n_h + tok_off) * ld + head * dh;
-  const float *qrow = static_cast<const float *>(a.qkv) + (static_cast<size_t>(b) * a.n_h + tok) * ld + head * dh;
-  const int t = threadIdx.x;
-  for (int d = t; d < dh; d += 128) qv[d] = qrow[d];
-  __syncthreads();
+  const float *base = static_cast<const float *>(a.qkv) + row0 * ld + head * dh;
+  auto quad = [&](const float *row, int k) {                 // row[k .. k + 3], zero past the head
+    if constexpr (VEC4) {
+      return k < dh ? *reinterpret_cast<const float4 *>(row + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+    } else {
+      return make_float4(k < dh ? row[k] : 0.f, k + 1 < dh ? row[k + 1] : 0.f, k + 2 < dh ? row[k + 2] : 0.f, k + 3 < dh ? row[k + 3] : 0.f);
+    }
+  };
   const float scale = rsqrtf(static_cast<float>(dh));
-  float mx = -INFINITY;
-  for (int j = t; j < n_t; j += 128) {
-    const float *kr = base + a.D + static_cast<size_t>(j) * ld;
-    float s = 0.f;
-    for (int d = 0; d < dh; ++d) s = fmaf(qv[d], kr[d], s);
-    s *= scale;
-    sc[j] = s;
-    mx = fmaxf(mx, s);
+  const int steps = (dh + 7) / 8, f0 = blockIdx.z * NB * 32;      // output features of this work-group
+  const float *qrow = base + static_cast<size_t>(min(q0 + l32, n_t - 1)) * ld;
+  f32x16 o[NB] = {};
+  float mx = -INFINITY, sum = 0.f;
+  for (int k0 = wave * 32; k0 < n_t; k0 += 128) {
+    const float *krow = base + a.D + static_cast<size_t>(min(k0 + l32, n_t - 1)) * ld;
+    f32x16 s = {};
+    for (int st = 0; st < steps; st += 4) {                  // of eight features, four at a time
+      float4 kv[4], qv[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        kv[i] = quad(krow, 8 * (st + i) + 4 * hi);
+        qv[i] = quad(qrow, 8 * (st + i) + 4 * hi);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        s = __builtin_amdgcn_mfma_f32_32x32x2f32(kv[i].x, qv[i].x, s, 0, 0, 0);
+        s = __builtin_amdgcn_mfma_f32_32x32x2f32(kv[i].y, qv[i].y, s, 0, 0, 0);
+        s = __builtin_amdgcn_mfma_f32_32x32x2f32(kv[i].z, qv[i].z, s, 0, 0, 0);
+        s = __builtin_amdgcn_mfma_f32_32x32x2f32(kv[i].w, qv[i].w, s, 0, 0, 0);
+      }
+    }
+    // the values are requested ahead of the softmax
+    float vv[NB][16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int key = min(k0 + 8 * (r / 4) + 4 * hi + r % 4, n_t - 1);      // past the tile: finite values times zero
+      const float *vrow = base + 2 * a.D + static_cast<size_t>(key) * ld;
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        const int f = f0 + nb * 32 + l32;
+        vv[nb][r] = f < dh ? vrow[f] : 0.f;
+      }
+    }
+    float top = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int key = k0 + 8 * (r / 4) + 4 * hi + r % 4;
+      s[r] = key < n_t ? s[r] * scale : -INFINITY;
+      top = fmaxf(top, s[r]);
+    }
+    top = fmaxf(mx, fmaxf(top, __shfl_xor(top, 32)));        // finite: the block holds a key
+    const float alpha = expf(mx - top);
+    mx = top;
+    float part = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      s[r] = expf(s[r] - mx);
+      part += s[r];
+    }
+    sum = fmaf(sum, alpha, part);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[nb][r] *= alpha;
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) o[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv[nb][r], s[r], o[nb], 0, 0, 0);
   }
-  red[t] = mx;
+  sum += __shfl_xor(sum, 32);                                // the two halves hold different keys of the same query
+  if (hi == 0) {
+    stat[wave][0][l32] = mx;
+    stat[wave][1][l32] = sum;
+  }
   __syncthreads();
-  for (int w = 64; w > 0; w >>= 1) {
-    if (t < w) red[t] = fmaxf(red[t], red[t + w]);
+  float m_all = stat[0][0][l32], total = 0.f;
+#pragma unroll
+  for (int w = 1; w < 4; ++w) m_all = fmaxf(m_all, stat[w][0][l32]);
+#pragma unroll
+  for (int w = 0; w < 4; ++w) total += stat[w][1][l32] * expf(stat[w][0][l32] - m_all);      // a wave without keys: 0 * exp(-inf)
+  const int qi = q0 + l32;
+  if (a.lse && f0 == 0 && wave == 0 && hi == 0 && qi < n_t)
+    a.lse[(static_cast<size_t>(b) * a.heads + head) * a.n_h + a.tiles[tile].tok_off + qi] = m_all + logf(total);
+  const float f_own = expf(mx - m_all) / total;
+  float *orow = static_cast<float *>(a.out) + (row0 + min(qi, n_t - 1)) * a.D + head * dh;
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
     __syncthreads();
-  }
-  mx = red[0];
-  __syncthreads();
-  float sum = 0.f;
-  for (int j = t; j < n_t; j += 128) {
-    const float p = expf(sc[j] - mx);
-    sc[j] = p;
-    sum += p;
-  }
-  red[t] = sum;
-  __syncthreads();
-  for (int w = 64; w > 0; w >>= 1) {
-    if (t < w) red[t] += red[t + w];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) box[wave][r][lane] = o[nb][r] * f_own;
     __syncthreads();
-  }
-  const float inv = 1.0f / red[0];
-  if (a.lse && t == 0) a.lse[(static_cast<size_t>(b) * a.heads + head) * a.n_h + tok] = mx + logf(red[0]);
-  float *orow = static_cast<float *>(a.out) + (static_cast<size_t>(b) * a.n_h + tok) * a.D + head * dh;
-  for (int d = t; d < dh; d += 128) {
-    const float *vc = base + 2 * a.D + d;
-    float acc = 0.f;
-    for (int j = 0; j < n_t; ++j) acc = fmaf(sc[j], vc[static_cast<size_t>(j) * ld], acc);
-    orow[d] = acc * inv;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {                            // wave w adds up registers 4 w .. 4 w + 3: features 8 w + 4 hi + j
+      const int r = 4 * wave + j, f = f0 + nb * 32 + 8 * wave + 4 * hi + j;
+      const float v = (box[0][r][lane] + box[1][r][lane]) + (box[2][r][lane] + box[3][r][lane]);
+      if (qi < n_t && f < dh) orow[f] = v;
+    }
   }
 }
 
@@ -670,12 +730,19 @@ hipError_t launch_tiles_attention(const reslim_ctx *c, const void *qkv, void *ou
     }
     return hipGetLastError();
   }
-  a.QB = sg.max_n_tok;
+  a.QB = (sg.max_n_tok + 31) / 32;
   a.total = 0;
-  const size_t lds = (static_cast<size_t>(sg.max_n_tok) + c->dh) * sizeof(float);
-  if (lds > 60 * 1024 || sg.n_h > INT32_MAX) return hipErrorInvalidValue;
-  tiles_attention_f32_kernel<<<dim3(static_cast<unsigned>(sg.n_h), a.heads, batch), dim3(128), lds, st>>>(
-      a, c->dh, sg.d_tile_of_tok);
+  const int64_t groups = static_cast<int64_t>(a.QB) * sg.T * batch;
+  if (groups > INT32_MAX || a.heads > 65535) return hipErrorInvalidValue;
+  const int nb = (c->dh + 31) / 32;
+  const dim3 grid(static_cast<unsigned>(groups), a.heads, (nb + 7) / 8), blk(256);
+  const bool vec = c->dh % 4 == 0 && a.D % 4 == 0 && (reinterpret_cast<uintptr_t>(qkv) & 15) == 0;
+#define RESLIM_ATTN32(NB) (vec ? tiles_attention_f32_kernel<NB, true><<<grid, blk, 0, st>>>(a, c->dh) : tiles_attention_f32_kernel<NB, false><<<grid, blk, 0, st>>>(a, c->dh))
+  if (nb <= 1) RESLIM_ATTN32(1);
+  else if (nb <= 2) RESLIM_ATTN32(2);
+  else if (nb <= 4) RESLIM_ATTN32(4);
+  else RESLIM_ATTN32(8);
+#undef RESLIM_ATTN32
   return hipGetLastError();
 }
 

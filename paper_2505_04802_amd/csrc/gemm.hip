@@ -10,7 +10,7 @@
 // renumbered so that each XCD (private L2) receives a contiguous run of tiles, and
 // inside a run tiles are ordered in bands of GROUP_M row-tiles so concurrently
 // resident tiles share A and W slabs.
-// fp32 path (debug): plain LDS-tiled FMA kernel.
+// fp32 path: MFMA 32x32x2 in fp32, operands straight from global memory.
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
@@ -403,7 +403,7 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void gemm_bf16_kernel(GemmArgs 
 
 #include "gemm_pp.inc"
 
-// ------------------------------------------------------------------ fp32 debug path
+// ------------------------------------------------------------------ fp32 path
 template <int EPI>
 __device__ __forceinline__ void epilogue_store_f32(const GemmArgs &g, int m, int n, float v) {
   const size_t o = static_cast<size_t>(m) * g.ldo + n;
@@ -426,46 +426,91 @@ __device__ __forceinline__ void epilogue_store_f32(const GemmArgs &g, int m, int
   }
 }
 
-template <int EPI>
+// v_mfma_f32_32x32x2_f32 (fp32 products and sums, twice the rate of the vector pipe), operands straight from global
+// memory: a lane holds row l % 32 and four consecutive k of a step of eight, so step s covers k = 8 s + 4 (l / 32) +
+// 0..3 and its matrix instruction j multiplies the j-th of them, the same k on both sides.  These products are small
+// and wait for memory, not for arithmetic: KS = 4 gives the four waves of a work-group the same 32 x 32 outputs and a
+// quarter of the k steps each (their sums meet in LDS, added in wave order), KS = 1 gives every wave 32 x 32 outputs
+// of its own once there are enough of them.  Steps are fetched AHEAD of their use.  The tiny workload's products
+// (512 x 128 x 512 the longest) take 4-5 us each; the LDS-tiled vector kernel before took 22 to 70.
+// VEC4: every row starts on 16 bytes.
+template <int EPI, int KS, bool VEC4>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
-  constexpr int BM = 64, BN = 64, BK = 16;
-  __shared__ float As[BK][BM + 4];
-  __shared__ float Bs[BK][BN + 4];
-  const float *A = static_cast<const float *>(g.A);
-  const float *W = static_cast<const float *>(g.W);
-  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-  const int t = threadIdx.x, tx = t % 16, ty = t / 16;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < g.K; k0 += BK) {
-    for (int c = t; c < BM * BK; c += 256) {
-      const int row = c / BK, k = c % BK;
-      const int gm = m0 + row, gk = k0 + k;
-      As[k][row] = (gm < g.M && gk < g.K) ? A[static_cast<size_t>(gm) * g.K + gk] : 0.f;
-      const int gn = n0 + row;
-      Bs[k][row] = (gn < g.N && gk < g.K) ? W[static_cast<size_t>(gn) * g.K + gk] : 0.f;
+  constexpr int AHEAD = 4;
+  __shared__ float part[KS == 4 ? 3 * 16 * 64 : 1];
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int l32 = lane & 31, hi = lane >> 5;
+  const int m0 = KS == 4 ? blockIdx.x * 32 : blockIdx.x * 64 + (wave >> 1) * 32;
+  const int n0 = KS == 4 ? blockIdx.y * 32 : blockIdx.y * 64 + (wave & 1) * 32;
+  const float *a = static_cast<const float *>(g.A) + static_cast<size_t>(min(m0 + l32, g.M - 1)) * g.K;
+  const float *w = static_cast<const float *>(g.W) + static_cast<size_t>(min(n0 + l32, g.N - 1)) * g.K;
+  const int steps = (g.K + 7) / 8, per = KS == 4 ? (steps + 3) / 4 : steps;
+  const int s0 = KS == 4 ? wave * per : 0, s1 = min(steps, s0 + per);
+  auto fetch = [&](const float *p, int s) {
+    const int k = 8 * s + 4 * hi;
+    if constexpr (VEC4) {
+      return k < g.K && s < s1 ? *reinterpret_cast<const float4 *>(p + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+    } else {
+      const bool in = s < s1;
+      return make_float4(in && k < g.K ? p[k] : 0.f, in && k + 1 < g.K ? p[k + 1] : 0.f, in && k + 2 < g.K ? p[k + 2] : 0.f,
+                         in && k + 3 < g.K ? p[k + 3] : 0.f);
     }
-    __syncthreads();
+  };
+  f32x16 acc = {};
+  float4 ra[AHEAD], rw[AHEAD];
 #pragma unroll
-    for (int k = 0; k < BK; ++k) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[k][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[k][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
+  for (int i = 0; i < AHEAD; ++i) {
+    ra[i] = fetch(a, s0 + i);
+    rw[i] = fetch(w, s0 + i);
   }
+  for (int s = s0; s < s1; s += AHEAD) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < AHEAD; ++i) {          // steps past s1 multiply zeros
+      const float4 x = ra[i], y = rw[i];
+      ra[i] = fetch(a, s + AHEAD + i);
+      rw[i] = fetch(w, s + AHEAD + i);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(y.x, x.x, acc, 0, 0, 0);      // operands swapped: the block is C^T
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(y.y, x.y, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(y.z, x.z, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(y.w, x.w, acc, 0, 0, 0);
+    }
+  }
+  const int m = m0 + l32;
+  auto store = [&](int q, const float (&v)[4]) {      // registers 4 q .. 4 q + 3: columns 8 q + 4 hi + 0..3 of row l % 32
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
-      if (m < g.M && n < g.N) epilogue_store_f32<EPI>(g, m, n, acc[i][j]);
+      const int n = n0 + 8 * q + 4 * hi + j;
+      if (m < g.M && n < g.N) epilogue_store_f32<EPI>(g, m, n, v[j]);
     }
+  };
+  if constexpr (KS == 1) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float v[4] = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+      store(q, v);
+    }
+  } else {
+    // every wave finishes one column quad: the others' sums of it come through LDS, wave w's part of quad q at ((w - (w > q)) * 4 + j)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (q != wave)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) part[(((wave - (wave > q ? 1 : 0)) * 4 + q) * 4 + j) * 64 + lane] = acc[4 * q + j];
+    __syncthreads();
+    float v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      float own = 0.f;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (q == wave) own = acc[4 * q + j];
+      float s = 0.f;
+#pragma unroll
+      for (int o = 0; o < 4; ++o) s += o == wave ? own : part[(((o - (o > wave ? 1 : 0)) * 4 + wave) * 4 + j) * 64 + lane];
+      v[j] = s;
+    }
+    store(wave, v);
+  }
 }
 
 // ------------------------------------------------------------------ launchers
@@ -546,8 +591,17 @@ static hipError_t launch_bf16(GemmArgs g, hipStream_t st) {
 
 template <int EPI>
 static hipError_t launch_f32(GemmArgs g, hipStream_t st) {
-  dim3 grid((g.N + 63) / 64, (g.M + 63) / 64);
-  gemm_f32_kernel<EPI><<<grid, dim3(256), 0, st>>>(g);
+  // four waves to a 32 x 32 tile while that is what it takes to give every CU two work-groups' worth of waves
+  const int64_t tiles = static_cast<int64_t>((g.M + 31) / 32) * ((g.N + 31) / 32);
+  const bool split = tiles < 8LL * g_num_cus;
+  const bool vec = g.K % 4 == 0 && ((reinterpret_cast<uintptr_t>(g.A) | reinterpret_cast<uintptr_t>(g.W)) & 15) == 0;
+  const int e = split ? 32 : 64;
+  const dim3 grid((g.M + e - 1) / e, (g.N + e - 1) / e);
+  if (grid.y > 65535) return hipErrorInvalidValue;
+  if (split && vec) gemm_f32_kernel<EPI, 4, true><<<grid, dim3(256), 0, st>>>(g);
+  else if (split) gemm_f32_kernel<EPI, 4, false><<<grid, dim3(256), 0, st>>>(g);
+  else if (vec) gemm_f32_kernel<EPI, 1, true><<<grid, dim3(256), 0, st>>>(g);
+  else gemm_f32_kernel<EPI, 1, false><<<grid, dim3(256), 0, st>>>(g);
   return hipGetLastError();
 }
 
