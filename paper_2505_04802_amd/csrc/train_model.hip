@@ -480,11 +480,6 @@ __global__ __launch_bounds__(256) void batch_sum_kernel(const float *__restrict_
   out[i] = s;
 }
 
-__global__ __launch_bounds__(256) void fill_kernel(float *p, int64_t n, float v) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (i < n) p[i] = v;
-}
-
 // Folded tokenisation + aggregation, backwards, first half: per token and head the softmax over
 // the variables a[g, v] (recomputed as in the forward) and the gradient of its logits
 //   d_s[g, v] = a[g, v] (d_a[g, v] - sum_v' a[g, v'] d_a[g, v']),  d_a[g, v] = sum_{d in head g} d_o[d] val[v, d],
@@ -498,7 +493,9 @@ struct AggBwdArgs {
   const float *x, *A, *a0, *U, *c;
   const void *d_o;            // act [BN, D]
   const float *E;             // [BN, ne] rows (g, v, j), j <= p2
-  float *a_out, *ds_out;      // [BN, heads, V]
+  float *a_out;               // [BN, heads, V] softmax weights
+  float *x_out;               // [BN, V (p2 + 1)] pixels of a token by variable, each variable's followed by a one
+  float *partial;             // [gridDim.x, V, p2 + 1, heads] sums over a work-group's tokens of d_s times those
   int V, H, W, p, Wp, N, D, heads, dh, ne;
   int64_t BN;
 };
@@ -518,214 +515,346 @@ __global__ __launch_bounds__(256) void agg_value_table_kernel(const float *__res
   Act<T>::store(Wt + i, val);
 }
 
-template <int TP>
+// A work-group takes groups of TP tokens in turn.  The gradients of the folded score tables, dA[v, g, i] = sum over the
+// tokens of d_s[g, v] pixels_v[i] and da0[v, g] = sum of d_s[g, v], are formed right here, where both factors lie in LDS:
+// thread = (variable, head), added to the work-group's own partial row (written by its first group).
+template <int TP, int p2>
 __global__ __launch_bounds__(256) void agg_scores_bwd_kernel(AggBwdArgs e) {
   extern __shared__ __align__(16) float smg[];
-  const int p2 = e.p * e.p, VP2 = e.V * p2, HV = e.heads * e.V;
+  constexpr int P3 = p2 + 1;
+  const int VP2 = e.V * p2, HV = e.heads * e.V, VP3 = e.V * P3;
   float *pix = smg;                        // [TP][V*p2]
-  float *sc = pix + TP * VP2;              // [TP][heads][V] softmax weights
-  float *da = sc + TP * HV;                // [TP][heads][V]
+  float *sc = pix + TP * VP2;              // [TP][heads][V] logits, then softmax weights
+  float *da = sc + TP * HV;                // [TP][heads][V] gradients of the weights, then of the logits
   const int t = threadIdx.x;
-  const int64_t bn0 = static_cast<int64_t>(blockIdx.x) * TP;
-  for (int idx = t; idx < TP * VP2; idx += 256) {
-    const int pi = idx / VP2, rem = idx % VP2, v = rem / p2, i = rem % p2;
-    const int64_t bn = bn0 + pi;
-    float val = 0.f;
-    if (bn < e.BN) {
-      const int64_t b = bn / e.N;
-      const int n = static_cast<int>(bn % e.N);
-      const int py = n / e.Wp, px = n % e.Wp;
-      val = e.x[((b * e.V + v) * e.H + py * e.p + i / e.p) * e.W + px * e.p + i % e.p];
+  float *part = e.partial + static_cast<size_t>(blockIdx.x) * VP3 * e.heads;
+  const int64_t groups = (e.BN + TP - 1) / TP;
+  for (int64_t grp = blockIdx.x; grp < groups; grp += gridDim.x) {
+    const int64_t bn0 = grp * TP;
+    __syncthreads();                       // the previous group's values are no longer read
+    for (int idx = t; idx < TP * VP2; idx += 256) {
+      const int pi = idx / VP2, rem = idx % VP2, v = rem / p2, i = rem % p2;
+      const int64_t bn = bn0 + pi;
+      float val = 0.f;
+      if (bn < e.BN) {
+        const int64_t b = bn / e.N;
+        const int n = static_cast<int>(bn % e.N);
+        const int py = n / e.Wp, px = n % e.Wp;
+        val = e.x[((b * e.V + v) * e.H + py * e.p + i / e.p) * e.W + px * e.p + i % e.p];
+      }
+      pix[idx] = val;
     }
-    pix[idx] = val;
-  }
-  __syncthreads();
-  for (int idx = t; idx < TP * e.heads; idx += 256) {
-    const int pi = idx / e.heads, g = idx % e.heads;
-    float *r = sc + static_cast<size_t>(idx) * e.V;
-    float mx = -INFINITY;
-    for (int v = 0; v < e.V; ++v) {
+    __syncthreads();
+    for (int idx = t; idx < TP * VP3; idx += 256) {
+      const int pi = idx / VP3, rem = idx % VP3, v = rem / P3, i = rem % P3;
+      if (bn0 + pi < e.BN) e.x_out[bn0 * VP3 + idx] = i < p2 ? pix[pi * VP2 + v * p2 + i] : 1.0f;
+    }
+    // logits, and d_a from E: consecutive threads read consecutive (p2 + 1)-float groups of a row of E
+    for (int idx = t; idx < TP * HV; idx += 256) {
+      const int pi = idx / HV, gv = idx % HV, g = gv / e.V, v = gv % e.V;
+      const int64_t bn = bn0 + pi;
       const float *Ar = e.A + (static_cast<size_t>(v) * e.heads + g) * p2;
       const float *px = pix + pi * VP2 + v * p2;
-      float s = e.a0[v * e.heads + g];
+      float s = e.a0[v * e.heads + g], dv = 0.f;
+#pragma unroll
       for (int i = 0; i < p2; ++i) s = fmaf(Ar[i], px[i], s);
-      r[v] = s;
-      mx = fmaxf(mx, s);
-    }
-    float sum = 0.f;
-    for (int v = 0; v < e.V; ++v) {
-      const float ex = __expf(r[v] - mx);
-      r[v] = ex;
-      sum += ex;
-    }
-    const float inv = 1.0f / sum;
-    for (int v = 0; v < e.V; ++v) r[v] *= inv;
-  }
-  // d_a[token, head, variable]: consecutive threads read consecutive (p2 + 1)-float groups of a row of E
-  for (int idx = t; idx < TP * HV; idx += 256) {
-    const int pi = idx / HV, gv = idx % HV, v = gv % e.V;
-    const int64_t bn = bn0 + pi;
-    float s = 0.f;
-    if (bn < e.BN) {
-      const float *er = e.E + bn * e.ne + static_cast<size_t>(gv) * (p2 + 1);
-      const float *px = pix + pi * VP2 + v * p2;
-      s = er[p2];
-      for (int i = 0; i < p2; ++i) s = fmaf(px[i], er[i], s);
-    }
-    da[idx] = s;
-  }
-  __syncthreads();
-  for (int idx = t; idx < TP * e.heads; idx += 256) {
-    const int pi = idx / e.heads;
-    const int64_t bn = bn0 + pi;
-    if (bn >= e.BN) continue;
-    const float *ar = sc + static_cast<size_t>(idx) * e.V, *dr = da + static_cast<size_t>(idx) * e.V;
-    float dot = 0.f;
-    for (int v = 0; v < e.V; ++v) dot = fmaf(ar[v], dr[v], dot);
-    const int g = idx % e.heads;
-    for (int v = 0; v < e.V; ++v) {
-      const size_t o = (static_cast<size_t>(bn) * e.heads + g) * e.V + v;
-      e.a_out[o] = ar[v];
-      e.ds_out[o] = ar[v] * (dr[v] - dot);
-    }
-  }
-}
-
-// Second half: gradients of the folded value tables.  Grid (token slab, block of 256 features,
-// chunk of VC variables); thread = one feature d, accumulators dU[v, d, 0..p2) and dc[v, d] for the
-// chunk's variables in registers; tokens of the slab in increasing order.  P2 = p * p.
-template <typename T, int P2, int VC>
-__global__ __launch_bounds__(256) void agg_values_bwd_kernel(AggBwdArgs e, float *__restrict__ partial, int tokens_per_slab) {
-  const int d = blockIdx.y * 256 + threadIdx.x;
-  const int v0 = blockIdx.z * VC;
-  const int64_t t0 = static_cast<int64_t>(blockIdx.x) * tokens_per_slab;
-  const int64_t t1 = min(t0 + tokens_per_slab, e.BN);
-  float acc[VC][P2 + 1];
+      if (bn < e.BN) {
+        const float *er = e.E + bn * e.ne + static_cast<size_t>(gv) * P3;
+        dv = er[p2];
 #pragma unroll
-  for (int v = 0; v < VC; ++v)
-#pragma unroll
-    for (int i = 0; i <= P2; ++i) acc[v][i] = 0.f;
-  const T *dop = static_cast<const T *>(e.d_o);
-  const int dc = min(d, e.D - 1), g = dc / e.dh;
-  for (int64_t bn = t0; bn < t1; ++bn) {
-    const float go = Act<T>::load(dop + bn * e.D + dc);
-    const int64_t b = bn / e.N;
-    const int n = static_cast<int>(bn % e.N);
-    const int py = n / e.Wp, px = n % e.Wp;
-    const float *ar = e.a_out + (static_cast<size_t>(bn) * e.heads + g) * e.V;
-#pragma unroll
-    for (int v = 0; v < VC; ++v) {
-      const int vv = min(v0 + v, e.V - 1);
-      const float w = ar[vv] * go;
-      const float *xp = e.x + ((b * e.V + vv) * e.H + py * e.p) * e.W + px * e.p;
-#pragma unroll
-      for (int i = 0; i < P2; ++i) acc[v][i] = fmaf(w, xp[(i / e.p) * e.W + i % e.p], acc[v][i]);
-      acc[v][P2] += w;
+        for (int i = 0; i < p2; ++i) dv = fmaf(px[i], er[i], dv);
+      }
+      sc[idx] = s;
+      da[idx] = dv;
     }
-  }
-  if (d >= e.D) return;
-  // partial row layout: [V][D][P2 + 1]
-  float *out = partial + static_cast<size_t>(blockIdx.x) * e.V * e.D * (P2 + 1);
-#pragma unroll
-  for (int v = 0; v < VC; ++v)
-    if (v0 + v < e.V)
-#pragma unroll
-      for (int i = 0; i <= P2; ++i) out[(static_cast<size_t>(v0 + v) * e.D + d) * (P2 + 1) + i] = acc[v][i];
-}
-
-// ... and of the folded score tables: thread = (variable, head), accumulators dA[v, g, 0..p2), da0[v, g]
-__global__ __launch_bounds__(256) void agg_logits_bwd_kernel(AggBwdArgs e, float *__restrict__ partial, int tokens_per_slab) {
-  const int p2 = e.p * e.p, HV = e.heads * e.V;
-  const int64_t t0 = static_cast<int64_t>(blockIdx.x) * tokens_per_slab;
-  const int64_t t1 = min(t0 + tokens_per_slab, e.BN);
-  for (int item = threadIdx.x; item < HV; item += 256) {
-    const int v = item / e.heads, g = item % e.heads;
-    float acc[17];
-    for (int i = 0; i <= p2; ++i) acc[i] = 0.f;
-    for (int64_t bn = t0; bn < t1; ++bn) {
-      const float ds = e.ds_out[(static_cast<size_t>(bn) * e.heads + g) * e.V + v];
-      const int64_t b = bn / e.N;
-      const int n = static_cast<int>(bn % e.N);
-      const int py = n / e.Wp, px = n % e.Wp;
-      const float *xp = e.x + ((b * e.V + v) * e.H + py * e.p) * e.W + px * e.p;
-      for (int i = 0; i < p2; ++i) acc[i] = fmaf(ds, xp[(i / e.p) * e.W + i % e.p], acc[i]);
-      acc[p2] += ds;
-    }
-    float *out = partial + (static_cast<size_t>(blockIdx.x) * HV + item) * (p2 + 1);
-    for (int i = 0; i <= p2; ++i) out[i] = acc[i];
-  }
-}
-
-// Small dense products of the chain rule through the fold (fp32, one thread per output element):
-// C[m scm + n scn] (+)= alpha * sum_k A[m sam + k sak] B[k sbk + n sbn]
-__global__ __launch_bounds__(256) void smm_kernel(const float *__restrict__ A, int64_t sam, int64_t sak, const float *__restrict__ B,
-                                                  int64_t sbk, int64_t sbn, float *__restrict__ C, int64_t scm, int64_t scn, int M,
-                                                  int N, int K, float alpha, int accumulate) {
-  const int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (e >= static_cast<int64_t>(M) * N) return;
-  const int m = static_cast<int>(e % M), n = static_cast<int>(e / M);      // m fastest: coalesced when sam == 1
-  float s = 0.f;
-  for (int k = 0; k < K; ++k) s = fmaf(A[m * sam + k * sak], B[k * sbk + n * sbn], s);
-  float *c = C + m * scm + n * scn;
-  *c = accumulate ? *c + alpha * s : alpha * s;
-}
-
-static hipError_t smm(const float *A, int64_t sam, int64_t sak, const float *B, int64_t sbk, int64_t sbn, float *C, int64_t scm,
-                      int64_t scn, int M, int N, int K, float alpha, bool accumulate, hipStream_t st) {
-  const int64_t n = static_cast<int64_t>(M) * N;
-  smm_kernel<<<dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, st>>>(A, sam, sak, B, sbk, sbn, C, scm, scn, M, N, K,
-                                                                                  alpha, accumulate ? 1 : 0);
-  return hipGetLastError();
-}
-
-// out[i] = a[i] + b[i]
-__global__ __launch_bounds__(256) void add2_kernel(const float *a, const float *b, float *out, int64_t n) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (i < n) out[i] = a[i] + b[i];
-}
-// the key and query ends of the fold: d_wk[d, j] = kappa q[d] d_r[head(d), j];  d_bk[d] = kappa q[d] s0[head(d)];
-// d_q[d] = kappa (wk[d, :] . d_r[head(d), :] + bk[d] s0[head(d)]),  s0[g] = sum_v da0[v, g]
-__global__ __launch_bounds__(256) void fold_key_bwd_kernel(const float *q, const float *wk, const float *bk, const float *d_r,
-                                                           const float *da0, float *d_wk, float *d_bk, float *d_q, int D, int dh,
-                                                           int heads, int V, float kappa) {
-  const int d = blockIdx.x;                       // one work-group per feature d
-  const int g = d / dh;
-  __shared__ float red[256];
-  float s = 0.f;
-  for (int j = threadIdx.x; j < D; j += 256) {
-    const float dr = d_r[static_cast<size_t>(g) * D + j];
-    d_wk[static_cast<size_t>(d) * D + j] = kappa * q[d] * dr;
-    s = fmaf(wk[static_cast<size_t>(d) * D + j], dr, s);
-  }
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
     __syncthreads();
+    for (int idx = t; idx < TP * e.heads; idx += 256) {
+      float *r = sc + static_cast<size_t>(idx) * e.V, *dr = da + static_cast<size_t>(idx) * e.V;
+      float mx = -INFINITY;
+      for (int v = 0; v < e.V; ++v) mx = fmaxf(mx, r[v]);
+      float sum = 0.f, dot = 0.f;
+      for (int v = 0; v < e.V; ++v) {
+        const float ex = __expf(r[v] - mx);
+        r[v] = ex;
+        sum += ex;
+        dot = fmaf(ex, dr[v], dot);
+      }
+      const float inv = 1.0f / sum;
+      dot *= inv;
+      for (int v = 0; v < e.V; ++v) {
+        const float w = r[v] * inv;
+        r[v] = w;
+        dr[v] = w * (dr[v] - dot);
+      }
+    }
+    __syncthreads();
+    for (int idx = t; idx < TP * HV; idx += 256)
+      if (bn0 + idx / HV < e.BN) e.a_out[bn0 * HV + idx] = sc[idx];
+    const int have = static_cast<int>(min(static_cast<int64_t>(TP), e.BN - bn0));
+    const bool first = grp == blockIdx.x;
+    for (int item = t; item < HV; item += 256) {
+      const int v = item / e.heads, g = item % e.heads;
+      float acc[P3];
+      float *o = part + static_cast<size_t>(v) * P3 * e.heads + g;
+#pragma unroll
+      for (int i = 0; i <= p2; ++i) acc[i] = first ? 0.f : o[static_cast<size_t>(i) * e.heads];
+      for (int pi = 0; pi < have; ++pi) {
+        const float ds = da[(pi * e.heads + g) * e.V + v];
+        const float *px = pix + pi * VP2 + v * p2;
+#pragma unroll
+        for (int i = 0; i < p2; ++i) acc[i] = fmaf(ds, px[i], acc[i]);
+        acc[p2] += ds;
+      }
+#pragma unroll
+      for (int i = 0; i <= p2; ++i) o[static_cast<size_t>(i) * e.heads] = acc[i];
+    }
   }
-  if (threadIdx.x == 0) {
-    float s0 = 0.f;
-    for (int v = 0; v < V; ++v) s0 += da0[v * heads + g];
-    d_bk[d] = kappa * q[d] * s0;
-    d_q[d] = kappa * (red[0] + bk[d] * s0);
-  }
-}
-// d_wq[d, j] = d_q[d] q0[j]
-__global__ __launch_bounds__(256) void outer_kernel(const float *a, const float *b, float *out, int M, int N) {
-  const int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (e < static_cast<int64_t>(M) * N) out[e] = a[e / N] * b[e % N];
-}
-// splits the reduced [V][D][p2 + 1] table into dU [V][D][p2] and dc [V][D] (same for the score tables)
-__global__ __launch_bounds__(256) void split_last_kernel(const float *in, float *main, float *last, int64_t rows, int p2) {
-  const int64_t r = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (r >= rows) return;
-  for (int i = 0; i < p2; ++i) main[r * p2 + i] = in[r * (p2 + 1) + i];
-  last[r] = in[r * (p2 + 1) + p2];
 }
 
-static hipError_t launch_1d(void (*k)(float *, int64_t, float), float *p, int64_t n, float v, hipStream_t st) {
-  k<<<dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, st>>>(p, n, v);
-  return hipGetLastError();
+// Second half: gradients of the folded value tables, for head g
+//   T[(v, i), d] = sum over tokens of (a[g, v] xt[v, i]) d_o[d],  xt = the pixels of variable v, then one,
+// a product over the tokens per head, on fp32 matrix instructions (32x32x2: two tokens each, the first factor
+// multiplied together in the lane that holds its row).  Grid (token slab, head and 64 of its features, 32 MB rows);
+// the four waves take every fourth pair of tokens and meet in LDS in wave order.  One partial table [V (p2 + 1), D]
+// per slab.  c2 with one sample (64,800 tokens): 1.24 ms with one thread per feature reading every factor, 0.25 here.
+template <typename T, int MB>
+__global__ __launch_bounds__(256) void agg_values_bwd_kernel(AggBwdArgs e, float *__restrict__ partial, int tokens_per_slab, int chunks) {
+  typedef __attribute__((ext_vector_type(16))) float f32x16;
+  constexpr int NB = 2, AHEAD = 4;
+  __shared__ float box[3][16][64];
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), l32 = lane & 31, hi = lane >> 5;
+  const int P3 = e.p * e.p + 1, rows = e.V * P3, HV = e.heads * e.V;
+  const int g = blockIdx.y / chunks, f0 = (blockIdx.y % chunks) * 64, m0 = blockIdx.z * MB * 32;
+  const int64_t t0 = static_cast<int64_t>(blockIdx.x) * tokens_per_slab, t1 = min(t0 + tokens_per_slab, e.BN);
+  const T *dop = static_cast<const T *>(e.d_o) + g * e.dh;
+  int m[MB], va[MB], f[NB];
+#pragma unroll
+  for (int k = 0; k < MB; ++k) {
+    m[k] = min(m0 + k * 32 + l32, rows - 1);           // rows past the table repeat the last one and are not stored
+    va[k] = g * e.V + m[k] / P3;
+  }
+#pragma unroll
+  for (int n = 0; n < NB; ++n) f[n] = min(f0 + n * 32 + l32, e.dh - 1);
+  f32x16 acc[MB][NB] = {};
+  float xr[AHEAD][MB], ar[AHEAD][MB], br[AHEAD][NB];
+  auto fetch = [&](int i, int64_t at) {                // tokens at, at + 1 of the two lane halves; zeros past the slab
+    const int64_t tok = at + hi, c = min(tok, t1 - 1);
+    const bool in = tok < t1;
+#pragma unroll
+    for (int k = 0; k < MB; ++k) {
+      xr[i][k] = e.x_out[c * rows + m[k]];
+      ar[i][k] = e.a_out[c * HV + va[k]];
+    }
+#pragma unroll
+    for (int n = 0; n < NB; ++n) br[i][n] = in ? Act<T>::load(dop + c * e.D + f[n]) : 0.f;
+  };
+  const int64_t first = t0 + 2 * wave;
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) fetch(i, first + 8 * i);
+  for (int64_t at = first; at < t1; at += 8 * AHEAD) {
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) {
+      float av[MB], bv[NB];
+#pragma unroll
+      for (int k = 0; k < MB; ++k) av[k] = xr[i][k] * ar[i][k];
+#pragma unroll
+      for (int n = 0; n < NB; ++n) bv[n] = br[i][n];
+      fetch(i, at + 8 * (AHEAD + i));
+#pragma unroll
+      for (int k = 0; k < MB; ++k)
+#pragma unroll
+        for (int n = 0; n < NB; ++n) acc[k][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[k], bv[n], acc[k][n], 0, 0, 0);
+    }
+  }
+  float *out = partial + static_cast<size_t>(blockIdx.x) * rows * e.D + g * e.dh;
+#pragma unroll
+  for (int k = 0; k < MB; ++k)
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+      __syncthreads();
+      if (wave > 0)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) box[wave - 1][r][lane] = acc[k][n][r];
+      __syncthreads();
+      if (wave == 0 && f0 + n * 32 + l32 < e.dh)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int row = m0 + k * 32 + 8 * (r / 4) + 4 * hi + r % 4;
+          if (row < rows) out[static_cast<size_t>(row) * e.D + f0 + n * 32 + l32] = ((acc[k][n][r] + box[0][r][lane]) + box[1][r][lane]) + box[2][r][lane];
+        }
+    }
+}
+
+// ---- Chain rule through the fold (fp32, small).  With the offsets as one more pixel, i = p2,
+//   Wt[(v, i), j] = W_pe[v][j, i] | t_v[j] = b_pe[v] + var_emb[v],   tU[(v, i), d] = dU[v][d, i] | dc[v][d],
+//   tA[(v, i), g] = dA[v, g, i] | da0[v, g],   q = Wq q0 + bq,   r[g, j] = kappa sum_{d in g} q[d] Wk[d, j],
+// the forward is A = r Wt per head, U = Wv Wt (+ bv), so
+//   d_r = tA^T Wt,   d_Wv = tU^T Wt,   d_Wt = tA r + tU Wv   (rows i < p2: d_W_pe, row p2: d_b_pe = d_var_emb).
+// Three products for all variables at once; one variable after the other they were 6 V launches of a few microseconds
+// (1.5 of the 5.6 ms of a step of the 9.5M model, about 6 of 125 ms at c2).
+struct FoldArgs {
+  const float *w_pe, *b_pe, *var_emb, *q0, *wq, *bq, *wk, *bk, *wv, *tU, *tA, *agg_bo_grad;
+  float *q, *r, *Wt, *d_r, *d_q;
+  float *g_w_pe, *g_b_pe, *g_var_emb, *g_wv, *g_bv, *g_wk, *g_bk, *g_wq, *g_bq, *g_q0, *g_res;
+  int V, D, dh, heads, p2, n_res, res_idx;
+  float kappa;
+};
+
+__device__ __forceinline__ float wave_total(float v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  return v;
+}
+
+// q (one wave per row of Wq), Wt, the bias of the values and the resolution table's gradient (one row is the output
+// map's bias gradient, the others are zero)
+__global__ __launch_bounds__(256) void fold_prepare_kernel(FoldArgs a, int q_blocks) {
+  const int P3 = a.p2 + 1;
+  if (static_cast<int>(blockIdx.x) < q_blocks) {
+    const int d = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (d >= a.D) return;
+    const float *w = a.wq + static_cast<size_t>(d) * a.D;
+    float s = 0.f;
+    for (int j = lane; j < a.D; j += 64) s = fmaf(w[j], a.q0[j], s);
+    s = wave_total(s);
+    if (lane == 0) a.q[d] = s + a.bq[d];
+    return;
+  }
+  const int64_t i = static_cast<int64_t>(blockIdx.x - q_blocks) * 256 + threadIdx.x;
+  const int64_t n_wt = static_cast<int64_t>(a.V) * P3 * a.D;
+  if (i < n_wt) {
+    const int j = static_cast<int>(i % a.D), k = static_cast<int>(i / a.D), v = k / P3, pi = k % P3;
+    const size_t vj = static_cast<size_t>(v) * a.D + j;
+    a.Wt[i] = pi < a.p2 ? a.w_pe[vj * a.p2 + pi] : a.b_pe[vj] + a.var_emb[vj];
+    return;
+  }
+  const int64_t k = i - n_wt;
+  if (k < a.D) {
+    float s = 0.f;
+    for (int v = 0; v < a.V; ++v) s += a.tU[(static_cast<size_t>(v) * P3 + a.p2) * a.D + k];
+    a.g_bv[k] = s;
+  } else if (k < a.D + static_cast<int64_t>(a.n_res) * a.D) {
+    const int64_t o = k - a.D;
+    a.g_res[o] = o / a.D == a.res_idx ? a.agg_bo_grad[o % a.D] : 0.f;
+  }
+}
+
+// r[g, j]: 64 columns per work-group, four row groups of the head added in order
+__global__ __launch_bounds__(256) void fold_query_kernel(FoldArgs a) {
+  __shared__ float box[4][64];
+  const int g = blockIdx.y, col = threadIdx.x & 63, part = threadIdx.x >> 6, j = blockIdx.x * 64 + col;
+  float s = 0.f;
+  if (j < a.D)
+    for (int d = part; d < a.dh; d += 4) s = fmaf(a.q[g * a.dh + d], a.wk[static_cast<size_t>(g * a.dh + d) * a.D + j], s);
+  box[part][col] = s;
+  __syncthreads();
+  if (part == 0 && j < a.D) a.r[static_cast<size_t>(g) * a.D + j] = a.kappa * ((box[0][col] + box[1][col]) + (box[2][col] + box[3][col]));
+}
+
+// One 32 x 32 tile of a product per work-group, on fp32 matrix instructions; its four waves take every fourth step of
+// two k and meet in LDS in wave order.  tile < n1: d_Wv; < n1 + n2: d_Wt; else d_r.
+__global__ __launch_bounds__(256) void fold_products_kernel(FoldArgs a, int n1, int n2, int cols) {
+  typedef __attribute__((ext_vector_type(16))) float f32x16;
+  __shared__ float box[3][16][64];
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), l32 = lane & 31, hi = lane >> 5;
+  const int rows3 = a.V * (a.p2 + 1), id = blockIdx.x;
+  const int kind = id < n1 ? 0 : id < n1 + n2 ? 1 : 2, tile = kind == 0 ? id : kind == 1 ? id - n1 : id - n1 - n2;
+  const int m0 = tile / cols * 32, n0 = tile % cols * 32, n = min(n0 + l32, a.D - 1);
+  const int M = kind == 0 ? a.D : kind == 1 ? rows3 : a.heads;
+  const int m = min(m0 + l32, M - 1);
+  f32x16 acc = {};
+  // A[m, k] at pa + k * ska, B[k, n] at pb + k * a.D
+  auto run = [&](const float *pa, size_t ska, const float *pb, int K) {
+    for (int s = wave; 2 * s < K; s += 32) {             // eight steps' factors at a time
+      float x[8], y[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int k = 2 * (s + 4 * i) + hi, kc = min(k, K - 1);
+        x[i] = pa[kc * ska];
+        y[i] = pb[static_cast<size_t>(kc) * a.D];
+        if (k >= K) x[i] = 0.f;
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[i], y[i], acc, 0, 0, 0);
+    }
+  };
+  if (kind == 0) {
+    run(a.tU + m, a.D, a.Wt + n, rows3);
+  } else if (kind == 1) {
+    run(a.tA + static_cast<size_t>(m) * a.heads, 1, a.r + n, a.heads);
+    run(a.tU + static_cast<size_t>(m) * a.D, 1, a.wv + n, a.D);
+  } else {
+    run(a.tA + m, a.heads, a.Wt + n, rows3);
+  }
+  if (wave > 0)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) box[wave - 1][r][lane] = acc[r];
+  __syncthreads();
+  if (wave > 0 || n0 + l32 >= a.D) return;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int row = m0 + 8 * (r / 4) + 4 * hi + r % 4, col = n0 + l32;
+    if (row >= M) continue;
+    const float v = ((acc[r] + box[0][r][lane]) + box[1][r][lane]) + box[2][r][lane];
+    if (kind == 0) {
+      a.g_wv[static_cast<size_t>(row) * a.D + col] = v;
+    } else if (kind == 2) {
+      a.d_r[static_cast<size_t>(row) * a.D + col] = v;
+    } else {
+      const int var = row / (a.p2 + 1), i = row % (a.p2 + 1);
+      const size_t vj = static_cast<size_t>(var) * a.D + col;
+      if (i < a.p2) {
+        a.g_w_pe[vj * a.p2 + i] = v;
+      } else {
+        a.g_b_pe[vj] = v;
+        a.g_var_emb[vj] = v;
+      }
+    }
+  }
+}
+
+// the key and query ends of the fold: d_wk[d, j] = kappa q[d] d_r[head(d), j];  d_bk[d] = kappa q[d] s0[head(d)];
+// d_q[d] = kappa (wk[d, :] . d_r[head(d), :] + bk[d] s0[head(d)]),  s0[g] = sum_v da0[v, g];  d_wq[d, j] = d_q[d] q0[j]
+__global__ __launch_bounds__(256) void fold_key_bwd_kernel(FoldArgs a) {
+  const int d = blockIdx.x, g = d / a.dh;         // one work-group per feature d
+  __shared__ float red[4];
+  const float kq = a.kappa * a.q[d];
+  const float *dr = a.d_r + static_cast<size_t>(g) * a.D, *wk = a.wk + static_cast<size_t>(d) * a.D;
+  float s = 0.f;
+  for (int j = threadIdx.x; j < a.D; j += 256) {
+    const float v = dr[j];
+    a.g_wk[static_cast<size_t>(d) * a.D + j] = kq * v;
+    s = fmaf(wk[j], v, s);
+  }
+  s = wave_total(s);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  float s0 = 0.f;
+  for (int v = 0; v < a.V; ++v) s0 += a.tA[(static_cast<size_t>(v) * (a.p2 + 1) + a.p2) * a.heads + g];
+  __syncthreads();
+  const float dq = a.kappa * (((red[0] + red[1]) + (red[2] + red[3])) + a.bk[d] * s0);
+  if (threadIdx.x == 0) {
+    a.g_bk[d] = kq * s0;
+    a.d_q[d] = dq;
+    a.g_bq[d] = dq;
+  }
+  for (int j = threadIdx.x; j < a.D; j += 256) a.g_wq[static_cast<size_t>(d) * a.D + j] = dq * a.q0[j];
+}
+
+// d_q0[j] = sum_d Wq[d, j] d_q[d]: 64 columns per work-group, sixteen row groups added in order
+__global__ __launch_bounds__(1024) void fold_q0_kernel(FoldArgs a) {
+  __shared__ float box[16][64];
+  const int col = threadIdx.x & 63, part = threadIdx.x >> 6, j = blockIdx.x * 64 + col;
+  float s = 0.f;
+  if (j < a.D)
+    for (int d = part; d < a.D; d += 16) s = fmaf(a.wq[static_cast<size_t>(d) * a.D + j], a.d_q[d], s);
+  box[part][col] = s;
+  __syncthreads();
+  if (part == 0 && j < a.D) {
+    float v = box[0][col];
+#pragma unroll
+    for (int k = 1; k < 16; ++k) v += box[k][col];
+    a.g_q0[j] = v;
+  }
 }
 
 // ------------------------------------------------------------------ buffers
@@ -779,14 +908,13 @@ struct EmbedWs {
   void *dz_act, *o, *d_o;    // act [Mi, D]: gradient of the aggregated tokens, aggregated values, their gradient
   void *wgrad;
   float *colp;
-  float *a, *ds;             // [Mi, heads, V]
+  float *a, *xt;             // [Mi, heads, V] softmax weights, [Mi, V (p2 + 1)] pixels
   float *E;                  // [Mi, n_e] d_o times the block-structured value table
   float *pU, *pA;            // partial rows of the folded tables' gradients
-  float *tU, *tA;            // reduced tables [V, D, p2 + 1], [V, heads, p2 + 1]
-  float *dU, *dc, *dA, *da0; // split
-  float *q, *r, *tv, *d_r, *d_q;   // fold intermediates: [D], [heads, D], [V, D], [heads, D], [D]
-  int slabs_u, tok_u, slabs_a, tok_a;
-  size_t total;
+  float *tU, *tA;            // reduced tables [V, p2 + 1, D], [V, p2 + 1, heads]
+  float *q, *r, *Wt, *d_r, *d_q;   // fold intermediates: [D], [heads, D], [V, p2 + 1, D], [heads, D], [D]
+  int slabs_u, tok_u, mb_u, slabs_a, tp;
+  size_t lds_a, total;
 };
 static EmbedWs plan_embed_ws(const reslim_ctx *c, int batch, void *base) {
   const size_t Mi = static_cast<size_t>(batch) * c->N, D = c->cfg.embed_dim, es = act_size(c);
@@ -802,28 +930,28 @@ static EmbedWs plan_embed_ws(const reslim_ctx *c, int batch, void *base) {
   w.wgrad = take(std::max<size_t>(wgrad_ws_bytes(c->cfg.dtype, static_cast<int>(Mi), c->cfg.embed_dim, c->cfg.embed_dim), 256));
   w.colp = reinterpret_cast<float *>(take(static_cast<size_t>(colsum_slabs(Mi)) * D * 4));
   w.a = reinterpret_cast<float *>(take(Mi * heads * V * 4));
-  w.ds = reinterpret_cast<float *>(take(Mi * heads * V * 4));
+  w.xt = reinterpret_cast<float *>(take(Mi * V * (p2 + 1) * 4));
   w.E = reinterpret_cast<float *>(take(Mi * static_cast<size_t>(agg_table_rows(c)) * 4));
-  // slabs of tokens: about 2048 work-groups in the value-table pass, at least 64 tokens per slab
-  const size_t per = ((D + 255) / 256) * ((V + 7) / 8);
-  size_t su = std::max<size_t>(1, std::min<size_t>(256, 2048 / per));
-  su = std::min(su, (Mi + 63) / 64);
+  // value tables: row blocks of 32 per work-group (up to four), then as many token slabs as give about four work-groups
+  // per CU, at least 64 tokens each
+  const size_t blocks = (V * (p2 + 1) + 31) / 32, z = (blocks + 3) / 4;
+  w.mb_u = static_cast<int>((blocks + z - 1) / z);
+  const size_t per = heads * ((static_cast<size_t>(c->dh) + 63) / 64) * z;
+  const size_t su = std::min(std::max<size_t>(1, std::min<size_t>(256, 1024 / per)), (Mi + 63) / 64);
   w.tok_u = static_cast<int>((Mi + su - 1) / su);
   w.slabs_u = static_cast<int>((Mi + w.tok_u - 1) / w.tok_u);
-  size_t sa = std::min<size_t>(256, (Mi + 63) / 64);
-  w.tok_a = static_cast<int>((Mi + sa - 1) / sa);
-  w.slabs_a = static_cast<int>((Mi + w.tok_a - 1) / w.tok_a);
+  // score tables: tokens per group by what fits LDS, at most 512 work-groups (their partial rows are added afterwards)
+  auto lds_for = [&](size_t tp) { return tp * (V * p2 + 2 * heads * V) * sizeof(float); };
+  w.tp = lds_for(16) <= 64 * 1024 ? 16 : 4;
+  w.lds_a = lds_for(w.tp);
+  w.slabs_a = static_cast<int>(std::min<size_t>(512, (Mi + w.tp - 1) / w.tp));
   w.pU = reinterpret_cast<float *>(take(static_cast<size_t>(w.slabs_u) * V * D * (p2 + 1) * 4));
   w.pA = reinterpret_cast<float *>(take(static_cast<size_t>(w.slabs_a) * V * heads * (p2 + 1) * 4));
   w.tU = reinterpret_cast<float *>(take(V * D * (p2 + 1) * 4));
   w.tA = reinterpret_cast<float *>(take(V * heads * (p2 + 1) * 4));
-  w.dU = reinterpret_cast<float *>(take(V * D * p2 * 4));
-  w.dc = reinterpret_cast<float *>(take(V * D * 4));
-  w.dA = reinterpret_cast<float *>(take(V * heads * p2 * 4));
-  w.da0 = reinterpret_cast<float *>(take(V * heads * 4));
   w.q = reinterpret_cast<float *>(take(D * 4));
   w.r = reinterpret_cast<float *>(take(heads * D * 4));
-  w.tv = reinterpret_cast<float *>(take(V * D * 4));
+  w.Wt = reinterpret_cast<float *>(take(V * D * (p2 + 1) * 4));
   w.d_r = reinterpret_cast<float *>(take(heads * D * 4));
   w.d_q = reinterpret_cast<float *>(take(D * 4));
   w.total = off;
@@ -946,12 +1074,9 @@ static int embed_bwd_impl(reslim_ctx *c, const char *fn, const float *x, const f
                   launch_wgrad(dt, w.dz_act, w.o, g->agg_wo, Mi, D, D, w.wgrad, c->d_zero_bias, st));
     RESLIM_LAUNCH("colsum", 0, dMi * dD * es + 4.0 * dD, launch_colsum(dt, w.dz_act, w.colp, g->agg_bo, Mi, D, st));
   }
-  // resolution table: the row the forward read gets the same column sums as the output bias, the others zero
-  RESLIM_TRY("fill", launch_1d(fill_kernel, g->res_emb, static_cast<int64_t>(c->cfg.n_res) * D, 0.f, st));
-  RESLIM_TRY("copy", hipMemcpyAsync(g->res_emb + static_cast<size_t>(c->cfg.res_idx) * D, g->agg_bo, D * sizeof(float), hipMemcpyDeviceToDevice, st));
   // folded aggregation backwards: logits, then the tables
   AggBwdArgs e;
-  e.x = x; e.A = c->d_agg_A; e.a0 = c->d_agg_a0; e.U = c->d_agg_U; e.c = c->d_agg_c; e.d_o = w.d_o; e.a_out = w.a; e.ds_out = w.ds;
+  e.x = x; e.A = c->d_agg_A; e.a0 = c->d_agg_a0; e.U = c->d_agg_U; e.c = c->d_agg_c; e.d_o = w.d_o; e.a_out = w.a; e.x_out = w.xt; e.partial = w.pA;
   e.V = V; e.H = c->cfg.H; e.W = c->cfg.W; e.p = p; e.Wp = c->Wp; e.N = c->N; e.D = D; e.heads = heads; e.dh = dh; e.BN = Mi;
   {
     const TrainModel &tmm = c->train;
@@ -959,81 +1084,56 @@ static int embed_bwd_impl(reslim_ctx *c, const char *fn, const float *x, const f
     RESLIM_LAUNCH("gemm_agg_dvalues", 2.0 * dMi * dNe * dD, dMi * dD * es + dNe * dD * es + 4.0 * dMi * dNe,
                   launch_gemm(dt, EPI_BIAS_F32, w.d_o, tmm.w_vtab, tmm.zero_e, w.E, tmm.n_e, nullptr, 0, Mi, tmm.n_e, D, st));
     e.E = w.E; e.ne = tmm.n_e;
-    auto lds_for = [&](int tp) {
-      return static_cast<size_t>(tp) * (static_cast<size_t>(V) * p2 + 2 * static_cast<size_t>(heads) * V) * sizeof(float);
-    };
-    const int tp = lds_for(16) <= 64 * 1024 ? 16 : 4;      // tokens per work-group: fewer where variables x heads is large
-    const size_t lds = lds_for(tp);
-    if (lds > 150 * 1024) return set_error(c, RESLIM_ESHAPE, std::string(fn) + ": too many variables x heads for the aggregation gradient");
-    const dim3 grid(static_cast<unsigned>((Mi + tp - 1) / tp));
-    const double fl = 2.0 * dMi * heads * V * (2.0 * p2 + 3.0);
-    const double by = 4.0 * dMi * dNe + 8.0 * dMi * heads * V;
-    if (tp == 16) RESLIM_LAUNCH("agg_scores_bwd", fl, by, (agg_scores_bwd_kernel<16><<<grid, dim3(256), lds, st>>>(e), hipGetLastError()));
-    else RESLIM_LAUNCH("agg_scores_bwd", fl, by, (agg_scores_bwd_kernel<4><<<grid, dim3(256), lds, st>>>(e), hipGetLastError()));
-  }
-  {
     if (p2 != 4 && p2 != 1 && p2 != 16) return set_error(c, RESLIM_ESHAPE, std::string(fn) + ": the aggregation gradient is built for patch sizes 1, 2 and 4");
-    const dim3 grid(w.slabs_u, (D + 255) / 256, (V + 7) / 8);
-    const double fl = 2.0 * dMi * V * dD * (p2 + 1);
-#define RESLIM_AGGV(T_, P2_) RESLIM_LAUNCH("agg_values_bwd", fl, dMi * dD * es + 4.0 * dMi * heads * V, (agg_values_bwd_kernel<T_, P2_, 8><<<grid, dim3(256), 0, st>>>(e, w.pU, w.tok_u), hipGetLastError()))
-    if (dt == RESLIM_BF16) {
-      if (p2 == 4) RESLIM_AGGV(bf16_t, 4); else if (p2 == 1) RESLIM_AGGV(bf16_t, 1); else RESLIM_AGGV(bf16_t, 16);
-    } else {
-      if (p2 == 4) RESLIM_AGGV(float, 4); else if (p2 == 1) RESLIM_AGGV(float, 1); else RESLIM_AGGV(float, 16);
-    }
-#undef RESLIM_AGGV
-    const int64_t nU = static_cast<int64_t>(V) * D * (p2 + 1);
-    RESLIM_LAUNCH("partial_reduce", 0, 4.0 * w.slabs_u * nU, launch_partial_reduce(w.pU, w.tU, w.slabs_u, nU, nU, st));
-    RESLIM_LAUNCH("agg_logits_bwd", 0, 4.0 * dMi * heads * V,
-                  (agg_logits_bwd_kernel<<<dim3(w.slabs_a), dim3(256), 0, st>>>(e, w.pA, w.tok_a), hipGetLastError()));
+    if (w.lds_a > 150 * 1024) return set_error(c, RESLIM_ESHAPE, std::string(fn) + ": too many variables x heads for the aggregation gradient");
+    const dim3 grid(static_cast<unsigned>(w.slabs_a));
+    const double fl = 2.0 * dMi * heads * V * (3.0 * p2 + 4.0);
+    const double by = 4.0 * dMi * dNe + 4.0 * dMi * V * (heads + p2 + 1.0);
+    hipError_t le = hipSuccess;
+#define RESLIM_AGGS(P2_) (w.tp == 16 ? (agg_scores_bwd_kernel<16, P2_><<<grid, dim3(256), w.lds_a, st>>>(e), hipGetLastError()) \
+                                     : (agg_scores_bwd_kernel<4, P2_><<<grid, dim3(256), w.lds_a, st>>>(e), hipGetLastError()))
+    RESLIM_LAUNCH("agg_scores_bwd", fl, by, (le = p2 == 4 ? RESLIM_AGGS(4) : p2 == 1 ? RESLIM_AGGS(1) : RESLIM_AGGS(16), le));
+#undef RESLIM_AGGS
     const int64_t nA = static_cast<int64_t>(V) * heads * (p2 + 1);
     RESLIM_LAUNCH("partial_reduce", 0, 4.0 * w.slabs_a * nA, launch_partial_reduce(w.pA, w.tA, w.slabs_a, nA, nA, st));
-    split_last_kernel<<<dim3((V * D + 255) / 256), dim3(256), 0, st>>>(w.tU, w.dU, w.dc, static_cast<int64_t>(V) * D, p2);
-    RESLIM_TRY("split", hipGetLastError());
-    split_last_kernel<<<dim3((V * heads + 255) / 256), dim3(256), 0, st>>>(w.tA, w.dA, w.da0, static_cast<int64_t>(V) * heads, p2);
-    RESLIM_TRY("split", hipGetLastError());
   }
-  // ---- chain rule through the fold (fp32, small):
-  //   q = Wq q0 + bq;  r_g = kappa Wk_g^T q_g;  t_v = b_pe[v] + var_emb[v]
-  //   A[v,g,:] = r_g^T W_pe[v];  a0[v,g] = r_g . t_v + kappa q_g . bk_g;  U[v] = Wv W_pe[v];  c[v] = Wv t_v + bv
-  RESLIM_TRY("fold", smm(tm.wq, D, 1, tm.q0, 1, 0, w.q, 1, 0, D, 1, D, 1.0f, false, st));
-  add2_kernel<<<dim3((D + 255) / 256), dim3(256), 0, st>>>(w.q, tm.bq, w.q, D);
-  RESLIM_TRY("fold", hipGetLastError());
-  for (int gh = 0; gh < heads; ++gh)      // r[g, j] = kappa sum_{d in g} q[d] Wk[d, j]
-    RESLIM_TRY("fold", smm(tm.wk + static_cast<size_t>(gh) * dh * D, 1, D, w.q + gh * dh, 1, 0, w.r + static_cast<size_t>(gh) * D, 1, 0, D, 1, dh, kappa, false, st));
-  add2_kernel<<<dim3((V * D + 255) / 256), dim3(256), 0, st>>>(tm.b_pe, tm.var_emb, w.tv, static_cast<int64_t>(V) * D);
-  RESLIM_TRY("fold", hipGetLastError());
-  for (int v = 0; v < V; ++v) {
-    const float *wpe = tm.w_pe + static_cast<size_t>(v) * D * p2;       // [D, p2]
-    const float *dA_v = w.dA + static_cast<size_t>(v) * heads * p2;     // [heads, p2]
-    const float *dU_v = w.dU + static_cast<size_t>(v) * D * p2;         // [D, p2]
-    // d_r[g, j] += sum_i dA[v,g,i] W_pe[v][j,i] + da0[v,g] t_v[j]       (C = d_r^T viewed [j, g]: m = j)
-    RESLIM_TRY("fold", smm(wpe, p2, 1, dA_v, 1, p2, w.d_r, 1, D, D, heads, p2, 1.0f, v > 0, st));
-    RESLIM_TRY("fold", smm(w.tv + static_cast<size_t>(v) * D, 1, 0, w.da0 + static_cast<size_t>(v) * heads, 0, 1, w.d_r, 1, D, D, heads, 1, 1.0f, true, st));
-    // d_W_pe[v][j, i] = sum_g r[g, j] dA[v,g,i] + sum_d Wv[d, j] dU[v][d, i]
-    float *dwpe = g->w_pe + static_cast<size_t>(v) * D * p2;
-    RESLIM_TRY("fold", smm(w.r, 1, D, dA_v, p2, 1, dwpe, p2, 1, D, p2, heads, 1.0f, false, st));
-    RESLIM_TRY("fold", smm(tm.wv, 1, D, dU_v, p2, 1, dwpe, p2, 1, D, p2, D, 1.0f, true, st));
-    // d_Wv[d, j] += sum_i dU[v][d, i] W_pe[v][j, i] + dc[v][d] t_v[j]
-    RESLIM_TRY("fold", smm(dU_v, p2, 1, wpe, 1, p2, g->agg_wv, D, 1, D, D, p2, 1.0f, v > 0, st));
-    RESLIM_TRY("fold", smm(w.dc + static_cast<size_t>(v) * D, 1, 0, w.tv + static_cast<size_t>(v) * D, 0, 1, g->agg_wv, D, 1, D, D, 1, 1.0f, true, st));
-  }
-  // d_t[v, j] = sum_g da0[v,g] r[g, j] + sum_d dc[v][d] Wv[d, j]  ->  d_b_pe = d_var_emb = d_t
-  RESLIM_TRY("fold", smm(w.da0, heads, 1, w.r, D, 1, g->b_pe, D, 1, V, D, heads, 1.0f, false, st));
-  RESLIM_TRY("fold", smm(w.dc, D, 1, tm.wv, D, 1, g->b_pe, D, 1, V, D, D, 1.0f, true, st));
-  RESLIM_TRY("copy", hipMemcpyAsync(g->var_emb, g->b_pe, static_cast<size_t>(V) * D * sizeof(float), hipMemcpyDeviceToDevice, st));
-  // d_bv[d] = sum_v dc[v][d]
-  RESLIM_TRY("fold", launch_partial_reduce(w.dc, g->agg_bv, V, D, D, st));
-  // key and query ends
-  fold_key_bwd_kernel<<<dim3(D), dim3(256), 0, st>>>(w.q, tm.wk, tm.bk, w.d_r, w.da0, g->agg_wk, g->agg_bk, w.d_q, D, dh, heads, V, kappa);
-  RESLIM_TRY("fold", hipGetLastError());
   {
-    const int64_t n = static_cast<int64_t>(D) * D;
-    outer_kernel<<<dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, st>>>(w.d_q, tm.q0, g->agg_wq, D, D);
+    const int chunks = (dh + 63) / 64, rows = V * (p2 + 1);
+    const dim3 grid(w.slabs_u, heads * chunks, (rows + 32 * w.mb_u - 1) / (32 * w.mb_u));
+    const double fl = 2.0 * dMi * V * dD * (p2 + 1), by = dMi * dD * es + 4.0 * dMi * V * (heads + p2 + 1.0);
+    hipError_t le = hipSuccess;
+#define RESLIM_AGGV(T_, MB_) (agg_values_bwd_kernel<T_, MB_><<<grid, dim3(256), 0, st>>>(e, w.pU, w.tok_u, chunks), hipGetLastError())
+    RESLIM_LAUNCH("agg_values_bwd", fl, by,
+                  (le = dt == RESLIM_BF16 ? (w.mb_u == 1 ? RESLIM_AGGV(bf16_t, 1) : w.mb_u == 2 ? RESLIM_AGGV(bf16_t, 2) : w.mb_u == 3 ? RESLIM_AGGV(bf16_t, 3) : RESLIM_AGGV(bf16_t, 4))
+                                          : (w.mb_u == 1 ? RESLIM_AGGV(float, 1) : w.mb_u == 2 ? RESLIM_AGGV(float, 2) : w.mb_u == 3 ? RESLIM_AGGV(float, 3) : RESLIM_AGGV(float, 4)),
+                   le));
+#undef RESLIM_AGGV
+    const int64_t nU = static_cast<int64_t>(rows) * D;
+    RESLIM_LAUNCH("partial_reduce", 0, 4.0 * w.slabs_u * nU, launch_partial_reduce(w.pU, w.tU, w.slabs_u, nU, nU, st));
+  }
+  // ---- chain rule through the fold
+  FoldArgs f;
+  f.w_pe = tm.w_pe; f.b_pe = tm.b_pe; f.var_emb = tm.var_emb; f.q0 = tm.q0; f.wq = tm.wq; f.bq = tm.bq; f.wk = tm.wk; f.bk = tm.bk; f.wv = tm.wv;
+  f.tU = w.tU; f.tA = w.tA; f.agg_bo_grad = g->agg_bo;
+  f.q = w.q; f.r = w.r; f.Wt = w.Wt; f.d_r = w.d_r; f.d_q = w.d_q;
+  f.g_w_pe = g->w_pe; f.g_b_pe = g->b_pe; f.g_var_emb = g->var_emb; f.g_wv = g->agg_wv; f.g_bv = g->agg_bv; f.g_wk = g->agg_wk; f.g_bk = g->agg_bk;
+  f.g_wq = g->agg_wq; f.g_bq = g->agg_bq; f.g_q0 = g->agg_q0; f.g_res = g->res_emb;
+  f.V = V; f.D = D; f.dh = dh; f.heads = heads; f.p2 = p2; f.n_res = c->cfg.n_res; f.res_idx = c->cfg.res_idx; f.kappa = kappa;
+  {
+    const int q_blocks = (D + 3) / 4, rows = V * (p2 + 1), cols = (D + 31) / 32;
+    const int64_t rest = static_cast<int64_t>(rows) * D + D + static_cast<int64_t>(c->cfg.n_res) * D;
+    fold_prepare_kernel<<<dim3(static_cast<unsigned>(q_blocks + (rest + 255) / 256)), dim3(256), 0, st>>>(f, q_blocks);
+    RESLIM_TRY("fold", hipGetLastError());
+    fold_query_kernel<<<dim3((D + 63) / 64, heads), dim3(256), 0, st>>>(f);
+    RESLIM_TRY("fold", hipGetLastError());
+    const int n1 = cols * cols, n2 = (rows + 31) / 32 * cols, n3 = (heads + 31) / 32 * cols;
+    fold_products_kernel<<<dim3(n1 + n2 + n3), dim3(256), 0, st>>>(f, n1, n2, cols);
+    RESLIM_TRY("fold", hipGetLastError());
+    fold_key_bwd_kernel<<<dim3(D), dim3(256), 0, st>>>(f);
+    RESLIM_TRY("fold", hipGetLastError());
+    fold_q0_kernel<<<dim3((D + 63) / 64), dim3(1024), 0, st>>>(f);
     RESLIM_TRY("fold", hipGetLastError());
   }
-  RESLIM_TRY("copy", hipMemcpyAsync(g->agg_bq, w.d_q, D * sizeof(float), hipMemcpyDeviceToDevice, st));
-  RESLIM_TRY("fold", smm(tm.wq, 1, D, w.d_q, 1, 0, g->agg_q0, 1, 0, D, 1, D, 1.0f, false, st));     // d_q0[j] = sum_d Wq[d, j] d_q[d]
   return RESLIM_OK;
 }
 
@@ -1066,8 +1166,12 @@ static hipError_t train_model_init() {
   hipError_t e = hipSuccess;
   const int lim = 150 * 1024;
 #define RESLIM_ATTR(K) if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void *>(&K), hipFuncAttributeMaxDynamicSharedMemorySize, lim)
-  RESLIM_ATTR(agg_scores_bwd_kernel<16>);
-  RESLIM_ATTR(agg_scores_bwd_kernel<4>);
+  RESLIM_ATTR((agg_scores_bwd_kernel<16, 1>));
+  RESLIM_ATTR((agg_scores_bwd_kernel<16, 4>));
+  RESLIM_ATTR((agg_scores_bwd_kernel<16, 16>));
+  RESLIM_ATTR((agg_scores_bwd_kernel<4, 1>));
+  RESLIM_ATTR((agg_scores_bwd_kernel<4, 4>));
+  RESLIM_ATTR((agg_scores_bwd_kernel<4, 16>));
   RESLIM_ATTR((residual_wgrad_kernel<4, 3>));
   RESLIM_ATTR((residual_wgrad_kernel<4, 5>));
   RESLIM_ATTR((residual_wgrad_kernel<4, 16>));
