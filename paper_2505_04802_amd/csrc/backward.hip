@@ -60,11 +60,14 @@ TrainSaved plan_saved(const reslim_ctx *c, int batch, void *base, int64_t n_h) {
 }
 
 struct TrainWs {           // scratch of the gradient pass
-  void *a, *b, *r;         // act [M, D], [M, D], [M, max(3D, R)]
+  // activation type; the gradients of the four linear layers' outputs (out, fc1, mid, qkv) stay until the end of the
+  // block, where the parameter gradients are computed in one launch
+  void *out, *fc1, *mid, *qkv;      // [M, D], [M, R], [M, D], [M, 3D]
+  void *b;                 // [M, D]: gradient of a linear layer's input, until the kernel after it
   float *g;                // [M, D]
   void *attn;              // tiles_attention_bwd scratch
   void *wgrad;             // partial tiles of the weight gradients
-  float *colp, *lnp;       // partial rows of the column sums and of the LayerNorm parameter gradients
+  float *lnp;              // partial rows of the LayerNorm parameter gradients
   size_t total;
 };
 TrainWs plan_train_ws(const reslim_ctx *c, int batch, void *base, const SeqGeom &sg) {
@@ -74,15 +77,16 @@ TrainWs plan_train_ws(const reslim_ctx *c, int batch, void *base, const SeqGeom 
   size_t off = 0;
   auto take = [&](size_t bytes) { unsigned char *q = p + off; off += align256(bytes); return q; };
   TrainWs w;
-  w.a = take(M * D * es);
+  w.out = take(M * D * es);
+  w.fc1 = take(M * R * es);
+  w.mid = take(M * D * es);
+  w.qkv = take(M * 3 * D * es);
   w.b = take(M * D * es);
-  w.r = take(M * std::max(3 * D, R) * es);
   w.g = reinterpret_cast<float *>(take(M * D * sizeof(float)));
   w.attn = take(tiles_attention_bwd_ws_bytes(c, batch, &sg));
-  size_t wg = std::max(std::max(wgrad_ws_bytes(dt, Mi, 3 * Di, Di), wgrad_ws_bytes(dt, Mi, Di, Di)),
-                       std::max(wgrad_ws_bytes(dt, Mi, Ri, Di), wgrad_ws_bytes(dt, Mi, Di, Ri)));
-  w.wgrad = take(std::max<size_t>(wg, 256));
-  w.colp = reinterpret_cast<float *>(take(static_cast<size_t>(colsum_slabs(M)) * std::max(3 * D, R) * sizeof(float)));
+  const WgradOp op[4] = {{nullptr, nullptr, nullptr, nullptr, Di, Ri}, {nullptr, nullptr, nullptr, nullptr, Ri, Di},
+                         {nullptr, nullptr, nullptr, nullptr, Di, Di}, {nullptr, nullptr, nullptr, nullptr, 3 * Di, Di}};
+  w.wgrad = take(std::max<size_t>(wgrad_ws_bytes(dt, op, 4, Mi), 256));
   w.lnp = reinterpret_cast<float *>(take(static_cast<size_t>(layernorm_bwd_slabs(M)) * 2 * D * sizeof(float)));
   w.total = off;
   return w;
@@ -101,17 +105,23 @@ int check_train(reslim_ctx *c, const char *fn, int layer, int batch, const void 
   return RESLIM_OK;
 }
 
-// one linear layer backwards: dx = dy W (optional), dW = dy^T x, db = column sums of dy
-int linear_bwd_impl(reslim_ctx *c, const char *fn, const void *x, const void *dy, const void *w_t, void *dx, float *dw,
-                    float *db, int M, int N, int K, void *wgrad_ws, float *colp, hipStream_t st) {
-  const int dt = c->cfg.dtype;
+// input gradient of a linear layer: dx[M, K] = dy[M, N] W
+int dgrad_impl(reslim_ctx *c, const char *fn, const void *dy, const void *w_t, void *dx, int M, int N, int K, hipStream_t st) {
   const double es = static_cast<double>(act_size(c)), dM = M, dN = N, dK = K;
-  if (dx)
-    RESLIM_LAUNCH("gemm_dgrad", 2.0 * dM * dN * dK, dM * dN * es + dN * dK * es + dM * dK * es,
-                  launch_gemm(dt, EPI_BIAS_ACT, dy, w_t, c->d_zero_bias, dx, K, nullptr, 0, M, K, N, st));
-  RESLIM_LAUNCH("gemm_wgrad", 2.0 * dM * dN * dK, dM * dN * es + dM * dK * es + 4.0 * dN * dK,
-                launch_wgrad(dt, dy, x, dw, M, N, K, wgrad_ws, c->d_zero_bias, st));
-  RESLIM_LAUNCH("colsum", 0, dM * dN * es + 4.0 * dN, launch_colsum(dt, dy, colp, db, M, N, st));
+  RESLIM_LAUNCH("gemm_dgrad", 2.0 * dM * dN * dK, dM * dN * es + dN * dK * es + dM * dK * es,
+                launch_gemm(c->cfg.dtype, EPI_BIAS_ACT, dy, w_t, c->d_zero_bias, dx, K, nullptr, 0, M, K, N, st));
+  return RESLIM_OK;
+}
+
+// parameter gradients of n linear layers: dW = dy^T x, db = column sums of dy
+int wgrad_impl(reslim_ctx *c, const char *fn, const WgradOp *op, int n, int M, void *wgrad_ws, hipStream_t st) {
+  const double es = static_cast<double>(act_size(c)), dM = M;
+  double flop = 0, bytes = 0;
+  for (int i = 0; i < n; ++i) {
+    flop += 2.0 * dM * op[i].N * op[i].K;
+    bytes += dM * (op[i].N + op[i].K) * es + 4.0 * op[i].N * (op[i].K + 1.0);
+  }
+  RESLIM_LAUNCH("gemm_wgrad", flop, bytes, launch_wgrad(c->cfg.dtype, op, n, M, wgrad_ws, st));
   return RESLIM_OK;
 }
 
@@ -173,20 +183,24 @@ extern "C" int reslim_linear_bwd(reslim_ctx *c, int32_t layer, int32_t which, co
   const int D = c->cfg.embed_dim, R = c->R;
   const int N = which == 0 ? 3 * D : (which == 2 ? R : D), K = which == 3 ? R : D;
   const void *w_t = which == 0 ? lw.wt_qkv : which == 1 ? lw.wt_proj : which == 2 ? lw.wt_fc1 : lw.wt_fc2;
-  const size_t wg = std::max<size_t>(wgrad_ws_bytes(c->cfg.dtype, rows, N, K), 256);
-  const size_t need = wg + align256(static_cast<size_t>(colsum_slabs(rows)) * N * sizeof(float));
+  const WgradOp op = {dy, x, dw, db, N, K};
+  const size_t need = std::max<size_t>(wgrad_ws_bytes(c->cfg.dtype, &op, 1, rows), 256);
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) || ws_bytes < need)
     return set_error(c, RESLIM_EWORKSPACE, std::string(fn) + ": workspace null, misaligned or too small");
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  return linear_bwd_impl(c, fn, x, dy, w_t, dx, dw, db, rows, N, K, workspace,
-                         reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + wg), st);
+  if (dx) {
+    const int rc = dgrad_impl(c, fn, dy, w_t, dx, rows, N, K, st);
+    if (rc != RESLIM_OK) return rc;
+  }
+  return wgrad_impl(c, fn, &op, 1, rows, workspace, st);
 }
 
 extern "C" int reslim_linear_bwd_workspace_bytes(const reslim_ctx *c, int32_t which, int32_t rows, size_t *out) {
   if (!c || !out || which < 0 || which > 3 || rows < 1) return RESLIM_EINVAL;
   const int D = c->cfg.embed_dim, R = c->R;
   const int N = which == 0 ? 3 * D : (which == 2 ? R : D), K = which == 3 ? R : D;
-  *out = std::max<size_t>(wgrad_ws_bytes(c->cfg.dtype, rows, N, K), 256) + align256(static_cast<size_t>(colsum_slabs(rows)) * N * sizeof(float));
+  const WgradOp op = {nullptr, nullptr, nullptr, nullptr, N, K};
+  *out = std::max<size_t>(wgrad_ws_bytes(c->cfg.dtype, &op, 1, rows), 256);
   return RESLIM_OK;
 }
 
@@ -259,25 +273,29 @@ static int block_bwd_impl(reslim_ctx *c, const char *fn, int layer, const float 
   const int64_t MD = static_cast<int64_t>(M) * D;
 
   // x_out = x_mid + fc2(gelu(fc1(ln2(x_mid))))
-  RESLIM_LAUNCH("to_act", 0, dM * dD * (4.0 + es), launch_to_act(dt, d_x_out, w.a, MD, st));
-  rc = linear_bwd_impl(c, fn, s.u, w.a, lw.wt_fc2, w.r, grads->w_fc2, grads->b_fc2, M, D, R, w.wgrad, w.colp, st);
+  RESLIM_LAUNCH("to_act", 0, dM * dD * (4.0 + es), launch_to_act(dt, d_x_out, w.out, MD, st));
+  rc = dgrad_impl(c, fn, w.out, lw.wt_fc2, w.fc1, M, D, R, st);
   if (rc != RESLIM_OK) return rc;
   // GELU's derivative as its own bandwidth-bound pass: fused into the epilogue of the GEMM above it cost more
   // than it saved (measured 0.32 ms against 0.12 + 0.09 at c1: the epilogue's arithmetic is not hidden)
-  RESLIM_LAUNCH("gelu_bwd", 0, 3.0 * static_cast<double>(M) * R * es, launch_gelu(dt, true, s.h, w.r, w.r, static_cast<int64_t>(M) * R, st));
-  rc = linear_bwd_impl(c, fn, s.ln2, w.r, lw.wt_fc1, w.b, grads->w_fc1, grads->b_fc1, M, R, D, w.wgrad, w.colp, st);
+  RESLIM_LAUNCH("gelu_bwd", 0, 3.0 * static_cast<double>(M) * R * es, launch_gelu(dt, true, s.h, w.fc1, w.fc1, static_cast<int64_t>(M) * R, st));
+  rc = dgrad_impl(c, fn, w.fc1, lw.wt_fc1, w.b, M, R, D, st);
   if (rc != RESLIM_OK) return rc;
   RESLIM_LAUNCH("layernorm_bwd", 0, dM * dD * (12.0 + 2.0 * es),
-                launch_layernorm_bwd(dt, s.x_mid, w.b, lw.ln2_g, d_x_out, w.g, w.a, w.lnp, grads->ln2_g, grads->ln2_b, M, D, st));
+                launch_layernorm_bwd(dt, s.x_mid, w.b, lw.ln2_g, d_x_out, w.g, w.mid, w.lnp, grads->ln2_g, grads->ln2_b, M, D, st));
   // x_mid = x_in + proj(tile_attention(qkv(ln1(x_in))))
-  rc = linear_bwd_impl(c, fn, s.attn, w.a, lw.wt_proj, w.b, grads->w_proj, grads->b_proj, M, D, D, w.wgrad, w.colp, st);
+  rc = dgrad_impl(c, fn, w.mid, lw.wt_proj, w.b, M, D, D, st);
   if (rc != RESLIM_OK) return rc;
   RESLIM_LAUNCH("tiles_attention_bwd", 10.0 * pairs * dD * batch, 8.0 * dM * dD * es,
-                launch_tiles_attention_bwd(c, s.qkv, s.attn, s.lse, w.b, w.r, batch, w.attn, dt == RESLIM_BF16, st, &sg));
-  rc = linear_bwd_impl(c, fn, s.ln1, w.r, lw.wt_qkv, w.a, grads->w_qkv, grads->b_qkv, M, 3 * D, D, w.wgrad, w.colp, st);
+                launch_tiles_attention_bwd(c, s.qkv, s.attn, s.lse, w.b, w.qkv, batch, w.attn, dt == RESLIM_BF16, st, &sg));
+  rc = dgrad_impl(c, fn, w.qkv, lw.wt_qkv, w.b, M, 3 * D, D, st);
   if (rc != RESLIM_OK) return rc;
   RESLIM_LAUNCH("layernorm_bwd", 0, dM * dD * (12.0 + es),
-                launch_layernorm_bwd(dt, x_in, w.a, lw.ln1_g, w.g, d_x_in, nullptr, w.lnp, grads->ln1_g, grads->ln1_b, M, D, st));
+                launch_layernorm_bwd(dt, x_in, w.b, lw.ln1_g, w.g, d_x_in, nullptr, w.lnp, grads->ln1_g, grads->ln1_b, M, D, st));
+  const WgradOp op[4] = {{w.out, s.u, grads->w_fc2, grads->b_fc2, D, R}, {w.fc1, s.ln2, grads->w_fc1, grads->b_fc1, R, D},
+                         {w.mid, s.attn, grads->w_proj, grads->b_proj, D, D}, {w.qkv, s.ln1, grads->w_qkv, grads->b_qkv, 3 * D, D}};
+  rc = wgrad_impl(c, fn, op, 4, M, w.wgrad, st);
+  if (rc != RESLIM_OK) return rc;
   return RESLIM_OK;
 }
 

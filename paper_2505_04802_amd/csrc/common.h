@@ -201,10 +201,16 @@ size_t tiles_attention_bwd_ws_bytes(const reslim_ctx *c, int batch, const SeqGeo
 hipError_t attention_bwd_init();
 // ---- training-side kernels
 hipError_t wgrad_init();
-size_t wgrad_ws_bytes(int dtype, int M, int N, int K);
-// dW[N, K] (fp32) = dY[M, N]^T X[M, K]; ws >= wgrad_ws_bytes; zeros: >= 16 zero bytes on the device
-hipError_t launch_wgrad(int dtype, const void *dy, const void *x, float *dw, int M, int N, int K, void *ws,
-                        const void *zeros, hipStream_t st);
+// Parameter gradients of linear layers over the same M tokens, up to kWgradMax of them at once:
+// dW[N, K] = dY[M, N]^T X[M, K] and db[N] = column sums of dY, both fp32; ws >= wgrad_ws_bytes
+constexpr int kWgradMax = 4;
+struct WgradOp {
+  const void *dy, *x;
+  float *dw, *db;
+  int N, K;
+};
+size_t wgrad_ws_bytes(int dtype, const WgradOp *op, int n_op, int M);
+hipError_t launch_wgrad(int dtype, const WgradOp *op, int n_op, int M, void *ws, hipStream_t st);
 int layernorm_bwd_slabs(int64_t rows);   // partial rows (of 2 D floats) launch_layernorm_bwd writes
 hipError_t launch_layernorm_bwd(int dtype, const float *x, const void *dy, const float *g, const float *res,
                                 float *dx_out, void *act_out, float *partial, float *dgamma, float *dbeta,

@@ -862,7 +862,7 @@ struct HeadWs {
   void *dP, *Af, *dAf;       // act [Mi, head_out], [Mi, D], [Mi, D]
   float *Xi, *dXi;           // [Mi, D]
   void *wgrad;
-  float *colp, *lnp, *resp;  // partial rows: column sums, LayerNorm parameters, residual path
+  float *lnp, *resp;         // partial rows: LayerNorm parameters, residual path
   int res_wg;
   size_t total;
 };
@@ -888,8 +888,8 @@ static HeadWs plan_head_ws(const reslim_ctx *c, int batch, void *base) {
   w.dAf = take(Mi * D * es);
   w.Xi = reinterpret_cast<float *>(take(Mi * D * 4));
   w.dXi = reinterpret_cast<float *>(take(Mi * D * 4));
-  w.wgrad = take(std::max<size_t>(wgrad_ws_bytes(c->cfg.dtype, static_cast<int>(Mi), c->head_out, c->cfg.embed_dim), 256));
-  w.colp = reinterpret_cast<float *>(take(static_cast<size_t>(colsum_slabs(Mi)) * ho * 4));
+  const WgradOp op = {nullptr, nullptr, nullptr, nullptr, c->head_out, c->cfg.embed_dim};
+  w.wgrad = take(std::max<size_t>(wgrad_ws_bytes(c->cfg.dtype, &op, 1, static_cast<int>(Mi)), 256));
   w.lnp = reinterpret_cast<float *>(take(static_cast<size_t>(layernorm_bwd_slabs(Mi)) * 2 * D * 4));
   int nbx, nby;
   w.res_wg = residual_grid(c, batch, &nbx, &nby);
@@ -907,7 +907,6 @@ struct EmbedWs {
   float *dz;                 // [Mi, D]
   void *dz_act, *o, *d_o;    // act [Mi, D]: gradient of the aggregated tokens, aggregated values, their gradient
   void *wgrad;
-  float *colp;
   float *a, *xt;             // [Mi, heads, V] softmax weights, [Mi, V (p2 + 1)] pixels
   float *E;                  // [Mi, n_e] d_o times the block-structured value table
   float *pU, *pA;            // partial rows of the folded tables' gradients
@@ -927,8 +926,8 @@ static EmbedWs plan_embed_ws(const reslim_ctx *c, int batch, void *base) {
   w.dz_act = take(Mi * D * es);
   w.o = take(Mi * D * es);
   w.d_o = take(Mi * D * es);
-  w.wgrad = take(std::max<size_t>(wgrad_ws_bytes(c->cfg.dtype, static_cast<int>(Mi), c->cfg.embed_dim, c->cfg.embed_dim), 256));
-  w.colp = reinterpret_cast<float *>(take(static_cast<size_t>(colsum_slabs(Mi)) * D * 4));
+  const WgradOp op = {nullptr, nullptr, nullptr, nullptr, c->cfg.embed_dim, c->cfg.embed_dim};
+  w.wgrad = take(std::max<size_t>(wgrad_ws_bytes(c->cfg.dtype, &op, 1, static_cast<int>(Mi)), 256));
   w.a = reinterpret_cast<float *>(take(Mi * heads * V * 4));
   w.xt = reinterpret_cast<float *>(take(Mi * V * (p2 + 1) * 4));
   w.E = reinterpret_cast<float *>(take(Mi * static_cast<size_t>(agg_table_rows(c)) * 4));
@@ -1026,9 +1025,8 @@ static int head_bwd_impl(reslim_ctx *c, const char *fn, const float *x, const fl
     const double dN = c->head_out, dK = D;
     RESLIM_LAUNCH("gemm_dgrad", 2.0 * dMi * dN * dK, dMi * dN * es + dN * dK * es + dMi * dK * es,
                   launch_gemm(dt, EPI_BIAS_ACT, w.dP, c->train.wt_head, c->d_zero_bias, w.dAf, D, nullptr, 0, Mi, D, c->head_out, st));
-    RESLIM_LAUNCH("gemm_wgrad", 2.0 * dMi * dN * dK, dMi * dN * es + dMi * dK * es + 4.0 * dN * dK,
-                  launch_wgrad(dt, w.dP, w.Af, g->w_head, Mi, c->head_out, D, w.wgrad, c->d_zero_bias, st));
-    RESLIM_LAUNCH("colsum", 0, dMi * dN * es + 4.0 * dN, launch_colsum(dt, w.dP, w.colp, g->b_head, Mi, c->head_out, st));
+    const WgradOp op = {w.dP, w.Af, g->w_head, g->b_head, c->head_out, D};
+    RESLIM_LAUNCH("gemm_wgrad", 2.0 * dMi * dN * dK, dMi * dN * es + dMi * dK * es + 4.0 * dN * dK, launch_wgrad(dt, &op, 1, Mi, w.wgrad, st));
   }
   // final LayerNorm backwards on the interior rows, then back into the tile-major stream (halo rows: zero)
   RESLIM_LAUNCH("gather", 0, 8.0 * dMi * dD, launch_gather_rows(tokens, c->d_interior_src, w.Xi, batch, c->N, static_cast<int>(c->n_h), D, st));
@@ -1070,9 +1068,8 @@ static int embed_bwd_impl(reslim_ctx *c, const char *fn, const float *x, const f
   {
     RESLIM_LAUNCH("gemm_dgrad", 2.0 * dMi * dD * dD, 2.0 * dMi * dD * es + dD * dD * es,
                   launch_gemm(dt, EPI_BIAS_ACT, w.dz_act, tm.wt_agg_wo, c->d_zero_bias, w.d_o, D, nullptr, 0, Mi, D, D, st));
-    RESLIM_LAUNCH("gemm_wgrad", 2.0 * dMi * dD * dD, 2.0 * dMi * dD * es + 4.0 * dD * dD,
-                  launch_wgrad(dt, w.dz_act, w.o, g->agg_wo, Mi, D, D, w.wgrad, c->d_zero_bias, st));
-    RESLIM_LAUNCH("colsum", 0, dMi * dD * es + 4.0 * dD, launch_colsum(dt, w.dz_act, w.colp, g->agg_bo, Mi, D, st));
+    const WgradOp op = {w.dz_act, w.o, g->agg_wo, g->agg_bo, D, D};
+    RESLIM_LAUNCH("gemm_wgrad", 2.0 * dMi * dD * dD, 2.0 * dMi * dD * es + 4.0 * dD * dD, launch_wgrad(dt, &op, 1, Mi, w.wgrad, st));
   }
   // folded aggregation backwards: logits, then the tables
   AggBwdArgs e;
