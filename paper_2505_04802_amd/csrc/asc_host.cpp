@@ -259,18 +259,21 @@ bool find_edges(const float *v, size_t stride, int H, int W, int low, int high, 
   return box_edges_base(v, stride, low, high, m);
 }
 
-// Edge pixels of every aligned square of 1, 2, 4 .. max_leaf patches, the grid padded with empty patches
+// Edge pixels of every aligned square of 1, 2, 4 .. max_leaf patches, as far as one fits into the grid (a node that
+// sticks out splits without a look at its count), the grid padded with empty patches
 struct Pyramid {
   std::vector<int32_t> n;
   std::vector<size_t> first;               // of every level
   int w0 = 0;                              // patches per row of level 0
   std::vector<uint16_t> col;
   void build(const Maps &m, int hp, int wp, int p, int max_leaf) {
-    const int hr = (hp + max_leaf - 1) / max_leaf * max_leaf;
-    w0 = (wp + max_leaf - 1) / max_leaf * max_leaf;
+    int most = 1;
+    while (most < max_leaf && most <= std::min(hp, wp) / 2) most *= 2;
+    const int hr = (hp + most - 1) / most * most;
+    w0 = (wp + most - 1) / most * most;
     first.clear();
     size_t total = 0;
-    for (int s = 1; s <= max_leaf; s *= 2) {
+    for (int s = 1; s <= most; s *= 2) {
       first.push_back(total);
       total += static_cast<size_t>(hr / s) * (w0 / s);
     }

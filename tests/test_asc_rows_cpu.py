@@ -43,3 +43,10 @@ def test_boxes_of_a_wide_field():
     img = np.cumsum(np.cumsum(r.standard_normal((2, 40, 94)), axis=-1), axis=-2).astype(np.float32)
     tiles = O.tiles_partition(20, 47, 3, 4, 2)[0]
     assert same(B.reslim_asc_build_tiles(img, 2, 3, 4, 2, 8, 1, 15, 45, 0.05), A.build_tiles(img, 2, tiles, 8, 1, 15, 45, 0.05, Wp=47))
+
+
+@pytest.mark.parametrize("max_leaf", [32, 64, 1 << 20, 1 << 30])
+def test_leaves_limited_by_the_grid_alone(max_leaf):
+    """A largest leaf beyond the grid: nodes that stick out split, and no table has its size."""
+    img = np.cumsum(np.random.default_rng(6).standard_normal((2, 46, 70)), axis=-1).astype(np.float32)
+    assert same(B.reslim_asc_build(img, 2, max_leaf, 1, 15, 45, 0.05), A.build(img, 2, max_leaf, 1, 15, 45, 0.05))
