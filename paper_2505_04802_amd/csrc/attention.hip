@@ -583,12 +583,12 @@ __global__ __launch_bounds__(256) void tiles_attention_f32_kernel(AttnArgs a, in
     float vv[NB][16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const int key = min(k0 + 8 * (r / 4) + 4 * hi + r % 4, n_t - 1);      // past the tile: finite values times zero
-      const float *vrow = base + 2 * a.D + static_cast<size_t>(key) * ld;
+      const int key = k0 + 8 * (r / 4) + 4 * hi + r % 4;                     // past the tile: zero times zero
+      const float *vrow = base + 2 * a.D + static_cast<size_t>(min(key, n_t - 1)) * ld;
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
         const int f = f0 + nb * 32 + l32;
-        vv[nb][r] = f < dh ? vrow[f] : 0.f;
+        vv[nb][r] = f < dh && key < n_t ? vrow[f] : 0.f;
       }
     }
     float top = -INFINITY;
@@ -598,13 +598,14 @@ __global__ __launch_bounds__(256) void tiles_attention_f32_kernel(AttnArgs a, in
       s[r] = key < n_t ? s[r] * scale : -INFINITY;
       top = fmaxf(top, s[r]);
     }
-    top = fmaxf(mx, fmaxf(top, __shfl_xor(top, 32)));        // finite: the block holds a key
-    const float alpha = expf(mx - top);
+    top = fmaxf(mx, fmaxf(top, __shfl_xor(top, 32)));
+    const float ref = top == -INFINITY ? 0.f : top;          // every score so far overflowed to -inf: weights of zero
+    const float alpha = expf(mx - ref);
     mx = top;
     float part = 0.f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      s[r] = expf(s[r] - mx);
+      s[r] = expf(s[r] - ref);
       part += s[r];
     }
     sum = fmaf(sum, alpha, part);

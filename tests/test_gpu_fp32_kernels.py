@@ -57,3 +57,27 @@ def test_input_gradient_of_a_linear_layer(D, which, rows, offset):
         ws = torch.empty(B.reslim_linear_bwd_workspace_bytes(m.ctx, which, rows), dtype=torch.uint8, device="cuda")
         B.reslim_linear_bwd(m.ctx, 0, which, x, dyd, dx, dw, db, rows, ws)
     assert float((dx.cpu().double() - ref).norm() / ref.norm()) <= 1e-5
+
+
+def test_attention_with_infinities():
+    """Scores that overflow to -inf have weight zero, also where a whole block of 32 keys does; an infinite value whose key
+    has weight is an infinite output in its own feature and nowhere else, also at the ragged end of a tile."""
+    cfg = BASE.with_(H=2 * 9, W=2 * 15)                     # 135 keys: the last block holds seven
+    n, D, dh = 135, 64, 32
+    r = np.random.default_rng(9)
+    qkv = r.standard_normal((cfg.batch, n, 3 * D)).astype(np.float32)
+    qkv[0, :, :dh] = np.abs(qkv[0, :, :dh])
+    qkv[0, 32:64, D:D + dh] = -np.inf                       # head 0, second block of keys
+    qkv[0, 128:, D:D + dh] = -np.inf                        # head 0, last block: after the first of the same wave
+    qkv[0, :32, D:D + dh] = -np.inf                         # and that one too
+    qkv[1, n - 1, 2 * D + 3] = np.inf
+    with B.Reslim(cfg, WL.make_weights(cfg)) as m:
+        assert m.n_h == n
+        out = m.attention_with_lse(torch.from_numpy(qkv).cuda())[0].cpu().numpy()
+    z = qkv[0].astype(np.float64)
+    keys = [k for k in range(n) if 64 <= k < 128]
+    s = z[:, :dh] @ z[keys, D:D + dh].T / np.sqrt(dh)
+    p = np.exp(s - s.max(1, keepdims=True))
+    assert O.rel_l2(out[0, :, :dh], p @ z[keys, 2 * D:2 * D + dh] / p.sum(1, keepdims=True)) <= 1e-5
+    assert np.isposinf(out[1, :, 3]).all()
+    assert np.isfinite(np.delete(out[1], 3, axis=1)).all()
