@@ -13,6 +13,7 @@
 namespace reslim {
 
 typedef uint16_t bf16_t;  // storage type of a bfloat16: the upper half of a float
+typedef float float4_any __attribute__((ext_vector_type(4), aligned(4)));  // four floats at any float's address
 
 // ---------------------------------------------------------------- device helpers
 __device__ __forceinline__ float bf16_to_f32(bf16_t h) {

@@ -35,6 +35,8 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
+// EVEN: no row ends inside a thread's four columns
+template <bool EVEN>
 __global__ __launch_bounds__(256) void bayes_loss_partial_kernel(LossArgs a) {
   __shared__ double red[2][4];
   const int t = threadIdx.x;
@@ -47,11 +49,13 @@ __global__ __launch_bounds__(256) void bayes_loss_partial_kernel(LossArgs a) {
   float data = 0.f, ax = 0.f, dg = 0.f;       // squared error; axial and diagonal absolute differences
   if (c0 < Wf) {
     // six prediction values of a row: columns c0-1 .. c0+4, clamped into the row (masked where used)
-    const bool vec = (Wf & 3) == 0;            // rows are 16-byte aligned and a thread's 4 columns lie inside
+    // 16-byte loads at any alignment wherever a thread's 4 columns lie inside (column by column everywhere, ragged rows
+    // took twice the time of even ones)
+    const bool vec = EVEN || Wf - c0 >= 4;
     auto load6 = [&](int r, float (&v)[6]) {
       const float *row = xp + static_cast<size_t>(r) * Wf;
       if (vec) {
-        const float4 own = *reinterpret_cast<const float4 *>(row + c0);
+        const float4_any own = *reinterpret_cast<const float4_any *>(row + c0);
         v[0] = row[max(c0 - 1, 0)];
         v[1] = own.x; v[2] = own.y; v[3] = own.z; v[4] = own.w;
         v[5] = row[min(c0 + 4, Wf - 1)];
@@ -69,7 +73,7 @@ __global__ __launch_bounds__(256) void bayes_loss_partial_kernel(LossArgs a) {
       const float lw = a.lat_w[r];
       float tv[4];
       if (vec) {
-        const float4 t4 = *reinterpret_cast<const float4 *>(trow + c0);
+        const float4_any t4 = *reinterpret_cast<const float4_any *>(trow + c0);
         tv[0] = t4.x; tv[1] = t4.y; tv[2] = t4.z; tv[3] = t4.w;
       } else {
 #pragma unroll
@@ -181,7 +185,9 @@ static int loss_launch(const float *pred, const float *target, const float *lat_
   a.pred = pred; a.target = target; a.lat_w = lat_w;
   a.partial = partial;
   a.Hf = Hf; a.Wf = Wf; a.strips_x = sx; a.strips_y = sy;
-  bayes_loss_partial_kernel<<<dim3(static_cast<unsigned>(sx * sy), static_cast<unsigned>(planes)), dim3(256), 0, st>>>(a);
+  const dim3 grid(static_cast<unsigned>(sx * sy), static_cast<unsigned>(planes));
+  if (Wf % 4 == 0) bayes_loss_partial_kernel<true><<<grid, dim3(256), 0, st>>>(a);
+  else bayes_loss_partial_kernel<false><<<grid, dim3(256), 0, st>>>(a);
   if (hipGetLastError() != hipSuccess) return RESLIM_EHIP;
   const double count = static_cast<double>(planes) * Hf * Wf;
   bayes_loss_final_kernel<<<dim3(1), dim3(256), 0, st>>>(partial, groups, count, static_cast<double>(tv_weight), out3);

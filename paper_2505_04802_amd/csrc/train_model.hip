@@ -27,59 +27,48 @@ namespace reslim {
 hipError_t launch_partial_reduce(const float *partial, float *out, int n_part, int64_t stride, int64_t n, hipStream_t st);
 
 // ------------------------------------------------------------------ loss gradient
+// Bound by memory: prediction and target read once, the gradient written once.  A thread owns four neighbouring columns and
+// walks down RB rows with the three rows it needs in registers, so a pixel costs a quarter of a 16-byte load and half a
+// 4-byte load of the prediction instead of nine 4-byte loads.  Rows of any length and alignment: the 16-byte accesses are
+// of a type aligned to 4 bytes, which the hardware takes as they are; only the thread at a ragged row's end goes column by
+// column (EVEN: there is none; its branches cost 4 % at 16 planes of 512 x 1024).  One thread per pixel took 9.2 ms at c3
+// where this takes 2.5; loss and gradient of 32 planes of 1024 x 2050 took 818 us with ragged rows left to one thread
+// per pixel, and take 297.
+// A neighbour outside the plane is held as NaN: every comparison with it is false, so its sign term is zero, which is
+// what leaving it out means.  The sums of signs are small integers, exact in any order.
+template <int RB, bool EVEN>
 __global__ __launch_bounds__(256) void bayes_loss_bwd_kernel(const float *__restrict__ pred, const float *__restrict__ target,
                                                              const float *__restrict__ lat_w, float *__restrict__ d_pred,
                                                              int Hf, int Wf, float data_f, float tv_f) {
-  // one thread per pixel, rows of a plane along blockIdx.y, planes along blockIdx.z
-  const int c = blockIdx.x * 256 + threadIdx.x, r = blockIdx.y;
-  if (c >= Wf) return;
-  const size_t plane = static_cast<size_t>(blockIdx.z) * Hf * Wf;
-  const float *xp = pred + plane;
-  const float x = xp[static_cast<size_t>(r) * Wf + c];
-  float ax = 0.f, dg = 0.f;                      // sums of signs towards the axial / diagonal neighbours
-  auto sgn = [](float v) { return static_cast<float>((v > 0.f) - (v < 0.f)); };
-#pragma unroll
-  for (int dy = -1; dy <= 1; ++dy)
-#pragma unroll
-    for (int dx = -1; dx <= 1; ++dx) {
-      if (dy == 0 && dx == 0) continue;
-      const int rr = r + dy, cc = c + dx;
-      if (rr < 0 || rr >= Hf || cc < 0 || cc >= Wf) continue;
-      const float s = sgn(x - xp[static_cast<size_t>(rr) * Wf + cc]);
-      if (dy == 0 || dx == 0) ax += s; else dg += s;
-    }
-  const float t = target[plane + static_cast<size_t>(r) * Wf + c];
-  d_pred[plane + static_cast<size_t>(r) * Wf + c] = data_f * lat_w[r] * (x - t) + tv_f * (ax + dg * 0.70710678118654752440f);
-}
-
-// The same for row lengths that are multiples of four: a thread owns four neighbouring columns and
-// walks down RB rows with the three rows it needs in registers, so a pixel costs a quarter of a
-// 16-byte load and half a 4-byte load of the prediction instead of nine 4-byte loads (c3: 9.2 ms
-// with one thread per pixel).  A neighbour outside the plane is held as NaN: every comparison with
-// it is false, so its sign term is zero, which is what leaving it out means.  The sums of signs are
-// small integers, exact in any order.
-template <int RB>
-__global__ __launch_bounds__(256) void bayes_loss_bwd4_kernel(const float *__restrict__ pred, const float *__restrict__ target,
-                                                              const float *__restrict__ lat_w, float *__restrict__ d_pred,
-                                                              int Hf, int Wf, float data_f, float tv_f) {
-  const int c0 = (blockIdx.x * 256 + threadIdx.x) * 4;
-  if (c0 >= Wf) return;
+  const int64_t first = (static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x) * 4;
+  if (first >= Wf) return;
+  const int c0 = static_cast<int>(first), left = Wf - c0;      // columns from this thread's first to the row's end
   const size_t plane = static_cast<size_t>(blockIdx.z) * Hf * Wf;
   const float *xp = pred + plane;
   const int r_begin = blockIdx.y * RB, r_end = min(Hf, r_begin + RB);
   const float out_of_plane = __builtin_nanf("");
   auto sgn = [](float v) { return static_cast<float>((v > 0.f) - (v < 0.f)); };
+  auto load4 = [&](const float *p, float (&v)[4]) {
+    if (EVEN || left >= 4) {
+      const float4_any m = *reinterpret_cast<const float4_any *>(p);
+      v[0] = m.x; v[1] = m.y; v[2] = m.z; v[3] = m.w;
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = k < left ? p[k] : out_of_plane;
+    }
+  };
   auto load_row = [&](int r, float (&v)[6]) {      // columns c0 - 1 .. c0 + 4 of row r
     if (r < 0 || r >= Hf) {
 #pragma unroll
       for (int k = 0; k < 6; ++k) v[k] = out_of_plane;
       return;
     }
-    const float *row = xp + static_cast<size_t>(r) * Wf;
-    const float4 m = *reinterpret_cast<const float4 *>(row + c0);
-    v[1] = m.x; v[2] = m.y; v[3] = m.z; v[4] = m.w;
-    v[0] = c0 > 0 ? row[c0 - 1] : out_of_plane;
-    v[5] = c0 + 4 < Wf ? row[c0 + 4] : out_of_plane;
+    const float *row = xp + static_cast<size_t>(r) * Wf + c0;
+    float m[4];
+    load4(row, m);
+    v[0] = c0 > 0 ? row[-1] : out_of_plane;
+    v[1] = m[0]; v[2] = m[1]; v[3] = m[2]; v[4] = m[3];
+    v[5] = left > 4 ? row[4] : out_of_plane;
   };
   float up[6], mid[6], dn[6];
   load_row(r_begin - 1, up);
@@ -90,10 +79,9 @@ __global__ __launch_bounds__(256) void bayes_loss_bwd4_kernel(const float *__res
     if (r >= r_end) break;
     load_row(r + 1, dn);
     const size_t at = plane + static_cast<size_t>(r) * Wf + c0;
-    const float4 t4 = *reinterpret_cast<const float4 *>(target + at);
-    const float t[4] = {t4.x, t4.y, t4.z, t4.w};
+    float t[4], o[4];
+    load4(target + at, t);
     const float lw = data_f * lat_w[r];
-    float o[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const float x = mid[k + 1];
@@ -101,7 +89,13 @@ __global__ __launch_bounds__(256) void bayes_loss_bwd4_kernel(const float *__res
       const float dg = sgn(x - up[k]) + sgn(x - up[k + 2]) + sgn(x - dn[k]) + sgn(x - dn[k + 2]);
       o[k] = lw * (x - t[k]) + tv_f * (ax + dg * 0.70710678118654752440f);
     }
-    *reinterpret_cast<float4 *>(d_pred + at) = make_float4(o[0], o[1], o[2], o[3]);
+    if (EVEN || left >= 4) {
+      *reinterpret_cast<float4_any *>(d_pred + at) = float4_any{o[0], o[1], o[2], o[3]};
+    } else {
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        if (k < left) d_pred[at + k] = o[k];
+    }
 #pragma unroll
     for (int k = 0; k < 6; ++k) { up[k] = mid[k]; mid[k] = dn[k]; }
   }
@@ -1147,15 +1141,25 @@ extern "C" int reslim_bayes_loss_bwd(const float *pred, const float *target, con
   const double norm = 4.0 + 4.0 / 1.4142135623730951;
   const float data_f = static_cast<float>(2.0 * upstream / count);
   const float tv_f = static_cast<float>(2.0 * static_cast<double>(upstream) * tv_weight / (norm * count));
-  const bool aligned = Wf % 4 == 0 && (reinterpret_cast<uintptr_t>(pred) | reinterpret_cast<uintptr_t>(target) | reinterpret_cast<uintptr_t>(d_pred)) % 16 == 0;
-  if (aligned) {
-    constexpr int RB = 8;
-    const dim3 grid((Wf / 4 + 255) / 256, (Hf + RB - 1) / RB, batch * vars);
-    bayes_loss_bwd4_kernel<RB><<<grid, dim3(256), 0, static_cast<hipStream_t>(hip_stream)>>>(pred, target, lat_w, d_pred, Hf, Wf, data_f, tv_f);
-  } else {
-    const dim3 grid((Wf + 255) / 256, Hf, batch * vars);
-    bayes_loss_bwd_kernel<<<grid, dim3(256), 0, static_cast<hipStream_t>(hip_stream)>>>(pred, target, lat_w, d_pred, Hf, Wf, data_f, tv_f);
-  }
+  // Work-groups of whole waves over a row, as even as they go.  Eight rows a thread where that still gives every CU eight waves
+  // (a row is read 1.25 times), two and then one below that: there the chain of rows is what takes the time 16 planes of 180 x 360, loss and
+  // gradient: 18.9 us with eight rows, 17.7 with two.
+  const int64_t quads = (static_cast<int64_t>(Wf) + 3) / 4, groups = (quads + 255) / 256;
+  const dim3 block(static_cast<unsigned>(((quads + groups - 1) / groups + 63) / 64 * 64));
+  const int64_t waves = (quads + 63) / 64 * batch * vars, enough = 2048;
+#define RESLIM_LOSS_BWD(RB, EVEN)                                                                                             \
+  bayes_loss_bwd_kernel<RB, EVEN><<<dim3(static_cast<unsigned>(groups), (Hf + RB - 1) / RB, batch * vars), block, 0,          \
+                                    static_cast<hipStream_t>(hip_stream)>>>(pred, target, lat_w, d_pred, Hf, Wf, data_f, tv_f)
+#define RESLIM_LOSS_BWD_ROWS(EVEN)                                       \
+  do {                                                                   \
+    if (waves * ((Hf + 7) / 8) >= enough) RESLIM_LOSS_BWD(8, EVEN);      \
+    else if (waves * ((Hf + 1) / 2) >= enough) RESLIM_LOSS_BWD(2, EVEN); \
+    else RESLIM_LOSS_BWD(1, EVEN);                                       \
+  } while (0)
+  if (Wf % 4 == 0) RESLIM_LOSS_BWD_ROWS(true);
+  else RESLIM_LOSS_BWD_ROWS(false);
+#undef RESLIM_LOSS_BWD_ROWS
+#undef RESLIM_LOSS_BWD
   return hipGetLastError() == hipSuccess ? RESLIM_OK : RESLIM_EHIP;
 }
 
