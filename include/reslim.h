@@ -486,8 +486,9 @@ int reslim_asc_edges(const float *image, int32_t H, int32_t W, int32_t canny_low
  * produces for this context's grid and tiling -- per (sample, tile) sequence: power-of-two
  * squares aligned to the tile's haloed box, inside it, covering each of its patches exactly
  * once; patch_leaf naming, for every patch, the leaf of the owning tile that holds it:
- * RESLIM_EINVAL otherwise, the kernels rely on it -- and copies it to the device (allocates;
- * a synchronous copy).  All pointers host; sample_off has n_sequences + 1
+ * RESLIM_EINVAL otherwise, the kernels rely on it -- and copies it to the device (complete
+ * when the call returns; the device memory and its staging come from at most four blocks the
+ * context keeps, or are allocated).  All pointers host; sample_off has n_sequences + 1
  * entries and n_sequences must be batch * T (T tiles of the context; sequences
  * sample-major).  *out is NULL on failure; destroy the plan before its context.
  * RESLIM_ESHAPE if n_sequences != batch * T or embed_dim % 4 != 0. */

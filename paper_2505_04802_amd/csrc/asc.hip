@@ -4,8 +4,6 @@
 // folded into the final LayerNorm's row map, then the usual head and residual path.
 #include <algorithm>
 #include <cstring>
-#include <memory>
-#include <new>
 #include <string>
 #include <vector>
 
@@ -155,12 +153,106 @@ __global__ __launch_bounds__(256) void asc_image_kernel(const float *__restrict_
   }
 }
 
-// The tables of a plan lie in one allocation of the plan's own.  Keeping the memory for the next plan (events instead of
-// the free that waits for the device) gave wrong outputs now and then with plans in flight on two streams.
-static void asc_free(reslim_asc_plan *pl) {
-  if (!pl) return;
-  if (pl->d_tables) (void)hipFree(pl->d_tables);       // waits for the device
-  delete pl;
+// ------------------------------------------------------------------ plan memory
+static void block_free(PlanBlock *b) {
+  if (!b) return;
+  (void)hipFree(b->dev);                               // waits for the device
+  (void)hipHostFree(b->host);
+  for (hipEvent_t e : b->ev)
+    if (e) (void)hipEventDestroy(e);
+  delete b;
+}
+
+void plan_pool_free(PlanPool &pool) {
+  for (PlanBlock *b : pool.idle) block_free(b);
+  pool.idle.clear();
+  if (pool.upload) (void)hipStreamDestroy(pool.upload);
+  pool.upload = nullptr;
+}
+
+void plan_used(const reslim_asc_plan *plan, hipStream_t st) {
+  reslim_asc_plan *pl = const_cast<reslim_asc_plan *>(plan);
+  PlanBlock *b = pl->block;
+  std::lock_guard<std::mutex> hold(pl->lock);
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    b->foreign = true;                                 // a graph may replay the reads at any later time
+    return;
+  }
+  int i = 0;
+  while (i < b->n_ev && b->stream[i] != st) ++i;
+  if (i == 4 || (!b->ev[i] && hipEventCreateWithFlags(&b->ev[i], hipEventDisableTiming) != hipSuccess) ||
+      hipEventRecord(b->ev[i], st) != hipSuccess) {
+    (void)hipGetLastError();
+    b->foreign = true;
+    return;
+  }
+  b->stream[i] = st;
+  b->n_ev = std::max(b->n_ev, i + 1);
+}
+
+// A block of at least `bytes`, idle on the device: a kept one, or a new one.  With kMost kept blocks that are all still
+// in use the oldest is waited for, so a host that runs ahead of the device cannot pile up memory.
+static hipError_t block_take(reslim_ctx *c, size_t bytes, PlanBlock **out) {
+  *out = nullptr;
+  PlanPool &pool = c->plans;
+  PlanBlock *b = nullptr;
+  {
+    std::lock_guard<std::mutex> hold(pool.lock);
+    if (!pool.upload) {
+      const hipError_t e = hipStreamCreateWithFlags(&pool.upload, hipStreamNonBlocking);
+      if (e != hipSuccess) return e;
+    }
+    for (size_t k = 0; k < pool.idle.size() && !b; ++k) {
+      bool done = true;
+      for (int i = 0; i < pool.idle[k]->n_ev && done; ++i) done = hipEventQuery(pool.idle[k]->ev[i]) == hipSuccess;
+      if (!done) (void)hipGetLastError();
+      if (done) {
+        b = pool.idle[k];
+        pool.idle.erase(pool.idle.begin() + k);
+      }
+    }
+    if (!b && pool.idle.size() == PlanPool::kMost) {
+      b = pool.idle.front();
+      pool.idle.erase(pool.idle.begin());
+    }
+  }
+  if (b)
+    for (int i = 0; i < b->n_ev; ++i)
+      if (hipEventSynchronize(b->ev[i]) != hipSuccess) b->foreign = true;
+  if (b && (b->cap < bytes || b->foreign)) {
+    block_free(b);
+    b = nullptr;
+  }
+  if (!b) {
+    b = new (std::nothrow) PlanBlock;
+    if (!b) return hipErrorOutOfMemory;
+    b->cap = (bytes + (bytes >> 2) + 65535) / 65536 * 65536;      // the next batch's tree may be somewhat larger
+    hipError_t e = hipMalloc(reinterpret_cast<void **>(&b->dev), b->cap);
+    if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void **>(&b->host), b->cap, hipHostMallocDefault);
+    if (e != hipSuccess) {
+      block_free(b);
+      return e;
+    }
+  }
+  b->n_ev = 0;
+  *out = b;
+  return hipSuccess;
+}
+
+static void block_give(reslim_ctx *c, PlanBlock *b) {
+  PlanBlock *drop = b;
+  if (!b->foreign) {
+    std::lock_guard<std::mutex> hold(c->plans.lock);
+    drop = nullptr;
+    if (c->plans.idle.size() == PlanPool::kMost) {
+      drop = c->plans.idle.front();
+      c->plans.idle.erase(c->plans.idle.begin());
+    }
+    c->plans.idle.push_back(b);
+  }
+  block_free(drop);
 }
 
 static int asc_check(reslim_ctx *c, const reslim_asc_plan *pl, const char *fn) {
@@ -193,19 +285,26 @@ extern "C" int reslim_asc_plan_create(reslim_ctx *c, int32_t batch, const int32_
   // aligned to the box, and patch_leaf must name, for every patch, its leaf in the tile that
   // owns it: the kernels trust the table.
   if (sample_off[0] != 0 || sample_off[n_seq] != n_leaves) return set_error(c, RESLIM_EINVAL, std::string(fn) + ": sample_off does not span the leaves");
-  // one allocation for all tables, filled on the host and copied at once; the leaf of every tile-major token is needed
+  // one block for all tables, filled in its pinned half and copied at once; the leaf of every tile-major token is needed
   // for the check anyway and goes along where tiles overlap (with one tile it is patch_leaf itself)
   const int64_t cells = batch * c->n_h;
   size_t at = 0;
   auto place = [&](size_t bytes) { const size_t o = at; at += align256(bytes); return o; };
   const size_t o_seq = place(n_seq * sizeof(tile_desc)), o_seqof = place(n_leaves * 4), o_leaf = place(n_leaves * 16), o_patch = place(batch * N * 4);
   const size_t o_owner = place(cells * 4), upload = T != 1 ? at : o_owner;
-  std::unique_ptr<unsigned char[]> host(new (std::nothrow) unsigned char[at]);
-  if (!host) return set_error(c, RESLIM_ENOMEM, std::string(fn) + ": host allocation failed");
-  auto refuse = [&](const char *why) { return set_error(c, RESLIM_EINVAL, std::string(fn) + ": " + why); };
-  tile_desc *seq = reinterpret_cast<tile_desc *>(host.get() + o_seq);
-  int32_t *seq_of = reinterpret_cast<int32_t *>(host.get() + o_seqof), *leaf = reinterpret_cast<int32_t *>(host.get() + o_leaf);
-  int32_t *owner = reinterpret_cast<int32_t *>(host.get() + o_owner);
+  PlanBlock *blk = nullptr;
+  hipError_t e = block_take(c, at, &blk);
+  auto device_error = [&]() {
+    return set_error(c, e == hipErrorOutOfMemory ? RESLIM_ENOMEM : RESLIM_EHIP, std::string(fn) + ": " + hipGetErrorString(e));
+  };
+  if (e != hipSuccess) return device_error();
+  auto refuse = [&](const char *why) {
+    block_give(c, blk);
+    return set_error(c, RESLIM_EINVAL, std::string(fn) + ": " + why);
+  };
+  tile_desc *seq = reinterpret_cast<tile_desc *>(blk->host + o_seq);
+  int32_t *seq_of = reinterpret_cast<int32_t *>(blk->host + o_seqof), *leaf = reinterpret_cast<int32_t *>(blk->host + o_leaf);
+  int32_t *owner = reinterpret_cast<int32_t *>(blk->host + o_owner);
   std::memset(owner, 0xff, cells * 4);
   int max_n = 0;
   double pairs = 0;
@@ -244,21 +343,21 @@ extern "C" int reslim_asc_plan_create(reslim_ctx *c, int32_t batch, const int32_
     max_n = std::max(max_n, seq[q].n_tok);
     pairs += static_cast<double>(hi - lo) * static_cast<double>(hi - lo);
   }
-  std::memcpy(host.get() + o_patch, patch_leaf, batch * N * 4);
-  reslim_asc_plan *pl = new (std::nothrow) reslim_asc_plan;
-  if (!pl) return set_error(c, RESLIM_ENOMEM, std::string(fn) + ": host allocation failed");
-  hipError_t e = hipMalloc(reinterpret_cast<void **>(&pl->d_tables), upload);
-  if (e == hipSuccess) e = hipMemcpy(pl->d_tables, host.get(), upload, hipMemcpyHostToDevice);
-  if (e != hipSuccess) {
-    asc_free(pl);
-    return set_error(c, e == hipErrorOutOfMemory ? RESLIM_ENOMEM : RESLIM_EHIP, std::string(fn) + ": " + hipGetErrorString(e));
+  std::memcpy(blk->host + o_patch, patch_leaf, batch * N * 4);
+  e = hipMemcpyAsync(blk->dev, blk->host, upload, hipMemcpyHostToDevice, c->plans.upload);
+  if (e == hipSuccess) e = hipStreamSynchronize(c->plans.upload);      // the tables are there before any stream reads them
+  reslim_asc_plan *pl = e == hipSuccess ? new (std::nothrow) reslim_asc_plan : nullptr;
+  if (!pl) {
+    blk->foreign = true;
+    block_give(c, blk);
+    return e != hipSuccess ? device_error() : set_error(c, RESLIM_ENOMEM, std::string(fn) + ": host allocation failed");
   }
-  pl->ctx = c; pl->batch = batch; pl->L = n_leaves;
-  pl->d_seq = reinterpret_cast<tile_desc *>(pl->d_tables + o_seq);
-  pl->d_seq_of_leaf = reinterpret_cast<int32_t *>(pl->d_tables + o_seqof);
-  pl->d_leaf = reinterpret_cast<int32_t *>(pl->d_tables + o_leaf);
-  pl->d_patch_leaf = reinterpret_cast<int32_t *>(pl->d_tables + o_patch);
-  pl->d_owner = T != 1 ? reinterpret_cast<int32_t *>(pl->d_tables + o_owner) : nullptr;
+  pl->ctx = c; pl->batch = batch; pl->L = n_leaves; pl->block = blk;
+  pl->d_seq = reinterpret_cast<tile_desc *>(blk->dev + o_seq);
+  pl->d_seq_of_leaf = reinterpret_cast<int32_t *>(blk->dev + o_seqof);
+  pl->d_leaf = reinterpret_cast<int32_t *>(blk->dev + o_leaf);
+  pl->d_patch_leaf = reinterpret_cast<int32_t *>(blk->dev + o_patch);
+  pl->d_owner = T != 1 ? reinterpret_cast<int32_t *>(blk->dev + o_owner) : nullptr;
   pl->geom.d_tiles = pl->d_seq;
   pl->geom.d_tile_of_tok = pl->d_seq_of_leaf;
   pl->geom.T = static_cast<int>(n_seq);
@@ -270,7 +369,11 @@ extern "C" int reslim_asc_plan_create(reslim_ctx *c, int32_t batch, const int32_
   return RESLIM_OK;
 }
 
-extern "C" void reslim_asc_plan_destroy(reslim_asc_plan *plan) { asc_free(plan); }
+extern "C" void reslim_asc_plan_destroy(reslim_asc_plan *plan) {
+  if (!plan) return;
+  block_give(plan->ctx, plan->block);
+  delete plan;
+}
 
 extern "C" int reslim_asc_image(reslim_ctx *c, const float *tokens, const float *w_img, const float *b_img, float *image,
                                 int32_t batch, void *hip_stream) {
@@ -293,6 +396,7 @@ extern "C" int reslim_asc_compress(reslim_ctx *c, const reslim_asc_plan *plan, c
   if (rc != RESLIM_OK) return rc;
   if (!tokens || !tokens_c) return set_error(c, RESLIM_EINVAL, std::string(fn) + ": null buffer");
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
+  const PlanUse use{plan, st};
   asc_compress_kernel<true><<<dim3(static_cast<unsigned>(plan->L)), dim3(256), 0, st>>>(tokens, plan->d_leaf, tokens_c, c->Wp, c->cfg.embed_dim);
   RESLIM_TRY("asc_compress", hipGetLastError());
   return RESLIM_OK;
@@ -305,6 +409,7 @@ static int asc_move(reslim_ctx *c, const reslim_asc_plan *plan, const char *fn, 
   if (rc != RESLIM_OK) return rc;
   if (!src || !dst) return set_error(c, RESLIM_EINVAL, std::string(fn) + ": null buffer");
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
+  const PlanUse use{plan, st};
   const int D = c->cfg.embed_dim;
   const int64_t patches = static_cast<int64_t>(plan->batch) * c->N;
   const dim3 pg(static_cast<unsigned>((patches + 3) / 4));
@@ -348,6 +453,7 @@ extern "C" int reslim_asc_forward(reslim_ctx *c, const reslim_asc_plan *plan, co
   if (rc != RESLIM_OK) return rc;
   const Workspace w = plan_workspace(c, batch, workspace);
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
+  const PlanUse use{plan, st};
   const int D = c->cfg.embed_dim, dt = c->cfg.dtype;
   const int Mi = batch * c->N;
   const double es = static_cast<double>(act_size(c)), dMi = Mi, dD = D, dO = c->head_out, dL = static_cast<double>(plan->L);

@@ -248,6 +248,7 @@ extern "C" int reslim_asc_block_fwd_train(reslim_ctx *c, const reslim_asc_plan *
                                           void *hip_stream) {
   if (!c) return RESLIM_EINVAL;
   if (!plan || plan->ctx != c) return set_error(c, RESLIM_EINVAL, "reslim_asc_block_fwd_train: null plan or plan of another context");
+  const PlanUse use{plan, static_cast<hipStream_t>(hip_stream)};
   return block_fwd_train_impl(c, "reslim_asc_block_fwd_train", layer, x_in, x_out, saved, saved_bytes, 1, workspace, ws_bytes,
                               hip_stream, plan->geom);
 }
@@ -311,6 +312,7 @@ extern "C" int reslim_asc_block_bwd(reslim_ctx *c, const reslim_asc_plan *plan, 
                                     const reslim_block_grads *grads, void *workspace, size_t ws_bytes, void *hip_stream) {
   if (!c) return RESLIM_EINVAL;
   if (!plan || plan->ctx != c) return set_error(c, RESLIM_EINVAL, "reslim_asc_block_bwd: null plan or plan of another context");
+  const PlanUse use{plan, static_cast<hipStream_t>(hip_stream)};
   return block_bwd_impl(c, "reslim_asc_block_bwd", layer, x_in, saved, saved_bytes, d_x_out, d_x_in, grads, 1, workspace,
                         ws_bytes, hip_stream, plan->geom);
 }

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -55,6 +56,24 @@ struct TrainModel {
   int n_e = 0;                 // heads * V * (p2 + 1) rounded up to a multiple of 8
 };
 
+// Device memory and pinned staging of a compression plan.  A context keeps a few of them between plans, because a user
+// makes one plan per batch of fields: allocating and freeing them each time took longer than the tables' upload, and a
+// free waits for the whole device.  The events mark the work that last used the block, one per stream that did.
+struct PlanBlock {
+  unsigned char *dev = nullptr, *host = nullptr;
+  size_t cap = 0;
+  hipEvent_t ev[4] = {};
+  hipStream_t stream[4] = {};
+  int n_ev = 0;              // pairs in use
+  bool foreign = false;      // used by a captured graph or by more streams than there are events: freed, not kept
+};
+struct PlanPool {
+  static constexpr size_t kMost = 4;
+  std::mutex lock;
+  std::vector<PlanBlock *> idle;
+  hipStream_t upload = nullptr;      // does not wait for the caller's streams
+};
+
 }  // namespace reslim
 
 struct reslim_ctx {
@@ -86,6 +105,7 @@ struct reslim_ctx {
   float *d_w_res, *d_b_res;                  // [C, C, 3, 3], [C]
   int32_t *d_out_var_idx;
   reslim::TrainModel train;
+  reslim::PlanPool plans;
   std::vector<void *> allocs;                // everything to hipFree
   std::string err;
   // optional per-launch timing (reslim_profile_*): events are created up front
@@ -222,13 +242,26 @@ struct reslim_asc_plan {
   int batch = 0;
   int64_t L = 0;                         // leaves of the whole batch
   reslim::SeqGeom geom{};
-  unsigned char *d_tables = nullptr;     // holds the tables below
+  reslim::PlanBlock *block = nullptr;    // holds the tables below
+  std::mutex lock;                       // of the block's events
   tile_desc *d_seq = nullptr;            // [batch * T] one entry per (sample, tile): tok_off, n_tok
   int32_t *d_seq_of_leaf = nullptr;      // [L]
   int32_t *d_leaf = nullptr;             // [L][4]: first patch row (b*N + y0*Wp + x0), side, unused, unused
   int32_t *d_patch_leaf = nullptr;       // [batch * N] leaf of the owning tile
   int32_t *d_owner = nullptr;            // contexts with tiles: [batch * n_h] leaf of every tile-major token
 };
+
+namespace reslim {
+// held by an entry point that launches kernels on `st` which read the plan's tables: marks the use when it ends,
+// also after an error half way
+void plan_used(const reslim_asc_plan *plan, hipStream_t st);
+struct PlanUse {
+  const reslim_asc_plan *plan;
+  hipStream_t st;
+  ~PlanUse() { plan_used(plan, st); }
+};
+void plan_pool_free(PlanPool &pool);
+}  // namespace reslim
 
 #define RESLIM_TRY(what, expr)                                   \
   do {                                                           \

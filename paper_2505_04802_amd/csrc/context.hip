@@ -100,6 +100,7 @@ extern "C" void reslim_destroy(reslim_ctx *ctx) {
   if (!ctx) return;
   for (void *p : ctx->allocs) (void)hipFree(p);
   for (hipEvent_t e : ctx->prof_ev) (void)hipEventDestroy(e);
+  plan_pool_free(ctx->plans);
   delete ctx;
 }
 

@@ -1,5 +1,5 @@
-"""Compression plans made and given back right after the call that uses them, on two streams in turn: a table must never be
-overwritten or freed under a kernel."""
+"""Compression plans made and given back while the kernels that read the previous ones are still queued: the memory of
+a plan is kept for the next one, and a table must never be overwritten under a kernel."""
 import numpy as np
 import pytest
 import torch
