@@ -42,7 +42,7 @@ def test_plans_in_flight(tiled):
             side = [torch.cuda.current_stream(), torch.cuda.Stream()]
             side[1].wait_stream(side[0])
             wss = [m.ws, torch.empty_like(m.ws)]
-            ys = [torch.full(shape, float("nan"), device="cuda") for _ in trees]
+            ys = [torch.full(shape, float("nan"), dtype=torch.float32, device="cuda") for _ in trees]
             torch.cuda.synchronize()
             for i in range(len(trees)):
                 one(i, ys[i], wss[i % 2], side[i % 2])

@@ -45,15 +45,15 @@ def test_input_gradient_of_a_linear_layer(D, which, rows, offset):
     cfg = BASE.with_(embed_dim=D, heads=1, mlp_ratio=2)
     w = WL.make_weights(cfg, std=0.1)
     n, k, name = ((3 * D, D, "w_qkv"), (D, D, "w_proj"), (2 * D, D, "w_fc1"))[which]
-    buf = torch.randn(rows * n + 8, generator=torch.Generator().manual_seed(rows))
+    buf = torch.randn(rows * n + 8, dtype=torch.float32, generator=torch.Generator().manual_seed(rows))
     dy = buf[offset:offset + rows * n].view(rows, n)
     ref = dy.double() @ torch.from_numpy(w[name][0]).double()
     with B.Reslim(cfg, w) as m:
         B.reslim_train_prepare(m.ctx)
         dyd = buf.cuda()[offset:offset + rows * n].view(rows, n)
-        x = torch.zeros((rows, k), device="cuda")
-        dx = torch.full((rows, k), float("nan"), device="cuda")
-        dw, db = torch.empty((n, k), device="cuda"), torch.empty(n, device="cuda")
+        x = torch.zeros((rows, k), dtype=torch.float32, device="cuda")
+        dx = torch.full((rows, k), float("nan"), dtype=torch.float32, device="cuda")
+        dw, db = torch.empty((n, k), dtype=torch.float32, device="cuda"), torch.empty(n, dtype=torch.float32, device="cuda")
         ws = torch.empty(B.reslim_linear_bwd_workspace_bytes(m.ctx, which, rows), dtype=torch.uint8, device="cuda")
         B.reslim_linear_bwd(m.ctx, 0, which, x, dyd, dx, dw, db, rows, ws)
     assert float((dx.cpu().double() - ref).norm() / ref.norm()) <= 1e-5

@@ -22,7 +22,7 @@ def test_rows(shape, offset):
     target = r.standard_normal(shape).astype(np.float32)
     lw = O.lat_weights(shape[2], -80.0, 85.0).astype(np.float32)
     def place(a):
-        buf = torch.zeros(n + 8, device="cuda")
+        buf = torch.zeros(n + 8, dtype=torch.float32, device="cuda")
         buf[offset:offset + n] = torch.from_numpy(a).cuda().flatten()
         return buf[offset:offset + n].view(shape)
     p, t, l = place(pred), place(target), torch.from_numpy(lw).cuda()
@@ -31,7 +31,7 @@ def test_rows(shape, offset):
     B.reslim_bayes_loss_fwd(p, t, l, 0.25, out, ws)
     ref = O.bayes_loss(pred, target, lw, tv_weight=0.25)
     assert np.allclose(out.cpu().numpy(), np.asarray(ref, dtype=np.float64), rtol=1e-5)      # 32-bit sums of up to 32 terms a thread
-    d = torch.full((n + 8,), float("nan"), device="cuda")
+    d = torch.full((n + 8,), float("nan"), dtype=torch.float32, device="cuda")
     B.reslim_bayes_loss_bwd(p, t, l, 0.25, 8.0, d[offset:offset + n].view(shape))
     d = d.cpu().numpy()
     assert np.isnan(d[:offset]).all() and np.isnan(d[offset + n:]).all()
