@@ -16,6 +16,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "gemm_cursor.h"
 
 namespace reslim {
 
