@@ -158,7 +158,7 @@ static void block_free(PlanBlock *b) {
   if (!b) return;
   (void)hipFree(b->dev);                               // waits for the device
   (void)hipHostFree(b->host);
-  for (hipEvent_t e : b->ev)
+  for (hipEvent_t e : b->used.ev)
     if (e) (void)hipEventDestroy(e);
   delete b;
 }
@@ -180,16 +180,10 @@ void plan_used(const reslim_asc_plan *plan, hipStream_t st) {
     b->foreign = true;                                 // a graph may replay the reads at any later time
     return;
   }
-  int i = 0;
-  while (i < b->n_ev && b->stream[i] != st) ++i;
-  if (i == 4 || (!b->ev[i] && hipEventCreateWithFlags(&b->ev[i], hipEventDisableTiming) != hipSuccess) ||
-      hipEventRecord(b->ev[i], st) != hipSuccess) {
+  if (!b->used.add(st)) {
     (void)hipGetLastError();
     b->foreign = true;
-    return;
   }
-  b->stream[i] = st;
-  b->n_ev = std::max(b->n_ev, i + 1);
 }
 
 // A block of at least `bytes`, idle on the device: a kept one, or a new one.  With kMost kept blocks that are all still
@@ -205,10 +199,9 @@ static hipError_t block_take(reslim_ctx *c, size_t bytes, PlanBlock **out) {
       if (e != hipSuccess) return e;
     }
     for (size_t k = 0; k < pool.idle.size() && !b; ++k) {
-      bool done = true;
-      for (int i = 0; i < pool.idle[k]->n_ev && done; ++i) done = hipEventQuery(pool.idle[k]->ev[i]) == hipSuccess;
-      if (!done) (void)hipGetLastError();
-      if (done) {
+      if (!pool.idle[k]->used.done()) {
+        (void)hipGetLastError();
+      } else {
         b = pool.idle[k];
         pool.idle.erase(pool.idle.begin() + k);
       }
@@ -219,8 +212,8 @@ static hipError_t block_take(reslim_ctx *c, size_t bytes, PlanBlock **out) {
     }
   }
   if (b)
-    for (int i = 0; i < b->n_ev; ++i)
-      if (hipEventSynchronize(b->ev[i]) != hipSuccess) b->foreign = true;
+    for (int i = 0; i < b->used.n; ++i)
+      if (hipEventSynchronize(b->used.ev[i]) != hipSuccess) b->foreign = true;
   if (b && (b->cap < bytes || b->foreign)) {
     block_free(b);
     b = nullptr;
@@ -236,7 +229,7 @@ static hipError_t block_take(reslim_ctx *c, size_t bytes, PlanBlock **out) {
       return e;
     }
   }
-  b->n_ev = 0;
+  b->used.n = 0;
   *out = b;
   return hipSuccess;
 }

@@ -8,6 +8,7 @@
 #include <string>
 #include <vector>
 
+#include "plan_pool.h"
 #include "../../include/reslim.h"
 
 namespace reslim {
@@ -58,14 +59,21 @@ struct TrainModel {
 
 // Device memory and pinned staging of a compression plan.  A context keeps a few of them between plans, because a user
 // makes one plan per batch of fields: allocating and freeing them each time took longer than the tables' upload, and a
-// free waits for the whole device.  The events mark the work that last used the block, one per stream that did.
+// free waits for the whole device.
+struct HipQueues {
+  typedef hipEvent_t Event;
+  typedef hipStream_t Stream;
+  static bool per_thread(hipStream_t st) { return st == hipStreamPerThread; }
+  static bool create(hipEvent_t *e) { return hipEventCreateWithFlags(e, hipEventDisableTiming) == hipSuccess; }
+  static bool wait(hipStream_t st, hipEvent_t e) { return hipStreamWaitEvent(st, e, 0) == hipSuccess; }
+  static bool record(hipEvent_t e, hipStream_t st) { return hipEventRecord(e, st) == hipSuccess; }
+  static bool done(hipEvent_t e) { return hipEventQuery(e) == hipSuccess; }
+};
 struct PlanBlock {
   unsigned char *dev = nullptr, *host = nullptr;
   size_t cap = 0;
-  hipEvent_t ev[4] = {};
-  hipStream_t stream[4] = {};
-  int n_ev = 0;              // pairs in use
-  bool foreign = false;      // used by a captured graph or by more streams than there are events: freed, not kept
+  UseMarks<HipQueues> used;
+  bool foreign = false;      // used by a captured graph or by more queues than there are marks: freed, not kept
 };
 struct PlanPool {
   static constexpr size_t kMost = 4;

@@ -1,5 +1,8 @@
 """Compression plans made and given back while the kernels that read the previous ones are still queued: the memory of
 a plan is kept for the next one, and a table must never be overwritten under a kernel."""
+from concurrent.futures import ThreadPoolExecutor
+from types import SimpleNamespace
+
 import numpy as np
 import pytest
 import torch
@@ -57,3 +60,41 @@ def test_plans_in_flight(tiled):
         one(0, y, m.ws)
         torch.cuda.synchronize()
         assert torch.equal(y, ref[0])
+
+
+def test_one_plan_on_the_per_thread_stream_of_two_threads():
+    # handle 2 is hipStreamPerThread: another queue in every thread
+    cfg = CFG
+    per_thread = SimpleNamespace(cuda_stream=2)
+    f = WL.make_fields(cfg)
+    trees = [B.reslim_asc_build(np.ascontiguousarray(f[:, 0]), 2, 8, 1, low, 2 * low, 0.05) for low in (20, 60)]
+    x = torch.from_numpy(f).cuda()
+    shape = (cfg.batch, cfg.out_vars, cfg.H * cfg.scale, cfg.W * cfg.scale)
+    with B.Reslim(cfg, WL.make_weights(cfg)) as m:
+        def result(plan, y, ws, stream=None):
+            B.reslim_asc_forward(m.ctx, plan, x, y, ws, stream)
+
+        ref = [torch.empty(shape, dtype=torch.float32, device="cuda") for _ in trees]
+        for t, y in zip(trees, ref):
+            plan = B.reslim_asc_plan_create(m.ctx, cfg.batch, t)
+            result(plan, y, m.ws)
+            torch.cuda.synchronize()
+            B.reslim_asc_plan_destroy(plan)
+        ys = [torch.full(shape, float("nan"), dtype=torch.float32, device="cuda") for _ in range(12)]
+        wss = [torch.empty_like(m.ws) for _ in ys]
+        torch.cuda.synchronize()
+        hosts = [ThreadPoolExecutor(1), ThreadPoolExecutor(1)]
+        for round_ in range(3):
+            print(f"per-thread streams: round {round_}", flush=True)
+            for k in range(0, len(ys), 2):          # the plan goes back while both threads' passes may still run
+                plan = B.reslim_asc_plan_create(m.ctx, cfg.batch, trees[k // 2 % 2])
+                for j in (0, 1):
+                    hosts[j].submit(result, plan, ys[k + j], wss[k + j], per_thread).result()
+                B.reslim_asc_plan_destroy(plan)
+            torch.cuda.synchronize()
+            for k, y in enumerate(ys):
+                assert torch.equal(y, ref[k // 2 % 2]), k
+                y.fill_(float("nan"))
+            torch.cuda.synchronize()
+        for h in hosts:
+            h.shutdown()
