@@ -186,8 +186,8 @@ void plan_used(const reslim_asc_plan *plan, hipStream_t st) {
   }
 }
 
-// A block of at least `bytes`, idle on the device: a kept one, or a new one.  With kMost kept blocks that are all still
-// in use the oldest is waited for, so a host that runs ahead of the device cannot pile up memory.
+// A block of at least `bytes`, idle on the device: a kept one (choose_block), or a new one.  With kMost kept blocks that
+// are all still in use one is waited for, so a host that runs ahead of the device cannot pile up memory.
 static hipError_t block_take(reslim_ctx *c, size_t bytes, PlanBlock **out) {
   *out = nullptr;
   PlanPool &pool = c->plans;
@@ -198,17 +198,14 @@ static hipError_t block_take(reslim_ctx *c, size_t bytes, PlanBlock **out) {
       const hipError_t e = hipStreamCreateWithFlags(&pool.upload, hipStreamNonBlocking);
       if (e != hipSuccess) return e;
     }
-    for (size_t k = 0; k < pool.idle.size() && !b; ++k) {
-      if (!pool.idle[k]->used.done()) {
-        (void)hipGetLastError();
-      } else {
-        b = pool.idle[k];
-        pool.idle.erase(pool.idle.begin() + k);
-      }
-    }
-    if (!b && pool.idle.size() == PlanPool::kMost) {
-      b = pool.idle.front();
-      pool.idle.erase(pool.idle.begin());
+    KeptBlock kept[PlanPool::kMost];
+    const int n = static_cast<int>(pool.idle.size());
+    for (int k = 0; k < n; ++k) kept[k] = {pool.idle[k]->cap, pool.idle[k]->used.done()};
+    (void)hipGetLastError();                           // of events that have not happened
+    const int k = choose_block(kept, n, PlanPool::kMost, bytes);
+    if (k >= 0) {
+      b = pool.idle[k];
+      pool.idle.erase(pool.idle.begin() + k);
     }
   }
   if (b)

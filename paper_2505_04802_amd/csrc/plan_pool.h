@@ -2,6 +2,7 @@
 // events and queues of its own.
 #pragma once
 
+#include <cstddef>
 #include <thread>
 
 namespace reslim {
@@ -41,5 +42,29 @@ struct UseMarks {
     return true;
   }
 };
+
+// Which of the n kept blocks (oldest first) a plan of `bytes` takes, -1: none, it gets a new one.  A new block or one too
+// small costs an allocation, a block given up also a wait for the whole device: the smallest finished block that is large
+// enough; else a new one while fewer than `most` are kept; else the smallest finished one, which is replaced; with all
+// of them still in use the oldest that is large enough, or the oldest, is waited for.
+struct KeptBlock {
+  size_t cap;
+  bool done;
+};
+inline int choose_block(const KeptBlock *b, int n, int most, size_t bytes) {
+  int fit = -1, least = -1, busy = -1;
+  for (int i = 0; i < n; ++i) {
+    const bool fits = b[i].cap >= bytes;
+    if (b[i].done) {
+      if (fits && (fit < 0 || b[i].cap < b[fit].cap)) fit = i;
+      if (least < 0 || b[i].cap < b[least].cap) least = i;
+    } else if (fits && busy < 0) {
+      busy = i;
+    }
+  }
+  if (fit >= 0) return fit;
+  if (n < most) return -1;
+  return least >= 0 ? least : busy >= 0 ? busy : 0;
+}
 
 }  // namespace reslim

@@ -1,6 +1,7 @@
-"""When a compression plan's memory counts as free (csrc/plan_pool.h), on queues simulated on the CPU: never before all
+"""The memory that compression plans hand on to one another (csrc/plan_pool.h).  When it counts as free, on queues simulated on the CPU: never before all
 work that was marked as reading it has run, also where two queues answer to one handle: the per-thread handle in two
-threads, and the handle of a destroyed stream that comes back for a new one."""
+threads, and the handle of a destroyed stream that comes back for a new one.  And which block a plan takes: plans of changing sizes settle on blocks of their
+own instead of replacing each other's."""
 import ctypes
 import os
 import shutil
@@ -96,6 +97,35 @@ extern "C" int bounded() {
   if (marks.add(marks.kMost + 1)) return 3;
   return marks.add(2) && marks.n == marks.kMost ? 0 : 4;
 }
+// plans of sizes[0 .. n) in turn, each given back before the next is made; blocks allocated in the second half of the run
+extern "C" int allocations(const int *sizes, int n, int passes, int busy_every) {
+  constexpr int kMost = 4;
+  std::vector<reslim::KeptBlock> kept;
+  int made = 0;
+  for (int i = 0; i < n * passes; ++i) {
+    const size_t bytes = sizes[i % n];
+    for (size_t k = 0; k < kept.size(); ++k) kept[k].done = !busy_every || (i + k) % busy_every != 0;
+    const int c = reslim::choose_block(kept.data(), static_cast<int>(kept.size()), kMost, bytes);
+    if (c < -1 || c >= static_cast<int>(kept.size()) || (c < 0 && kept.size() == kMost)) return -1;
+    reslim::KeptBlock b{0, true};
+    if (c >= 0) {
+      b = kept[c];
+      for (const auto &o : kept)      // a finished block that fits is never passed over for a worse one
+        if (o.done && o.cap >= bytes && (!b.done || b.cap < bytes || b.cap > o.cap)) return -2;
+      kept.erase(kept.begin() + c);
+    } else {
+      for (const auto &o : kept)
+        if (o.done && o.cap >= bytes) return -3;
+    }
+    if (b.cap < bytes) {
+      b.cap = bytes + bytes / 4;
+      made += i >= n * passes / 2;
+    }
+    if (kept.size() == kMost) return -4;
+    kept.push_back(b);
+  }
+  return made;
+}
 """
 
 
@@ -117,3 +147,11 @@ def test_a_block_is_free_only_when_its_readers_have_run(model, seed, handles):
 
 def test_marks_are_bounded(model):
     assert model.bounded() == 0
+
+
+@pytest.mark.parametrize("sizes", [[100], [1000, 10], [10, 1000], [10, 100, 1000], [10, 10000, 100, 1000], [7, 900, 30, 30, 5000, 8]])
+def test_changing_sizes_settle(model, sizes):
+    a = (ctypes.c_int * len(sizes))(*sizes)
+    assert model.allocations(a, len(sizes), 40, 0) == 0
+    for busy_every in (2, 3, 5):
+        assert model.allocations(a, len(sizes), 40, busy_every) >= 0
