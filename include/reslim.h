@@ -207,7 +207,8 @@ int reslim_layernorm_bwd(reslim_ctx *ctx, const float *x, const void *dy, const 
  * 1: proj (D -> D), 2: fc1 (D -> R), 3: fc2 (R -> D), R = mlp_ratio * D:
  *   dx = dy W (skipped when dx is NULL),  dW = dy^T x,  db = column sums of dy.
  *   x act [rows, in]; dy act [rows, out]; dx act [rows, in] out; dw float [out, in] out;
- *   db float [out] out; workspace >= reslim_linear_bwd_workspace_bytes(). */
+ *   db float [out] out; workspace >= reslim_linear_bwd_workspace_bytes(): partial sums of
+ *   token slices, in bf16 at most 1024 tiles of 256 x 256 floats beside their biases (257 MiB). */
 int reslim_linear_bwd_workspace_bytes(const reslim_ctx *ctx, int32_t which, int32_t rows, size_t *out);
 int reslim_linear_bwd(reslim_ctx *ctx, int32_t layer, int32_t which, const void *x, const void *dy,
                       void *dx, float *dw, float *db, int32_t rows, void *workspace, size_t ws_bytes,
@@ -223,7 +224,11 @@ typedef struct {
 /* Sizes of the per-block buffer of saved activations (what reslim_block_fwd_train keeps for
  * reslim_block_bwd: both LayerNorm outputs, qkv, the attention output and its log-sum-exp,
  * the stream after the attention half, the feed-forward hidden layer before and after GELU)
- * and of the scratch either call needs.  Either pointer may be NULL. */
+ * and of the scratch either call needs, which changes from version to version of this library (ask,
+ * do not keep the number): with M = batch * n_h tokens 4 M D bytes, 2 M D + M max(3 D, R)
+ * activations, up to 128 MiB more activations where that saves a launch, the scratch of
+ * tiles_attention_bwd and partial sums of parameter gradients as for reslim_linear_bwd.
+ * Either pointer may be NULL. */
 int reslim_block_train_bytes(const reslim_ctx *ctx, int32_t batch, size_t *saved_bytes, size_t *ws_bytes);
 
 /* reslim_block_fwd that keeps its intermediates: x_out = block(x_in), both float

@@ -60,8 +60,10 @@ TrainSaved plan_saved(const reslim_ctx *c, int batch, void *base, int64_t n_h) {
 }
 
 struct TrainWs {           // scratch of the gradient pass
-  // activation type; the gradients of the four linear layers' outputs (out, fc1, mid, qkv) stay until the end of the
-  // block, where the parameter gradients are computed in one launch
+  // activation type, the gradients of the four linear layers' outputs.  one_launch: they stay until the end of the block,
+  // where all parameter gradients are computed in one launch.  Otherwise those of the feed-forward layer are computed half way and
+  // mid and qkv take the place of out and fc1.
+  bool one_launch;
   void *out, *fc1, *mid, *qkv;      // [M, D], [M, R], [M, D], [M, 3D]
   void *b;                 // [M, D]: gradient of a linear layer's input, until the kernel after it
   float *g;                // [M, D]
@@ -77,16 +79,21 @@ TrainWs plan_train_ws(const reslim_ctx *c, int batch, void *base, const SeqGeom 
   size_t off = 0;
   auto take = [&](size_t bytes) { unsigned char *q = p + off; off += align256(bytes); return q; };
   TrainWs w;
+  // One launch fills the chip with few tokens, where a second one adds start-up and a sum over slices (some 10 us); it
+  // needs four more activations of M x D (at ratio 4).  From 128 MiB of them on (16,384 tokens at D = 1024) the products
+  // take 0.4 ms and more, so that one launch gains little, and the memory is worth more.
+  const size_t apart = (D + std::max(3 * D, R)) * M * es, together = (D + R + D + 3 * D) * M * es;
+  w.one_launch = together - apart <= static_cast<size_t>(128) << 20;
   w.out = take(M * D * es);
-  w.fc1 = take(M * R * es);
-  w.mid = take(M * D * es);
-  w.qkv = take(M * 3 * D * es);
+  w.fc1 = take(M * (w.one_launch ? R : std::max(3 * D, R)) * es);
+  w.mid = w.one_launch ? take(M * D * es) : w.out;
+  w.qkv = w.one_launch ? take(M * 3 * D * es) : w.fc1;
   w.b = take(M * D * es);
   w.g = reinterpret_cast<float *>(take(M * D * sizeof(float)));
   w.attn = take(tiles_attention_bwd_ws_bytes(c, batch, &sg));
   const WgradOp op[4] = {{nullptr, nullptr, nullptr, nullptr, Di, Ri}, {nullptr, nullptr, nullptr, nullptr, Ri, Di},
                          {nullptr, nullptr, nullptr, nullptr, Di, Di}, {nullptr, nullptr, nullptr, nullptr, 3 * Di, Di}};
-  w.wgrad = take(std::max<size_t>(wgrad_ws_bytes(dt, op, 4, Mi), 256));
+  w.wgrad = take(std::max<size_t>(w.one_launch ? wgrad_ws_bytes(dt, op, 4, Mi) : std::max(wgrad_ws_bytes(dt, op, 2, Mi), wgrad_ws_bytes(dt, op + 2, 2, Mi)), 256));
   w.lnp = reinterpret_cast<float *>(take(static_cast<size_t>(layernorm_bwd_slabs(M)) * 2 * D * sizeof(float)));
   w.total = off;
   return w;
@@ -281,6 +288,9 @@ static int block_bwd_impl(reslim_ctx *c, const char *fn, int layer, const float 
   RESLIM_LAUNCH("gelu_bwd", 0, 3.0 * static_cast<double>(M) * R * es, launch_gelu(dt, true, s.h, w.fc1, w.fc1, static_cast<int64_t>(M) * R, st));
   rc = dgrad_impl(c, fn, w.fc1, lw.wt_fc1, w.b, M, R, D, st);
   if (rc != RESLIM_OK) return rc;
+  const WgradOp op[4] = {{w.out, s.u, grads->w_fc2, grads->b_fc2, D, R}, {w.fc1, s.ln2, grads->w_fc1, grads->b_fc1, R, D},
+                         {w.mid, s.attn, grads->w_proj, grads->b_proj, D, D}, {w.qkv, s.ln1, grads->w_qkv, grads->b_qkv, 3 * D, D}};
+  if (!w.one_launch && (rc = wgrad_impl(c, fn, op, 2, M, w.wgrad, st)) != RESLIM_OK) return rc;
   RESLIM_LAUNCH("layernorm_bwd", 0, dM * dD * (12.0 + 2.0 * es),
                 launch_layernorm_bwd(dt, s.x_mid, w.b, lw.ln2_g, d_x_out, w.g, w.mid, w.lnp, grads->ln2_g, grads->ln2_b, M, D, st));
   // x_mid = x_in + proj(tile_attention(qkv(ln1(x_in))))
@@ -292,11 +302,7 @@ static int block_bwd_impl(reslim_ctx *c, const char *fn, int layer, const float 
   if (rc != RESLIM_OK) return rc;
   RESLIM_LAUNCH("layernorm_bwd", 0, dM * dD * (12.0 + es),
                 launch_layernorm_bwd(dt, x_in, w.b, lw.ln1_g, w.g, d_x_in, nullptr, w.lnp, grads->ln1_g, grads->ln1_b, M, D, st));
-  const WgradOp op[4] = {{w.out, s.u, grads->w_fc2, grads->b_fc2, D, R}, {w.fc1, s.ln2, grads->w_fc1, grads->b_fc1, R, D},
-                         {w.mid, s.attn, grads->w_proj, grads->b_proj, D, D}, {w.qkv, s.ln1, grads->w_qkv, grads->b_qkv, 3 * D, D}};
-  rc = wgrad_impl(c, fn, op, 4, M, w.wgrad, st);
-  if (rc != RESLIM_OK) return rc;
-  return RESLIM_OK;
+  return w.one_launch ? wgrad_impl(c, fn, op, 4, M, w.wgrad, st) : wgrad_impl(c, fn, op + 2, 2, M, w.wgrad, st);
 }
 
 extern "C" int reslim_block_bwd(reslim_ctx *c, int32_t layer, const float *x_in, const void *saved, size_t saved_bytes,

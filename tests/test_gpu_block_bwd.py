@@ -152,6 +152,63 @@ def test_block_train_c1_full_size():
         assert_parity(got, ref, 2e-2, f"c1 block train {name}", say, **({} if name == "x_out" else GRAD_BF16))
 
 
+@pytest.mark.parametrize("cfg", [SMALL_BF16.with_(name="batch_256", H=128, W=256, batch=8, embed_dim=256, heads=4, depth=1, tiles_y=4, tiles_x=8, halo=2),
+                                 SMALL_BF16.with_(name="batch_640_ratio_2", H=96, W=100, batch=16, embed_dim=640, heads=10, depth=1, mlp_ratio=2,
+                                                  tiles_y=3, tiles_x=2, halo=1),
+                                 SMALL_F32.with_(name="batch_192_f32", H=96, W=100, batch=28, embed_dim=192, heads=6, depth=1, tiles_y=3, tiles_x=2, halo=1)],
+                         ids=lambda c: c.name)
+def test_block_bwd_of_a_batch_is_the_sum_of_its_samples(cfg):
+    """Above 128 MiB of further activations the parameter gradients come in two launches that share their buffers; the
+    samples one by one stay below.  Same bits in d_x in bf16 (rows do not meet); parameter gradients differ by the order of
+    fp32 sums of random sign: 1e-5."""
+    tiles, _, _, n_h = O.tiles_partition(cfg.Hp, cfg.Wp, cfg.tiles_y, cfg.tiles_x, cfg.halo)
+    D = cfg.embed_dim
+    further = n_h * D * (1 + min(3, cfg.mlp_ratio)) * (2 if cfg.dtype else 4)
+    assert further < 1 << 27 < further * cfg.batch, "the case is meant to lie across the line"
+    w = weights_for(cfg)
+    x, d_out = cuda(rnd((cfg.batch, n_h, D), 50, False)), cuda(rnd((cfg.batch, n_h, D), 51, False))
+    with B.Reslim(cfg, w) as m:
+        B.reslim_train_prepare(m.ctx)
+
+        def backward(x, d_out):
+            n = x.shape[0]
+            sb, wb = B.reslim_block_train_bytes(m.ctx, n)
+            saved, ws = u8(sb), u8(wb)
+            out, dx = torch.empty_like(x), torch.empty_like(x)
+            grads = {k: torch.full(np.shape(w[k][0]), float("nan"), dtype=torch.float32, device="cuda") for k in B.BLOCK_PARAMS}
+            B.reslim_block_fwd_train(m.ctx, 0, x, out, saved, n, ws)
+            B.reslim_block_bwd(m.ctx, 0, x, saved, d_out, dx, grads, n, ws)
+            torch.cuda.synchronize()
+            return dx, grads
+
+        dx, grads = backward(x, d_out)
+        parts = [backward(x[b:b + 1].contiguous(), d_out[b:b + 1].contiguous()) for b in range(cfg.batch)]
+        ref_dx = torch.cat([p[0] for p in parts])
+        if cfg.dtype:
+            assert torch.equal(dx, ref_dx)
+        else:                                   # the fp32 products split their sums by the size of the problem
+            assert float((dx - ref_dx).norm() / ref_dx.norm()) <= 1e-5
+        for k in B.BLOCK_PARAMS:
+            ref = sum(p[1][k].double() for p in parts)
+            err = float((grads[k].double() - ref).norm() / ref.norm())
+            say(f"  {cfg.name} d_{k} batch against samples {err:.3e}")
+            assert err <= 1e-5, k
+
+
+def test_block_bwd_scratch_at_a_large_size():
+    """Two activations and the wider of qkv and hidden layer, one fp32 stream, at most 128 MiB for the single launch and
+    1024 tiles of partial sums (and up to 64 MiB of small ones) beside the attention's own scratch."""
+    cfg = WL.CONFIGS["c2"].with_(depth=1)
+    with B.Reslim(cfg, weights_for(cfg)) as m:
+        for batch in (1, 4):
+            n_h = B.reslim_tokens_per_sample(m.ctx)
+            _, wb = B.reslim_block_train_bytes(m.ctx, batch)
+            MD = batch * n_h * cfg.embed_dim
+            bound = MD * 4 + MD * (2 + cfg.mlp_ratio) * 2 + (128 + 256 + 64 << 20) + B.tiles_attention_bwd_workspace_bytes(m.ctx, batch)
+            say(f"  c2 batch {batch}: block scratch {wb / 2**20:.0f} MiB, bound {bound / 2**20:.0f}")
+            assert wb <= bound
+
+
 def test_training_entry_point_errors_and_tiny_tiles():
     """Error codes (no launch happens): training calls before reslim_train_prepare, null buffers,
     short or misaligned buffers, bad layer; then a tile grid as fine as the patch grid (one-token
