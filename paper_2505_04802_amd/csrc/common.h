@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "plan_pool.h"
+#include "wgrad_plan.h"
 #include "../../include/reslim.h"
 
 namespace reslim {
@@ -210,14 +211,7 @@ size_t tiles_attention_bwd_ws_bytes(const reslim_ctx *c, int batch, const SeqGeo
 hipError_t attention_bwd_init();
 // ---- training-side kernels
 hipError_t wgrad_init();
-// Parameter gradients of linear layers over the same M tokens, up to kWgradMax of them at once:
-// dW[N, K] = dY[M, N]^T X[M, K] and db[N] = column sums of dY, both fp32; ws >= wgrad_ws_bytes
-constexpr int kWgradMax = 4;
-struct WgradOp {
-  const void *dy, *x;
-  float *dw, *db;
-  int N, K;
-};
+// parameter gradients of up to kWgradMax linear layers at once
 size_t wgrad_ws_bytes(int dtype, const WgradOp *op, int n_op, int M);
 hipError_t launch_wgrad(int dtype, const WgradOp *op, int n_op, int M, void *ws, hipStream_t st);
 int layernorm_bwd_slabs(int64_t rows);   // partial rows (of 2 D floats) launch_layernorm_bwd writes

@@ -1,6 +1,7 @@
 """Parameter gradients of linear layers where the tiled kernel can go wrong: one token, one less and one more than the 64
 tokens of a slab, an odd and an even number of slabs, a last slice that is not whole, feature counts at the edges of both
-tiles (128 and 256).  Reference: the same sums in float64 on the CPU."""
+tiles (128 and 256; test_wgrad_plan_cpu.py asks the library's own rule which one each shape takes).  Reference: the same
+sums in float64 on the CPU."""
 import numpy as np
 import pytest
 import torch
@@ -13,8 +14,12 @@ BASE = WL.ReslimConfig("wgrad", batch=1, in_vars=2, out_vars=2, H=8, W=16, scale
                        depth=1, tiles_y=1, tiles_x=1, halo=0, dtype=1, seed=17)
 
 
-@pytest.mark.parametrize("D,which,rows", [(64, 1, 1), (64, 0, 63), (64, 2, 65), (128, 1, 128), (128, 3, 4097), (256, 1, 192), (256, 2, 19551),
-                                          (320, 0, 1000), (320, 1, 70001), (1024, 2, 2000)], ids=str)
+SHAPES = [(64, 1, 1), (64, 0, 63), (64, 2, 65), (128, 1, 128), (128, 3, 4097), (256, 1, 192), (256, 2, 19551), (320, 0, 1000), (320, 1, 70001),
+          (1024, 2, 2000),
+          (1984, 0, 1), (1984, 0, 65), (1984, 0, 129), (2048, 0, 63), (2048, 0, 192), (1088, 0, 4001), (1024, 0, 8000), (320, 0, 64001)]
+
+
+@pytest.mark.parametrize("D,which,rows", SHAPES, ids=str)
 def test_weight_and_bias_gradient(D, which, rows):
     print(f"wgrad D={D} which={which} rows={rows}", flush=True)
     cfg = BASE.with_(embed_dim=D, heads=D // 64)
