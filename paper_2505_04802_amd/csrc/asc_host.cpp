@@ -322,9 +322,13 @@ struct TreeBuilder {
     if (y0 >= Hp || x0 >= Wp) return;                     // wholly in the padding of a ragged grid
     const int s = 1 << level;
     const bool inside = y0 + s <= Hp && x0 + s <= Wp;     // a node that sticks out always splits
-    const float area = static_cast<float>(static_cast<int64_t>(s) * p * s * p);
-    const float bound = tau * area;
-    if (!inside || (s > min_leaf && static_cast<float>(py.count(level, y0, x0)) > bound)) {
+    bool split = !inside;
+    if (inside && s > min_leaf) {                         // only here is the area sure to fit: the node lies in the image
+      const float area = static_cast<float>(static_cast<int64_t>(s) * p * s * p);
+      const float bound = tau * area;
+      split = static_cast<float>(py.count(level, y0, x0)) > bound;
+    }
+    if (split) {
       const int h = s / 2;
       visit(y0, x0, level - 1);
       visit(y0, x0 + h, level - 1);
