@@ -26,16 +26,20 @@ def test_widths(W):
 
 def test_extreme_ranges():
     r = np.random.default_rng(3)
-    base = r.integers(0, 2, (4, 24, 40)).astype(np.float32)
+    base = r.integers(0, 2, (5, 24, 40)).astype(np.float32)
     base[0] *= np.float32(1e-44)                      # 255 / range overflows to infinity
     base[1] = np.where(base[1] > 0, np.float32(0.0), np.float32(-0.0))      # two zeros: a constant field
-    base[2] = (base[2] - 0.5) * np.float32(3e38)      # the range overflows
+    base[2] = (2 * base[2] - 1) * np.float32(3e38)    # the range overflows
     base[3] -= 7.0                                    # negative values only
+    base[4] = (base[4] - 0.5) * np.float32(3e38)      # the largest range that does not overflow, nearly
     with np.errstate(all="ignore"):
-        for b in (0, 1, 3):
+        for b in (0, 1, 3, 4):
             got, ref = B.reslim_asc_build(base[b:b + 1], 2, 8, 1, 20, 60, 0.05), A.build(base[b:b + 1], 2, 8, 1, 20, 60, 0.05)
             assert same(got, ref), b
-    B.reslim_asc_build(base[2:3], 2, 8, 1, 20, 60, 0.05)
+    # 255 / infinity is 0 and every product is 0 or the NaN of 0 * infinity, which counts as 0: the tree of a constant field
+    assert not B.reslim_asc_edges(base[2], 20, 60).any()
+    flat = A.build(np.zeros_like(base[2:3]), 2, 8, 1, 20, 60, 0.05)
+    assert same(B.reslim_asc_build(base[2:3], 2, 8, 1, 20, 60, 0.05), flat)
 
 
 def test_boxes_of_a_wide_field():
