@@ -3,7 +3,8 @@
 // forward kernels of elementwise.hip and the GEMM epilogues):
 //   layernorm_bwd   gradient of the per-token normalisation + partial sums of d gamma, d beta
 //   gelu_fwd/bwd    exact (erf) GELU and its derivative, element by element
-//   colsum          column sums of an activation gradient = gradient of a bias
+//   colsum          column sums of an activation gradient = gradient of a bias (fp32 path; the bf16 one takes them from
+//                   the fragments of the weight gradient, wgrad.hip)
 //   partial_reduce  fixed-order sum of per-work-group partial rows (deterministic)
 //   to_act          fp32 -> activation type
 //   transpose       weight [out, in] -> [in, out], once, for the input-gradient GEMMs
@@ -295,7 +296,7 @@ __global__ __launch_bounds__(NG * 32) void partial_reduce_kernel(const float *__
   }
 }
 
-// Few partial rows, many columns (the split-K slices of a weight gradient): a thread owns four
+// Few partial rows, many columns (the token slabs of the folded value tables' gradient): a thread owns four
 // adjacent columns and adds the rows in order, 16-byte loads, no LDS.
 __global__ __launch_bounds__(256) void partial_reduce_wide_kernel(const float4 *__restrict__ partial, float4 *__restrict__ out,
                                                                   int n_part, int64_t stride4, int64_t n4) {
@@ -444,64 +445,47 @@ hipError_t launch_to_act(int dtype, const float *src, void *dst, int64_t n, hipS
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ column sums (bias gradient)
-// A thread owns 16 bytes of columns (8 bfloat16 or 4 float); TPR threads cover a row segment of
-// up to 256 * 16 bytes (grid.x segments), the 256 / TPR row lanes of a work-group take the rows
-// of the work-group's slab (grid.y) in turn and are added through LDS in a fixed order.
-template <class T>
-__global__ __launch_bounds__(256) void colsum_kernel(const T *__restrict__ a, float *__restrict__ partial, int64_t rows,
+// ------------------------------------------------------------------ column sums (bias gradient of the fp32 path)
+// A thread owns four columns; TPR threads cover a row segment of up to 1024 columns (grid.x segments), the 256 / TPR row
+// lanes of a work-group take the rows of the work-group's slab (grid.y) in turn and are added through LDS in a fixed order.
+__global__ __launch_bounds__(256) void colsum_kernel(const float *__restrict__ a, float *__restrict__ partial, int64_t rows,
                                                      int rows_per_slab, int N, int tpr) {
-  constexpr int VEC = 16 / sizeof(T);
-  __shared__ float sm[256 * VEC];
+  __shared__ float4 sm[256];
   const int cg = threadIdx.x % tpr, rl = threadIdx.x / tpr, nrl = 256 / tpr;
-  const int c = (blockIdx.x * tpr + cg) * VEC;
+  const int c = (blockIdx.x * tpr + cg) * 4;
   const int64_t r0 = static_cast<int64_t>(blockIdx.y) * rows_per_slab;
   const int64_t r1 = r0 + rows_per_slab < rows ? r0 + rows_per_slab : rows;
-  float acc[VEC];
-#pragma unroll
-  for (int e = 0; e < VEC; ++e) acc[e] = 0.f;
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
   if (c < N) {
     for (int64_t r = r0 + rl; r < r1; r += nrl) {
-      const uint4 raw = *reinterpret_cast<const uint4 *>(a + r * N + c);
-      if constexpr (sizeof(T) == 2) {
-        const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          acc[2 * e] += __uint_as_float(w[e] << 16);
-          acc[2 * e + 1] += __uint_as_float(w[e] & 0xffff0000u);
-        }
-      } else {
-        acc[0] += __uint_as_float(raw.x); acc[1] += __uint_as_float(raw.y);
-        acc[2] += __uint_as_float(raw.z); acc[3] += __uint_as_float(raw.w);
-      }
+      const float4 v = *reinterpret_cast<const float4 *>(a + r * N + c);
+      acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
     }
   }
-#pragma unroll
-  for (int e = 0; e < VEC; ++e) sm[threadIdx.x * VEC + e] = acc[e];
+  sm[threadIdx.x] = acc;
   __syncthreads();
   if (rl == 0 && c < N) {
-    for (int g = 1; g < nrl; ++g)
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) acc[e] += sm[(g * tpr + cg) * VEC + e];
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) partial[static_cast<size_t>(blockIdx.y) * N + c + e] = acc[e];
+    for (int g = 1; g < nrl; ++g) {
+      const float4 v = sm[g * tpr + cg];
+      acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+    }
+    float *o = partial + static_cast<size_t>(blockIdx.y) * N + c;
+    o[0] = acc.x; o[1] = acc.y; o[2] = acc.z; o[3] = acc.w;
   }
 }
 
 int colsum_slabs(int64_t rows) { return static_cast<int>(rows < 32 * 1024 ? (rows + 31) / 32 : 1024); }
 
 // partial: dev float, at least colsum_slabs(rows) * N elements
-hipError_t launch_colsum(int dtype, const void *a, float *partial, float *out, int64_t rows, int N, hipStream_t st) {
-  const int vec = dtype == RESLIM_BF16 ? 8 : 4;
-  if (N % vec != 0 || rows <= 0) return hipErrorInvalidValue;
+hipError_t launch_colsum(const float *a, float *partial, float *out, int64_t rows, int N, hipStream_t st) {
+  if (N % 4 != 0 || rows <= 0) return hipErrorInvalidValue;
   int slabs = colsum_slabs(rows);
   const int rps = static_cast<int>((rows + slabs - 1) / slabs);
   slabs = static_cast<int>((rows + rps - 1) / rps);
-  int tpr = 256;                               // threads per row segment: a power of two <= 256 covering N / vec
-  while (tpr > 1 && tpr / 2 >= N / vec) tpr /= 2;
-  const dim3 grid((N / vec + tpr - 1) / tpr, slabs), blk(256);
-  if (dtype == RESLIM_BF16) colsum_kernel<bf16_t><<<grid, blk, 0, st>>>(static_cast<const bf16_t *>(a), partial, rows, rps, N, tpr);
-  else colsum_kernel<float><<<grid, blk, 0, st>>>(static_cast<const float *>(a), partial, rows, rps, N, tpr);
+  int tpr = 256;                               // threads per row segment: a power of two <= 256 covering N / 4
+  while (tpr > 1 && tpr / 2 >= N / 4) tpr /= 2;
+  const dim3 grid((N / 4 + tpr - 1) / tpr, slabs), blk(256);
+  colsum_kernel<<<grid, blk, 0, st>>>(a, partial, rows, rps, N, tpr);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_partial_reduce(partial, out, slabs, N, N, st);

@@ -484,7 +484,7 @@ __global__ __launch_bounds__(256) void batch_sum_kernel(const float *__restrict_
 // where d is outside head g: the matrix unit does heads times the needed products and is still far
 // quicker than the vector units on the plain form), and this kernel only combines E with the pixels.
 struct AggBwdArgs {
-  const float *x, *A, *a0, *U, *c;
+  const float *x, *A, *a0;
   const void *d_o;            // act [BN, D]
   const float *E;             // [BN, ne] rows (g, v, j), j <= p2
   float *a_out;               // [BN, heads, V] softmax weights
@@ -1067,7 +1067,7 @@ static int embed_bwd_impl(reslim_ctx *c, const char *fn, const float *x, const f
   }
   // folded aggregation backwards: logits, then the tables
   AggBwdArgs e;
-  e.x = x; e.A = c->d_agg_A; e.a0 = c->d_agg_a0; e.U = c->d_agg_U; e.c = c->d_agg_c; e.d_o = w.d_o; e.a_out = w.a; e.x_out = w.xt; e.partial = w.pA;
+  e.x = x; e.A = c->d_agg_A; e.a0 = c->d_agg_a0; e.d_o = w.d_o; e.a_out = w.a; e.x_out = w.xt; e.partial = w.pA;
   e.V = V; e.H = c->cfg.H; e.W = c->cfg.W; e.p = p; e.Wp = c->Wp; e.N = c->N; e.D = D; e.heads = heads; e.dh = dh; e.BN = Mi;
   {
     const TrainModel &tmm = c->train;

@@ -515,7 +515,7 @@ hipError_t launch_wgrad(int dtype, const WgradOp *op, int n_op, int M, void *ws,
     wgrad_f32_kernel<<<dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, st>>>(
         static_cast<const float *>(op[i].dy), static_cast<const float *>(op[i].x), op[i].dw, M, op[i].N, op[i].K);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = launch_colsum(dtype, op[i].dy, static_cast<float *>(ws), op[i].db, M, op[i].N, st);
+    if (e == hipSuccess) e = launch_colsum(static_cast<const float *>(op[i].dy), static_cast<float *>(ws), op[i].db, M, op[i].N, st);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
