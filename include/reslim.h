@@ -61,7 +61,7 @@ typedef struct {
   int32_t halo;       /* halo width in patches, clipped at the domain edge       */
   int32_t res_idx;    /* row of the resolution-embedding table to add (Sec. 4.1) */
   int32_t n_res;      /* rows of that table                                      */
-  int32_t dtype;      /* RESLIM_F32 (debug path) or RESLIM_BF16                  */
+  int32_t dtype;      /* RESLIM_F32 (fp32 throughout) or RESLIM_BF16             */
 } reslim_config;
 
 /* Parameters, all HOST pointers to float (out_var_idx: int32), row-major, read

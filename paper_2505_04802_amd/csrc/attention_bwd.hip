@@ -617,7 +617,7 @@ __global__ __launch_bounds__(256, MINW) void attn_bwd_bf16_kernel(AttnBwdArgs a)
   }
 }
 
-// ------------------------------------------------------------------ fp32 debug path
+// ------------------------------------------------------------------ fp32 path
 __global__ __launch_bounds__(256) void attn_bwd_delta_f32_kernel(const float *out, const float *dout, float *delta,
                                                                  int64_t n, int64_t n_h, int heads, int dh) {
   // one thread per (sample, token, head)

@@ -2,14 +2,15 @@
 // projection and feed-forward maps, the aggregation's output map and the decoder's
 // linear projection):   C[M, N] (+)= A[M, K] * W[N, K]^T + bias, fused epilogues.
 //
-// bf16 path: gfx950 MFMA 32x32x16 (bf16 in, fp32 accumulate).  A work-group owns a
-// BM x BN tile of C, stages BM x BK and BN x BK operand slabs through LDS (rows
+// bf16 path: gfx950 MFMA 32x32x16 (bf16 in, fp32 accumulate), three kernels of which
+// choose_bf16 takes one by estimated time: the persistent ones of 256 x 256 and
+// 128 x 256 tiles (gemm_pp.inc) and gemm_bf16_kernel with one 128 x 128 tile per
+// work-group.  That one stages BM x BK and BN x BK operand slabs through LDS (rows
 // padded by 16 B so the 16-byte fragment reads of 16 consecutive rows fall in
-// distinct bank groups), double-buffered with the next slab prefetched into
-// registers while the current one feeds the matrix cores.  Work-groups are
-// renumbered so that each XCD (private L2) receives a contiguous run of tiles, and
-// inside a run tiles are ordered in bands of GROUP_M row-tiles so concurrently
-// resident tiles share A and W slabs.
+// distinct bank groups), the next slab prefetched into registers while the current
+// one feeds the matrix cores.  Its work-groups are renumbered so that each XCD
+// (private L2) receives a contiguous run of tiles, and inside a run tiles are ordered
+// in bands of GROUP_M row-tiles so concurrently resident tiles share A and W slabs.
 // fp32 path: MFMA 32x32x2 in fp32, operands straight from global memory.
 #include <algorithm>
 #include <cmath>

@@ -11,9 +11,9 @@
 // tiles are summed in a fixed order afterwards (deterministic, no atomics).  The four products of a
 // block run as ONE launch over a common tile list with common slices: at D = 256 and 19,552 tokens
 // they took 104 us one by one plus 110 us for the bias sums, most of it partial tiles (64 slices of
-// every product, 192 MB a block) and start-up; together 45 us (10 slices, 31 MB), bias sums included.  At D = 1024 and 97,760 tokens (c2) 2.43 ms and 0.40 ms become
-// 2.11 ms, 1170 TFLOP/s; on operands of zeros the kernel reaches 1600, so what is left there is the
-// chip's power limit.
+// every product, 192 MB a block) and start-up; together 45 us (10 slices, 31 MB), bias sums included.  At D = 1024 and 161,408 tokens (c2) the four products took 4.00 ms and
+// the bias sums 0.56; the two launches of such a block take 2.40 + 1.19 ms, 1130 TFLOP/s, with the matrix pipe busy 88 % of
+// the cycles of a clock of 1.2 GHz (1600 TFLOP/s on operands of zeros): the chip's power limit.
 #include <type_traits>
 
 #include "attention_common.h"
@@ -369,7 +369,7 @@ __global__ __launch_bounds__(512, 2) void wgrad_bf16_kernel(WgradArgs a) {
   }
 }
 
-// fp32 debug path: one thread per element of dW
+// fp32 path: one thread per element of dW
 __global__ __launch_bounds__(256) void wgrad_f32_kernel(const float *__restrict__ dy, const float *__restrict__ x,
                                                         float *__restrict__ out, int M, int N, int K) {
   const int64_t idx = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;

@@ -37,7 +37,7 @@ class ReslimConfig:
     halo: int
     res_idx: int = 0
     n_res: int = 2
-    dtype: int = 1          # 0 = fp32 debug path, 1 = bf16 operands / fp32 accumulate
+    dtype: int = 1          # 0 = fp32 throughout, 1 = bf16 operands / fp32 accumulate
     seed: int = 0
 
     @property
