@@ -3,7 +3,7 @@
 // linear projection):   C[M, N] (+)= A[M, K] * W[N, K]^T + bias, fused epilogues.
 //
 // bf16 path: gfx950 MFMA 32x32x16 (bf16 in, fp32 accumulate), three kernels of which
-// choose_bf16 takes one by estimated time: the persistent ones of 256 x 256 and
+// gemm_choose (gemm_plan.h) takes one by estimated time: the persistent ones of 256 x 256 and
 // 128 x 256 tiles (gemm_pp.inc) and gemm_bf16_kernel with one 128 x 128 tile per
 // work-group.  That one stages BM x BK and BN x BK operand slabs through LDS (rows
 // padded by 16 B so the 16-byte fragment reads of 16 consecutive rows fall in
@@ -18,6 +18,7 @@
 
 #include "common.h"
 #include "gemm_cursor.h"
+#include "gemm_plan.h"
 
 namespace reslim {
 
@@ -550,43 +551,20 @@ typedef TileCfg<128, 128, 64, 2, 2, 1, 3> TileSmall;   // 64x64 per wave, 36 KB 
 static int g_col_fast = 0;
 static int g_gemm_tile_override = -1;   // test / tuning hook: 2 = 128x128 tiles, 3 / 4 = persistent 256x256 / 128x256
 
-// Which bf16 kernel a product gets: the smallest of three estimates of its time in microseconds.  A launch runs in
-// rounds of as many tiles as the chip holds at once (one per CU for the persistent kernels, three for the small tiles,
-// whose last round is not a whole one because nothing ties their work-groups together); a round costs its 64-deep slabs
-// and one epilogue, both cheaper when part of the chip is idle.  The constants are fitted to 52 products (M 2280 ..
-// 403,200, N 192 .. 16,384, K 256 .. 16,384, every epilogue) on MI355X: the pick is within 2 % of the best of the three
-// on average.  In words: 256 x 256 tiles where there are at least about two rounds of them; 128 x 256 where their
-// rounds come out emptier (42,560 x 512 x 2048: 0.124 -> 0.106 ms) or K is deep and there is less than one
-// (5000 x 1024 x 4096: 0.072 -> 0.047); 128 x 128 for shallow products with heavy epilogues and for the smallest.
-struct EpiCost { double pp2, pp1, small; };
 template <int EPI>
-static constexpr EpiCost epi_cost() {
-  if (EPI == EPI_BIAS_GELU_ACT) return {10.0, 5.0, 4.0};
-  if (EPI == EPI_BIAS_ACT_GELU2) return {14.0, 8.0, 7.5};
-  if (EPI == EPI_BIAS_F32) return {10.0, 4.5, 4.0};
-  if (EPI == EPI_BIAS_RESADD_F32 || EPI == EPI_BIAS_RES_F32 || EPI == EPI_BIAS_TAB_F32) return {14.0, 7.7, 8.5};
-  return {6.0, 3.0, 2.5};
-}
-
-template <int EPI>
-static int choose_bf16(const GemmArgs &g) {
-  constexpr EpiCost e = epi_cost<EPI>();
-  const double nk = g.K / 64, cus = g_num_cus;
-  auto tiles = [&](int bm, int bn) { return static_cast<double>((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn); };
-  const double t2 = tiles(256, 256), t1 = tiles(128, 256), ts = tiles(128, 128);
-  const double f2 = std::min(1.0, t2 / cus), f1 = std::min(1.0, t1 / cus);                 // share of the chip at work
-  const double fs = std::min(1.0, std::max(0.0, (ts / cus - 1.0) / 2.0));                  // second and third work-group of a CU
-  const double c2 = std::ceil(t2 / cus) * (nk * (0.9 + 0.55 * f2) + e.pp2 * (0.5 + 0.5 * f2)) + 3.0;
-  const double c1 = std::ceil(t1 / cus) * (nk * (0.5 + 0.37 * f1) + e.pp1 * (0.5 + 0.5 * f1)) + 3.0;
-  const double cs = std::max(1.0, ts / (3.0 * cus)) * (nk * (1.05 + 0.85 * fs) + e.small * (0.6 + 0.4 * fs));
-  return cs <= c1 && cs <= c2 ? 2 : c1 < c2 ? 4 : 3;
+static constexpr GemmEpi epi_cost() {
+  if (EPI == EPI_BIAS_GELU_ACT) return kEpiGelu;
+  if (EPI == EPI_BIAS_ACT_GELU2) return kEpiTwo;
+  if (EPI == EPI_BIAS_F32) return kEpiF32;
+  if (EPI == EPI_BIAS_RESADD_F32 || EPI == EPI_BIAS_RES_F32 || EPI == EPI_BIAS_TAB_F32) return kEpiStream;
+  return kEpiAct;
 }
 
 template <int EPI>
 static hipError_t launch_bf16(GemmArgs g, hipStream_t st) {
-  switch (g_gemm_tile_override >= 0 ? g_gemm_tile_override : choose_bf16<EPI>(g)) {
-    case 3: return launch_bf16_pp<2, EPI>(g, st);
-    case 4: return launch_bf16_pp<1, EPI>(g, st);
+  switch (g_gemm_tile_override >= 0 ? g_gemm_tile_override : gemm_choose(g.M, g.N, g.K, epi_cost<EPI>(), g_num_cus)) {
+    case kGemm256x256: return launch_bf16_pp<2, EPI>(g, st);
+    case kGemm128x256: return launch_bf16_pp<1, EPI>(g, st);
     default: return launch_bf16_tc<TileSmall, EPI>(g, st);
   }
 }
