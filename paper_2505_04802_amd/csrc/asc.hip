@@ -454,8 +454,9 @@ extern "C" int reslim_asc_forward(reslim_ctx *c, const reslim_asc_plan *plan, co
                      static_cast<const float *>(w.big), plan->d_leaf, w.X, c->Wp, D),
                  hipGetLastError()));
   // blocks on the leaves: the batch is one run of L rows, one attention set per sample
+  const bool ahead = panel_used(c, plan->geom.n_h, w.X);
   for (int l = 0; l < c->cfg.depth; ++l)
-    if ((rc = block_impl(c, fn, l, w.X, 1, w, st, &plan->geom)) != RESLIM_OK) return rc;
+    if ((rc = block_impl(c, fn, l, w.X, 1, w, st, &plan->geom, nullptr, ahead && l > 0, ahead && l + 1 < c->cfg.depth)) != RESLIM_OK) return rc;
   // decompression = the final LayerNorm reading each patch's row from its leaf
   RESLIM_LAUNCH("layernorm_final", 0, dMi * dD * (4.0 + es),
                 launch_layernorm(dt, w.X, plan->d_patch_leaf, Mi, plan->L, c->d_lnf_g, c->d_lnf_b, w.A, Mi, D, st));

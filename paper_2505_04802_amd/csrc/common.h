@@ -108,6 +108,7 @@ struct reslim_ctx {
   float *d_zero_bias;// [max(3D, R, head_out)] zeros
   // device: blocks and head
   std::vector<reslim::LayerWeights> layers;
+  reslim::bf16_t *d_panel_w = nullptr;       // the blocks' matrices in the order of the panel kernel's fragments; null where it does not apply
   float *d_lnf_g, *d_lnf_b;
   void *d_w_head;    // act [head_out, D]
   float *d_b_head;
@@ -120,7 +121,7 @@ struct reslim_ctx {
   // optional per-launch timing (reslim_profile_*): events are created up front
   bool prof_on = false;
   std::vector<hipEvent_t> prof_ev;           // 2 per record slot
-  struct ProfRec { const char *name; double flop, bytes; };
+  struct ProfRec { const char *name; double flop, bytes; size_t ev; double share; };      // share of the time between events ev and ev + 1
   std::vector<ProfRec> prof_rec;             // records of the launches since the last reset
 };
 
@@ -162,8 +163,10 @@ Workspace plan_workspace(const reslim_ctx *c, int batch, void *base);
 // one transformer block on X [batch * geom.n_h, D] in place (geom == nullptr: the context's tiles)
 // z_first: the embedding in patch order [batch * N, D] when X does not hold the stream yet (the
 // first block of a whole forward; bf16 path, the context's own tiles)
+// qkv_ready: w.big holds the block's qkv already; qkv_next: leave the next block's there (contexts with packed
+// matrices; in a chain of blocks, see panel.hip)
 int block_impl(reslim_ctx *c, const char *fn, int layer, float *X, int batch, const Workspace &w, hipStream_t st,
-               const SeqGeom *geom = nullptr, const float *z_first = nullptr);
+               const SeqGeom *geom = nullptr, const float *z_first = nullptr, bool qkv_ready = false, bool qkv_next = false);
 int embed_full_impl(reslim_ctx *c, const char *fn, const float *x, int batch, const Workspace &w, hipStream_t st,
                     float *dst = nullptr);
 
@@ -189,6 +192,20 @@ hipError_t launch_gemm(int dtype, Epilogue epi, const void *A, const void *W, co
                        const ResRowMap *res_map = nullptr);
 // aux: EPI_BIAS_RES_F32: float skip input, [M, ldo] or the rows res_map names.  out2: EPI_BIAS_ACT_GELU2: act [M, ldo].
 hipError_t gemm_init();
+bool gemm_pinned();      // the debugging hook has chosen the GEMM kernel
+
+// ---- everything in a block that is not attention, one launch (panel.hip; same bits as the separate kernels)
+bool panel_takes(const reslim_ctx *c);      // contexts that get packed matrices
+// whether a block of so many rows is one launch: those of the patches without halo copies, so that a whole forward and its blocks
+// one by one choose alike.  Not for a stream that is not aligned to 16 bytes (its rows go straight into LDS), nor while the
+// debugging hook pins the GEMM kernel, which is then to be seen in launches of its own.
+bool panel_used(const reslim_ctx *c, int64_t rows, const void *stream);
+hipError_t panel_init();
+size_t panel_layer_elems(const reslim_ctx *c);      // of the four matrices of a layer
+hipError_t panel_pack(const reslim_ctx *c, int layer, bf16_t *dst, hipStream_t st);      // dst: of all layers
+// x <- res + proj(a) + mlp; qkv_next: with LayerNorm and QKV of layer + 1 behind it, else null
+hipError_t launch_panel_block(const reslim_ctx *c, int layer, const void *a, const float *res, const ResRowMap *res_map, float *x, void *qkv_next,
+                              int M, hipStream_t st);
 
 hipError_t launch_layernorm(int dtype, const float *x, const int32_t *row_src, int rows_per_sample_out,
                             int64_t rows_per_sample_in, const float *g, const float *b, void *out,
@@ -281,6 +298,25 @@ void plan_pool_free(PlanPool &pool);
     RESLIM_TRY(label, expr);                                                           \
     if (p_) {                                                                          \
       RESLIM_TRY("event", hipEventRecord(c->prof_ev[2 * slot_ + 1], st));              \
-      c->prof_rec.push_back({label, static_cast<double>(flop_), static_cast<double>(bytes_)}); \
+      c->prof_rec.push_back({label, static_cast<double>(flop_), static_cast<double>(bytes_), 2 * slot_, 1.0}); \
+    }                                                                                  \
+  } while (0)
+
+namespace reslim {
+struct LaunchPart { const char *label; double flop, bytes; };
+}
+// A launch that does the work of several steps: one record each, the time divided by their flop
+#define RESLIM_LAUNCH_PARTS(parts_, n_, expr)                                          \
+  do {                                                                                 \
+    const size_t slot_ = c->prof_rec.size();                                           \
+    const bool p_ = c->prof_on && 2 * (slot_ + (n_)) <= c->prof_ev.size();             \
+    if (p_) RESLIM_TRY("event", hipEventRecord(c->prof_ev[2 * slot_], st));            \
+    RESLIM_TRY((parts_)[0].label, expr);                                               \
+    if (p_) {                                                                          \
+      RESLIM_TRY("event", hipEventRecord(c->prof_ev[2 * slot_ + 1], st));              \
+      double sum_ = 0;                                                                 \
+      for (int i_ = 0; i_ < (n_); ++i_) sum_ += (parts_)[i_].flop;                     \
+      for (int i_ = 0; i_ < (n_); ++i_)                                                \
+        c->prof_rec.push_back({(parts_)[i_].label, (parts_)[i_].flop, (parts_)[i_].bytes, 2 * slot_, (parts_)[i_].flop / sum_}); \
     }                                                                                  \
   } while (0)

@@ -9,6 +9,7 @@
 #include <algorithm>
 
 #include "common.h"
+#include "layernorm_common.h"
 
 namespace reslim {
 
@@ -31,28 +32,33 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const float *__restrict_
   const float4 *xr = reinterpret_cast<const float4 *>(x + in_row * D);
   const int nv = D / 4;
   float4 v[NV];
-  float sum = 0.f;
+  // the sums follow the order of layernorm_common.h; rows of more than 512 columns, which no other kernel normalises, add up their
+  // pieces lane by lane first (one tree instead of one a piece)
+  constexpr int PIECES = NV <= 2 ? NV : 1;
+  float part[PIECES];
+#pragma unroll
+  for (int i = 0; i < PIECES; ++i) part[i] = 0.f;
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
     const int k = lane + 64 * i;
     v[i] = k < nv ? xr[k] : make_float4(0.f, 0.f, 0.f, 0.f);
-    sum += (v[i].x + v[i].y) + (v[i].z + v[i].w);
+    part[i % PIECES] += ln_sum4(v[i].x, v[i].y, v[i].z, v[i].w);
   }
+  auto total = [&]() {
+    float s = ln_lane_sum(part[0]);
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-  const float mean = sum / static_cast<float>(D);
-  float sq = 0.f;
+    for (int i = 1; i < PIECES; ++i) s += ln_lane_sum(part[i]);
+    return s;
+  };
+  const float mean = total() / static_cast<float>(D);
+#pragma unroll
+  for (int i = 0; i < PIECES; ++i) part[i] = 0.f;
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
     const int k = lane + 64 * i;
-    if (k < nv) {
-      const float a = v[i].x - mean, b = v[i].y - mean, c = v[i].z - mean, d = v[i].w - mean;
-      sq += (a * a + b * b) + (c * c + d * d);
-    }
+    if (k < nv) part[i % PIECES] += ln_square4(v[i].x - mean, v[i].y - mean, v[i].z - mean, v[i].w - mean);
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o);
-  const float rstd = rsqrtf(sq / static_cast<float>(D) + 1e-5f);
+  const float rstd = ln_rstd(total(), static_cast<float>(D));
   const float4 *g4 = reinterpret_cast<const float4 *>(g);
   const float4 *b4 = reinterpret_cast<const float4 *>(be);
   T *orow = out + row * D;
@@ -61,10 +67,8 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const float *__restrict_
     const int k = lane + 64 * i;
     if (k < nv) {
       const float4 gg = g4[k], bb = b4[k];
-      const float y0 = (v[i].x - mean) * rstd * gg.x + bb.x;
-      const float y1 = (v[i].y - mean) * rstd * gg.y + bb.y;
-      const float y2 = (v[i].z - mean) * rstd * gg.z + bb.z;
-      const float y3 = (v[i].w - mean) * rstd * gg.w + bb.w;
+      const float y0 = ln_apply(v[i].x, mean, rstd, gg.x, bb.x), y1 = ln_apply(v[i].y, mean, rstd, gg.y, bb.y);
+      const float y2 = ln_apply(v[i].z, mean, rstd, gg.z, bb.z), y3 = ln_apply(v[i].w, mean, rstd, gg.w, bb.w);
       if constexpr (sizeof(T) == 4) {
         reinterpret_cast<float4 *>(orow)[k] = make_float4(y0, y1, y2, y3);
       } else {

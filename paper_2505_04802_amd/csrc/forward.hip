@@ -81,8 +81,22 @@ static int embed_impl(reslim_ctx *c, const char *fn, const float *x, float *toke
   return RESLIM_OK;
 }
 
+// everything after the attention of a block in one launch; rows of the stream: dM
+static int panel_block_impl(reslim_ctx *c, const char *fn, int layer, const void *a, const float *res, const ResRowMap *skip, float *X, void *qkv_next,
+                            int M, hipStream_t st) {
+  const double es = static_cast<double>(act_size(c)), dM = M, dD = c->cfg.embed_dim, dR = c->R;
+  const LaunchPart parts[] = {{"gemm_proj", 2.0 * dM * dD * dD, dM * dD * es + dD * dD * es + 4.0 * dM * dD},
+                              {"layernorm", 0, 0},
+                              {"gemm_fc1", 2.0 * dM * dD * dR, dD * dR * es},
+                              {"gemm_fc2", 2.0 * dM * dD * dR, dD * dR * es + 4.0 * dM * dD},
+                              {"layernorm", 0, 0},
+                              {"gemm_qkv", 6.0 * dM * dD * dD, 3.0 * dD * dD * es + 3.0 * dM * dD * es}};
+  RESLIM_LAUNCH_PARTS(parts, qkv_next ? 6 : 4, launch_panel_block(c, layer, a, res, skip, X, qkv_next, M, st));
+  return RESLIM_OK;
+}
+
 int block_impl(reslim_ctx *c, const char *fn, int layer, float *X, int batch, const Workspace &w, hipStream_t st,
-               const SeqGeom *geom, const float *z_first) {
+               const SeqGeom *geom, const float *z_first, bool qkv_ready, bool qkv_next) {
   const int D = c->cfg.embed_dim, R = c->R, dt = c->cfg.dtype;
   const SeqGeom sg = geom ? *geom : ctx_geom(c);
   const int M = static_cast<int>(batch * sg.n_h);
@@ -92,20 +106,26 @@ int block_impl(reslim_ctx *c, const char *fn, int layer, float *X, int batch, co
   // z_first (first block of a whole forward): the stream is still the embedding in patch order;
   // the tile-major rows, halo copies included, are read from it through the gather list here and
   // by the projection's skip connection, which is what writes X for the first time
-  if (z_first)
-    RESLIM_LAUNCH("layernorm", 0, dM * dD * (4.0 + es),
-                  launch_layernorm(dt, z_first, c->d_gather, static_cast<int>(sg.n_h), c->N, lw.ln1_g, lw.ln1_b, w.A, M, D, st));
-  else
-    RESLIM_LAUNCH("layernorm", 0, dM * dD * (4.0 + es), launch_layernorm(dt, X, nullptr, 0, 0, lw.ln1_g, lw.ln1_b, w.A, M, D, st));
-  // bf16 path: the QKV epilogue multiplies q by log2(e)/sqrt(dh) before its one
-  // rounding to bf16, and the attention kernel then exponentiates in base 2 directly
   const bool qs = dt == RESLIM_BF16 && attention_accepts_prescaled_q();
-  const float qscale = 1.4426950408889634f / sqrtf(static_cast<float>(c->dh));
-  RESLIM_LAUNCH("gemm_qkv", 6.0 * dM * dD * dD, dM * dD * es + 3.0 * dD * dD * es + 3.0 * dM * dD * es,
-                launch_gemm(dt, qs ? EPI_BIAS_QSCALE_ACT : EPI_BIAS_ACT, w.A, lw.w_qkv, lw.b_qkv, w.big, 3 * D, nullptr, 0, M,
-                            3 * D, D, st, qscale, D));
+  if (!qkv_ready) {
+    if (z_first)
+      RESLIM_LAUNCH("layernorm", 0, dM * dD * (4.0 + es),
+                    launch_layernorm(dt, z_first, c->d_gather, static_cast<int>(sg.n_h), c->N, lw.ln1_g, lw.ln1_b, w.A, M, D, st));
+    else
+      RESLIM_LAUNCH("layernorm", 0, dM * dD * (4.0 + es), launch_layernorm(dt, X, nullptr, 0, 0, lw.ln1_g, lw.ln1_b, w.A, M, D, st));
+    // bf16 path: the QKV epilogue multiplies q by log2(e)/sqrt(dh) before its one
+    // rounding to bf16, and the attention kernel then exponentiates in base 2 directly
+    const float qscale = 1.4426950408889634f / sqrtf(static_cast<float>(c->dh));
+    RESLIM_LAUNCH("gemm_qkv", 6.0 * dM * dD * dD, dM * dD * es + 3.0 * dD * dD * es + 3.0 * dM * dD * es,
+                  launch_gemm(dt, qs ? EPI_BIAS_QSCALE_ACT : EPI_BIAS_ACT, w.A, lw.w_qkv, lw.b_qkv, w.big, 3 * D, nullptr, 0, M,
+                              3 * D, D, st, qscale, D));
+  }
   RESLIM_LAUNCH("tiles_attention", 4.0 * pairs * dD * batch, 4.0 * dM * dD * es,
                 launch_tiles_attention(c, w.big, w.A, batch, qs, st, nullptr, &sg));
+  if (panel_used(c, geom ? sg.n_h : static_cast<int64_t>(batch) * c->N, X)) {
+    const ResRowMap skip = {c->d_gather, static_cast<int>(sg.n_h), c->N};
+    return panel_block_impl(c, fn, layer, w.A, z_first ? z_first : X, z_first ? &skip : nullptr, X, qkv_next ? w.big : nullptr, M, st);
+  }
   if (z_first) {
     const ResRowMap skip = {c->d_gather, static_cast<int>(sg.n_h), c->N};
     RESLIM_LAUNCH("gemm_proj", 2.0 * dM * dD * dD, dM * dD * es + dD * dD * es + 8.0 * dM * dD,
@@ -124,22 +144,25 @@ int block_impl(reslim_ctx *c, const char *fn, int layer, float *X, int batch, co
 
 // The last block of a whole forward, when some tokens are halo copies: X is read (tile-major), the
 // block's output for the patches goes to w.Xc [batch * N, D] in patch order.
-static int last_block_impl(reslim_ctx *c, const char *fn, const float *X, int batch, const Workspace &w, hipStream_t st) {
+static int last_block_impl(reslim_ctx *c, const char *fn, const float *X, int batch, const Workspace &w, hipStream_t st, bool qkv_ready) {
   const int D = c->cfg.embed_dim, R = c->R, dt = c->cfg.dtype;
   const SeqGeom sg = ctx_geom(c);
   const int M = static_cast<int>(batch * sg.n_h), Mi = batch * c->N;
   const LayerWeights &lw = c->layers[c->cfg.depth - 1];
   const double es = static_cast<double>(act_size(c)), dM = M, dMi = Mi, dD = D, dR = R;
-  RESLIM_LAUNCH("layernorm", 0, dM * dD * (4.0 + es), launch_layernorm(dt, X, nullptr, 0, 0, lw.ln1_g, lw.ln1_b, w.A, M, D, st));
   const bool qs = attention_accepts_prescaled_q();
-  const float qscale = 1.4426950408889634f / sqrtf(static_cast<float>(c->dh));
-  RESLIM_LAUNCH("gemm_qkv", 6.0 * dM * dD * dD, dM * dD * es + 3.0 * dD * dD * es + 3.0 * dM * dD * es,
-                launch_gemm(dt, qs ? EPI_BIAS_QSCALE_ACT : EPI_BIAS_ACT, w.A, lw.w_qkv, lw.b_qkv, w.big, 3 * D, nullptr, 0, M,
-                            3 * D, D, st, qscale, D));
+  if (!qkv_ready) {
+    RESLIM_LAUNCH("layernorm", 0, dM * dD * (4.0 + es), launch_layernorm(dt, X, nullptr, 0, 0, lw.ln1_g, lw.ln1_b, w.A, M, D, st));
+    const float qscale = 1.4426950408889634f / sqrtf(static_cast<float>(c->dh));
+    RESLIM_LAUNCH("gemm_qkv", 6.0 * dM * dD * dD, dM * dD * es + 3.0 * dD * dD * es + 3.0 * dM * dD * es,
+                  launch_gemm(dt, qs ? EPI_BIAS_QSCALE_ACT : EPI_BIAS_ACT, w.A, lw.w_qkv, lw.b_qkv, w.big, 3 * D, nullptr, 0, M,
+                              3 * D, D, st, qscale, D));
+  }
   // queries: the owned tokens; keys and values: the whole haloed tile
   RESLIM_LAUNCH("tiles_attention", 4.0 * sg.pairs_owned * dD * batch, 3.0 * dM * dD * es + dMi * dD * es,
                 launch_tiles_attention(c, w.big, w.A, batch, qs, st, nullptr, nullptr, true));
   const ResRowMap skip = {c->d_interior_src, c->N, sg.n_h};
+  if (panel_used(c, Mi, X)) return panel_block_impl(c, fn, c->cfg.depth - 1, w.A, X, &skip, w.Xc, nullptr, Mi, st);
   RESLIM_LAUNCH("gemm_proj", 2.0 * dMi * dD * dD, dMi * dD * es + dD * dD * es + 8.0 * dMi * dD,
                 launch_gemm(dt, EPI_BIAS_RES_F32, w.A, lw.w_proj, lw.b_proj, w.Xc, D, nullptr, 0, Mi, D, D, st, 1.0f, 0, X, nullptr, &skip));
   RESLIM_LAUNCH("layernorm", 0, dMi * dD * (4.0 + es), launch_layernorm(dt, w.Xc, nullptr, 0, 0, lw.ln2_g, lw.ln2_b, w.A, Mi, D, st));
@@ -198,12 +221,13 @@ extern "C" int reslim_profile_read(reslim_ctx *c, reslim_profile_record *out, in
   *n_out = n;
   if (!out) return RESLIM_OK;
   for (int i = 0; i < n && i < max_out; ++i) {
-    if (hipEventSynchronize(c->prof_ev[2 * i + 1]) != hipSuccess) return set_error(c, RESLIM_EHIP, "reslim_profile_read: event sync failed");
+    const size_t ev = c->prof_rec[i].ev;
+    if (hipEventSynchronize(c->prof_ev[ev + 1]) != hipSuccess) return set_error(c, RESLIM_EHIP, "reslim_profile_read: event sync failed");
     float ms = 0.f;
-    if (hipEventElapsedTime(&ms, c->prof_ev[2 * i], c->prof_ev[2 * i + 1]) != hipSuccess)
+    if (hipEventElapsedTime(&ms, c->prof_ev[ev], c->prof_ev[ev + 1]) != hipSuccess)
       return set_error(c, RESLIM_EHIP, "reslim_profile_read: elapsed time failed");
     out[i].name = c->prof_rec[i].name;
-    out[i].ms = ms;
+    out[i].ms = static_cast<float>(ms * c->prof_rec[i].share);
     out[i].flop = c->prof_rec[i].flop;
     out[i].bytes = c->prof_rec[i].bytes;
   }
@@ -314,9 +338,12 @@ extern "C" int reslim_forward(reslim_ctx *c, const float *x, float *y, int32_t b
   if (fold_gather) rc = embed_full_impl(c, fn, x, batch, w, st, w.Xc);
   else rc = embed_impl(c, fn, x, w.X, batch, w, st);
   if (rc != RESLIM_OK) return rc;
+  // where a block's products are one launch, it leaves the next block's qkv as well
+  const bool ahead = panel_used(c, static_cast<int64_t>(batch) * c->N, w.X);
   for (int l = 0; l < c->cfg.depth - (stitch ? 1 : 0); ++l)
-    if ((rc = block_impl(c, fn, l, w.X, batch, w, st, nullptr, l == 0 && fold_gather ? w.Xc : nullptr)) != RESLIM_OK) return rc;
+    if ((rc = block_impl(c, fn, l, w.X, batch, w, st, nullptr, l == 0 && fold_gather ? w.Xc : nullptr, ahead && l > 0,
+                         ahead && l + 1 < c->cfg.depth)) != RESLIM_OK) return rc;
   if (!stitch) return head_impl(c, fn, x, w.X, y, batch, w, st);
-  if ((rc = last_block_impl(c, fn, w.X, batch, w, st)) != RESLIM_OK) return rc;
+  if ((rc = last_block_impl(c, fn, w.X, batch, w, st, ahead && c->cfg.depth > 1)) != RESLIM_OK) return rc;
   return head_impl(c, fn, x, w.Xc, y, batch, w, st, true);
 }

@@ -17,6 +17,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "gelu.h"
 #include "gemm_cursor.h"
 #include "gemm_plan.h"
 
@@ -51,23 +52,6 @@ __device__ __forceinline__ float gelu_erf(float x) {
   return 0.5f * x * (1.0f + erff(x * 0.70710678118654752440f));
 }
 
-// GELU for bf16 outputs without the reciprocal and the branches of the library erf:
-// with u = min(|x|, 5), Phi(-u) = 2^P(u) where P is a degree-6 fit of log2 of the
-// normal tail on [0, 5] (interpolated at Chebyshev nodes), and
-// gelu(x) = max(x, 0) - u Phi(-u).  Relative error <= 1.5e-5 of gelu(x) on |x| <= 5
-// and absolute error <= 1.5e-6 beyond, against 2^-9 for the bf16 rounding that
-// follows; 11 vector operations per element, one of them an exponential.
-__device__ __forceinline__ float gelu_erf_fast(float x) {
-  const float u = fminf(fabsf(x), 5.0f);
-  float p = fmaf(2.975744064e-05f, u, -7.135751075e-04f);
-  p = fmaf(p, u, 7.775241509e-03f);
-  p = fmaf(p, u, -5.269032717e-02f);
-  p = fmaf(p, u, -4.595123231e-01f);
-  p = fmaf(p, u, -1.150926590e+00f);
-  p = fmaf(p, u, -1.000011683e+00f);
-  return fmaf(-u, __builtin_amdgcn_exp2f(p), fmaxf(x, 0.0f));
-}
-
 // Every epilogue runs with the MFMA operand roles swapped: the accumulator block is
 // then C^T, a lane holds one output row (lane % 32) and four consecutive columns per
 // register quad.  All outputs go through a 4 KB staging area of the wave in LDS, bf16
@@ -88,13 +72,6 @@ __device__ __forceinline__ float epi_act_value(float v, float sc) {
   if constexpr (EPI == EPI_BIAS_QSCALE_ACT) return v * sc;
   if constexpr (EPI == EPI_BIAS_GELU_ACT || (EPI == EPI_BIAS_ACT_GELU2 && SECOND)) return gelu_erf_fast(v);
   return v;
-}
-
-// two floats -> two bf16 in one register (one hardware conversion)
-__device__ __forceinline__ uint32_t pack2(float lo, float hi) {
-  typedef __attribute__((ext_vector_type(2))) float f32x2;
-  typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
 }
 
 // Rows m_first .. m_first + 31, columns n_first .. n_first + 63 (two accumulator
@@ -592,6 +569,8 @@ static hipError_t init_epi() {
   if ((e = set_attr_pp<1, EPI>()) != hipSuccess) return e;
   return set_attr<TileSmall, EPI>();
 }
+
+bool gemm_pinned() { return g_gemm_tile_override >= 0; }
 
 hipError_t gemm_init() {
   hipError_t e;
