@@ -528,6 +528,223 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
   }
 }
 
+// ------------------------------------------------------------------ bf16 kernel for few queries: keys split over the waves
+// With fewer units of 128 queries than compute units (one sample's 2300 leaves at four heads are 72) the kernel above leaves
+// most of the chip idle and every wave walks all keys, 36 blocks of 64 one after the other: 14.7 us.  Here a work-group takes 32
+// queries and its four waves take every fourth block of 32 keys each, with a softmax of their own and without a barrier; the four
+// meet once in LDS, added in wave order: 288 work-groups of 18 blocks, 7.8 us.  What bounds it is the path that feeds K and V from
+// L2 (every 32 queries read all of them) and the chain of a wave's blocks.
+//
+// A wave's K and V tiles (32 keys, 4 KiB each) go through a ring of its own of five tiles in the order K0 V0 K1 V1 ...: when
+// tile i has been read its place takes tile i + 5, so two blocks are in flight and two work-groups fit a compute unit.  Fragments,
+// swizzles, the running reference and the row sums are those of the kernel above.
+template <int DH, bool QS, bool ST>
+__global__ __launch_bounds__(256, 2) void tiles_attention_split_bf16_kernel(AttnArgs a) {
+  static_assert(DH == 64, "fragment tables below");
+  constexpr int ROWB = DH * 2, TILE = 32 * ROWB, RING = 5, NKS = DH / 16;
+  __shared__ __align__(1024) unsigned char smem[4 * RING * TILE];
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int l32 = lane & 31, hi = lane >> 5;
+  const int ld = 3 * a.D, ld2 = ld * 2;
+  const int QB = a.QB * 4;                                       // units of 32 queries
+  const int logical = xcd_remap_attn(blockIdx.x, a.total * 4);
+  const int qb = logical % QB;
+  int rest = logical / QB;
+  const int head = rest % a.heads;
+  rest /= a.heads;
+  const int tile = rest % a.T, b = rest / a.T;
+  const tile_desc &td = a.tiles[tile];
+  const int n_t = td.n_tok, q0 = qb * 32;
+  if (q0 >= n_t) return;                                         // uniform
+  const int bw = td.X1 - td.X0;
+  if constexpr (ST) {                                            // no query of these belongs to the tile
+    const int lo = (td.y0 - td.Y0) * bw + (td.x0 - td.X0), up = (td.y1 - 1 - td.Y0) * bw + (td.x1 - 1 - td.X0);
+    if (q0 > up || q0 + 31 < lo) return;
+  }
+  const size_t row0 = static_cast<size_t>(b) * a.n_h + td.tok_off;
+  const bf16_t *base = static_cast<const bf16_t *>(a.qkv) + row0 * ld + head * DH;
+  const int blocks = (n_t + 31) / 32, mine = (blocks - wave + 3) / 4;      // this wave's blocks: wave, wave + 4, ...
+  unsigned char *const ring = smem + wave * RING * TILE;
+
+  // ---- load side: 4 KiB = 4 loads of 8 rows
+  auto swzK = [](int r) { return (r & 7) ^ ((r >> 3) & 1); };
+  auto swzV = [](int r) { return (((r >> 1) & 1) << 2) | (((r >> 3) & 1) << 1); };
+  int offK[4], offV[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = 8 * i + (lane >> 3);
+    offK[i] = r * ld2 + ((lane & 7) ^ swzK(r)) * 16;
+    offV[i] = r * ld2 + ((lane & 7) ^ swzV(r)) * 16;
+  }
+  // tile i of this wave: K (even) or V (odd) of its block i / 2; rows past the end re-read the last one (finite, masked)
+  auto issue = [&](int i) {
+    const int k0 = (wave + 4 * (i >> 1)) * 32, lim = n_t - 1 - k0;
+    const unsigned char *g = reinterpret_cast<const unsigned char *>(base + ((i & 1) + 1) * a.D + static_cast<size_t>(k0) * ld);
+    unsigned char *dst = ring + (i % RING) * TILE;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int back = max(8 * j + (lane >> 3) - lim, 0) * ld2;
+      attn_dl_load16(reinterpret_cast<const bf16_t *>(g + static_cast<uint32_t>(((i & 1) ? offV[j] : offK[j]) - back)), dst + j * 1024);
+    }
+  };
+  const int tiles = 2 * mine;
+  bf16x8 qf[NKS];
+  {
+    const bf16_t *qp = base + static_cast<size_t>(min(q0 + l32, n_t - 1)) * ld + hi * 8;
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8 *>(qp + ks * 16);
+  }
+  for (int i = 0; i < RING && i < tiles; ++i) issue(i);
+
+  // ---- read side (see the kernel above)
+  const int kr = key_perm(l32), k_row = kr * ROWB, k_swz = swzK(kr), L16 = lane & 15;
+  unsigned v_addr[2][2];
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const int vr = 8 * hi + 4 * e + (L16 >> 2);
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+      const int o = 32 * d + 16 * ((lane >> 4) & 1) + 4 * (L16 & 3);
+      v_addr[e][d] = vr * ROWB + (((o >> 3) ^ swzV(vr)) << 4) + ((o >> 2) & 1) * 8;
+    }
+  }
+  // tile i has landed; with four or more tiles behind it their loads stay in flight
+  auto landed = [&](int i) {
+    if (i + RING <= tiles) __builtin_amdgcn_s_waitcnt(0x0F70 | (16 & 15) | ((16 >> 4) << 14));
+    else __builtin_amdgcn_s_waitcnt(0x0F70);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  f32x16 o[2], minit;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) o[0][r] = o[1][r] = minit[r] = 0.f;
+  float lsum = 0.f;
+  const float c = QS ? 1.0f : a.scale_log2, TAU = 10.0f / c;
+  bool have_ref = false;
+  const unsigned ring0 = static_cast<unsigned>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const unsigned char *)ring));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const bf16x2 one2 = {static_cast<__bf16>(1.0f), static_cast<__bf16>(1.0f)};
+  for (int n = 0; n < mine; ++n) {
+    landed(2 * n);
+    const unsigned char *st = ring + (2 * n % RING) * TILE;
+    bf16x8 kf[NKS];
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) kf[ks] = *reinterpret_cast<const bf16x8 *>(st + k_row + (((2 * ks + hi) ^ k_swz) << 4));
+    f32x16 s;
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[ks], ks == 0 ? minit : s, 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);      // the fragments are in registers: their place may be loaded again
+    if (2 * n + RING < tiles) issue(2 * n + RING);
+    const int k0 = (wave + 4 * n) * 32;
+    if (k0 + 32 > n_t) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (k0 + 16 * (r / 8) + 8 * hi + (r % 8) >= n_t) s[r] = -INFINITY;
+    }
+    float mx = s[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
+    {
+      unsigned m_lo, m_up;
+      lane_pair_exchange(__builtin_bit_cast(unsigned, mx), m_lo, m_up);
+      mx = fmaxf(__builtin_bit_cast(float, m_lo), __builtin_bit_cast(float, m_up));      // finite: every block holds a valid key
+    }
+    if (!have_ref || __any(mx > TAU)) {
+      const float d = have_ref ? fmaxf(mx, 0.f) : mx;
+      const float alpha = have_ref ? __builtin_amdgcn_exp2f(-d * c) : 0.f;
+      const float ninit = minit[0] - d;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        s[r] -= d;
+        o[0][r] *= alpha;
+        o[1][r] *= alpha;
+        minit[r] = ninit;
+      }
+      lsum *= alpha;
+      have_ref = true;
+    }
+    bf16x8 pf[2];
+#pragma unroll
+    for (int h2 = 0; h2 < 2; ++h2)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) pf[h2][e] = static_cast<__bf16>(__builtin_amdgcn_exp2f(QS ? s[8 * h2 + e] : s[8 * h2 + e] * c));
+    landed(2 * n + 1);
+    const unsigned vbase = ring0 + (2 * n + 1) % RING * TILE;
+    unsigned va[2][2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+      for (int d = 0; d < 2; ++d) va[e][d] = vbase + v_addr[e][d];
+    VFrag64 vf;
+    v_frag_issue<0>(vf, va);
+#pragma unroll
+    for (int h2 = 0; h2 < 2; ++h2)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) lsum = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pf[h2][2 * i], pf[h2][2 * i + 1]}, one2, lsum, false);
+    v_frag_wait(vf);
+    __builtin_amdgcn_sched_barrier(0);
+    if (2 * n + 1 + RING < tiles) issue(2 * n + 1 + RING);
+#pragma unroll
+    for (int h2 = 0; h2 < 2; ++h2)
+#pragma unroll
+      for (int d = 0; d < 2; ++d) {
+        typedef __attribute__((ext_vector_type(2))) uint64_t u64x2;
+        const u64x2 both = {vf.r[h2][d][0], vf.r[h2][d][1]};
+        o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), pf[h2], o[d], 0, 0, 0);
+      }
+  }
+
+  // ---- the four waves meet: references and sums first, then the outputs, each wave's part of the features
+  __syncthreads();                                               // nobody reads or loads a ring any more
+  float *const stat = reinterpret_cast<float *>(smem);           // [4][2][32]
+  float *const box = stat + 4 * 2 * 32;                          // [4][32][64]
+  {
+    unsigned l_lo, l_up;
+    lane_pair_exchange(__builtin_bit_cast(unsigned, lsum), l_lo, l_up);
+    if (hi == 0) {
+      stat[(wave * 2) * 32 + l32] = have_ref ? -minit[0] * c : -INFINITY;      // a wave without keys
+      stat[(wave * 2 + 1) * 32 + l32] = __builtin_bit_cast(float, l_lo) + __builtin_bit_cast(float, l_up);
+    }
+  }
+#pragma unroll
+  for (int d = 0; d < 2; ++d)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) box[(wave * 32 + d * 16 + r) * 64 + lane] = o[d][r];
+  __syncthreads();
+  float top = stat[l32], f[4], total = 0.f;                      // wave 0 has the first block: finite
+#pragma unroll
+  for (int w = 1; w < 4; ++w) top = fmaxf(top, stat[w * 2 * 32 + l32]);
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    f[w] = __builtin_amdgcn_exp2f(stat[w * 2 * 32 + l32] - top);
+    total = fmaf(stat[(w * 2 + 1) * 32 + l32], f[w], total);
+  }
+  const int qrow = q0 + l32;
+  if (qrow >= n_t) return;
+  size_t orow = row0 + qrow;
+  if constexpr (ST) {
+    const int yy = td.Y0 + qrow / bw, xx = td.X0 + qrow % bw;
+    if (!(yy >= td.y0 && yy < td.y1 && xx >= td.x0 && xx < td.x1)) return;
+    orow = static_cast<size_t>(b) * a.N + static_cast<size_t>(yy) * a.Wp + xx;
+  }
+  const float inv = 1.0f / total;
+  if (!ST && a.lse && wave == 0 && hi == 0)
+    a.lse[(static_cast<size_t>(b) * a.heads + head) * a.n_h + td.tok_off + qrow] = (__builtin_amdgcn_logf(total) + top) * 0.69314718055994531f;
+  bf16_t *op = static_cast<bf16_t *>(a.out) + orow * a.D + head * DH + hi * 4 + (wave >> 1) * 32 + (wave & 1) * 16;
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {                                  // registers 4 r4 .. + 3 of feature block wave / 2, r4 = 2 (wave % 2) + p
+    bf16x4 tmp;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int r = (wave >> 1) * 16 + (wave & 1) * 8 + 4 * p + e;
+      float v = 0.f;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) v = fmaf(box[(w * 32 + r) * 64 + lane], f[w], v);
+      tmp[e] = static_cast<__bf16>(v * inv);
+    }
+    *reinterpret_cast<u32x2 *>(op + p * 8) = __builtin_bit_cast(u32x2, tmp);
+  }
+}
+
 // ------------------------------------------------------------------ fp32 path
 // 32 queries of one (sample, tile, head) per work-group, MFMA 32x32x2 in fp32 with operands straight from global memory.
 // The four waves take every fourth block of 32 keys, each with a softmax of its own (running maximum, sum and output);
@@ -719,7 +936,14 @@ hipError_t launch_tiles_attention(const reslim_ctx *c, const void *qkv, void *ou
     if (g_attn_cus <= 0) return hipErrorInvalidValue;
     const int pg2 = a.total < 2 * g_attn_cus ? a.total : 2 * g_attn_cus;   // persistent grids
     const int pg3 = a.total < 3 * g_attn_cus ? a.total : 3 * g_attn_cus;
-    if (c->dh == 64 && g_attn_variant == 0) launch_bf16_variant<64, 64, 3, 2, 1>(a, q_prescaled, stitched, pg3, st);
+    // no more units of 128 queries than compute units, and long enough that a wave has several blocks of its own: see the kernel
+    if (c->dh == 64 && g_attn_variant == 0 && a.total <= g_attn_cus && sg.max_n_tok >= 512) {
+      const dim3 grid(4 * a.total), blk(256);
+      if (stitched && q_prescaled) tiles_attention_split_bf16_kernel<64, true, true><<<grid, blk, 0, st>>>(a);
+      else if (stitched) tiles_attention_split_bf16_kernel<64, false, true><<<grid, blk, 0, st>>>(a);
+      else if (q_prescaled) tiles_attention_split_bf16_kernel<64, true, false><<<grid, blk, 0, st>>>(a);
+      else tiles_attention_split_bf16_kernel<64, false, false><<<grid, blk, 0, st>>>(a);
+    } else if (c->dh == 64 && g_attn_variant == 0) launch_bf16_variant<64, 64, 3, 2, 1>(a, q_prescaled, stitched, pg3, st);
     else if (c->dh == 64) launch_bf16_variant<64, 128, 2>(a, q_prescaled, stitched, pg2, st);
     else if (c->dh == 128) launch_bf16_variant<128, 64, 2>(a, q_prescaled, stitched, pg2, st);
     else if (c->dh == 256) {
