@@ -191,6 +191,10 @@ hipError_t launch_gemm(int dtype, Epilogue epi, const void *A, const void *W, co
                        hipStream_t st, float qscale = 1.0f, int qcols = 0, const void *aux = nullptr, void *out2 = nullptr,
                        const ResRowMap *res_map = nullptr);
 // aux: EPI_BIAS_RES_F32: float skip input, [M, ldo] or the rows res_map names.  out2: EPI_BIAS_ACT_GELU2: act [M, ldo].
+// out = LayerNorm(x) W^T (+ epilogue) in one launch, fp32 path: rows of up to 256 features while the outputs are few; `rows`: which rows of x
+bool gemm_takes_layernorm(int dtype, const void *A, const void *W, const float *ln_g, const float *ln_b, int M, int N, int K);
+hipError_t launch_layernorm_gemm(Epilogue epi, const float *x, const ResRowMap *rows, const float *ln_g, const float *ln_b, const float *W,
+                                 const float *bias, float *out, int M, int N, int K, hipStream_t st);
 hipError_t gemm_init();
 bool gemm_pinned();      // the debugging hook has chosen the GEMM kernel
 

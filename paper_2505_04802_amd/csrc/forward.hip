@@ -81,6 +81,24 @@ static int embed_impl(reslim_ctx *c, const char *fn, const float *x, float *toke
   return RESLIM_OK;
 }
 
+// LayerNorm and the product behind it: one launch where gemm_takes_layernorm(), else two, the normalised rows in w.A.
+// x: the stream; rows: which of its rows (see ResRowMap), else all M
+static int layernorm_product(reslim_ctx *c, const char *fn, const char *ln_label, const char *label, double flop, double bytes, Epilogue epi,
+                             const float *x, const ResRowMap *rows, const float *ln_g, const float *ln_b, const void *W, const float *bias, void *out,
+                             void *normalised, int M, int N, hipStream_t st, float qscale = 1.0f, int qcols = 0) {
+  const int D = c->cfg.embed_dim, dt = c->cfg.dtype;
+  const double es = static_cast<double>(act_size(c)), dM = M, dD = D;
+  if ((epi == EPI_BIAS_ACT || epi == EPI_BIAS_GELU_ACT || epi == EPI_BIAS_F32) && gemm_takes_layernorm(dt, x, W, ln_g, ln_b, M, N, D)) {
+    const LaunchPart parts[] = {{ln_label, 0, 0}, {label, flop, bytes}};
+    RESLIM_LAUNCH_PARTS(parts, 2, launch_layernorm_gemm(epi, x, rows, ln_g, ln_b, static_cast<const float *>(W), bias, static_cast<float *>(out), M, N, D, st));
+    return RESLIM_OK;
+  }
+  RESLIM_LAUNCH(ln_label, 0, dM * dD * (4.0 + es),
+                launch_layernorm(dt, x, rows ? rows->map : nullptr, rows ? rows->rows_out : 0, rows ? rows->rows_in : 0, ln_g, ln_b, normalised, M, D, st));
+  RESLIM_LAUNCH(label, flop, bytes, launch_gemm(dt, epi, normalised, W, bias, out, N, nullptr, 0, M, N, D, st, qscale, qcols));
+  return RESLIM_OK;
+}
+
 // everything after the attention of a block in one launch; rows of the stream: dM
 static int panel_block_impl(reslim_ctx *c, const char *fn, int layer, const void *a, const float *res, const ResRowMap *skip, float *X, void *qkv_next,
                             int M, hipStream_t st) {
@@ -108,17 +126,14 @@ int block_impl(reslim_ctx *c, const char *fn, int layer, float *X, int batch, co
   // by the projection's skip connection, which is what writes X for the first time
   const bool qs = dt == RESLIM_BF16 && attention_accepts_prescaled_q();
   if (!qkv_ready) {
-    if (z_first)
-      RESLIM_LAUNCH("layernorm", 0, dM * dD * (4.0 + es),
-                    launch_layernorm(dt, z_first, c->d_gather, static_cast<int>(sg.n_h), c->N, lw.ln1_g, lw.ln1_b, w.A, M, D, st));
-    else
-      RESLIM_LAUNCH("layernorm", 0, dM * dD * (4.0 + es), launch_layernorm(dt, X, nullptr, 0, 0, lw.ln1_g, lw.ln1_b, w.A, M, D, st));
     // bf16 path: the QKV epilogue multiplies q by log2(e)/sqrt(dh) before its one
     // rounding to bf16, and the attention kernel then exponentiates in base 2 directly
     const float qscale = 1.4426950408889634f / sqrtf(static_cast<float>(c->dh));
-    RESLIM_LAUNCH("gemm_qkv", 6.0 * dM * dD * dD, dM * dD * es + 3.0 * dD * dD * es + 3.0 * dM * dD * es,
-                  launch_gemm(dt, qs ? EPI_BIAS_QSCALE_ACT : EPI_BIAS_ACT, w.A, lw.w_qkv, lw.b_qkv, w.big, 3 * D, nullptr, 0, M,
-                              3 * D, D, st, qscale, D));
+    const ResRowMap gather = {c->d_gather, static_cast<int>(sg.n_h), c->N};
+    const int rc = layernorm_product(c, fn, "layernorm", "gemm_qkv", 6.0 * dM * dD * dD, dM * dD * es + 3.0 * dD * dD * es + 3.0 * dM * dD * es,
+                                     qs ? EPI_BIAS_QSCALE_ACT : EPI_BIAS_ACT, z_first ? z_first : X, z_first ? &gather : nullptr, lw.ln1_g, lw.ln1_b,
+                                     lw.w_qkv, lw.b_qkv, w.big, w.A, M, 3 * D, st, qscale, D);
+    if (rc != RESLIM_OK) return rc;
   }
   RESLIM_LAUNCH("tiles_attention", 4.0 * pairs * dD * batch, 4.0 * dM * dD * es,
                 launch_tiles_attention(c, w.big, w.A, batch, qs, st, nullptr, &sg));
@@ -134,9 +149,9 @@ int block_impl(reslim_ctx *c, const char *fn, int layer, float *X, int batch, co
     RESLIM_LAUNCH("gemm_proj", 2.0 * dM * dD * dD, dM * dD * es + dD * dD * es + 8.0 * dM * dD,
                   launch_gemm(dt, EPI_BIAS_RESADD_F32, w.A, lw.w_proj, lw.b_proj, X, D, nullptr, 0, M, D, D, st));
   }
-  RESLIM_LAUNCH("layernorm", 0, dM * dD * (4.0 + es), launch_layernorm(dt, X, nullptr, 0, 0, lw.ln2_g, lw.ln2_b, w.A, M, D, st));
-  RESLIM_LAUNCH("gemm_fc1", 2.0 * dM * dD * dR, dM * dD * es + dD * dR * es + dM * dR * es,
-                launch_gemm(dt, EPI_BIAS_GELU_ACT, w.A, lw.w_fc1, lw.b_fc1, w.big, R, nullptr, 0, M, R, D, st));
+  const int rc = layernorm_product(c, fn, "layernorm", "gemm_fc1", 2.0 * dM * dD * dR, dM * dD * es + dD * dR * es + dM * dR * es, EPI_BIAS_GELU_ACT, X,
+                                   nullptr, lw.ln2_g, lw.ln2_b, lw.w_fc1, lw.b_fc1, w.big, w.A, M, R, st);
+  if (rc != RESLIM_OK) return rc;
   RESLIM_LAUNCH("gemm_fc2", 2.0 * dM * dD * dR, dM * dR * es + dD * dR * es + 8.0 * dM * dD,
                 launch_gemm(dt, EPI_BIAS_RESADD_F32, w.big, lw.w_fc2, lw.b_fc2, X, D, nullptr, 0, M, D, R, st));
   return RESLIM_OK;
@@ -176,14 +191,15 @@ static int last_block_impl(reslim_ctx *c, const char *fn, const float *X, int ba
 // tokens: tile-major [batch * n_h, D], or with `stitched` the patches' rows [batch * N, D] in patch order
 static int head_impl(reslim_ctx *c, const char *fn, const float *x, const float *tokens, float *y, int batch, const Workspace &w, hipStream_t st,
                      bool stitched = false) {
-  const int D = c->cfg.embed_dim, dt = c->cfg.dtype;
+  const int D = c->cfg.embed_dim;
   const int Mi = batch * c->N;
   const double es = static_cast<double>(act_size(c)), dMi = Mi, dD = D, dO = c->head_out;
   const double fine = static_cast<double>(batch) * c->cfg.out_vars * c->cfg.H * c->cfg.W * c->cfg.scale * c->cfg.scale;
-  RESLIM_LAUNCH("layernorm_final", 0, dMi * dD * (4.0 + es),
-                launch_layernorm(dt, tokens, stitched ? nullptr : c->d_interior_src, c->N, c->n_h, c->d_lnf_g, c->d_lnf_b, w.A, Mi, D, st));
-  RESLIM_LAUNCH("gemm_head", 2.0 * dMi * dD * dO, dMi * dD * es + dD * dO * es + 4.0 * dMi * dO,
-                launch_gemm(dt, EPI_BIAS_F32, w.A, c->d_w_head, c->d_b_head, w.big, c->head_out, nullptr, 0, Mi, c->head_out, D, st));
+  const ResRowMap owned = {c->d_interior_src, c->N, c->n_h};
+  const int rc = layernorm_product(c, fn, "layernorm_final", "gemm_head", 2.0 * dMi * dD * dO, dMi * dD * es + dD * dO * es + 4.0 * dMi * dO,
+                                   EPI_BIAS_F32, tokens, stitched ? nullptr : &owned, c->d_lnf_g, c->d_lnf_b, c->d_w_head, c->d_b_head, w.big, w.A, Mi,
+                                   c->head_out, st);
+  if (rc != RESLIM_OK) return rc;
   RESLIM_LAUNCH("residual_unpatchify", 0,
                 4.0 * batch * c->cfg.out_vars * c->cfg.H * c->cfg.W + 4.0 * dMi * dO + 4.0 * fine,
                 launch_residual_unpatchify(c, x, w.big, 0, y, batch, st));

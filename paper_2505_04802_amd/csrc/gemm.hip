@@ -45,6 +45,11 @@ struct GemmArgs {
   int res_out;
   int64_t res_in;
   void *out2;              // EPI_BIAS_ACT_GELU2: second output (act), layout of out
+  // fp32 kernel with LayerNorm in front: gain and bias; rows of A through a map (see ResRowMap) where it is set
+  const float *ln_g, *ln_b;
+  const int32_t *a_map;
+  int a_out;
+  int64_t a_in;
 };
 
 
@@ -414,15 +419,24 @@ __device__ __forceinline__ void epilogue_store_f32(const GemmArgs &g, int m, int
 // of its own once there are enough of them.  Steps are fetched AHEAD of their use.  The tiny workload's products
 // (512 x 128 x 512 the longest) take 4-5 us each; the LDS-tiled vector kernel before took 22 to 70.
 // VEC4: every row starts on 16 bytes.
-template <int EPI, int KS, bool VEC4>
+// LN: A is the stream, normalised here (KS = 4, VEC4, K <= kLnK: a wave's part of its 32 rows stays in registers between
+// the statistics and the products).  Every column tile of the output repeats that, but a LayerNorm launch of its own takes 3 us on the tiny
+// workload, whatever there is to do, and this adds one: 512 x 384 x 128 and its LayerNorm 8.6 -> 6.5 us, the tiny forward 99 -> 90.
+constexpr int kLnK = 256;
+template <int EPI, int KS, bool VEC4, bool LN = false>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
   constexpr int AHEAD = 4;
+  static_assert(!LN || (KS == 4 && VEC4), "rows in registers");
   __shared__ float part[KS == 4 ? 3 * 16 * 64 : 1];
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int l32 = lane & 31, hi = lane >> 5;
   const int m0 = KS == 4 ? blockIdx.x * 32 : blockIdx.x * 64 + (wave >> 1) * 32;
   const int n0 = KS == 4 ? blockIdx.y * 32 : blockIdx.y * 64 + (wave & 1) * 32;
-  const float *a = static_cast<const float *>(g.A) + static_cast<size_t>(min(m0 + l32, g.M - 1)) * g.K;
+  size_t arow = min(m0 + l32, g.M - 1);
+  if constexpr (LN) {
+    if (g.a_map) arow = static_cast<size_t>(arow / g.a_out) * g.a_in + g.a_map[arow % g.a_out];
+  }
+  const float *a = static_cast<const float *>(g.A) + arow * g.K;
   const float *w = static_cast<const float *>(g.W) + static_cast<size_t>(min(n0 + l32, g.N - 1)) * g.K;
   const int steps = (g.K + 7) / 8, per = KS == 4 ? (steps + 3) / 4 : steps;
   const int s0 = KS == 4 ? wave * per : 0, s1 = min(steps, s0 + per);
@@ -437,22 +451,64 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
     }
   };
   f32x16 acc = {};
-  float4 ra[AHEAD], rw[AHEAD];
+  auto multiply = [&](const float4 &x, const float4 &y) {
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(y.x, x.x, acc, 0, 0, 0);      // operands swapped: the block is C^T
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(y.y, x.y, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(y.z, x.z, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(y.w, x.w, acc, 0, 0, 0);
+  };
+  if constexpr (LN) {
+    constexpr int MOST = kLnK / 8 / 4;         // steps of a wave
+    __shared__ float box[2][4][32];
+    float4 ra[MOST], rw[MOST], ga[MOST], be[MOST];
+    auto in_row = [&](int i) { return s0 + i < s1 && 8 * (s0 + i) + 4 * hi < g.K; };
 #pragma unroll
-  for (int i = 0; i < AHEAD; ++i) {
-    ra[i] = fetch(a, s0 + i);
-    rw[i] = fetch(w, s0 + i);
-  }
-  for (int s = s0; s < s1; s += AHEAD) {
+    for (int i = 0; i < MOST; ++i) ra[i] = fetch(a, s0 + i);
 #pragma unroll
-    for (int i = 0; i < AHEAD; ++i) {          // steps past s1 multiply zeros
-      const float4 x = ra[i], y = rw[i];
-      ra[i] = fetch(a, s + AHEAD + i);
-      rw[i] = fetch(w, s + AHEAD + i);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(y.x, x.x, acc, 0, 0, 0);      // operands swapped: the block is C^T
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(y.y, x.y, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(y.z, x.z, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(y.w, x.w, acc, 0, 0, 0);
+    for (int i = 0; i < MOST; ++i) {
+      ga[i] = fetch(g.ln_g, s0 + i);
+      be[i] = fetch(g.ln_b, s0 + i);
+      rw[i] = fetch(w, s0 + i);
+    }
+    auto row_total = [&](float s, float (*b)[32]) {      // over the two lanes and the four waves that hold the row
+      s += __shfl_xor(s, 32);
+      if (hi == 0) b[wave][l32] = s;
+      __syncthreads();
+      return (b[0][l32] + b[1][l32]) + (b[2][l32] + b[3][l32]);
+    };
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < MOST; ++i) s += (ra[i].x + ra[i].y) + (ra[i].z + ra[i].w);
+    const float mean = row_total(s, box[0]) / static_cast<float>(g.K);
+    s = 0.f;
+#pragma unroll
+    for (int i = 0; i < MOST; ++i)
+      if (in_row(i)) {
+        const float x = ra[i].x - mean, y = ra[i].y - mean, z = ra[i].z - mean, u = ra[i].w - mean;
+        s += (x * x + y * y) + (z * z + u * u);
+      }
+    const float rstd = rsqrtf(row_total(s, box[1]) / static_cast<float>(g.K) + 1e-5f);
+#pragma unroll
+    for (int i = 0; i < MOST; ++i) {           // gain, bias and weights past the row are zero
+      const float4 v = ra[i];
+      multiply(make_float4((v.x - mean) * rstd * ga[i].x + be[i].x, (v.y - mean) * rstd * ga[i].y + be[i].y,
+                           (v.z - mean) * rstd * ga[i].z + be[i].z, (v.w - mean) * rstd * ga[i].w + be[i].w), rw[i]);
+    }
+  } else {
+    float4 ra[AHEAD], rw[AHEAD];
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) {
+      ra[i] = fetch(a, s0 + i);
+      rw[i] = fetch(w, s0 + i);
+    }
+    for (int s = s0; s < s1; s += AHEAD) {
+#pragma unroll
+      for (int i = 0; i < AHEAD; ++i) {          // steps past s1 multiply zeros
+        const float4 x = ra[i], y = rw[i];
+        ra[i] = fetch(a, s + AHEAD + i);
+        rw[i] = fetch(w, s + AHEAD + i);
+        multiply(x, y);
+      }
     }
   }
   const int m = m0 + l32;
@@ -546,11 +602,14 @@ static hipError_t launch_bf16(GemmArgs g, hipStream_t st) {
   }
 }
 
+static bool f32_split(int M, int N) {      // four waves to a 32 x 32 tile
+  return static_cast<int64_t>((M + 31) / 32) * ((N + 31) / 32) < 8LL * g_num_cus;
+}
+
 template <int EPI>
 static hipError_t launch_f32(GemmArgs g, hipStream_t st) {
   // four waves to a 32 x 32 tile while that is what it takes to give every CU two work-groups' worth of waves
-  const int64_t tiles = static_cast<int64_t>((g.M + 31) / 32) * ((g.N + 31) / 32);
-  const bool split = tiles < 8LL * g_num_cus;
+  const bool split = f32_split(g.M, g.N);
   const bool vec = g.K % 4 == 0 && ((reinterpret_cast<uintptr_t>(g.A) | reinterpret_cast<uintptr_t>(g.W)) & 15) == 0;
   const int e = split ? 32 : 64;
   const dim3 grid((g.M + e - 1) / e, (g.N + e - 1) / e);
@@ -559,6 +618,27 @@ static hipError_t launch_f32(GemmArgs g, hipStream_t st) {
   else if (split) gemm_f32_kernel<EPI, 4, false><<<grid, dim3(256), 0, st>>>(g);
   else if (vec) gemm_f32_kernel<EPI, 1, true><<<grid, dim3(256), 0, st>>>(g);
   else gemm_f32_kernel<EPI, 1, false><<<grid, dim3(256), 0, st>>>(g);
+  return hipGetLastError();
+}
+
+bool gemm_takes_layernorm(int dtype, const void *A, const void *W, const float *ln_g, const float *ln_b, int M, int N, int K) {
+  return dtype == RESLIM_F32 && M > 0 && N > 0 && K > 0 && K <= kLnK && K % 4 == 0 && f32_split(M, N) && (N + 31) / 32 <= 65535 &&
+         ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(W) | reinterpret_cast<uintptr_t>(ln_g) | reinterpret_cast<uintptr_t>(ln_b)) & 15) == 0;
+}
+
+hipError_t launch_layernorm_gemm(Epilogue epi, const float *x, const ResRowMap *rows, const float *ln_g, const float *ln_b, const float *W,
+                                 const float *bias, float *out, int M, int N, int K, hipStream_t st) {
+  if (!gemm_takes_layernorm(RESLIM_F32, x, W, ln_g, ln_b, M, N, K)) return hipErrorInvalidValue;
+  GemmArgs g = {};
+  g.A = x; g.W = W; g.bias = bias; g.out = out; g.ldo = N; g.tab_rows = 1; g.M = M; g.N = N; g.K = K;
+  g.qscale = 1.0f;
+  g.ln_g = ln_g; g.ln_b = ln_b;
+  g.a_map = rows ? rows->map : nullptr; g.a_out = rows ? rows->rows_out : 1; g.a_in = rows ? rows->rows_in : 1;
+  const dim3 grid((M + 31) / 32, (N + 31) / 32), blk(256);
+  if (epi == EPI_BIAS_ACT) gemm_f32_kernel<EPI_BIAS_ACT, 4, true, true><<<grid, blk, 0, st>>>(g);
+  else if (epi == EPI_BIAS_GELU_ACT) gemm_f32_kernel<EPI_BIAS_GELU_ACT, 4, true, true><<<grid, blk, 0, st>>>(g);
+  else if (epi == EPI_BIAS_F32) gemm_f32_kernel<EPI_BIAS_F32, 4, true, true><<<grid, blk, 0, st>>>(g);
+  else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
@@ -591,7 +671,7 @@ hipError_t launch_gemm(int dtype, Epilogue epi, const void *A, const void *W, co
                        void *out, int ldo, const float *tab, int tab_rows, int M, int N, int K,
                        hipStream_t st, float qscale, int qcols, const void *aux, void *out2, const ResRowMap *res_map) {
   if (M <= 0 || N <= 0 || K <= 0) return hipErrorInvalidValue;
-  GemmArgs g;
+  GemmArgs g = {};
   g.A = A; g.W = W; g.bias = bias; g.out = out; g.tab = tab;
   g.ldo = ldo; g.tab_rows = tab_rows > 0 ? tab_rows : 1;
   g.M = M; g.N = N; g.K = K; g.grid_m = g.grid_n = 0; g.col_fast = g_col_fast;
