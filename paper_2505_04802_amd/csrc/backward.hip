@@ -262,7 +262,7 @@ extern "C" int reslim_asc_block_fwd_train(reslim_ctx *c, const reslim_asc_plan *
 
 static int block_bwd_impl(reslim_ctx *c, const char *fn, int layer, const float *x_in, const void *saved, size_t saved_bytes,
                           const float *d_x_out, float *d_x_in, const reslim_block_grads *grads, int batch, void *workspace,
-                          size_t ws_bytes, void *hip_stream, const SeqGeom &sg) {
+                          size_t ws_bytes, void *hip_stream, const SeqGeom &sg, bool act_given = false, bool act_wanted = false) {
   if (!x_in || !d_x_out || !d_x_in || !grads) return set_error(c, RESLIM_EINVAL, std::string(fn) + ": null buffer");
   const float *const *gp = reinterpret_cast<const float *const *>(grads);
   for (int i = 0; i < 12; ++i)
@@ -280,7 +280,7 @@ static int block_bwd_impl(reslim_ctx *c, const char *fn, int layer, const float 
   const int64_t MD = static_cast<int64_t>(M) * D;
 
   // x_out = x_mid + fc2(gelu(fc1(ln2(x_mid))))
-  RESLIM_LAUNCH("to_act", 0, dM * dD * (4.0 + es), launch_to_act(dt, d_x_out, w.out, MD, st));
+  if (!act_given) RESLIM_LAUNCH("to_act", 0, dM * dD * (4.0 + es), launch_to_act(dt, d_x_out, w.out, MD, st));
   rc = dgrad_impl(c, fn, w.out, lw.wt_fc2, w.fc1, M, D, R, st);
   if (rc != RESLIM_OK) return rc;
   // GELU's derivative as its own bandwidth-bound pass: fused into the epilogue of the GEMM above it cost more
@@ -300,9 +300,13 @@ static int block_bwd_impl(reslim_ctx *c, const char *fn, int layer, const float 
                 launch_tiles_attention_bwd(c, s.qkv, s.attn, s.lse, w.b, w.qkv, batch, w.attn, dt == RESLIM_BF16, st, &sg));
   rc = dgrad_impl(c, fn, w.qkv, lw.wt_qkv, w.b, M, 3 * D, D, st);
   if (rc != RESLIM_OK) return rc;
-  RESLIM_LAUNCH("layernorm_bwd", 0, dM * dD * (12.0 + es),
-                launch_layernorm_bwd(dt, x_in, w.b, lw.ln1_g, w.g, d_x_in, nullptr, w.lnp, grads->ln1_g, grads->ln1_b, M, D, st));
-  return w.one_launch ? wgrad_impl(c, fn, op, 4, M, w.wgrad, st) : wgrad_impl(c, fn, op + 2, 2, M, w.wgrad, st);
+  // the last use of w.out's present content
+  rc = w.one_launch ? wgrad_impl(c, fn, op, 4, M, w.wgrad, st) : wgrad_impl(c, fn, op + 2, 2, M, w.wgrad, st);
+  if (rc != RESLIM_OK) return rc;
+  RESLIM_LAUNCH("layernorm_bwd", 0, dM * dD * (12.0 + (act_wanted ? 2.0 : 1.0) * es),
+                launch_layernorm_bwd(dt, x_in, w.b, lw.ln1_g, w.g, d_x_in, act_wanted ? w.out : nullptr, w.lnp, grads->ln1_g,
+                                     grads->ln1_b, M, D, st));
+  return RESLIM_OK;
 }
 
 extern "C" int reslim_block_bwd(reslim_ctx *c, int32_t layer, const float *x_in, const void *saved, size_t saved_bytes,
@@ -311,6 +315,16 @@ extern "C" int reslim_block_bwd(reslim_ctx *c, int32_t layer, const float *x_in,
   if (!c) return RESLIM_EINVAL;
   return block_bwd_impl(c, "reslim_block_bwd", layer, x_in, saved, saved_bytes, d_x_out, d_x_in, grads, batch, workspace,
                         ws_bytes, hip_stream, ctx_geom(c));
+}
+
+// A block's gradient in the chain of a whole step: every block has the same workspace, whose first part is the gradient of the
+// stream in the activation type.  The LayerNorm gradient that ends a block has it in registers and leaves it there (act_wanted) for the block
+// below (act_given): 2 bytes a value written, where a conversion of its own reads 4 and writes 2 (85,000 rows of 1024: 80 us).
+int reslim::block_bwd_chained(reslim_ctx *c, int layer, const float *x_in, const void *saved, size_t saved_bytes, const float *d_x_out,
+                              float *d_x_in, const reslim_block_grads *grads, int batch, void *workspace, size_t ws_bytes,
+                              void *hip_stream, bool act_given, bool act_wanted) {
+  return block_bwd_impl(c, "reslim_block_bwd", layer, x_in, saved, saved_bytes, d_x_out, d_x_in, grads, batch, workspace,
+                        ws_bytes, hip_stream, ctx_geom(c), act_given, act_wanted);
 }
 
 extern "C" int reslim_asc_block_bwd(reslim_ctx *c, const reslim_asc_plan *plan, int32_t layer, const float *x_in,

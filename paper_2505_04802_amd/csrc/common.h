@@ -256,6 +256,9 @@ hipError_t launch_residual_unpatchify(const reslim_ctx *c, const float *x, const
 // ---- shared by the files that hold entry points -------------------------------
 int check_common(reslim_ctx *c, const char *fn, int batch, const void *ws, size_t ws_bytes, bool need_ws);
 int hip_fail(reslim_ctx *c, const char *fn, const char *what, hipError_t e);
+int block_bwd_chained(reslim_ctx *c, int layer, const float *x_in, const void *saved, size_t saved_bytes, const float *d_x_out,
+                      float *d_x_in, const reslim_block_grads *grads, int batch, void *workspace, size_t ws_bytes, void *hip_stream,
+                      bool act_given, bool act_wanted);
 
 }  // namespace reslim
 

@@ -1395,7 +1395,7 @@ extern "C" int reslim_train_step_grads(reslim_ctx *c, const float *x, const floa
     bg.ln2_g = grads->ln2_g + static_cast<size_t>(l) * D; bg.ln2_b = grads->ln2_b + static_cast<size_t>(l) * D;
     bg.w_fc1 = grads->w_fc1 + l * R * D; bg.b_fc1 = grads->b_fc1 + l * R;
     bg.w_fc2 = grads->w_fc2 + l * R * D; bg.b_fc2 = grads->b_fc2 + static_cast<size_t>(l) * D;
-    if ((rc = reslim_block_bwd(c, l, stream(l), bsaved(l), p.block_saved, ga, gb, &bg, batch, stage, stage_bytes, hip_stream)) != RESLIM_OK) return rc;
+    if ((rc = block_bwd_chained(c, l, stream(l), bsaved(l), p.block_saved, ga, gb, &bg, batch, stage, stage_bytes, hip_stream, l < L - 1, l > 0)) != RESLIM_OK) return rc;
     std::swap(ga, gb);
   }
   return embed_bwd_impl(c, fn, x, ga, grads, batch, stage, st);
