@@ -8,7 +8,7 @@
 //                   tile on its haloed box) fused with un-patchify, stitch and add
 #include <algorithm>
 
-#include "common.h"
+#include "attention_common.h"
 #include "layernorm_common.h"
 
 namespace reslim {
@@ -230,12 +230,144 @@ struct EmbedArgs {
   int64_t BN;   // batch * N patches
 };
 
+// The folded aggregation on fp32 matrix instructions: bf16 path, 2 x 2 patches, head dimensions that are multiples of 64.
+//
+//   o[t][d] = sum_v a[t][g][v] (c[v][d] + sum_j U[v][d][j] pix[t][v][j]),  g the head of feature d, a its softmax over the variables
+//
+// is a product over k = (v, j) and (v): with 32 features of one head as rows and 32 patches as columns, five values of k a variable.
+// v_mfma_f32_32x32x2_f32 multiplies and adds in fp32 as the vector pipe does, at twice its rate, and a wave reads each value of the
+// tables once for 32 PT patches (from L2; 16 with a thread per four features).  A step takes two variables: the two halves of a
+// wave hold pixels 0, 1 and 2, 3 of either, and the offset of one variable each.  Row r of a block of 32 features is feature
+// 16 (r / 4 % 2) + 4 (r / 8) + r % 4, so that a lane ends with 16 adjacent ones of its patch.
+//
+// A work-group takes 32 PT patches and hc heads at a time, so that LDS stays small for many heads; a wave takes 64 features, then
+// those that lie four waves on.
+//
+// What it measured (MI355X), against a thread per four features and 8 or 16 patches on the vector pipe: 16,200 patches of 23 variables
+// at 256 features 35.4 us -> 22.7 (one work-group after the other of loads, softmax and product: latency bounds it), 32,768 of 8 at 512
+// 38.5 -> 29.4, 259,200 at 1024 854 -> 572, twice the matrix pipe's time.
+template <int PT>
+__global__ __launch_bounds__(256) void embed_agg_mfma_kernel(EmbedArgs e, int hc) {
+  constexpr int TP = 32 * PT, NG = 256 / TP;
+  extern __shared__ float sm[];
+  float4 *const pix = reinterpret_cast<float4 *>(sm);        // [V][TP]
+  float *const sc = sm + 4 * TP * e.V;                       // [hc][V][TP] softmax weights
+  const int t = threadIdx.x, V = e.V, heads = e.heads, D = e.D;
+  const int64_t bn0 = static_cast<int64_t>(blockIdx.x) * TP;
+  const int tp = t % TP, tg = t / TP;
+  {
+    const int64_t bn = bn0 + tp;
+    const bool in = bn < e.BN;
+    const int64_t b = in ? bn / e.N : 0;
+    const int n = in ? static_cast<int>(bn % e.N) : 0;
+    const float *xp = e.x + (b * V * e.H + n / e.Wp * 2) * static_cast<int64_t>(e.W) + n % e.Wp * 2;
+    const int64_t plane = static_cast<int64_t>(e.H) * e.W;
+#pragma unroll 4
+    for (int v = tg; v < V; v += NG) {
+      const float *q = xp + v * plane;
+      pix[v * TP + tp] = in ? make_float4(q[0], q[1], q[e.W], q[e.W + 1]) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  }
+  const int lane = t & 63, wave = t >> 6, col = lane & 31, hi = lane >> 5;
+  const int feat = 16 * ((col >> 2) & 1) + 4 * (col >> 3) + (col & 3);
+  bf16_t *const out = static_cast<bf16_t *>(e.o);
+  for (int g0 = 0; g0 < heads; g0 += hc) {
+    const int gn = min(hc, heads - g0);
+    __syncthreads();                                         // pixels written; the weights of the heads before are used up
+    for (int v = tg; v < V; v += NG) {
+      const float4 px = pix[v * TP + tp];
+      const float4 *Ar = reinterpret_cast<const float4 *>(e.A) + static_cast<size_t>(v) * heads + g0;
+      const float *a0 = e.a0 + static_cast<size_t>(v) * heads + g0;
+#pragma unroll 4
+      for (int g = 0; g < gn; ++g) {
+        const float4 A = Ar[g];
+        sc[(g * V + v) * TP + tp] = fmaf(A.w, px.w, fmaf(A.z, px.z, fmaf(A.y, px.y, fmaf(A.x, px.x, a0[g]))));
+      }
+    }
+    __syncthreads();
+    for (int g = tg; g < gn; g += NG) {
+      float *r = sc + static_cast<size_t>(g) * V * TP + tp;
+      float mx = -INFINITY, sum = 0.f;
+#pragma unroll 8
+      for (int v = 0; v < V; ++v) mx = fmaxf(mx, r[v * TP]);
+#pragma unroll 4
+      for (int v = 0; v < V; ++v) {
+        const float ex = __expf(r[v * TP] - mx);
+        r[v * TP] = ex;
+        sum += ex;
+      }
+      const float inv = 1.0f / sum;
+#pragma unroll 4
+      for (int v = 0; v < V; ++v) r[v * TP] *= inv;
+    }
+    __syncthreads();
+    for (int f0 = g0 * e.dh + 64 * wave; f0 < (g0 + gn) * e.dh; f0 += 256) {
+      const float *w = sc + static_cast<size_t>(f0 / e.dh - g0) * V * TP + col;
+      const float *U = e.U + 4 * static_cast<size_t>(f0 + feat) + 2 * hi, *cp = e.c + f0 + feat;
+      f32x16 acc[PT][2] = {};
+      // the tables' values of variables v and v + 1; past the last one zero
+      struct Tab { float2 u[2][2]; float c[2]; };
+      auto fetch = [&](int v) {
+        Tab k;
+        const bool two = v + 1 < V;
+        const int v1 = two ? v + 1 : v, vc = hi ? v1 : v;
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) {
+          k.u[0][nt] = *reinterpret_cast<const float2 *>(U + 4 * (static_cast<size_t>(v) * D + 32 * nt));
+          const float2 u1 = *reinterpret_cast<const float2 *>(U + 4 * (static_cast<size_t>(v1) * D + 32 * nt));
+          k.u[1][nt] = two ? u1 : make_float2(0.f, 0.f);
+          const float c = cp[static_cast<size_t>(vc) * D + 32 * nt];
+          k.c[nt] = two || !hi ? c : 0.f;
+        }
+        return k;
+      };
+      auto multiply = [&](const Tab &k, int v) {
+        const bool two = v + 1 < V;
+        const int v1 = two ? v + 1 : v;
+#pragma unroll
+        for (int pt = 0; pt < PT; ++pt) {
+          const float a = w[v * TP + 32 * pt], a1 = w[v1 * TP + 32 * pt];
+          const float2 p = reinterpret_cast<const float2 *>(pix + v * TP + 32 * pt + col)[hi];
+          const float2 p1 = reinterpret_cast<const float2 *>(pix + v1 * TP + 32 * pt + col)[hi];
+          const float x[5] = {a * p.x, a * p.y, two ? a1 * p1.x : 0.f, two ? a1 * p1.y : 0.f, hi ? (two ? a1 : 0.f) : a};
+#pragma unroll
+          for (int nt = 0; nt < 2; ++nt) {
+            acc[pt][nt] = __builtin_amdgcn_mfma_f32_32x32x2f32(k.u[0][nt].x, x[0], acc[pt][nt], 0, 0, 0);
+            acc[pt][nt] = __builtin_amdgcn_mfma_f32_32x32x2f32(k.u[0][nt].y, x[1], acc[pt][nt], 0, 0, 0);
+            acc[pt][nt] = __builtin_amdgcn_mfma_f32_32x32x2f32(k.u[1][nt].x, x[2], acc[pt][nt], 0, 0, 0);
+            acc[pt][nt] = __builtin_amdgcn_mfma_f32_32x32x2f32(k.u[1][nt].y, x[3], acc[pt][nt], 0, 0, 0);
+            acc[pt][nt] = __builtin_amdgcn_mfma_f32_32x32x2f32(k.c[nt], x[4], acc[pt][nt], 0, 0, 0);
+          }
+        }
+      };
+      Tab k0 = fetch(0), k1 = fetch(min(2, V - 1));          // two steps ahead
+      for (int v = 0; v < V; v += 2) {
+        const Tab k2 = fetch(min(v + 4, V - 1));
+        multiply(k0, v);
+        k0 = k1;
+        k1 = k2;
+      }
+#pragma unroll
+      for (int pt = 0; pt < PT; ++pt) {
+        const int64_t bn = bn0 + 32 * pt + col;
+        if (bn >= e.BN) continue;
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) {
+          uint4 *o = reinterpret_cast<uint4 *>(out + bn * D + f0 + 32 * nt + 16 * hi);
+          const f32x16 r = acc[pt][nt];
+          o[0] = make_uint4(pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3]), pack_bf16x2(r[4], r[5]), pack_bf16x2(r[6], r[7]));
+          o[1] = make_uint4(pack_bf16x2(r[8], r[9]), pack_bf16x2(r[10], r[11]), pack_bf16x2(r[12], r[13]), pack_bf16x2(r[14], r[15]));
+        }
+      }
+    }
+  }
+}
+
+// The same on the vector pipe: the fp32 path, other patch sides, and variables so many that LDS does not hold 32 patches.
 // P2 = p*p when known at compile time (4 for the paper's 2x2 patches), 0 = run-time.
-// PPI: patches per work item of the P2 = 4 path.  An item reads the value tables of its four
-// features for every variable (80 bytes per variable, from L2) and uses them for PPI patches, so
-// the table traffic per patch goes with 1 / PPI: at c3 1.24 ms with 4, 0.84 with 8, 0.82 with 16
-// (c4: 1.57 / 1.27 / 1.10); 16 leaves half the threads without an item below 1024 features.
-template <class T, int P2, int PPI_ = 8>
+// A work item of the P2 = 4 path reads the value tables of its four features for every variable (80 bytes per variable,
+// from L2) and uses them for 8 patches.
+template <class T, int P2>
 __global__ __launch_bounds__(256) void embed_agg_kernel(EmbedArgs e) {
   constexpr int TP = 16;                      // patches per work-group
   extern __shared__ float sm[];
@@ -289,7 +421,7 @@ __global__ __launch_bounds__(256) void embed_agg_kernel(EmbedArgs e) {
     if (e.dh % 4 == 0) {
       // A work item is four adjacent features (one head) of PPI patches: the pixel and
       // weight reads from LDS (broadcast over the wave) are shared by 4 PPI outputs.
-      constexpr int PPI = PPI_;
+      constexpr int PPI = 8;
       const int Q = e.D / 4;
       for (int item = t; item < Q * (TP / PPI); item += 256) {
         const int dq = item % Q, p0 = (item / Q) * PPI;
@@ -360,7 +492,8 @@ hipError_t elementwise_init() {
   const int lim = 160 * 1024;
 #define RESLIM_ATTR(K) if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void *>(&K), hipFuncAttributeMaxDynamicSharedMemorySize, lim)
   RESLIM_ATTR((embed_agg_kernel<bf16_t, 4>));
-  RESLIM_ATTR((embed_agg_kernel<bf16_t, 4, 16>));
+  RESLIM_ATTR((embed_agg_mfma_kernel<1>));
+  RESLIM_ATTR((embed_agg_mfma_kernel<2>));
   RESLIM_ATTR((embed_agg_kernel<bf16_t, 0>));
   RESLIM_ATTR((embed_agg_kernel<float, 4>));
   RESLIM_ATTR((embed_agg_kernel<float, 0>));
@@ -375,14 +508,35 @@ hipError_t launch_embed_agg(const reslim_ctx *c, const float *x, void *o, int ba
   e.V = c->cfg.in_vars; e.H = c->cfg.H; e.W = c->cfg.W; e.p = c->cfg.patch; e.Wp = c->Wp; e.N = c->N;
   e.D = c->cfg.embed_dim; e.heads = c->cfg.heads; e.dh = c->dh;
   e.BN = static_cast<int64_t>(batch) * c->N;
+  const bool bf = c->cfg.dtype == RESLIM_BF16, p4 = e.p == 2;
+  if (bf && p4 && e.dh % 64 == 0) {
+    // LDS of 32 patches and hc heads: 512 V + 128 V hc bytes, 40 KiB where that can be (four work-groups a compute unit),
+    // but heads for four waves, 256 features, together.
+    const int least = std::min(e.heads, (256 + e.dh - 1) / e.dh);
+    auto lds_of = [&](int pt, int hc) { return static_cast<size_t>(pt) * 128 * e.V * (4 + hc); };
+    auto heads_of = [&](int pt) {
+      const int fit = static_cast<int>(40 * 1024 / (128 * pt * e.V)) - 4;
+      return fit >= e.heads ? e.heads : std::max(least, fit / least * least);
+    };
+    // 64 patches read the tables half as often, 32 give twice the work-groups: above four of those per compute unit the
+    // tables count (48,867 patches: 36.7 us with 32, 30.0 with 64; 32,768: 31.3 and 30.8; 16,200: 24.7 and 26.7)
+    const bool wide = e.BN > 32LL * 1024 && lds_of(2, heads_of(2)) <= 80 * 1024;
+    const int pt = wide ? 2 : 1, hc = heads_of(pt);
+    const size_t bytes = lds_of(pt, hc);
+    const int64_t groups = (e.BN + 32 * pt - 1) / (32 * pt);
+    if (bytes <= 160 * 1024 && groups <= INT32_MAX) {
+      const dim3 grid(static_cast<unsigned>(groups)), blk(256);
+      if (wide) embed_agg_mfma_kernel<2><<<grid, blk, bytes, st>>>(e, hc);
+      else embed_agg_mfma_kernel<1><<<grid, blk, bytes, st>>>(e, hc);
+      return hipGetLastError();
+    }
+  }
   const size_t lds = static_cast<size_t>(TP) * (static_cast<size_t>(e.V) * e.p * e.p + static_cast<size_t>(e.heads) * e.V) * sizeof(float);
   if (lds > 160 * 1024) return hipErrorInvalidValue;
   const int64_t blocks = (e.BN + TP - 1) / TP;
   if (blocks > INT32_MAX) return hipErrorInvalidValue;
   const dim3 grid(static_cast<unsigned>(blocks)), blk(256);
-  const bool bf = c->cfg.dtype == RESLIM_BF16, p4 = e.p == 2;
-  if (bf && p4 && e.D >= 1024) embed_agg_kernel<bf16_t, 4, 16><<<grid, blk, lds, st>>>(e);
-  else if (bf && p4) embed_agg_kernel<bf16_t, 4><<<grid, blk, lds, st>>>(e);
+  if (bf && p4) embed_agg_kernel<bf16_t, 4><<<grid, blk, lds, st>>>(e);
   else if (bf) embed_agg_kernel<bf16_t, 0><<<grid, blk, lds, st>>>(e);
   else if (p4) embed_agg_kernel<float, 4><<<grid, blk, lds, st>>>(e);
   else embed_agg_kernel<float, 0><<<grid, blk, lds, st>>>(e);
