@@ -310,9 +310,9 @@ void plan_pool_free(PlanPool &pool);
   } while (0)
 
 namespace reslim {
-struct LaunchPart { const char *label; double flop, bytes; };
+struct LaunchPart { const char *label; double flop, bytes, uncounted = 0; };      // uncounted: operations that are no part of the flop count
 }
-// A launch that does the work of several steps: one record each, the time divided by their flop
+// A launch that does the work of several steps: one record each, the time divided by their operations
 #define RESLIM_LAUNCH_PARTS(parts_, n_, expr)                                          \
   do {                                                                                 \
     const size_t slot_ = c->prof_rec.size();                                           \
@@ -322,8 +322,8 @@ struct LaunchPart { const char *label; double flop, bytes; };
     if (p_) {                                                                          \
       RESLIM_TRY("event", hipEventRecord(c->prof_ev[2 * slot_ + 1], st));              \
       double sum_ = 0;                                                                 \
-      for (int i_ = 0; i_ < (n_); ++i_) sum_ += (parts_)[i_].flop;                     \
+      for (int i_ = 0; i_ < (n_); ++i_) sum_ += (parts_)[i_].flop + (parts_)[i_].uncounted;                     \
       for (int i_ = 0; i_ < (n_); ++i_)                                                \
-        c->prof_rec.push_back({(parts_)[i_].label, (parts_)[i_].flop, (parts_)[i_].bytes, 2 * slot_, (parts_)[i_].flop / sum_}); \
+        c->prof_rec.push_back({(parts_)[i_].label, (parts_)[i_].flop, (parts_)[i_].bytes, 2 * slot_, ((parts_)[i_].flop + (parts_)[i_].uncounted) / sum_}); \
     }                                                                                  \
   } while (0)

@@ -89,7 +89,7 @@ static int layernorm_product(reslim_ctx *c, const char *fn, const char *ln_label
   const int D = c->cfg.embed_dim, dt = c->cfg.dtype;
   const double es = static_cast<double>(act_size(c)), dM = M, dD = D;
   if ((epi == EPI_BIAS_ACT || epi == EPI_BIAS_GELU_ACT || epi == EPI_BIAS_F32) && gemm_takes_layernorm(dt, x, W, ln_g, ln_b, M, N, D)) {
-    const LaunchPart parts[] = {{ln_label, 0, 0}, {label, flop, bytes}};
+    const LaunchPart parts[] = {{ln_label, 0, 0, 10.0 * dM * dD}, {label, flop, bytes}};
     RESLIM_LAUNCH_PARTS(parts, 2, launch_layernorm_gemm(epi, x, rows, ln_g, ln_b, static_cast<const float *>(W), bias, static_cast<float *>(out), M, N, D, st));
     return RESLIM_OK;
   }
@@ -104,10 +104,10 @@ static int panel_block_impl(reslim_ctx *c, const char *fn, int layer, const void
                             int M, hipStream_t st) {
   const double es = static_cast<double>(act_size(c)), dM = M, dD = c->cfg.embed_dim, dR = c->R;
   const LaunchPart parts[] = {{"gemm_proj", 2.0 * dM * dD * dD, dM * dD * es + dD * dD * es + 4.0 * dM * dD},
-                              {"layernorm", 0, 0},
+                              {"layernorm", 0, 0, 10.0 * dM * dD},
                               {"gemm_fc1", 2.0 * dM * dD * dR, dD * dR * es},
                               {"gemm_fc2", 2.0 * dM * dD * dR, dD * dR * es + 4.0 * dM * dD},
-                              {"layernorm", 0, 0},
+                              {"layernorm", 0, 0, 10.0 * dM * dD},
                               {"gemm_qkv", 6.0 * dM * dD * dD, 3.0 * dD * dD * es + 3.0 * dM * dD * es}};
   RESLIM_LAUNCH_PARTS(parts, qkv_next ? 6 : 4, launch_panel_block(c, layer, a, res, skip, X, qkv_next, M, st));
   return RESLIM_OK;

@@ -29,3 +29,16 @@ def test_block_and_head(D, grid):
         xd = torch.from_numpy(x).cuda()
         assert_parity(m.head(xd, torch.from_numpy(inter["block0"].astype(np.float32)).cuda()).cpu().numpy(), y_ref, 1e-5, "head", print)
         assert_parity(m.forward(xd).cpu().numpy(), y_ref, 1e-5, "forward", print)
+
+
+@pytest.mark.parametrize("cfg", [WL.CONFIGS["c0"], WL.CONFIGS["m9m"]], ids=lambda c: c.name)
+def test_every_launch_record_has_a_time(cfg):
+    """A launch that does several steps leaves a record for each, and a rate is computed from every record's time: none may be zero."""
+    w, x = WL.make_weights(cfg), torch.from_numpy(WL.make_fields(cfg)).cuda()
+    with B.Reslim(cfg, w) as m:
+        B.reslim_profile_enable(m.ctx, 256)
+        m.forward(x)
+        torch.cuda.synchronize()
+        recs = B.reslim_profile_read(m.ctx)
+        B.reslim_profile_enable(m.ctx, 0)
+    assert recs and all(ms > 0 for _, ms, _, _ in recs), recs
