@@ -7,7 +7,7 @@
 // or two column tiles leave the products at 250-550 TFLOP/s, and the hidden layer, qkv and the stream go through memory between
 // them.  In one launch the rows stay in registers and LDS and only the weights stream in, 1.6 MB a panel at D = 256 and 6.3 MB at 512,
 // which a compute unit takes from L2 at 110 bytes a nanosecond.  What it measured (MI355X, with the next qkv): 19,552 rows of 256
-// features 91 us in seven launches, 43 here (720 TFLOP/s, 204 panels of 96 rows); 42,560 rows of 512 384 us, 289 here (930).
+// features 91 us in seven launches, 47 here (204 panels of 96 rows: 660 TFLOP/s); 42,560 rows of 512 384 us, 325 here (822).
 // What bounds it: the matrix pipe is busy 42 % of the time at D = 256 and shares the SIMD with the vector work of GELU, LayerNorm and
 // addresses (two waves' matrix and vector instructions take the sum of the one and half the other at best); panels of 32 rows
 // wait for the weights.
@@ -19,12 +19,16 @@
 // is at position c ^ (row & 15): conflict-free for the 16-byte fragment reads of 16 rows.
 //
 // The hidden layer is taken in chunks of CH columns through two LDS buffers.  GELU of chunk c is placed between the matrix instructions of
-// FC2 of chunk c - 1 and FC1 of chunk c + 1 (51 us without, 46 with), sums start from the bias or the skip connection, and
-// the order in which LDS reads, matrix and vector instructions of a step are issued is pinned (43).
+// FC2 of chunk c - 1 and FC1 of chunk c + 1 (51 us without, 46 with), and the order in which LDS reads, matrix and vector
+// instructions of a step are issued is pinned (43).
 //
-// LayerNorm and qkv are the same bits as those of the separate kernels (layernorm_common.h; k upwards in one accumulator, then
-// the bias); so a chain of blocks through the entry points, which has them separate, gives what a whole forward gives.
+// Every result is the same bits as that of the separate kernels: a product sums k upwards from zero in one accumulator, then comes the
+// bias, then the skip connection; GELU and LayerNorm are shared (gelu.h, layernorm_common.h).  So it does not matter to a
+// result which of the two forms a call takes, by its rows, its batch or its alignment.  Sums that start from the skip connection and
+// the bias need no second set of registers, but their rounding grows with the stream; they would be 2 % faster (46.2 and 47.1 us
+// side by side for 19,552 rows of 256 features, 322 and 325 for 42,560 of 512).
 #include <type_traits>
+#include <utility>
 
 #include "attention_common.h"
 #include "gelu.h"
@@ -36,8 +40,19 @@ namespace reslim {
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 struct Nothing {
-  __device__ __forceinline__ void operator()(int) const {}
+  template <class I>
+  __device__ __forceinline__ void operator()(I) const {}
 };
+
+// f(0) .. f(N - 1) with compile-time numbers: `#pragma unroll` gives up on bodies of this size
+template <class F, int... I>
+__device__ __forceinline__ void each_of(F &&f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void each(F &&f) {
+  each_of(f, std::make_integer_sequence<int, N>{});
+}
 
 struct PanelArgs {
   const bf16_t *a;         // [M, D] attention output
@@ -62,7 +77,9 @@ struct PanelShape {
   static constexpr int kA = ROWS * D * 2, kH = ROWS * CH * 2, kStat = ROWS * NW * NB * 4;
   static constexpr int kRowX = D * 4;                                          // a row of the stream
   static constexpr int kHs = 2 * kH > 32 * kRowX ? 2 * kH : 32 * kRowX;        // both buffers of the hidden layer, or 32 rows of the stream
-  static constexpr int kLds = kA + kHs + 2 * kStat;
+  // The stream waits in registers while FC2 is summed, but for these quads of a lane, which wait in LDS: there are not registers for all.
+  static constexpr int kWait = RB * NB == 4 ? 2 : 0;
+  static constexpr int kLds = kA + kHs + 2 * kStat + kWait * NW * 1024;
   static constexpr int PF = RB * NB == 1 ? 16 : 8;      // weight fragments in flight
   static constexpr int AF = RB == 1 ? 4 : RB == 2 ? 3 : 2;      // row fragments, the one in use included
 };
@@ -149,29 +166,28 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void panel_block_kernel(PanelArgs 
     };
 #pragma unroll
     for (int kk = 0; kk < AF - 1; ++kk) fetch(kk);
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      if (kk + AF - 1 < KK) fetch(kk + AF - 1);
-#pragma unroll
-      for (int j = 0; j < N; ++j) {
-        const int f = kk * N + j;
+    each<KK>([&](auto kk_c) {
+      constexpr int kk = decltype(kk_c)::value;
+      if constexpr (kk + AF - 1 < KK) fetch(kk + AF - 1);
+      each<N>([&](auto j_c) {
+        constexpr int j = decltype(j_c)::value, f = kk * N + j;
         const bf16x8 w = ring[f % PF];
 #pragma unroll
         for (int i = 0; i < RB; ++i)            // operands swapped: the block is C^T
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, af[kk % AF][i], kk == 0 ? init(i, j) : acc[i][j], 0, 0, 0);
         ring[f % PF] = f + PF < KK * N ? fragment(cur, f + PF) : fragment(next, f + PF - KK * N);
-        beside(f);
+        beside(std::integral_constant<int, f>{});
         if constexpr (!std::is_same<decltype(beside), Nothing>::value) {
 #pragma unroll
           for (int i = 0; i < RB; ++i) {
             if (i == 0) __builtin_amdgcn_sched_group_barrier(0x100, RB, 0);      // the next step's row fragments are requested first
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                   // a matrix instruction,
-            __builtin_amdgcn_sched_group_barrier(0x002, RB == 3 ? 8 : 11, 0);    // then its share of a piece of vector work
+            __builtin_amdgcn_sched_group_barrier(0x002, RB == 3 ? 10 : 13, 0);    // then its share of a piece of vector work
           }
         }
         __builtin_amdgcn_sched_barrier(0);
-      }
-    }
+      });
+    });
   };
   typedef std::integral_constant<int, KD> KDc;
   typedef std::integral_constant<int, KC> KCc;
@@ -273,7 +289,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void panel_block_kernel(PanelArgs 
     }
     sync();
   };
-  // ---- projection: its sums start from the skip connection and the bias.  Rows of the stream come and go through LDS as fp32,
+  // ---- projection.  Rows of the stream come and go through LDS as fp32,
   // 16-byte chunk c of row r at c ^ (r & 15): in memory a wave moves whole lines.  Straight from and to the accumulator layout it
   // touches 32 lines an instruction, and at D = 256 the stores of 96 rows took 4.5 us of a panel's 43.
   constexpr int kRowX = S::kRowX, XPR = D / 4, XB = S::kHs / (32 * kRowX) < RB ? S::kHs / (32 * kRowX) : RB;      // row blocks at a time
@@ -308,68 +324,90 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void panel_block_kernel(PanelArgs 
         }
     }
   }
+  f32x16 sum[RB][NB];
+  auto from_sum = [&](int i, int j) { return sum[i][j]; };
+  auto from_zero = [](int, int) { return f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}; };
+  // x <- (sum + bias) + x, the order of the products' epilogues
+  auto add_to_stream = [&](const float *bias) {
 #pragma unroll
-  for (int j = 0; j < NB; ++j) {
-    const f32x16 b = load_quads(g.b_proj + (wave * NB + j) * 32);
+    for (int j = 0; j < NB; ++j) {
+      const f32x16 b = load_quads(bias + (wave * NB + j) * 32);
 #pragma unroll
-    for (int i = 0; i < RB; ++i)
+      for (int i = 0; i < RB; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) x[i][j][r] += b[r];
-  }
-  auto from_x = [&](int i, int j) { return x[i][j]; };
-  unit(KDc{}, NBc{}, PitchD{}, x, from_x, sA, p_proj, p_fc1(0), Nothing{});
-  f32x16 bias = load_quads(g.b_fc1 + wave * 32);
+        for (int r = 0; r < 16; ++r) x[i][j][r] = (sum[i][j][r] + b[r]) + x[i][j][r];
+    }
+  };
+  unit(KDc{}, NBc{}, PitchD{}, sum, from_zero, sA, p_proj, p_fc1(0), Nothing{});
+  add_to_stream(g.b_proj);
+  __builtin_amdgcn_sched_barrier(0);             // registers: nothing of what follows is requested before the LayerNorm is done
   layernorm(x, g.ln2_g, g.ln2_b, []() {});       // its first barrier: nobody reads the attention output any more
-
+  __builtin_amdgcn_sched_barrier(0);
+  auto waiting = [&](int k) { return lds(lds0 + S::kLds - (k + 1) * NW * 1024 + (wave * 64 + fresh_lane()) * 16, f32x4{}); };
 #pragma unroll
-  for (int j = 0; j < NB; ++j) {
-    const f32x16 b = load_quads(g.b_fc2 + (wave * NB + j) * 32);
-#pragma unroll
-    for (int i = 0; i < RB; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) x[i][j][r] += b[r];
+  for (int k = 0; k < S::kWait; ++k) {
+    const f32x16 &v = x[RB - 1][NB - 1];
+    *waiting(k) = f32x4{v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]};
   }
 
-  // ---- feed-forward layer: FC1 of a chunk from the bias on, FC2 on top of the stream.  GELU of chunk c runs beside the matrix
-  // instructions of FC2 of chunk c - 1 and FC1 of chunk c + 1, two values at a time; then a barrier, and chunk c is whole.
+  // ---- feed-forward layer.  GELU of chunk c runs beside the matrix instructions of FC2 of chunk c - 1 and FC1 of chunk c + 1, two
+  // values at a time; then a barrier, and chunk c is whole.
   const int chunks = g.R / CH;
   f32x16 ha[RB][1], hb[RB][1];                  // FC1 of even and odd chunks
+  // the bias of the column quad that GELU takes and of the one after it: quad q at 4 (q % 2)
+  typedef __attribute__((ext_vector_type(8))) float f32x8;
+  const float *const b_fc1 = g.b_fc1 + wave * 32;
+  f32x8 bias;
+  auto fetch_bias = [&](int c, int q) {
+    const float4 f = load4(b_fc1 + c * CH + 8 * q + 4 * (fresh_lane() >> 5));
+    const int k = 4 * (q & 1);
+    bias[k] = f.x; bias[k + 1] = f.y; bias[k + 2] = f.z; bias[k + 3] = f.w;
+  };
+  fetch_bias(0, 0);
+  fetch_bias(0, 1);
+#pragma unroll
+  for (int i = 0; i < RB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) sum[i][j] = from_zero(i, j);
   constexpr int PIECES = 8 * RB, F1 = KD, F2 = KC * NB;      // pieces of two values; fragments of the units
   uint32_t low = 0;
-  auto gelu_piece = [&](const f32x16 (&h)[RB][1], unsigned w0, int n) {
-    const int q = n / (2 * RB), i = n / 2 % RB, e = 4 * q + 2 * (n & 1);
-    const uint32_t p = pack2(gelu_erf_fast(h[i][0][e]), gelu_erf_fast(h[i][0][e + 1]));
-    if (n & 1) *lds((w0 ^ (q * 16)) + i * 32 * (2 * CH), u32x2{}) = u32x2{low, p};
+  auto gelu_piece = [&](const f32x16 (&h)[RB][1], unsigned w0, int c, auto n_c) {
+    constexpr int n = decltype(n_c)::value, q = n / (2 * RB), i = n / 2 % RB, e = 4 * q + 2 * (n & 1), k = e & 7;
+    const uint32_t p = pack2(gelu_erf_fast(h[i][0][e] + bias[k]), gelu_erf_fast(h[i][0][e + 1] + bias[k + 1]));
+    if constexpr (n & 1) *lds((w0 ^ (q * 16)) + i * 32 * (2 * CH), u32x2{}) = u32x2{low, p};
     else low = p;
+    if constexpr (n % (2 * RB) == 2 * RB - 1) fetch_bias(q < 2 ? c : min(c + 1, chunks - 1), (q + 2) % 4);
   };
-  // the pieces that go with fragment f of `of`
-  auto gelu_beside = [&](const f32x16 (&h)[RB][1], unsigned w0, int f, int of) {
-#pragma unroll
-    for (int n = f * PIECES / of; n < (f + 1) * PIECES / of; ++n) gelu_piece(h, w0, n);
+  // the pieces of chunk c that go with fragment F of OF
+  auto gelu_beside = [&](const f32x16 (&h)[RB][1], unsigned w0, int c, auto f_c, auto of_c) {
+    constexpr int F = decltype(f_c)::value, OF = decltype(of_c)::value, first = F * PIECES / OF;
+    each<(F + 1) * PIECES / OF - first>([&](auto k) { gelu_piece(h, w0, c, std::integral_constant<int, first + decltype(k)::value>{}); });
   };
+  typedef std::integral_constant<int, F1> OfF1;
+  typedef std::integral_constant<int, F2> OfF2;
+  typedef std::integral_constant<int, F1 + F2> OfBoth;
   auto buffer = [&](int c) { return sH + (c & 1) * S::kH; };
   auto fc1 = [&](int c, f32x16 (&h)[RB][1], int next, auto beside) {
-    unit(KDc{}, One{}, PitchD{}, h, [&](int, int) { return bias; }, sA, p_fc1(c), next, beside);
-    if (c + 1 < chunks) bias = load_quads(g.b_fc1 + (c + 1) * CH + wave * 32);
+    unit(KDc{}, One{}, PitchD{}, h, from_zero, sA, p_fc1(c), next, beside);
   };
-  auto fc2 = [&](int c, int next, auto beside) { unit(KCc{}, NBc{}, PitchC{}, x, from_x, buffer(c), p_fc2(c), next, beside); };
+  auto fc2 = [&](int c, int next, auto beside) { unit(KCc{}, NBc{}, PitchC{}, sum, from_sum, buffer(c), p_fc2(c), next, beside); };
   const int after = g.qkv ? p_qkv(0) : p_proj;      // no next block: fetched, not used
   // FC2 of chunk c - 1, GELU of chunk c (in h), FC1 of chunk c + 1 (into other)
   auto interval = [&](int c, const f32x16 (&h)[RB][1], f32x16 (&other)[RB][1]) {
     const unsigned w0 = write_base(buffer(c), 2 * CH, wave);
-    fc2(c - 1, p_fc1(c + 1), [&](int f) { gelu_beside(h, w0, f, F2 + F1); });
-    fc1(c + 1, other, p_fc2(c), [&](int f) { gelu_beside(h, w0, F2 + f, F2 + F1); });
+    fc2(c - 1, p_fc1(c + 1), [&](auto f) { gelu_beside(h, w0, c, f, OfBoth{}); });
+    fc1(c + 1, other, p_fc2(c), [&](auto f) { gelu_beside(h, w0, c, std::integral_constant<int, F2 + decltype(f)::value>{}, OfBoth{}); });
     sync();
   };
   auto last = [&](const f32x16 (&h)[RB][1]) {
     const int c = chunks - 1, w0 = write_base(buffer(c), 2 * CH, wave);
-    fc2(c - 1, p_fc2(c), [&](int f) { gelu_beside(h, w0, f, F2); });
+    fc2(c - 1, p_fc2(c), [&](auto f) { gelu_beside(h, w0, c, f, OfF2{}); });
     sync();
   };
   fc1(0, ha, p_fc1(1), Nothing{});
   {
     const unsigned w0 = write_base(buffer(0), 2 * CH, wave);
-    fc1(1, hb, p_fc2(0), [&](int f) { gelu_beside(ha, w0, f, F1); });
+    fc1(1, hb, p_fc2(0), [&](auto f) { gelu_beside(ha, w0, 0, f, OfF1{}); });
     sync();
   }
 #pragma unroll 1
@@ -379,6 +417,13 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void panel_block_kernel(PanelArgs 
   }
   last(hb);
   fc2(chunks - 1, after, Nothing{});
+#pragma unroll
+  for (int k = 0; k < S::kWait; ++k) {
+    const f32x4 v = *waiting(k);
+    f32x16 &d = x[RB - 1][NB - 1];
+    d[4 * k] = v[0]; d[4 * k + 1] = v[1]; d[4 * k + 2] = v[2]; d[4 * k + 3] = v[3];
+  }
+  add_to_stream(g.b_fc2);
   // the stream's rows to LDS (nothing else lies there any more once everybody has left FC2) and from there to memory
   auto x_to_lds = [&]() {
     sync();
@@ -414,7 +459,6 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void panel_block_kernel(PanelArgs 
   layernorm(x, g.ln1_g, g.ln1_b, x_to_memory);
   constexpr int PASSES = D / CH;
   f32x16 h[RB][3];
-  auto from_zero = [](int, int) { return f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}; };
   auto to_lds = [&](int u, int j, int base) {
     const float sc = u * CH + wave * 32 < D ? g.qscale : 1.0f;
     const f32x16 b = load_quads(g.b_qkv + u * CH + wave * 32);
