@@ -353,7 +353,13 @@ int reslim_head_fwd(reslim_ctx *ctx, const float *x, const float *tokens, float 
  * the head reads: its attention computes the queries their tiles own (halo
  * tokens remain keys and values), and its projection and MLP run on those rows
  * alone; per kept row the arithmetic is that of reslim_block_fwd, so y equals
- * the chained entry points' bit for bit. */
+ * the chained entry points' bit for bit, whatever the alignment of their stream.
+ * A sample's y does not depend, to the bit, on the batch it comes in on the bf16
+ * path, but for tile attention at head dimension 64 with few queries: whether its
+ * keys are split over the waves of a work-group, which rounds differently, goes by
+ * the queries of the whole launch (tiles of at least 512 tokens, and no more units
+ * of 128 queries, counted over tiles, heads and samples, than compute units).  On
+ * the fp32 path the products split their sums by the size of the problem. */
 int reslim_forward(reslim_ctx *ctx, const float *x, float *y, int32_t batch,
                    void *workspace, size_t ws_bytes, void *hip_stream);
 
@@ -559,14 +565,17 @@ int reslim_debug_copy(const void *src, void *dst, size_t bytes, void *hip_stream
 
 /* Tuning hook for benchmarks and tests: pins the bf16 GEMM kernel (-1 = built-in heuristic,
  * 2 = one 128x128 tile per work-group, 3 and 4 = persistent 256x256 / 128x256 tiles; add 100
- * to 2 for columns-fastest tile order; other values act like 2).  A plain process-wide
+ * to 2 for columns-fastest tile order; other values act like 2).  While it is pinned, blocks of
+ * 256 and 512 features are not taken by the one launch that otherwise holds their products (the
+ * results are the same bits).  A plain process-wide
  * variable read at every launch: not thread-safe, not part of the method; set it while no
  * other thread is inside the library and restore -1 afterwards. */
 void reslim_debug_set_gemm_tile(int choice);
 
 /* Tuning hook for benchmarks and tests: launch shape of the bf16 tile-attention kernel at
- * head dimension 64 (0 = 64-key blocks, three work-groups per compute unit, the default;
- * 1 = 128-key blocks, two work-groups per compute unit).  Process-wide and not thread-safe,
+ * head dimension 64 (0, the default = 64-key blocks, three work-groups per compute unit, or,
+ * for few queries, the keys split over the waves of a work-group; 1 = 128-key blocks, two
+ * work-groups per compute unit).  Process-wide and not thread-safe,
  * like the hook above. */
 void reslim_debug_set_attention_variant(int variant);
 

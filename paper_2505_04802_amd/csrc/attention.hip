@@ -16,6 +16,7 @@
 #include <type_traits>
 
 #include "attention_common.h"
+#include "attention_plan.h"
 
 namespace reslim {
 
@@ -529,11 +530,11 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
 }
 
 // ------------------------------------------------------------------ bf16 kernel for few queries: keys split over the waves
-// With fewer units of 128 queries than compute units (one sample's 2300 leaves at four heads are 72) the kernel above leaves
-// most of the chip idle and every wave walks all keys, 36 blocks of 64 one after the other: 14.7 us.  Here a work-group takes 32
-// queries and its four waves take every fourth block of 32 keys each, with a softmax of their own and without a barrier; the four
-// meet once in LDS, added in wave order: 288 work-groups of 18 blocks, 7.8 us.  What bounds it is the path that feeds K and V from
-// L2 (every 32 queries read all of them) and the chain of a wave's blocks.
+// With fewer units of 128 queries than compute units (2300 tokens at four heads are 72) the kernel above leaves most of the chip
+// idle and every wave walks all keys, 36 blocks of 64 one after the other: 41 us.  Here a work-group takes 32 queries and its four
+// waves take every fourth block of 32 keys each, with a softmax of their own and without a barrier; the four meet once in LDS,
+// added in wave order: 288 work-groups of 18 blocks, 22 us (642 tokens at four heads 13.9 and 7.9).  What bounds it is the path that
+// feeds K and V from L2 (every 32 queries read all of them) and the chain of a wave's blocks; so it is for few queries only, see attention_plan.h.
 //
 // A wave's K and V tiles (32 keys, 4 KiB each) go through a ring of its own of five tiles in the order K0 V0 K1 V1 ...: when
 // tile i has been read its place takes tile i + 5, so two blocks are in flight and two work-groups fit a compute unit.  Fragments,
@@ -936,8 +937,7 @@ hipError_t launch_tiles_attention(const reslim_ctx *c, const void *qkv, void *ou
     if (g_attn_cus <= 0) return hipErrorInvalidValue;
     const int pg2 = a.total < 2 * g_attn_cus ? a.total : 2 * g_attn_cus;   // persistent grids
     const int pg3 = a.total < 3 * g_attn_cus ? a.total : 3 * g_attn_cus;
-    // no more units of 128 queries than compute units, and long enough that a wave has several blocks of its own: see the kernel
-    if (c->dh == 64 && g_attn_variant == 0 && a.total <= g_attn_cus && sg.max_n_tok >= 512) {
+    if (c->dh == 64 && g_attn_variant == 0 && attn_split_keys(a.total, g_attn_cus, sg.max_n_tok)) {
       const dim3 grid(4 * a.total), blk(256);
       if (stitched && q_prescaled) tiles_attention_split_bf16_kernel<64, true, true><<<grid, blk, 0, st>>>(a);
       else if (stitched) tiles_attention_split_bf16_kernel<64, false, true><<<grid, blk, 0, st>>>(a);
@@ -973,5 +973,5 @@ hipError_t launch_tiles_attention(const reslim_ctx *c, const void *qkv, void *ou
 
 }  // namespace reslim
 
-// tuning hook for dh = 64: 0 = 64-key blocks, three work-groups per CU (default), 1 = 128-key blocks, two per CU
+// tuning hook for dh = 64: 0 = 64-key blocks, three work-groups per CU, or the keys split over the waves (default), 1 = 128-key blocks, two per CU
 extern "C" void reslim_debug_set_attention_variant(int v) { reslim::g_attn_variant = v; }
