@@ -9,6 +9,7 @@
 #include <thread>
 
 #include "common.h"
+#include "optional_memory.h"
 
 namespace reslim {
 
@@ -271,15 +272,17 @@ extern "C" int reslim_create(const reslim_config *cfg, const reslim_weights *w, 
     if (e == hipSuccess) e = elementwise_init();
     if (e == hipSuccess) e = panel_init();
     if (e == hipSuccess && panel_takes(c) && L > 0) {
-      void *p = nullptr;
-      if ((e = hipMalloc(&p, panel_layer_elems(c) * L * sizeof(bf16_t))) == hipSuccess) {
+      // a second copy of the blocks' matrices for one kernel; without it the blocks run as separate launches, same bits
+      void *p = optional_memory(panel_layer_elems(c) * L * sizeof(bf16_t), [](void **q, size_t n) { return hipMalloc(q, n) == hipSuccess; },
+                                []() { (void)hipGetLastError(); });
+      if (p) {
         c->allocs.push_back(p);
         c->d_panel_w = static_cast<bf16_t *>(p);
+        for (int l = 0; l < L && e == hipSuccess; ++l) e = panel_pack(c, l, c->d_panel_w, nullptr);
       }
-      for (int l = 0; l < L && e == hipSuccess; ++l) e = panel_pack(c, l, c->d_panel_w, nullptr);
     }
     if (e == hipSuccess) e = hipDeviceSynchronize();
-    if (e != hipSuccess) return fail(e == hipErrorOutOfMemory ? RESLIM_ENOMEM : RESLIM_EHIP, std::string("kernel setup failed: ") + hipGetErrorString(e));
+    if (e != hipSuccess) return fail(RESLIM_EHIP, std::string("kernel setup failed: ") + hipGetErrorString(e));
   } catch (const std::bad_alloc &) {
     return fail(RESLIM_ENOMEM, "out of host memory");
   } catch (...) {
