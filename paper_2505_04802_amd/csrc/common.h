@@ -205,7 +205,7 @@ bool panel_takes(const reslim_ctx *c);      // contexts that get packed matrices
 // debugging hook pins the GEMM kernel, which is then to be seen in launches of its own.
 bool panel_used(const reslim_ctx *c, int64_t rows, const void *stream);
 hipError_t panel_init();
-size_t panel_layer_elems(const reslim_ctx *c);      // of the four matrices of a layer
+size_t panel_elems(const reslim_ctx *c);      // of all packed matrices
 hipError_t panel_pack(const reslim_ctx *c, int layer, bf16_t *dst, hipStream_t st);      // dst: of all layers
 // x <- res + proj(a) + mlp; qkv_next: with LayerNorm and QKV of layer + 1 behind it, else null
 hipError_t launch_panel_block(const reslim_ctx *c, int layer, const void *a, const float *res, const ResRowMap *res_map, float *x, void *qkv_next,

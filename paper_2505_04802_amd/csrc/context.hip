@@ -273,7 +273,7 @@ extern "C" int reslim_create(const reslim_config *cfg, const reslim_weights *w, 
     if (e == hipSuccess) e = panel_init();
     if (e == hipSuccess && panel_takes(c) && L > 0) {
       // a second copy of the blocks' matrices for one kernel; without it the blocks run as separate launches, same bits
-      void *p = optional_memory(panel_layer_elems(c) * L * sizeof(bf16_t), [](void **q, size_t n) { return hipMalloc(q, n) == hipSuccess; },
+      void *p = optional_memory(panel_elems(c) * sizeof(bf16_t), [](void **q, size_t n) { return hipMalloc(q, n) == hipSuccess; },
                                 []() { (void)hipGetLastError(); });
       if (p) {
         c->allocs.push_back(p);

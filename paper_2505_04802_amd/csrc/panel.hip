@@ -62,7 +62,7 @@ struct PanelArgs {
   int64_t res_in;
   float *x;                // [M, D] stream after the block (may be res)
   bf16_t *qkv;             // [M, 3 D], null: no next block
-  const bf16_t *w;         // packed matrices of all layers
+  const bf16_t *w;         // packed matrices that this launch reads
   unsigned w_bytes;
   int w_proj, w_fc1, w_fc2, w_qkv;      // byte offsets in them
   const float *b_proj, *b_fc1, *b_fc2, *b_qkv, *ln2_g, *ln2_b, *ln1_g, *ln1_b;
@@ -111,7 +111,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void panel_block_kernel(PanelArgs 
     }
   }
 
-  // ---- weight stream: a ring of PF fragments.  One buffer covers the packed matrices of all layers; a unit is named by the
+  // ---- weight stream: a ring of PF fragments.  One buffer covers the packed matrices that the launch reads; a unit is named by the
   // byte offset of the wave's first fragment in it, a scalar, to which a lane adds 16 bytes times its number.
   const __amdgpu_buffer_rsrc_t weights = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(g.w), 0, static_cast<int>(g.w_bytes), 0x00020000);
   const int lane16 = lane * 16;
@@ -545,16 +545,23 @@ bool panel_used(const reslim_ctx *c, int64_t rows, const void *stream) {
 
 bool panel_takes(const reslim_ctx *c) { return c->cfg.dtype == RESLIM_BF16 && (c->cfg.embed_dim == 256 || c->cfg.embed_dim == 512) && c->R % 512 == 0 && c->cfg.mlp_ratio <= 256; }
 
-size_t panel_layer_elems(const reslim_ctx *c) { return static_cast<size_t>(c->cfg.embed_dim) * (4 * c->cfg.embed_dim + 2 * c->R); }
+// What one launch reads lies together: a layer's three matrices, then the qkv of the layer after it.  The first layer's qkv has no
+// launch that would read it.
+static size_t panel_layer_elems(const reslim_ctx *c) { return static_cast<size_t>(c->cfg.embed_dim) * (4 * c->cfg.embed_dim + 2 * c->R); }
+static size_t panel_qkv_elems(const reslim_ctx *c) { return static_cast<size_t>(3) * c->cfg.embed_dim * c->cfg.embed_dim; }
+size_t panel_elems(const reslim_ctx *c) { return panel_layer_elems(c) * c->cfg.depth - panel_qkv_elems(c); }
 
 hipError_t panel_pack(const reslim_ctx *c, int layer, bf16_t *dst, hipStream_t st) {
   const LayerWeights &lw = c->layers[layer];
   dst += panel_layer_elems(c) * layer;
   const int D = c->cfg.embed_dim, R = c->R, nw = 8, nb = D / (32 * nw), ch = 32 * nw;
+  const bool last = layer + 1 == c->cfg.depth;
   // one after the other, as launch_panel_block() counts
   const struct { const void *src; int N, K, nb, kk, spread; } todo[4] = {
-      {lw.w_proj, D, D, nb, D / 16, 0}, {lw.w_fc1, R, D, 1, D / 16, 0}, {lw.w_fc2, D, R, nb, ch / 16, 0}, {lw.w_qkv, 3 * D, D, 3, D / 16, 1}};
+      {lw.w_proj, D, D, nb, D / 16, 0}, {lw.w_fc1, R, D, 1, D / 16, 0}, {lw.w_fc2, D, R, nb, ch / 16, 0},
+      {last ? nullptr : c->layers[layer + 1].w_qkv, 3 * D, D, 3, D / 16, 1}};
   for (auto &td : todo) {
+    if (!td.src) continue;
     const int64_t n = static_cast<int64_t>(td.N) * td.K;
     panel_pack_kernel<<<dim3(static_cast<unsigned>((n / 8 + 255) / 256)), dim3(256), 0, st>>>(static_cast<const bf16_t *>(td.src), dst, td.N, td.K,
                                                                                              nw, td.nb, td.kk, td.spread);
@@ -576,14 +583,13 @@ hipError_t launch_panel_block(const reslim_ctx *c, int layer, const void *a, con
   g.res_in = res_map ? res_map->rows_in : 1;
   g.x = x;
   g.qkv = static_cast<bf16_t *>(qkv_next);
-  // from this layer on; at most the next one's matrices are read, so the offsets stay small
-  const size_t D = c->cfg.embed_dim, R = c->R, per = panel_layer_elems(c), es = sizeof(bf16_t);
-  g.w = c->d_panel_w + per * layer;
-  g.w_bytes = static_cast<unsigned>(per * es * (qkv_next ? 2 : 1));
+  const size_t D = c->cfg.embed_dim, R = c->R, es = sizeof(bf16_t);
+  g.w = c->d_panel_w + panel_layer_elems(c) * layer;
+  g.w_bytes = static_cast<unsigned>((panel_layer_elems(c) - (qkv_next ? 0 : panel_qkv_elems(c))) * es);
   g.w_proj = 0;
   g.w_fc1 = static_cast<int>(D * D * es);
   g.w_fc2 = static_cast<int>((D * D + R * D) * es);
-  g.w_qkv = static_cast<int>((D * D + 2 * R * D + (qkv_next ? per : 0)) * es);
+  g.w_qkv = static_cast<int>((D * D + 2 * R * D) * es);
   g.b_proj = lw.b_proj; g.b_fc1 = lw.b_fc1; g.b_fc2 = lw.b_fc2; g.b_qkv = nx.b_qkv;
   g.ln2_g = lw.ln2_g; g.ln2_b = lw.ln2_b; g.ln1_g = nx.ln1_g; g.ln1_b = nx.ln1_b;
   g.M = M;
