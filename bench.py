@@ -22,18 +22,15 @@ sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 MFMA
 PEAK_HBM_GBS = 8000.0          # MI355X HBM3E
-PEAK_FP32_VECTOR_TFLOPS = 157.3  # MI355X fp32 vector (packed); plain fp32 instructions reach half of it
-ALU_BOUND = ("embed_agg",)      # kernels whose time is plain fp32 vector arithmetic, not HBM or MFMA
+PEAK_FP32_TFLOPS = 157.3       # MI355X fp32: matrix instructions, and vector ones where packed; plain vector ones reach half of it
+ALU_BOUND = ("embed_agg",)      # kernels whose time is fp32 arithmetic (bf16 path: matrix instructions), not HBM or bf16 MFMA
 
 # HBM bytes per launch from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs (see
 # profiles/), keyed by (workload, kernel label); None where not measured.
 # Source: profiles/forward_and_train_block_c1_all_kernels.md (fetched + written, scaled by the copy kernel).
 # FC2 and the projection share one kernel symbol in every profile: no separate figure for them.
 MEASURED_TRAFFIC = {
-    ("c1", "gemm_fc1"): 140.5e6 + 167.6e6,
     ("c1", "tiles_attention"): 203.8e6,            # both kernel symbols (five launches of six, the last block's one), weighted
-    ("c1", "gemm_qkv"): 98.2e6 + 130.7e6,
-    ("c1", "layernorm"): 84.7e6 + 42.3e6,
     # profiles/forward_and_train_block_c2_all_kernels.md
     ("c2", "gemm_fc1"): 1961.5e6 + 1300.5e6,
     ("c2", "gemm_qkv"): 1504.2e6 + 991.7e6,
@@ -47,6 +44,20 @@ MEASURED_TRAFFIC = {
     ("c3", "residual_unpatchify"): 4860.3e6 + 4246.7e6,
     ("c3", "gemm_head"): 3278.1e6 + 4252.4e6,
 }
+
+
+def launches(B, model):
+    """(label, ms, flop, bytes) of every recorded launch.  A launch that does the work of several steps has a record for each, with a
+    share of its time by operation count; measured is the launch, so they are added up here, under all their labels."""
+    out, last = [], None
+    for (name, ms, flop, nbytes), launch in zip(B.reslim_profile_read(model.ctx), B.reslim_profile_launches(model.ctx)):
+        if launch == last:
+            n, m, f, b = out[-1]
+            out[-1] = (f"{n}+{name}", m + ms, f + flop, b + nbytes)
+        else:
+            out.append((name, ms, flop, nbytes))
+        last = launch
+    return out
 
 
 def train_block(B, torch, model, cfg, K, verbose):
@@ -81,7 +92,7 @@ def train_block(B, torch, model, cfg, K, verbose):
         bwd()
     torch.cuda.synchronize()
     agg = {}
-    for name, ms, flop, nbytes in B.reslim_profile_read(model.ctx):
+    for name, ms, flop, nbytes in launches(B, model):
         a = agg.setdefault(name, dict(calls=0, ms=0.0, flop=0.0, bytes=0.0))
         a["calls"] += 1
         a["ms"] += ms
@@ -138,7 +149,7 @@ def train_step(B, torch, np, model, cfg, w, x_host, K, verbose):
     step()
     torch.cuda.synchronize()
     agg = {}
-    for name, kms, flop, nbytes in B.reslim_profile_read(model.ctx):
+    for name, kms, flop, nbytes in launches(B, model):
         a = agg.setdefault(name, dict(calls=0, ms=0.0, flop=0.0, bytes=0.0))
         a["calls"] += 1
         a["ms"] += kms
@@ -299,7 +310,7 @@ def measure(B, torch, cfg, w, x_host, K, W, verbose, want_train, note, want_step
     for _ in range(K):
         model.forward(x, y)
     torch.cuda.synchronize()
-    recs = B.reslim_profile_read(model.ctx)
+    recs = launches(B, model)
     B.reslim_profile_enable(model.ctx, 0)
     agg = {}
     for name, ms, flop, nbytes in recs:
@@ -321,7 +332,7 @@ def measure(B, torch, cfg, w, x_host, K, W, verbose, want_train, note, want_step
                             ms_per_step=round(a["ms"] / K, 5),
                             tflops=round(tfl, 2) if tfl else None, gbs=round(gbs, 1),
                             bound="alu" if name in ALU_BOUND else "mfma" if tfl else "hbm",
-                            frac=round(tfl / (PEAK_FP32_VECTOR_TFLOPS if name in ALU_BOUND else PEAK_BF16_TFLOPS), 4) if tfl
+                            frac=round(tfl / (PEAK_FP32_TFLOPS if name in ALU_BOUND else PEAK_BF16_TFLOPS), 4) if tfl
                             else round(gbs / PEAK_HBM_GBS, 4)))
     kernels.sort(key=lambda k: -k["ms_per_step"])
     dom = kernels[0]
@@ -330,7 +341,7 @@ def measure(B, torch, cfg, w, x_host, K, W, verbose, want_train, note, want_step
     if a["flop"] > 0:
         achieved = a["flop"] / avg_s / 1e12
         alu = dom["kernel"] in ALU_BOUND
-        peak = PEAK_FP32_VECTOR_TFLOPS if alu else PEAK_BF16_TFLOPS
+        peak = PEAK_FP32_TFLOPS if alu else PEAK_BF16_TFLOPS
         roof = dict(bound="alu" if alu else "mfma", kernel=dom["kernel"], achieved=round(achieved, 2), peak=peak,
                     unit="TFLOP/s", frac=round(achieved / peak, 4),
                     traffic=MEASURED_TRAFFIC.get((cfg.name, dom["kernel"])), avg_launch_ms=round(avg_s * 1e3, 5),

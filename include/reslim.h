@@ -373,12 +373,17 @@ int reslim_flop_counts(const reslim_ctx *ctx, int32_t batch, double *gemm_flop,
 /* Per-launch timing for benchmarks.  reslim_profile_enable(ctx, n) creates 2*n HIP
  * events (the only allocation; call it outside timed regions; n = 0 switches
  * profiling off and frees them).  While on, every kernel launch of the entry
- * points is bracketed by two event records on the caller's stream, up to n launches
+ * points is bracketed by two event records on the caller's stream, up to n records
  * since the last reslim_profile_reset().  reslim_profile_read() waits for the
- * recorded events and returns, per launch in issue order, a static label, the
- * elapsed milliseconds and the launch's ALGORITHMIC work: flop (2 per
- * multiply-add of the contraction, 0 for copies) and bytes (each operand read once,
- * each result written once).  With out == NULL only the count is returned. */
+ * recorded events and returns, in issue order, a static label, the elapsed
+ * milliseconds and the ALGORITHMIC work: flop (2 per multiply-add of the
+ * contraction, 0 for copies) and bytes (each operand read once, each result written
+ * once).  A launch has one record; one that does the work of several steps (a product
+ * that normalises its rows, a block's products in one launch) has one for each step,
+ * and the launch's milliseconds are divided among them by their operations, so rates
+ * are to be taken of the records of a launch together: reslim_profile_launches()
+ * gives the launch of every record, numbered from 0, records of one launch adjacent.
+ * With out == NULL only the count is returned. */
 typedef struct {
   const char *name;
   float ms;
@@ -387,6 +392,7 @@ typedef struct {
 int reslim_profile_enable(reslim_ctx *ctx, int32_t max_records);
 int reslim_profile_reset(reslim_ctx *ctx);
 int reslim_profile_read(reslim_ctx *ctx, reslim_profile_record *out, int32_t max_out, int32_t *n_out);
+int reslim_profile_launches(reslim_ctx *ctx, int32_t *out, int32_t max_out, int32_t *n_out);
 
 /* Bayesian training loss, forward value only (Sec. 4.1, "Bayesian Training Loss":
  * latitude-weighted squared error plus a total-variation prior over each pixel's

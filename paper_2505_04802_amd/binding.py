@@ -29,6 +29,7 @@ EXPORTS = ["tiles_partition", "reslim_create", "reslim_destroy", "reslim_last_er
            "reslim_tokens_per_sample", "reslim_workspace_bytes", "reslim_embed_fwd", "tiles_attention_fwd",
            "reslim_block_fwd", "reslim_head_fwd", "reslim_forward", "reslim_flop_counts",
            "reslim_debug_set_gemm_tile", "reslim_profile_enable", "reslim_profile_reset", "reslim_profile_read",
+           "reslim_profile_launches",
            "reslim_debug_copy", "reslim_debug_set_attention_variant",
            "reslim_bayes_loss_workspace_bytes", "reslim_bayes_loss_fwd", "reslim_bayes_loss_static_max_groups",
            "reslim_bayes_loss_fwd_static", "tiles_attention_fwd_lse",
@@ -138,6 +139,7 @@ def load() -> C.CDLL:
     lib.reslim_profile_enable.argtypes = [vp, i32]
     lib.reslim_profile_reset.argtypes = [vp]
     lib.reslim_profile_read.argtypes = [vp, C.POINTER(ProfileRecord), i32, C.POINTER(i32)]
+    lib.reslim_profile_launches.argtypes = [vp, C.POINTER(i32), i32, C.POINTER(i32)]
     lib.reslim_debug_copy.argtypes = [vp, vp, C.c_size_t, vp]
     lib.reslim_bayes_loss_workspace_bytes.argtypes = [i32, i32, i32, i32, C.POINTER(C.c_size_t)]
     lib.reslim_bayes_loss_fwd.argtypes = [vp, vp, vp, i32, i32, i32, i32, C.c_float, vp, vp, C.c_size_t, vp]
@@ -280,13 +282,24 @@ def reslim_profile_reset(ctx: int) -> None:
 
 
 def reslim_profile_read(ctx: int):
-    """[(label, ms, flop, bytes)] of the launches since the last reset (waits for them)."""
+    """[(label, ms, flop, bytes)] of the launches since the last reset (waits for them); a launch that does the work of
+    several steps has a record for each, see reslim_profile_launches."""
     lib = load()
     n = C.c_int32()
     _check(lib.reslim_profile_read(ctx, None, 0, C.byref(n)), ctx)
     recs = (ProfileRecord * max(n.value, 1))()
     _check(lib.reslim_profile_read(ctx, recs, n.value, C.byref(n)), ctx)
     return [(recs[i].name.decode(), float(recs[i].ms), recs[i].flop, recs[i].bytes) for i in range(n.value)]
+
+
+def reslim_profile_launches(ctx: int):
+    """The launch of every record of reslim_profile_read, numbered from 0; records of one launch are adjacent."""
+    lib = load()
+    n = C.c_int32()
+    _check(lib.reslim_profile_launches(ctx, None, 0, C.byref(n)), ctx)
+    out = (C.c_int32 * max(n.value, 1))()
+    _check(lib.reslim_profile_launches(ctx, out, n.value, C.byref(n)), ctx)
+    return list(out[:n.value])
 
 
 def _stream_ptr(stream=None) -> int:

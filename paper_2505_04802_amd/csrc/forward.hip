@@ -250,6 +250,19 @@ extern "C" int reslim_profile_read(reslim_ctx *c, reslim_profile_record *out, in
   return RESLIM_OK;
 }
 
+extern "C" int reslim_profile_launches(reslim_ctx *c, int32_t *out, int32_t max_out, int32_t *n_out) {
+  if (!c || !n_out) return RESLIM_EINVAL;
+  const int n = static_cast<int>(c->prof_rec.size());
+  *n_out = n;
+  if (!out) return RESLIM_OK;
+  int launch = -1;
+  for (int i = 0; i < n && i < max_out; ++i) {
+    if (i == 0 || c->prof_rec[i].ev != c->prof_rec[i - 1].ev) ++launch;
+    out[i] = launch;
+  }
+  return RESLIM_OK;
+}
+
 extern "C" int reslim_debug_copy(const void *src, void *dst, size_t bytes, void *hip_stream) {
   if (!src || !dst || bytes == 0 || bytes % 16) return RESLIM_EINVAL;
   return launch_copy_probe(src, dst, bytes, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? RESLIM_OK : RESLIM_EHIP;

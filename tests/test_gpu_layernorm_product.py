@@ -39,6 +39,16 @@ def test_every_launch_record_has_a_time(cfg):
         B.reslim_profile_enable(m.ctx, 256)
         m.forward(x)
         torch.cuda.synchronize()
-        recs = B.reslim_profile_read(m.ctx)
+        recs, launch = B.reslim_profile_read(m.ctx), B.reslim_profile_launches(m.ctx)
         B.reslim_profile_enable(m.ctx, 0)
     assert recs and all(ms > 0 for _, ms, _, _ in recs), recs
+    # records of one launch are adjacent and named; the launches are those of a forward
+    assert len(launch) == len(recs) and launch[0] == 0 and all(b - a in (0, 1) for a, b in zip(launch, launch[1:]))
+    names = ["+".join(r[0] for r, k in zip(recs, launch) if k == i) for i in range(launch[-1] + 1)]
+    if cfg.dtype == 0:
+        block = ["layernorm+gemm_qkv", "tiles_attention", "gemm_proj", "layernorm+gemm_fc1", "gemm_fc2"]
+        assert names == ["embed_agg", "gemm_agg_out", "gather"] + block * cfg.depth + ["layernorm_final+gemm_head", "residual_unpatchify"]
+    else:
+        mlp = "gemm_proj+layernorm+gemm_fc1+gemm_fc2"
+        assert names == (["embed_agg", "gemm_agg_out", "layernorm", "gemm_qkv"] + ["tiles_attention", mlp + "+layernorm+gemm_qkv"] * (cfg.depth - 1) +
+                         ["tiles_attention", mlp, "layernorm_final", "gemm_head", "residual_unpatchify"])
