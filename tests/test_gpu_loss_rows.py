@@ -36,3 +36,21 @@ def test_rows(shape, offset):
     d = d.cpu().numpy()
     assert np.isnan(d[:offset]).all() and np.isnan(d[offset + n:]).all()
     assert O.rel_l2(d[offset:offset + n].reshape(shape), TO.bayes_loss_bwd(pred, target, lw, 0.25) * 8.0) <= 1e-6
+
+
+@pytest.mark.parametrize("shape", [(1, 3072, 2, 3), (1, 3073, 8, 4), (2, 2047, 2, 4), (1, 4096, 3, 4), (1, 4097, 8, 4), (1, 7168, 2, 3), (1, 8191, 3, 5),
+                                   (4, 2049, 1, 2)], ids=str)
+def test_many_partial_sums(shape):
+    """A partial sum a plane: from 3073 of them on a thread of the last kernel takes four at once while there is a fourth, then up to
+    three singly.  One of them left out or taken twice is 1e-4 of the value."""
+    print(f"loss partial sums {shape}", flush=True)
+    r = np.random.default_rng(shape)
+    pred = (r.integers(-8, 9, shape) / 4).astype(np.float32)
+    target = (pred + 1.0 + 0.25 * r.standard_normal(shape)).astype(np.float32)
+    lw = O.lat_weights(shape[2], -80.0, 85.0).astype(np.float32)
+    assert B.reslim_bayes_loss_workspace_bytes(*shape) == 16 * shape[0] * shape[1]
+    out = torch.zeros(3, dtype=torch.float64, device="cuda")
+    ws = torch.empty(16 * shape[0] * shape[1], dtype=torch.uint8, device="cuda")
+    B.reslim_bayes_loss_fwd(torch.from_numpy(pred).cuda(), torch.from_numpy(target).cuda(), torch.from_numpy(lw).cuda(), 0.25, out, ws)
+    ref = np.asarray(O.bayes_loss(pred, target, lw, tv_weight=0.25), dtype=np.float64)
+    assert np.allclose(out.cpu().numpy(), ref, rtol=1e-5)
