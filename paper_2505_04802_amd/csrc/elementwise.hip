@@ -10,13 +10,16 @@
 
 #include "attention_common.h"
 #include "layernorm_common.h"
+#include "panel_plan.h"
 
 namespace reslim {
 
 // ------------------------------------------------------------------ LayerNorm
 // One wave per token row; the row lives in registers between the two statistics
 // passes (mean, then centred variance) and the normalise pass.
-template <class T, int NV>
+// PANEL: a width that the panel kernel normalises too, whose sums have the order of layernorm_common.h: a piece of 256 columns at a time.
+// Other rows add up their pieces lane by lane first: one tree over the lanes instead of one a piece.
+template <class T, int NV, bool PANEL>
 __global__ __launch_bounds__(256) void layernorm_kernel(const float *__restrict__ x, const int32_t *__restrict__ row_src,
                                                         int rows_per_sample_out, int64_t rows_per_sample_in,
                                                         const float *__restrict__ g, const float *__restrict__ be,
@@ -32,9 +35,7 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const float *__restrict_
   const float4 *xr = reinterpret_cast<const float4 *>(x + in_row * D);
   const int nv = D / 4;
   float4 v[NV];
-  // the sums follow the order of layernorm_common.h; rows of more than 512 columns, which no other kernel normalises, add up their
-  // pieces lane by lane first (one tree instead of one a piece)
-  constexpr int PIECES = NV <= 2 ? NV : 1;
+  constexpr int PIECES = PANEL ? NV : 1;
   float part[PIECES];
 #pragma unroll
   for (int i = 0; i < PIECES; ++i) part[i] = 0.f;
@@ -45,7 +46,13 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const float *__restrict_
     part[i % PIECES] += ln_sum4(v[i].x, v[i].y, v[i].z, v[i].w);
   }
   auto total = [&]() {
-    float s = ln_lane_sum(part[0]);
+    float s = part[0];
+    if constexpr (!PANEL) {
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+      return s;
+    }
+    s = ln_lane_sum(s);
 #pragma unroll
     for (int i = 1; i < PIECES; ++i) s += ln_lane_sum(part[i]);
     return s;
@@ -155,7 +162,14 @@ static hipError_t launch_ln_t(const float *x, const int32_t *row_src, int rpo, i
   const int nv = (D / 4 + 63) / 64;
   const dim3 grid(static_cast<unsigned>((rows_out + 3) / 4)), blk(256);
   T *o = static_cast<T *>(out);
-#define RESLIM_LN(NV) layernorm_kernel<T, NV><<<grid, blk, 0, st>>>(x, row_src, rpo, rpi, g, b, o, rows_out, D)
+#define RESLIM_LN(NV) layernorm_kernel<T, NV, false><<<grid, blk, 0, st>>>(x, row_src, rpo, rpi, g, b, o, rows_out, D)
+  if constexpr (sizeof(T) == 2) {
+    if (panel_width(D)) {
+      if (nv <= 1) layernorm_kernel<T, 1, true><<<grid, blk, 0, st>>>(x, row_src, rpo, rpi, g, b, o, rows_out, D);
+      else layernorm_kernel<T, 2, true><<<grid, blk, 0, st>>>(x, row_src, rpo, rpi, g, b, o, rows_out, D);
+      return hipGetLastError();
+    }
+  }
   if (nv <= 1) RESLIM_LN(1);
   else if (nv <= 2) RESLIM_LN(2);
   else if (nv <= 4) RESLIM_LN(4);

@@ -3,6 +3,9 @@
 
 namespace reslim {
 
+// Widths that the panel kernel is made for, 32 columns times eight waves times one or two.
+inline bool panel_width(int D) { return D == 256 || D == 512; }
+
 // Rows from which one launch beats the separate ones.  A panel cannot take less than the time in which the weights stream through a
 // compute unit: 13 us at D = 256, where a block of 64 rows takes 27 us against 41, and 54 us at D = 512, where one of 512
 // rows takes 67 us against 62, of 1024 rows 66 against 67 and of 2304 rows 70 against 75.
