@@ -200,8 +200,7 @@ bool gemm_pinned();      // the debugging hook has chosen the GEMM kernel
 
 // ---- everything in a block that is not attention, one launch (panel.hip; same bits as the separate kernels)
 bool panel_takes(const reslim_ctx *c);      // contexts that get packed matrices
-// whether a block of so many rows is one launch: those of the patches without halo copies, so that a whole forward and its blocks
-// one by one choose alike.  Not for a stream that is not aligned to 16 bytes (its rows go straight into LDS), nor while the
+// whether a block of so many rows (those of the patches, without halo copies) is one launch; it decides the time only.  Not for a stream that is not aligned to 16 bytes (its rows go straight into LDS), nor while the
 // debugging hook pins the GEMM kernel, which is then to be seen in launches of its own.
 bool panel_used(const reslim_ctx *c, int64_t rows, const void *stream);
 hipError_t panel_init();

@@ -540,7 +540,7 @@ hipError_t panel_init() {
 }
 
 bool panel_used(const reslim_ctx *c, int64_t rows, const void *stream) {
-  return c->d_panel_w && !gemm_pinned() && rows >= panel_rows_from(c->cfg.embed_dim) && (reinterpret_cast<uintptr_t>(stream) & 15) == 0;
+  return c->d_panel_w && !gemm_pinned() && rows >= panel_rows_from(c->cfg.embed_dim, c->R) && (reinterpret_cast<uintptr_t>(stream) & 15) == 0;
 }
 
 bool panel_takes(const reslim_ctx *c) { return c->cfg.dtype == RESLIM_BF16 && panel_width(c->cfg.embed_dim) && c->R % 512 == 0 && c->cfg.mlp_ratio <= 256; }

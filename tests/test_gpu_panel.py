@@ -103,7 +103,7 @@ def test_a_stream_that_is_not_aligned(separate_kernels):
 def test_compressed_and_plain_forward_choose_apart():
     """One patch per leaf at D = 512, 1008 patches owned and 1280 with halo copies: the compressed forward counts the leaves, copies included,
     and takes the kernel; the plain forward counts the patches and does not.  The outputs are the same bits all the same."""
-    cfg = BASE.with_(H=72, W=56, in_vars=1, out_vars=1, embed_dim=512, heads=8, tiles_y=2, tiles_x=2, halo=2)
+    cfg = BASE.with_(H=72, W=56, in_vars=1, out_vars=1, embed_dim=512, heads=8, mlp_ratio=2, tiles_y=2, tiles_x=2, halo=2)
     w, x = WL.make_weights(cfg, std=0.05), WL.make_fields(cfg)
     tiles, _, _, n_h = O.tiles_partition(cfg.Hp, cfg.Wp, cfg.tiles_y, cfg.tiles_x, cfg.halo)
     assert cfg.batch * cfg.n_tokens < 1024 <= cfg.batch * n_h, "the case is meant to lie across the line"
@@ -122,7 +122,7 @@ def test_compressed_and_plain_forward_choose_apart():
 
 def test_a_sample_does_not_depend_on_its_batch():
     """D = 512 with 900 patches a sample: alone they are separate launches, two of them are panels."""
-    cfg = BASE.with_(batch=2, H=60, W=60, embed_dim=512, heads=8, tiles_y=2, tiles_x=2, halo=1)
+    cfg = BASE.with_(batch=2, H=60, W=60, embed_dim=512, heads=8, mlp_ratio=2, tiles_y=2, tiles_x=2, halo=1)
     w = WL.make_weights(cfg, std=0.1)
     x = torch.from_numpy(WL.make_fields(cfg)).cuda()
     assert cfg.n_tokens < 1024 <= 2 * cfg.n_tokens
