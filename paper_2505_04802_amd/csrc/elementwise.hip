@@ -9,6 +9,7 @@
 #include <algorithm>
 
 #include "attention_common.h"
+#include "embed_plan.h"
 #include "layernorm_common.h"
 #include "panel_plan.h"
 
@@ -259,7 +260,7 @@ struct EmbedArgs {
 //
 // What it measured (MI355X), against a thread per four features and 8 or 16 patches on the vector pipe: 16,200 patches of 23 variables
 // at 256 features 35.4 us -> 22.7 (one work-group after the other of loads, softmax and product: latency bounds it), 32,768 of 8 at 512
-// 38.5 -> 29.4, 259,200 at 1024 854 -> 572, twice the matrix pipe's time.
+// 38.5 -> 29.4, 259,200 of 16 at 1024 854 -> 572, twice the matrix pipe's time.  Where it does not pay: embed_plan.h.
 template <int PT>
 __global__ __launch_bounds__(256) void embed_agg_mfma_kernel(EmbedArgs e, int hc) {
   constexpr int TP = 32 * PT, NG = 256 / TP;
@@ -377,11 +378,12 @@ __global__ __launch_bounds__(256) void embed_agg_mfma_kernel(EmbedArgs e, int hc
   }
 }
 
-// The same on the vector pipe: the fp32 path, other patch sides, and variables so many that LDS does not hold 32 patches.
+// The same on the vector pipe: the fp32 path, other patch sides, few variables for their features (embed_plan.h), and variables so many
+// that LDS does not hold 32 patches.
 // P2 = p*p when known at compile time (4 for the paper's 2x2 patches), 0 = run-time.
 // A work item of the P2 = 4 path reads the value tables of its four features for every variable (80 bytes per variable,
-// from L2) and uses them for 8 patches.
-template <class T, int P2>
+// from L2) and uses them for PPI patches: 16 from 1024 features on, below which 16 would leave half the threads without an item.
+template <class T, int P2, int PPI = 8>
 __global__ __launch_bounds__(256) void embed_agg_kernel(EmbedArgs e) {
   constexpr int TP = 16;                      // patches per work-group
   extern __shared__ float sm[];
@@ -435,7 +437,6 @@ __global__ __launch_bounds__(256) void embed_agg_kernel(EmbedArgs e) {
     if (e.dh % 4 == 0) {
       // A work item is four adjacent features (one head) of PPI patches: the pixel and
       // weight reads from LDS (broadcast over the wave) are shared by 4 PPI outputs.
-      constexpr int PPI = 8;
       const int Q = e.D / 4;
       for (int item = t; item < Q * (TP / PPI); item += 256) {
         const int dq = item % Q, p0 = (item / Q) * PPI;
@@ -506,6 +507,7 @@ hipError_t elementwise_init() {
   const int lim = 160 * 1024;
 #define RESLIM_ATTR(K) if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void *>(&K), hipFuncAttributeMaxDynamicSharedMemorySize, lim)
   RESLIM_ATTR((embed_agg_kernel<bf16_t, 4>));
+  RESLIM_ATTR((embed_agg_kernel<bf16_t, 4, 16>));
   RESLIM_ATTR((embed_agg_mfma_kernel<1>));
   RESLIM_ATTR((embed_agg_mfma_kernel<2>));
   RESLIM_ATTR((embed_agg_kernel<bf16_t, 0>));
@@ -523,7 +525,7 @@ hipError_t launch_embed_agg(const reslim_ctx *c, const float *x, void *o, int ba
   e.D = c->cfg.embed_dim; e.heads = c->cfg.heads; e.dh = c->dh;
   e.BN = static_cast<int64_t>(batch) * c->N;
   const bool bf = c->cfg.dtype == RESLIM_BF16, p4 = e.p == 2;
-  if (bf && p4 && e.dh % 64 == 0) {
+  if (bf && p4 && e.dh % 64 == 0 && embed_on_matrix_pipe(e.D, e.V, e.N)) {
     // LDS of 32 patches and hc heads: 512 V + 128 V hc bytes, 40 KiB where that can be (four work-groups a compute unit),
     // but heads for four waves, 256 features, together.
     const int least = std::min(e.heads, (256 + e.dh - 1) / e.dh);
@@ -550,7 +552,8 @@ hipError_t launch_embed_agg(const reslim_ctx *c, const float *x, void *o, int ba
   const int64_t blocks = (e.BN + TP - 1) / TP;
   if (blocks > INT32_MAX) return hipErrorInvalidValue;
   const dim3 grid(static_cast<unsigned>(blocks)), blk(256);
-  if (bf && p4) embed_agg_kernel<bf16_t, 4><<<grid, blk, lds, st>>>(e);
+  if (bf && p4 && e.D >= 1024) embed_agg_kernel<bf16_t, 4, 16><<<grid, blk, lds, st>>>(e);
+  else if (bf && p4) embed_agg_kernel<bf16_t, 4><<<grid, blk, lds, st>>>(e);
   else if (bf) embed_agg_kernel<bf16_t, 0><<<grid, blk, lds, st>>>(e);
   else if (p4) embed_agg_kernel<float, 4><<<grid, blk, lds, st>>>(e);
   else embed_agg_kernel<float, 0><<<grid, blk, lds, st>>>(e);

@@ -20,7 +20,10 @@ def _cfg(hp, wp, batch, variables, heads, dh):
 CASES = [_cfg(4, 8, 1, 1, 1, 64), _cfg(3, 11, 1, 2, 2, 64), _cfg(1, 31, 3, 3, 5, 64), _cfg(8, 8, 1, 23, 4, 64),
          _cfg(5, 13, 1, 30, 11, 64), _cfg(5, 7, 2, 7, 3, 128), _cfg(9, 7, 1, 33, 5, 128), _cfg(4, 9, 1, 6, 2, 256), _cfg(5, 9, 1, 150, 4, 64),
          _cfg(3, 5, 1, 200, 4, 64), _cfg(128, 512, 1, 3, 2, 64), _cfg(255, 257, 1, 4, 3, 64), _cfg(257, 257, 1, 1, 1, 128),
-         _cfg(129, 509, 1, 9, 5, 64)]
+         _cfg(129, 509, 1, 9, 5, 64),
+         # both sides of the rule that chooses the kernel (csrc/embed_plan.h): at 192, 256, 512 and 1024 features, the last by the patches too
+         _cfg(1, 31, 3, 3, 3, 64), _cfg(4, 8, 1, 2, 1, 64), _cfg(5, 9, 1, 1, 4, 64), _cfg(4, 9, 1, 6, 4, 128), _cfg(4, 9, 1, 7, 2, 256),
+         _cfg(7, 9, 2, 8, 8, 128), _cfg(3, 21, 1, 32, 16, 64), _cfg(125, 128, 1, 8, 16, 64), _cfg(5, 11, 1, 23, 24, 128)]
 
 
 @pytest.mark.parametrize("cfg", CASES, ids=lambda c: c.name)
