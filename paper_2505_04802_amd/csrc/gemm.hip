@@ -422,6 +422,7 @@ __device__ __forceinline__ void epilogue_store_f32(const GemmArgs &g, int m, int
 // LN: A is the stream, normalised here (KS = 4, VEC4, K <= kLnK: a wave's part of its 32 rows stays in registers between
 // the statistics and the products).  Every column tile of the output repeats that, but a LayerNorm launch of its own takes 3 us on the tiny
 // workload, whatever there is to do, and this adds one: 512 x 384 x 128 and its LayerNorm 8.6 -> 6.5 us, the tiny forward 99 -> 90.
+// Which products: gemm_f32_normalises().
 constexpr int kLnK = 256;
 template <int EPI, int KS, bool VEC4, bool LN = false>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
@@ -622,7 +623,7 @@ static hipError_t launch_f32(GemmArgs g, hipStream_t st) {
 }
 
 bool gemm_takes_layernorm(int dtype, const void *A, const void *W, const float *ln_g, const float *ln_b, int M, int N, int K) {
-  return dtype == RESLIM_F32 && M > 0 && N > 0 && K > 0 && K <= kLnK && K % 4 == 0 && f32_split(M, N) && (N + 31) / 32 <= 65535 &&
+  return dtype == RESLIM_F32 && M > 0 && N > 0 && K > 0 && K <= kLnK && K % 4 == 0 && gemm_f32_normalises(M, N, K, g_num_cus) && f32_split(M, N) && (N + 31) / 32 <= 65535 &&
          ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(W) | reinterpret_cast<uintptr_t>(ln_g) | reinterpret_cast<uintptr_t>(ln_b)) & 15) == 0;
 }
 

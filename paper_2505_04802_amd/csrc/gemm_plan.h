@@ -40,4 +40,14 @@ inline GemmKernel gemm_choose(int M, int N, int K, GemmEpi epi, int num_cus) {
   return cs <= c1 && cs <= c2 ? kGemm128 : c1 < c2 ? kGemm128x256 : kGemm256x256;
 }
 
+// fp32 path: whether a product M x N x K normalises its rows itself (gemm_f32_kernel with LN) instead of after a launch of its own.
+// Every column tile of the outputs repeats the LayerNorm, which is free while a compute unit has no more than three tiles of 32 x 32: it saves
+// 1 to 2 us then (512 x 384 x 128: 1.6; 2048 x 384 x 128, 768 tiles: 0.3).  With more it costs up to 4 (4096 x 384 x 128, 1536 tiles: 2.8; 1536 x
+// 768 x 96, 1152 tiles: 3.8), but for products with no more columns than features, which repeat it too seldom to notice (8192 x
+// 64 x 64, 512 tiles: saves 3.2; 12,288 x 160 x 160, 1920 tiles: 2.4).
+inline bool gemm_f32_normalises(int M, int N, int K, int num_cus) {
+  const long long tiles = static_cast<long long>((M + 31LL) / 32) * ((N + 31LL) / 32);
+  return tiles <= 3LL * num_cus || ((N <= K || N <= 32) && tiles < 8LL * num_cus);
+}
+
 }  // namespace reslim
