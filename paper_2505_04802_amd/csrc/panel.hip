@@ -7,7 +7,7 @@
 // or two column tiles leave the products at 250-550 TFLOP/s, and the hidden layer, qkv and the stream go through memory between
 // them.  In one launch the rows stay in registers and LDS and only the weights stream in, 1.6 MB a panel at D = 256 and 6.3 MB at 512,
 // which a compute unit takes from L2 at 110 bytes a nanosecond.  What it measured (MI355X, with the next qkv): 19,552 rows of 256
-// features 91 us in seven launches, 47 here (204 panels of 96 rows: 660 TFLOP/s); 42,560 rows of 512 384 us, 325 here (822).
+// features 91 us in seven launches, 47 here (204 panels of 96 rows: 653 TFLOP/s); 42,560 rows of 512 384 us, 325 here (823).
 // What bounds it: the matrix pipe is busy 42 % of the time at D = 256 and shares the SIMD with the vector work of GELU, LayerNorm and
 // addresses (two waves' matrix and vector instructions take the sum of the one and half the other at best); panels of 32 rows
 // wait for the weights.

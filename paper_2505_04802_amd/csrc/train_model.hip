@@ -34,9 +34,10 @@ hipError_t launch_partial_reduce(const float *partial, float *out, int n_part, i
 // column (EVEN: there is none; its branches cost 4 % at 16 planes of 512 x 1024).  One thread per pixel took 9.2 ms at c3
 // where this takes 2.5; loss and gradient of 32 planes of 1024 x 2050 took 818 us with ragged rows left to one thread
 // per pixel, and take 297.
-// The gradient is stored past the caches: it is as large as what the caches should keep of the two inputs, and evicting its dirty
-// lines cost the next reader: 4 x 8 planes of 512 x 1024, value and gradient on inputs that change from pass to pass,
-// 67.2 -> 62.8 us; one plane set of 16 x 5760 x 11520 2.48 -> 2.42 ms.
+// The gradient is stored past the caches: it is as large as what the caches should keep of the two inputs, and what that buys is that
+// inputs stay there until they are used again: 4 x 8 planes of 512 x 1024, value and gradient on a few sets of inputs in
+// turn, 67.2 -> 62.8 us.  On inputs that lie in no cache it gains nothing to speak of (92 -> 89 us with the value's last kernel, which
+// became faster too).  One plane set of 16 x 5760 x 11520 2.48 -> 2.42 ms.
 // A neighbour outside the plane is held as NaN: every comparison with it is false, so its sign term is zero, which is
 // what leaving it out means.  The sums of signs are small integers, exact in any order.
 template <int RB, bool EVEN>
