@@ -74,7 +74,7 @@ def test_a_stream_far_larger_than_the_update(separate_kernels, cfg):
     print(f"panel, large stream {cfg.name}", flush=True)
     with B.Reslim(cfg, WL.make_weights(cfg, std=0.1)) as m:
         g = torch.Generator(device="cuda").manual_seed(5)
-        x = 4096.0 + torch.randn((cfg.batch, m.n_h, cfg.embed_dim), generator=g, device="cuda")
+        x = 4096.0 + torch.randn((cfg.batch, m.n_h, cfg.embed_dim), generator=g, device="cuda", dtype=torch.float32)
         got, sep = x.clone(), x.clone()
         m.block(0, got)
         separate_kernels(True)
