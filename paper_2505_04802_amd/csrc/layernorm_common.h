@@ -1,5 +1,5 @@
 // The arithmetic of LayerNorm, shared by the kernels that apply it to whole rows (elementwise.hip) and to rows that lie
-// across the waves of a work-group (panel.hip).  Both have to give the same bits, so the order is fixed here: four consecutive
+// across the waves of a work-group (panel.hip).  At the widths that both take they have to give the same bits, so the order is fixed here: four consecutive
 // columns first (below), then 32 columns (lanes 2, 4, then 1 apart where a lane holds four columns), then 64, 128 and
 // 256, then the 256-column pieces of the row from the first on.  Contractions are written out: left to the compiler they would depend on the
 // code around them.
