@@ -31,9 +31,10 @@ namespace reslim {
 // feature column i -- the transpose happens in the LDS read.  Per 32 lanes that
 // read touches 4 chunks of 4 consecutive rows; rows r and r+2 (dh = 64; all four
 // rows at dh = 128) would hit the same banks, so V rows use their own swizzle swzV
-// that moves the chunk group by row.  The address of a direct load is one uniform
-// base per block plus a per-lane 32-bit offset.  Keys past the end of a ragged tile
-// re-read the last valid row (finite data; their probabilities are exactly zero).
+// that moves the chunk group by row.  The address of a direct load is a
+// buffer per block, made of scalars, plus a per-lane 32-bit offset that never changes.  Keys
+// past the end of a ragged tile lie beyond the buffer and are loaded as zeros (finite data; their
+// probabilities are exactly zero).
 //
 // Softmax bookkeeping with few vector instructions per score (at dh = 64 the fp32
 // vector pipe, not the matrix pipe, is the scarcer one):
@@ -43,9 +44,8 @@ namespace reslim {
 //    meets a logit more than TAU above it -- rare after the first block -- so the
 //    common block costs one max3 per three scores, one exp2 and half a convert
 //    per score;
-//  * the row sums L come from the bf16 probabilities the P V product uses, two per
-//    v_dot2c_f32_bf16 into one register per lane (a block of ones through the matrix
-//    pipe gives the same sums for a fifth of the matrix instructions at dh = 64).
+//  * the row sums L come from the bf16 probabilities the P V product uses, sixteen keys of 32
+//    queries per matrix instruction of half the size (see RowSums).
 // QS: the caller has already multiplied q by log2(e)/sqrt(dh) (the fused QKV
 // epilogue does, before its single rounding to bf16), so the MFMA output is the
 // base-2 logit itself.
@@ -60,6 +60,34 @@ namespace reslim {
 // ST: stitched output -- a query that its tile owns writes its patch's row of a [batch, N, D]
 // output, halo queries write nothing, and units or waves without an owned query are skipped (they
 // still take part in the loads and barriers of their work-group).
+// Row sums of the bf16 probabilities, taken from the same values the P V product uses.  The registers of P (lane l: query l % 32, eight
+// keys of half l / 32) are, to v_mfma_f32_16x16x32_bf16, columns of 16 queries with queries c and c + 16 in different k; rows 0
+// and 1 of `ones` pick them out.  The sum of query c ends up in register 0 of lane c, of query c + 16 in register 1 of lane c.
+// It takes the matrix unit for half as long as one instruction of the P V product.  v_dot2c_f32_bf16, two probabilities an instruction
+// on the vector unit, looks cheaper and is not: it does not run beside matrix instructions (two waves a SIMD, each one matrix instruction
+// and then eight others: 65 ns with v_dot2c, 39 with conversions or multiplications, 33 with none).  With it a launch of 9.5M-model tiles
+// took 43.8 us, 40.5 now; 37,520 tokens of 32 heads of 128 features 1924 us, 1710 now.
+struct RowSums {
+  typedef __attribute__((ext_vector_type(4))) float f32x4;
+  f32x4 v;
+  __device__ __forceinline__ static bf16x8 ones(int lane) {
+    bf16x8 o;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = static_cast<__bf16>((lane & 15) == ((lane >> 4) & 1) ? 1.0f : 0.0f);
+    return o;
+  }
+  __device__ __forceinline__ void reset() { v = f32x4{0.f, 0.f, 0.f, 0.f}; }
+  __device__ __forceinline__ void add(const bf16x8 &ones, const bf16x8 &p) { v = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, p, v, 0, 0, 0); }
+  __device__ __forceinline__ void scale(float alpha, int lane) {
+    v[0] *= alpha;
+    v[1] *= __shfl(alpha, (lane & 15) + 16);
+  }
+  __device__ __forceinline__ float total(int lane) const {
+    const float lo = __shfl(v[0], lane & 15), up = __shfl(v[1], lane & 15);
+    return lane & 16 ? up : lo;
+  }
+};
+
 template <int DH, int BKV, bool QS, int MINW = 2, bool ST = false, int PQK = 1, int PPV = 1>
 __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArgs a) {
   constexpr int BQ = 128;
@@ -143,33 +171,23 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
   bool has_next = vb < a.total;
 
   // ---- load side: lane -> (row of the block, 16-byte chunk), per-lane byte offsets
-  int ld_row[LPW], offK[LPW], offV[LPW];
+  unsigned offK[LPW], offV[LPW];
   const int ld2 = ld * 2;
 #pragma unroll
   for (int i = 0; i < LPW; ++i) {
-    ld_row[i] = (wave + 4 * i) * RPB + lane / CPR;
-    offK[i] = ld_row[i] * ld2 + ((lane % CPR) ^ swzK(ld_row[i])) * 16;
-    offV[i] = ld_row[i] * ld2 + ((lane % CPR) ^ swzV(ld_row[i])) * 16 + a.D * 2;
+    const int r = (wave + 4 * i) * RPB + lane / CPR;
+    offK[i] = r * ld2 + ((lane % CPR) ^ swzK(r)) * 16;
+    offV[i] = r * ld2 + ((lane % CPR) ^ swzV(r)) * 16 + a.D * 2;
   }
+  // The buffer covers exactly the rows of a block that exist, from the head's keys on: rows past the tile's end are loaded as zeros.
   auto issue = [&](const Unit &u, int kv0, int buf) {
     unsigned char *sk = smem + buf * STAGE;
-    const unsigned char *gk = reinterpret_cast<const unsigned char *>(u.base + a.D + static_cast<size_t>(kv0) * ld);
-    const int lim = u.n_t - 1 - kv0;
-    if (lim >= BKV - 1) {                // whole block inside the tile (uniform): offsets need no arithmetic
+    const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(u.base + a.D + static_cast<size_t>(kv0) * ld), 0,
+                                                                         min(u.n_t - kv0, BKV) * ld2 - 2 * a.D, 0x00020000);
 #pragma unroll
-      for (int i = 0; i < LPW; ++i) {
-        attn_dl_load16(reinterpret_cast<const bf16_t *>(gk + static_cast<uint32_t>(offK[i])), sk + (wave + 4 * i) * 1024);
-        attn_dl_load16(reinterpret_cast<const bf16_t *>(gk + static_cast<uint32_t>(offV[i])),
-                       sk + TILE_B + (wave + 4 * i) * 1024);
-      }
-    } else {                             // rows past the tile end re-read its last row (finite, masked later)
-#pragma unroll
-      for (int i = 0; i < LPW; ++i) {
-        const int back = max(ld_row[i] - lim, 0) * ld2;
-        attn_dl_load16(reinterpret_cast<const bf16_t *>(gk + static_cast<uint32_t>(offK[i] - back)), sk + (wave + 4 * i) * 1024);
-        attn_dl_load16(reinterpret_cast<const bf16_t *>(gk + static_cast<uint32_t>(offV[i] - back)),
-                       sk + TILE_B + (wave + 4 * i) * 1024);
-      }
+    for (int i = 0; i < LPW; ++i) {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rows, (__attribute__((address_space(3))) void *)(sk + (wave + 4 * i) * 1024), 16, static_cast<int>(offK[i]), 0, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rows, (__attribute__((address_space(3))) void *)(sk + TILE_B + (wave + 4 * i) * 1024), 16, static_cast<int>(offV[i]), 0, 0, 0);
     }
   };
   bf16x8 qf[NKS];
@@ -200,21 +218,8 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
   }
 
   f32x16 o[NDT], minit;
-  // Sum of this lane's probabilities (its query, its half of the keys), taken from the same bf16
-  // values the P V product uses, two per instruction (v_dot2c_f32_bf16 against a pair of ones).
-  // A block of ones through the matrix unit gives the same sums but costs a fifth of the matrix
-  // instructions at head dimension 64 and sixteen registers; the two key halves meet at the end.
-  float lsum;
-  auto rowsum = [](const bf16x8 &p, float acc) {
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    const bf16x2 one2 = {static_cast<__bf16>(1.0f), static_cast<__bf16>(1.0f)};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const bf16x2 pr = {p[2 * i], p[2 * i + 1]};
-      acc = __builtin_amdgcn_fdot2_f32_bf16(pr, one2, acc, false);
-    }
-    return acc;
-  };
+  RowSums lsum;
+  const bf16x8 ones = RowSums::ones(lane);
   const float c = QS ? 1.0f : a.scale_log2;     // MFMA output -> base-2 logit
   const float TAU = 10.0f / c;                    // in units of the MFMA output
   bool have_ref = false;
@@ -225,7 +230,7 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
       for (int r = 0; r < 16; ++r) o[d][r] = 0.f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) minit[r] = 0.f;
-    lsum = 0.f;
+    lsum.reset();
     have_ref = false;
   };
   reset();
@@ -326,7 +331,7 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
         const float ninit = minit[0] - d;
 #pragma unroll
         for (int r = 0; r < 16; ++r) minit[r] = ninit;
-        lsum *= alpha;
+        lsum.scale(alpha, lane);
         have_ref = true;
       }
       if constexpr (!PIPE) {
@@ -365,7 +370,7 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int h2 = 0; h2 < 2; ++h2) {
-          lsum = rowsum(pf0[h2], lsum);
+          lsum.add(ones, pf0[h2]);
 #pragma unroll
           for (int d = 0; d < 2; ++d) {
             const u64x2 both = {vf0.r[h2][d][0], vf0.r[h2][d][1]};
@@ -388,7 +393,7 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
         v_frag_wait(vf1);
 #pragma unroll
         for (int h2 = 0; h2 < 2; ++h2) {
-          lsum = rowsum(pf1[h2], lsum);
+          lsum.add(ones, pf1[h2]);
 #pragma unroll
           for (int d = 0; d < 2; ++d) {
             const u64x2 both = {vf1.r[h2][d][0], vf1.r[h2][d][1]};
@@ -416,7 +421,7 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
           v_frag_wait(vf);
 #pragma unroll
           for (int h2 = 0; h2 < 2; ++h2) {
-            lsum = rowsum(pf[h2], lsum);
+            lsum.add(ones, pf[h2]);
 #pragma unroll
             for (int d = 0; d < 2; ++d) {
               typedef __attribute__((ext_vector_type(2))) uint64_t u64x2;
@@ -439,7 +444,7 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
             bf16x8 pf;
 #pragma unroll
             for (int e = 0; e < 8; ++e) pf[e] = static_cast<__bf16>(s[kt][8 * h2 + e]);
-            lsum = rowsum(pf, lsum);
+            lsum.add(ones, pf);
 #pragma unroll
             for (int d = 0; d < NDT; ++d) {
               const unsigned char *vp = st + (kt * 32 + h2 * 16) * ROWB;
@@ -475,7 +480,7 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
           if (d == 0) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) pf[e] = static_cast<__bf16>(s[kt][8 * h2 + e]);
-            lsum = rowsum(pf, lsum);
+            lsum.add(ones, pf);
           }
           const s16x8 both = __builtin_shufflevector(vlo[i % (PF + 1)], vhi[i % (PF + 1)], 0, 1, 2, 3, 4, 5, 6, 7);
           o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), pf, o[d], 0, 0, 0);
@@ -498,10 +503,7 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
       orow = yy * a.Wp + xx;
     }
     if (active && qrow < cur.n_t) {
-      // lanes l and l + 32 hold the two key halves of query l: full sum = own + partner
-      unsigned l_lo, l_up;
-      lane_pair_exchange(__builtin_bit_cast(unsigned, lsum), l_lo, l_up);
-      const float ltot = __builtin_bit_cast(float, l_lo) + __builtin_bit_cast(float, l_up);
+      const float ltot = lsum.total(lane);
       const float inv = 1.0f / ltot;
       // log-sum-exp of the logits (kept for the gradient): reference + log of the sum
       if (!ST && cur.lse && hi == 0) cur.lse[qrow] = (__builtin_amdgcn_logf(ltot) - minit[0] * c) * 0.69314718055994531f;
