@@ -298,6 +298,7 @@ extern "C" int reslim_asc_plan_create(reslim_ctx *c, int32_t batch, const int32_
   std::memset(owner, 0xff, cells * 4);
   int max_n = 0;
   double pairs = 0;
+  int64_t blocks128 = 0, blocks256 = 0;
   for (int64_t q = 0; q < n_seq; ++q) {
     const int64_t b = q / T;
     const tile_desc &td = c->tiles[q % T];
@@ -332,6 +333,8 @@ extern "C" int reslim_asc_plan_create(reslim_ctx *c, int32_t batch, const int32_
     seq[q].n_tok = static_cast<int32_t>(hi - lo);
     max_n = std::max(max_n, seq[q].n_tok);
     pairs += static_cast<double>(hi - lo) * static_cast<double>(hi - lo);
+    blocks128 += (hi - lo + 127) / 128;
+    blocks256 += (hi - lo + 255) / 256;
   }
   std::memcpy(blk->host + o_patch, patch_leaf, batch * N * 4);
   e = hipMemcpyAsync(blk->dev, blk->host, upload, hipMemcpyHostToDevice, c->plans.upload);
@@ -354,6 +357,8 @@ extern "C" int reslim_asc_plan_create(reslim_ctx *c, int32_t batch, const int32_
   pl->geom.n_h = n_leaves;
   pl->geom.max_n_tok = max_n;
   pl->geom.pairs = pairs;
+  pl->geom.blocks128 = blocks128;
+  pl->geom.blocks256 = blocks256;
   pl->geom.pairs_owned = pairs;   // no stitched launches on compressed sequences
   *out = pl;
   return RESLIM_OK;

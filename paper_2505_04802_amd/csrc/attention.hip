@@ -531,6 +531,337 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
   }
 }
 
+// ------------------------------------------------------------------ bf16 kernel at head dimension 64: two query groups a wave
+// The kernel above spends the matrix instructions' time plus the vector instructions' time: a wave issues in order, so its softmax runs
+// beside its own matrix instructions only where the two are woven, and there the scores and the last quarter of P V are not.  Here a
+// wave has two groups of 32 queries, A and B, and every phase of 32 keys weaves the matrix instructions of one (scores of the next
+// block, P V of the last) with the softmax of the other:
+//   phase 0: S_A(i + 1), O_A += V(i) P_A(i)  beside the softmax of S_B(i);   phase 1: S_B(i + 1), O_B += V(i) P_B(i)  beside that of S_A(i + 1)
+// Fragments of K and V are read from LDS once for both.  Order within a phase is pinned, one matrix instruction and what fits beside it
+// at a time (scheduling barriers; the empty statements keep the compiler from sinking vector work out of its place).
+// A block of 32 keys is 8 KiB; four lie in LDS, two of them in flight (five to ten took the same time).  K fragments of block i + 2 are read as soon as
+// block i + 1's last have been used, V's behind the first scores, so only the barrier in the middle (block i + 2 has landed, block i is
+// free) and the rare change of a reference stand between the phases; loads are issued between the scores of phase 1.
+// A query's reference moves only when it meets a logit more than TAU above it, whatever its neighbours do, so that its result
+// depends on neither the work-group's shape nor the queries beside it.
+// What bounds it: matrix pipe and vector unit are each busy about half of the time at 1.9 GHz, and every part costs its power: without
+// the loads a launch takes 0.89 of its time, without the exponentials 0.95.  403,200 tokens of 16 heads in tiles of 1274 to 1643: 3.06 ms with the kernel
+// above, 2.71 here (815 and 920 TFLOP/s); 42,560 of 8 in tiles of 612 to 720 89.8 us and 83.5.  When it is taken: attention_plan.h.
+template <bool QS, bool ST, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void tiles_attention_pair_bf16_kernel(AttnArgs a) {
+  constexpr int DH = 64, ROWB = DH * 2, TILE = 32 * ROWB, STAGE = 2 * TILE, NST = 4, NKS = DH / 16;
+  constexpr int BQ = 64 * NW, LPO = 4 / NW;            // direct loads of a wave per block and operand
+  __shared__ __align__(1024) unsigned char smem[NST * STAGE];
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int l32 = lane & 31, hi = lane >> 5;
+  const int ld = 3 * a.D, ld2 = ld * 2;
+  const int logical = xcd_remap_attn(blockIdx.x, a.total);
+  const int qb = logical % a.QB;
+  int rest = logical / a.QB;
+  const int head = rest % a.heads;
+  rest /= a.heads;
+  const int tile = rest % a.T, b = rest / a.T;
+  const tile_desc &td = a.tiles[tile];
+  const int n_t = td.n_tok, q0 = qb * BQ, wq0 = q0 + wave * 64;
+  if (q0 >= n_t) return;                               // uniform
+  const int bw = td.X1 - td.X0;
+  bool active = wq0 < n_t;
+  if constexpr (ST) {                                  // first and last query that the tile owns
+    const int lo = (td.y0 - td.Y0) * bw + (td.x0 - td.X0), up = (td.y1 - 1 - td.Y0) * bw + (td.x1 - 1 - td.X0);
+    if (q0 > up || q0 + BQ - 1 < lo) return;
+    active = active && wq0 <= up && wq0 + 63 >= lo;
+  }
+  const int64_t row0 = static_cast<int64_t>(b) * a.n_h + td.tok_off;
+  const bf16_t *const base = static_cast<const bf16_t *>(a.qkv) + row0 * ld + head * DH;
+  const int nkb = (n_t + 31) / 32;
+
+  // ---- load side
+  auto swzK = [](int r) { return (r & 7) ^ ((r >> 3) & 1); };
+  auto swzV = [](int r) { return (((r >> 1) & 1) << 2) | (((r >> 3) & 1) << 1); };
+  unsigned offK[LPO], offV[LPO];
+#pragma unroll
+  for (int i = 0; i < LPO; ++i) {
+    const int r = (wave + NW * i) * 8 + lane / 8;
+    offK[i] = r * ld2 + ((lane % 8) ^ swzK(r)) * 16;
+    offV[i] = r * ld2 + ((lane % 8) ^ swzV(r)) * 16 + a.D * 2;
+  }
+  auto after = [](unsigned stage) { return stage == (NST - 1) * STAGE ? 0u : stage + STAGE; };
+  // The buffer covers exactly the rows of one block that exist, from the head's keys on: rows past the tile's end and blocks past the
+  // last one are loaded as zeros without an access.
+  const bf16_t *k_ptr = base + a.D;
+  int rows_left = n_t;
+  unsigned l_stage = 0;
+  __amdgpu_buffer_rsrc_t rows;
+  auto next_block = [&]() {
+    rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(k_ptr), 0, max(min(rows_left, 32) * ld2 - 2 * a.D, 0), 0x00020000);
+    k_ptr += static_cast<size_t>(32) * ld;
+    rows_left -= 32;
+  };
+  auto load_keys = [&]() {
+#pragma unroll
+    for (int i = 0; i < LPO; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rows, (__attribute__((address_space(3))) void *)(smem + l_stage + (wave + NW * i) * 1024), 16,
+                                               static_cast<int>(offK[i]), 0, 0, 0);
+  };
+  auto load_values = [&]() {
+#pragma unroll
+    for (int i = 0; i < LPO; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rows, (__attribute__((address_space(3))) void *)(smem + l_stage + TILE + (wave + NW * i) * 1024), 16,
+                                               static_cast<int>(offV[i]), 0, 0, 0);
+    l_stage = after(l_stage);
+  };
+  auto load_block = [&]() {
+    next_block();
+    load_keys();
+    load_values();
+  };
+  // all but the youngest NST - 3 blocks of this wave's loads are done, then everybody's
+  auto landed = [&]() {
+    constexpr int N = 2 * LPO * (NST - 3);
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | (N >> 4 << 14));
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  bf16x8 q[2][NKS];
+  if (active) {
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      const bf16_t *qp = base + static_cast<size_t>(min(wq0 + 32 * g + l32, n_t - 1)) * ld + hi * 8;
+#pragma unroll
+      for (int ks = 0; ks < NKS; ++ks) q[g][ks] = *reinterpret_cast<const bf16x8 *>(qp + ks * 16);
+    }
+  }
+  for (int i = 0; i < NST - 1; ++i) load_block();
+  landed();                              // blocks 0 and 1
+  load_block();
+  if (!active) {                         // loads and barriers only
+    for (int i = 0; i + 1 < nkb; ++i) {
+      landed();
+      load_block();
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // no load into LDS outlives its work-group
+    return;
+  }
+
+  // ---- read side
+  const unsigned lds0 = static_cast<unsigned>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const unsigned char *)smem));
+  const int kr = key_perm(l32);
+  const unsigned k_base = lds0 + kr * ROWB + ((hi ^ swzK(kr)) << 4);
+  const int vr = 8 * hi + ((lane & 15) >> 2), vo = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+  const unsigned v_base = lds0 + TILE + vr * ROWB + (((vo >> 3) ^ swzV(vr)) << 4) + ((vo >> 2) & 1) * 8;
+  bf16x8 kf[NKS];
+  unsigned k_stage = 0, v_stage = 0;
+  auto read_k = [&]() __attribute__((always_inline)) {
+    const unsigned at = k_base + k_stage;
+    k_stage = after(k_stage);
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) kf[ks] = *reinterpret_cast<__attribute__((address_space(3))) bf16x8 *>(at ^ (ks * 32));
+  };
+  VFrag64 vf;
+  auto issue_v = [&]() __attribute__((always_inline)) {
+    const unsigned at = v_base + v_stage;
+    v_stage = after(v_stage);
+    asm volatile(
+        "ds_read_b64_tr_b16 %0, %8\n\t"
+        "ds_read_b64_tr_b16 %1, %8 offset:512\n\t"
+        "ds_read_b64_tr_b16 %2, %9\n\t"
+        "ds_read_b64_tr_b16 %3, %9 offset:512\n\t"
+        "ds_read_b64_tr_b16 %4, %8 offset:2048\n\t"
+        "ds_read_b64_tr_b16 %5, %8 offset:2560\n\t"
+        "ds_read_b64_tr_b16 %6, %9 offset:2048\n\t"
+        "ds_read_b64_tr_b16 %7, %9 offset:2560"
+        : "=&v"(vf.r[0][0][0]), "=&v"(vf.r[0][0][1]), "=&v"(vf.r[0][1][0]), "=&v"(vf.r[0][1][1]),
+          "=&v"(vf.r[1][0][0]), "=&v"(vf.r[1][0][1]), "=&v"(vf.r[1][1][0]), "=&v"(vf.r[1][1][1])
+        : "v"(at), "v"(at ^ 64u));
+  };
+
+  const float c = QS ? 1.0f : a.scale_log2;     // MFMA output -> base-2 logit
+  const float TAU = 10.0f / c;                    // in units of the MFMA output
+  f32x16 s[2], o[2][2], minit[2];
+  bf16x8 p[2][2];
+  RowSums lsum[2];
+  lsum[0].reset();
+  lsum[1].reset();
+  const bf16x8 ones = RowSums::ones(lane);
+#pragma unroll
+  for (int g = 0; g < 2; ++g)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      minit[g][r] = 0.f;
+      o[g][0][r] = 0.f;
+      o[g][1][r] = 0.f;
+    }
+  auto score = [&](auto g_c, auto ks_c) __attribute__((always_inline)) {
+    constexpr int g = decltype(g_c)::value, ks = decltype(ks_c)::value;
+    if constexpr (ks == 0) {               // the empty statements: from minit in its place, without a copy of it
+      asm volatile("" : "+v"(minit[g]));
+      s[g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[0], q[g][0], minit[g], 0, 0, 0);
+      asm volatile("" : "+v"(s[g]), "+v"(minit[g]));
+    }
+    else s[g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], q[g][ks], s[g], 0, 0, 0);
+  };
+  auto value = [&](auto g_c, auto i_c) __attribute__((always_inline)) {        // i: half of the keys, block of features
+    constexpr int g = decltype(g_c)::value, h2 = decltype(i_c)::value / 2, d = decltype(i_c)::value % 2;
+    typedef __attribute__((ext_vector_type(2))) uint64_t u64x2;
+    const u64x2 both = {vf.r[h2][d][0], vf.r[h2][d][1]};
+    o[g][d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), p[g][h2], o[g][d], 0, 0, 0);
+  };
+  auto max3 = [](float x, float y, float z) __attribute__((always_inline)) { return __builtin_elementwise_maximum(__builtin_elementwise_maximum(x, y), z); };
+  auto exps = [&](auto g_c, auto r_c) __attribute__((always_inline)) {         // four values
+    constexpr int g = decltype(g_c)::value, r = decltype(r_c)::value;
+    float e0 = __builtin_amdgcn_exp2f(QS ? s[g][r] : s[g][r] * c), e1 = __builtin_amdgcn_exp2f(QS ? s[g][r + 1] : s[g][r + 1] * c);
+    float e2 = __builtin_amdgcn_exp2f(QS ? s[g][r + 2] : s[g][r + 2] * c), e3 = __builtin_amdgcn_exp2f(QS ? s[g][r + 3] : s[g][r + 3] * c);
+    asm volatile("" : "+v"(e0), "+v"(e1), "+v"(e2), "+v"(e3));
+    s[g][r] = e0; s[g][r + 1] = e1; s[g][r + 2] = e2; s[g][r + 3] = e3;
+  };
+  auto convert = [&](auto g_c, auto h_c) __attribute__((always_inline)) {
+    constexpr int g = decltype(g_c)::value, h2 = decltype(h_c)::value;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) p[g][h2][e] = static_cast<__bf16>(s[g][8 * h2 + e]);
+    asm volatile("" : "+v"(p[g][h2]));
+  };
+  auto add_up = [&](auto g_c, auto h_c) __attribute__((always_inline)) {
+    constexpr int g = decltype(g_c)::value, h2 = decltype(h_c)::value;
+    lsum[g].add(ones, p[g][h2]);
+  };
+  auto fence = []() { __builtin_amdgcn_sched_barrier(0); };
+  // moves the reference of the queries that need it (block blk's scores in s[g])
+  auto settle = [&](auto g_c, int blk, float mx) __attribute__((always_inline)) {
+    constexpr int g = decltype(g_c)::value;
+    if (blk * 32 + 32 > n_t) {           // ragged last block: keys past the tile end get -inf
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (blk * 32 + 16 * (r / 8) + 8 * hi + (r % 8) >= n_t) s[g][r] = -INFINITY;
+      mx = s[g][0];
+#pragma unroll
+      for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[g][r]);
+    }
+    unsigned m_lo, m_up;
+    lane_pair_exchange(__builtin_bit_cast(unsigned, mx), m_lo, m_up);
+    mx = fmaxf(__builtin_bit_cast(float, m_lo), __builtin_bit_cast(float, m_up));
+    const float d = blk == 0 || mx > TAU ? mx : 0.f;
+    const float alpha = blk == 0 ? 0.f : __builtin_amdgcn_exp2f(-d * c);
+    const float ninit = minit[g][0] - d;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      s[g][r] -= d;
+      o[g][0][r] *= alpha;
+      o[g][1][r] *= alpha;
+      minit[g][r] = ninit;
+    }
+    lsum[g].scale(alpha, lane);
+  };
+  typedef std::integral_constant<int, 0> I0;
+  typedef std::integral_constant<int, 1> I1;
+  typedef std::integral_constant<int, 2> I2;
+  typedef std::integral_constant<int, 3> I3;
+  typedef std::integral_constant<int, 4> I4;
+  typedef std::integral_constant<int, 8> I8;
+  typedef std::integral_constant<int, 12> I12;
+  // One phase: matrix instructions of group gm (scores of a block where qk, P V of the block before where pv) with the softmax of block
+  // blk of the other group between them.
+  auto phase = [&](auto gm, auto qk, auto pv, int blk) __attribute__((always_inline)) {
+    constexpr int GM = decltype(gm)::value, GS = 1 - GM;
+    constexpr bool QK = decltype(qk)::value, PV = decltype(pv)::value;
+    std::integral_constant<int, GS> gs;
+    const f32x16 &x = s[GS];
+    const float limit = blk == 0 || blk * 32 + 32 > n_t ? __builtin_nanf("") : TAU;      // not a number: settle in any case
+    if constexpr (QK) score(gm, I0{});
+    fence();
+    if constexpr (PV && QK && GM == 1) { next_block(); load_keys(); }
+    if constexpr (PV && GM == 0) issue_v();
+    float m0 = max3(x[0], x[1], x[2]), m1 = max3(x[3], x[4], x[5]);
+    m0 = max3(m0, x[6], x[7]); m1 = max3(m1, x[8], x[9]);
+    fence();
+    if constexpr (QK) score(gm, I1{});
+    fence();
+    if constexpr (PV && QK && GM == 1) load_values();
+    m0 = max3(m0, x[10], x[11]); m1 = max3(m1, x[12], x[13]);
+    m0 = max3(m0, x[14], x[15]);
+    const float mx = __builtin_elementwise_maximum(m0, m1);
+    if (__builtin_expect(__any(!(mx <= limit)), 0)) settle(gs, blk, mx);
+    fence();
+    if constexpr (QK) score(gm, I2{});
+    fence();
+    exps(gs, I0{});
+    fence();
+    if constexpr (QK) score(gm, I3{});
+    fence();
+    if constexpr (QK && GM == 1) read_k();       // of the block after; past the last one zeros
+    exps(gs, I4{});
+    if constexpr (PV && GM == 0) v_frag_wait(vf);
+    fence();
+    if constexpr (PV) value(gm, I0{});
+    fence();
+    exps(gs, I8{});
+    fence();
+    if constexpr (PV) add_up(gm, I0{});
+    if constexpr (PV) value(gm, I1{});
+    fence();
+    exps(gs, I12{});
+    fence();
+    if constexpr (PV) value(gm, I2{});
+    fence();
+    convert(gs, I0{});
+    fence();
+    if constexpr (PV) value(gm, I3{});
+    fence();
+    convert(gs, I1{});
+    fence();
+    if constexpr (PV) add_up(gm, I1{});
+    fence();
+  };
+  typedef std::true_type Yes;
+  typedef std::false_type No;
+
+  read_k();
+  score(I0{}, I0{}); score(I0{}, I1{}); score(I0{}, I2{}); score(I0{}, I3{});
+  phase(I1{}, Yes{}, No{}, 0);
+#pragma unroll 1
+  for (int i = 0; i + 1 < nkb; ++i) {
+    phase(I0{}, Yes{}, Yes{}, i);
+    landed();                            // block i + 2; everybody has left block i, whose place takes block i + NST
+    phase(I1{}, Yes{}, Yes{}, i + 1);
+  }
+  phase(I0{}, No{}, Yes{}, nkb - 1);
+  value(I1{}, I0{}); value(I1{}, I1{}); value(I1{}, I2{}); value(I1{}, I3{});
+  add_up(I1{}, I0{});
+  add_up(I1{}, I1{});
+
+  if constexpr (ST) asm volatile("" : : "v"(minit[0][0]), "v"(minit[1][0]));      // alive to the end as for the log-sum-exp: it spills otherwise
+  __builtin_amdgcn_s_waitcnt(0x0F70);    // no load into LDS outlives its work-group
+
+  // ---- normalise and store this lane's two query rows
+  float *const lse = (ST || !a.lse) ? nullptr : a.lse + (static_cast<size_t>(b) * a.heads + head) * a.n_h + td.tok_off;
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    const int qrow = wq0 + 32 * g + l32;
+    int64_t orow = row0 + qrow;
+    bool keep = qrow < n_t;
+    if constexpr (ST) {                  // the query's patch, if this tile owns it
+      const int yy = td.Y0 + qrow / bw, xx = td.X0 + qrow % bw;
+      keep = keep && yy >= td.y0 && yy < td.y1 && xx >= td.x0 && xx < td.x1;
+      orow = static_cast<int64_t>(b) * a.N + static_cast<int64_t>(yy) * a.Wp + xx;
+    }
+    const float ltot = lsum[g].total(lane);
+    const float inv = 1.0f / ltot;
+    if (!ST && lse && hi == 0 && keep) lse[qrow] = (__builtin_amdgcn_logf(ltot) - minit[g][0] * c) * 0.69314718055994531f;
+    if (keep) {
+      bf16_t *op = static_cast<bf16_t *>(a.out) + orow * a.D + head * DH + hi * 4;
+#pragma unroll
+      for (int d = 0; d < 2; ++d)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+          bf16x4 tmp;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) tmp[e] = static_cast<__bf16>(o[g][d][4 * r4 + e] * inv);
+          *reinterpret_cast<u32x2 *>(op + d * 32 + r4 * 8) = __builtin_bit_cast(u32x2, tmp);
+        }
+    }
+  }
+}
+
 // ------------------------------------------------------------------ bf16 kernel for few queries: keys split over the waves
 // With fewer units of 128 queries than compute units (2300 tokens at four heads are 72) the kernel above leaves most of the chip
 // idle and every wave walks all keys, 36 blocks of 64 one after the other: 41 us.  Here a work-group takes 32 queries and its four
@@ -869,7 +1200,7 @@ __global__ __launch_bounds__(256) void tiles_attention_f32_kernel(AttnArgs a, in
   }
 }
 
-// 0: 64-key blocks, three work-groups per CU at dh = 64 (default); 1: 128-key blocks, two per CU
+// at dh = 64, 0: what attention_plan.h names (default); 1: 128-key blocks, two work-groups per CU
 static int g_attn_variant = 0;
 static int g_attn_cus = 0;
 
@@ -890,7 +1221,10 @@ SeqGeom ctx_geom(const reslim_ctx *c) {
   g.max_n_tok = c->max_n_tok;
   g.pairs = 0;
   g.pairs_owned = 0;
+  g.blocks128 = g.blocks256 = 0;
   for (const tile_desc &t : c->tiles) {
+    g.blocks128 += (t.n_tok + 127) / 128;
+    g.blocks256 += (t.n_tok + 255) / 256;
     g.pairs += static_cast<double>(t.n_tok) * t.n_tok;
     g.pairs_owned += static_cast<double>(t.y1 - t.y0) * (t.x1 - t.x0) * t.n_tok;
   }
@@ -906,6 +1240,18 @@ static void launch_bf16_variant(const AttnArgs &a, bool q_prescaled, bool stitch
   } else {
     if (q_prescaled) tiles_attention_bf16_kernel<DH, BKV, true, MINW, false, PQK, PPV><<<dim3(grid), dim3(256), 0, st>>>(a);
     else tiles_attention_bf16_kernel<DH, BKV, false, MINW, false, PQK, PPV><<<dim3(grid), dim3(256), 0, st>>>(a);
+  }
+}
+
+template <int NW>
+static void launch_pair(const AttnArgs &a, bool q_prescaled, bool stitched, hipStream_t st) {
+  const dim3 grid(a.total), blk(64 * NW);
+  if (stitched) {
+    if (q_prescaled) tiles_attention_pair_bf16_kernel<true, true, NW><<<grid, blk, 0, st>>>(a);
+    else tiles_attention_pair_bf16_kernel<false, true, NW><<<grid, blk, 0, st>>>(a);
+  } else {
+    if (q_prescaled) tiles_attention_pair_bf16_kernel<true, false, NW><<<grid, blk, 0, st>>>(a);
+    else tiles_attention_pair_bf16_kernel<false, false, NW><<<grid, blk, 0, st>>>(a);
   }
 }
 
@@ -932,7 +1278,7 @@ hipError_t launch_tiles_attention(const reslim_ctx *c, const void *qkv, void *ou
   }
   if (c->cfg.dtype == RESLIM_BF16) {
     a.QB = (sg.max_n_tok + 127) / 128;
-    const int64_t total = static_cast<int64_t>(batch) * sg.T * a.heads * a.QB;
+    const int64_t sets = static_cast<int64_t>(batch) * a.heads, total = sets * sg.T * a.QB;
     if (total > INT32_MAX) return hipErrorInvalidValue;
     a.total = static_cast<int>(total);
     if (a.total == 0) return hipSuccess;
@@ -945,6 +1291,11 @@ hipError_t launch_tiles_attention(const reslim_ctx *c, const void *qkv, void *ou
       else if (stitched) tiles_attention_split_bf16_kernel<64, false, true><<<grid, blk, 0, st>>>(a);
       else if (q_prescaled) tiles_attention_split_bf16_kernel<64, true, false><<<grid, blk, 0, st>>>(a);
       else tiles_attention_split_bf16_kernel<64, false, false><<<grid, blk, 0, st>>>(a);
+    } else if (const int nw = c->dh == 64 && g_attn_variant == 0 ? attn_pair_waves(sets * sg.blocks128, sets * sg.blocks256, g_attn_cus) : 0) {
+      a.QB = (sg.max_n_tok + 64 * nw - 1) / (64 * nw);
+      a.total = static_cast<int>(sets * sg.T * a.QB);
+      if (nw == 2) launch_pair<2>(a, q_prescaled, stitched, st);
+      else launch_pair<4>(a, q_prescaled, stitched, st);
     } else if (c->dh == 64 && g_attn_variant == 0) launch_bf16_variant<64, 64, 3, 2, 1>(a, q_prescaled, stitched, pg3, st);
     else if (c->dh == 64) launch_bf16_variant<64, 128, 2>(a, q_prescaled, stitched, pg2, st);
     else if (c->dh == 128) launch_bf16_variant<128, 64, 2>(a, q_prescaled, stitched, pg2, st);
@@ -975,5 +1326,5 @@ hipError_t launch_tiles_attention(const reslim_ctx *c, const void *qkv, void *ou
 
 }  // namespace reslim
 
-// tuning hook for dh = 64: 0 = 64-key blocks, three work-groups per CU, or the keys split over the waves (default), 1 = 128-key blocks, two per CU
+// tuning hook for dh = 64: 0 = the kernel that attention_plan.h names (default), 1 = 128-key blocks, one query group a wave, two work-groups per CU
 extern "C" void reslim_debug_set_attention_variant(int v) { reslim::g_attn_variant = v; }

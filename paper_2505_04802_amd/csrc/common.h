@@ -144,6 +144,7 @@ struct SeqGeom {
   int max_n_tok;
   double pairs;                    // sum over entries of n_tok^2 (flop accounting)
   double pairs_owned;              // sum of (owned tokens) * n_tok: the pairs of a stitched attention launch
+  int64_t blocks128, blocks256;    // sums over entries of their tokens in blocks of 128 and of 256, the last one partly filled
 };
 SeqGeom ctx_geom(const reslim_ctx *c);
 

@@ -1,0 +1,91 @@
+"""Tile attention with two query groups a wave (csrc/attention.hip), taken for launches of many blocks of queries: waves and groups without
+queries, one block of keys and several, a last block of one key, references that move in the middle, keys past the end that
+would outweigh the real ones, the log-sum-exp, halo copies (stitched output)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import reslim_oracle as O
+from paper_2505_04802_amd import binding as B
+from paper_2505_04802_amd import workloads as WL
+from parity_checks import assert_parity
+
+pytestmark = pytest.mark.gpu
+BASE = WL.ReslimConfig("pair", batch=1, in_vars=1, out_vars=1, H=2, W=2, scale=4, patch=2, embed_dim=1024, heads=16, mlp_ratio=1, depth=1,
+                       tiles_y=1, tiles_x=1, halo=0, dtype=1, seed=41)
+
+
+def tiled(h, w, ty, tx, **other):
+    """ty x tx tiles; h x w patches each where they divide"""
+    return BASE.with_(name=f"{h}x{w}_{ty}x{tx}_{'_'.join(map(str, other.values()))}", H=2 * h, W=2 * w, tiles_y=ty, tiles_x=tx, **other)
+
+
+# at 16 heads 49 to 64 blocks of 128 queries in all, tiles of 129 to 256 tokens or near a multiple of 256: four waves in a work-group
+FOUR = [tiled(3, 43 * 25, 1, 25),                           # 129: no query for the fourth wave, one for the third
+        tiled(8, 20 * 25, 1, 25),                           # 160: five whole blocks of keys, none in the third wave's second group
+        tiled(7, 23 * 25, 1, 25),                           # 161: a last block of one key
+        tiled(15, 15 * 25 + 9, 1, 25),                      # 225 and 240: one query in the last group
+        tiled(16, 16 * 13, 1, 13, batch=2),                 # 256
+        tiled(60, 84, 2, 3, batch=3, halo=2)]               # 32 by 30 to 32
+# at 64 heads 128 blocks and more, at least a twentieth fewer waves than with four: two
+TWO = [tiled(n, 128, 1, 128, embed_dim=4096, heads=64) for n in (1, 33, 65)] + [tiled(257, 43, 1, 43, embed_dim=4096, heads=64)]
+
+
+def qkv_of(cfg, n_h, kind):
+    D = cfg.embed_dim
+    x = WL.make_qkv(cfg.batch * n_h, D, seed=6, peaked=kind == "peaked", bf16=True).reshape(cfg.batch, n_h, 3 * D).copy()
+    tok = np.arange(n_h)
+    if kind == "moving":           # every seventh query meets a logit 13 times as large at every 37th key, 104 in base 2
+        x[:, tok % 7 == 3, :D] = 3.0
+        x[:, :, D:2 * D] *= 0.25
+        x[:, tok % 37 == 36, D:2 * D] = 3.0
+    if kind == "low":              # every logit is about -100 in base 2: a zero would be all there is
+        x[..., :D], x[..., D:2 * D] = 3.0, -3.0 + 0.25 * np.sign(x[..., D:2 * D])
+    return x
+
+
+@pytest.mark.parametrize("cfg,kind", [(c, k) for c in FOUR for k in ("normal", "peaked", "moving", "low")] +
+                         [(c, k) for c in TWO for k in ("moving", "low")], ids=lambda v: v if isinstance(v, str) else v.name)
+def test_against_the_oracle(cfg, kind):
+    print(f"pair attention {cfg.name} {kind}", flush=True)
+    tiles, _, _, n_h = O.tiles_partition(cfg.Hp, cfg.Wp, cfg.tiles_y, cfg.tiles_x, cfg.halo)
+    D = cfg.embed_dim
+    qkv = qkv_of(cfg, n_h, kind)
+    with B.Reslim(cfg, WL.make_weights(cfg)) as m:
+        act = torch.from_numpy(qkv.astype(np.float32)).cuda().to(m.act_dtype)
+        out = m.attention(act)
+        out2, lse = m.attention_with_lse(act)
+        B.reslim_debug_set_attention_variant(1)                            # one query group a wave
+        try:
+            other = m.attention(act)
+        finally:
+            B.reslim_debug_set_attention_variant(0)
+    assert torch.equal(out, out2)
+    some = tiles if cfg in FOUR else tiles[:2]                             # tiles never interact
+    rows = slice(0, int(some[-1]["tok_off"]) + int(some[-1]["n_tok"]))
+    ref = O.tiles_attention(qkv[:, rows], some, cfg.heads)
+    # an element: the usual 0.05 rms, and half a unit in the last place of the largest output (2^-8 of it; a query whose softmax falls on one
+    # key has outputs 12 times the rms of those that average over 384)
+    elem = 0.05 + 2.0 ** -8 * np.abs(ref).max() / np.sqrt((ref ** 2).mean())
+    assert_parity(out[:, rows].float().cpu().numpy(), ref, 2e-2, "attention", print, k_elem=elem)
+    # both kernels round P and the output to bf16 relative to other references: 2^-8 each at most
+    assert_parity(other.float().cpu().numpy(), out.float().cpu().numpy(), 2.0 ** -7, "against one group a wave", print, k_elem=elem)
+    t = some[-1]
+    s = slice(int(t["tok_off"]), int(t["tok_off"]) + int(t["n_tok"]))
+    for h in (0, cfg.heads - 1):
+        f = slice(h * 64, h * 64 + 64)
+        logits = (qkv[-1, s, :D][:, f].astype(np.float64) @ qkv[-1, s, D:2 * D][:, f].astype(np.float64).T) / 8.0
+        want = np.log(np.exp(logits - logits.max(1, keepdims=True)).sum(1)) + logits.max(1)
+        # the sum is of probabilities rounded to bf16 (8 significant bits: up to 2^-8 of each), beside 1e-5 of the fp32 arithmetic
+        assert np.abs(lse[-1, h, s].cpu().numpy() - want).max() <= 2.0 ** -8 + 1e-5 * np.abs(want).max()
+
+
+def test_stitched_output_is_the_same_bits():
+    """The last block of a whole forward writes the owned queries alone; the chain of entry points runs the same kernel unstitched."""
+    cfg = FOUR[-1].with_(depth=2)
+    w, x = WL.make_weights(cfg, std=0.1), torch.from_numpy(WL.make_fields(cfg)).cuda()
+    with B.Reslim(cfg, w) as m:
+        tok = m.embed(x)
+        for l in range(cfg.depth):
+            m.block(l, tok)
+        assert torch.equal(m.forward(x), m.head(x, tok))
