@@ -88,6 +88,58 @@ struct RowSums {
   }
 };
 
+// Head dimension 64, 32 keys of 32 queries before their exponentials (register r: key 16 (r / 8) + 8 hi + r % 8).  A query's reference is the
+// largest logit of its first 32 keys; it moves to any later 32 keys' largest logit more than kTau above it: by the query's own logits
+// alone, so that what it gets depends neither on its neighbours nor on the shape of the launch.  (Starting from zero needs no first move,
+// but then the largest probability is not the 1 that rounding to bf16 leaves as it is: 2.02e-3 of the result in place of 2.00e-3 with logits
+// of a standard deviation of 3.)
+constexpr float kTau = 10.0f;            // in base-2 logits
+__device__ __forceinline__ void mask_block(f32x16 &s, int key0, int n_t, int hi) {      // keys past the tile end get -inf
+#pragma unroll
+  for (int r = 0; r < 16; ++r)
+    if (key0 + 16 * (r / 8) + 8 * hi + (r % 8) >= n_t) s[r] = -INFINITY;
+}
+__device__ __forceinline__ float max3(float x, float y, float z) { return __builtin_elementwise_maximum(__builtin_elementwise_maximum(x, y), z); }
+__device__ __forceinline__ float max_of_block(const f32x16 &s) {      // of this lane's half of the keys
+  float m0 = max3(s[0], s[1], s[2]), m1 = max3(s[3], s[4], s[5]);
+  m0 = max3(m0, s[6], s[7]); m1 = max3(m1, s[8], s[9]);
+  m0 = max3(m0, s[10], s[11]); m1 = max3(m1, s[12], s[13]);
+  m0 = max3(m0, s[14], s[15]);
+  return __builtin_elementwise_maximum(m0, m1);
+}
+__device__ __forceinline__ void move_reference(f32x16 &s, f32x16 &o0, f32x16 &o1, f32x16 &minit, RowSums &lsum, float mx, bool first, float tau, float c, int lane) {
+  // The two lane halves exchange with v_permlane32_swap, not through LDS: an LDS lane permute makes the wave wait on the LDS counter,
+  // and that wait also covers the direct-to-LDS loads just issued (measured: the prefetch stops being asynchronous).
+  unsigned m_lo, m_up;
+  lane_pair_exchange(__builtin_bit_cast(unsigned, mx), m_lo, m_up);
+  mx = fmaxf(__builtin_bit_cast(float, m_lo), __builtin_bit_cast(float, m_up));
+  const float d = first || mx > tau ? mx : 0.f;
+  const float alpha = first ? 0.f : __builtin_amdgcn_exp2f(-d * c);
+  const float ninit = minit[0] - d;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    s[r] -= d;
+    o0[r] *= alpha;
+    o1[r] *= alpha;
+    minit[r] = ninit;
+  }
+  lsum.scale(alpha, lane);
+}
+
+// one V^T fragment of a 32-key group (32 features, the 16 keys of half h2), read and waited for in one statement; addresses as in v_frag_issue(f, at)
+template <int OFF>
+__device__ __forceinline__ bf16x8 v_frag_read(unsigned at, int h2) {
+  uint64_t lo, up;
+  if (h2 == 0)
+    asm volatile("ds_read_b64_tr_b16 %0, %2 offset:%3\n\tds_read_b64_tr_b16 %1, %2 offset:%4\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(lo), "=&v"(up) : "v"(at), "n"(OFF), "n"(OFF + 4 * 128));
+  else
+    asm volatile("ds_read_b64_tr_b16 %0, %2 offset:%3\n\tds_read_b64_tr_b16 %1, %2 offset:%4\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(lo), "=&v"(up) : "v"(at), "n"(OFF + 16 * 128), "n"(OFF + 20 * 128));
+  typedef __attribute__((ext_vector_type(2))) uint64_t u64x2;
+  return __builtin_bit_cast(bf16x8, u64x2{lo, up});
+}
+
 template <int DH, int BKV, bool QS, int MINW = 2, bool ST = false, int PQK = 1, int PPV = 1>
 __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArgs a) {
   constexpr int BQ = 128;
@@ -221,7 +273,7 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
   RowSums lsum;
   const bf16x8 ones = RowSums::ones(lane);
   const float c = QS ? 1.0f : a.scale_log2;     // MFMA output -> base-2 logit
-  const float TAU = 10.0f / c;                    // in units of the MFMA output
+  const float TAU = kTau / c;                     // in units of the MFMA output
   bool have_ref = false;
   auto reset = [&]() {
 #pragma unroll
@@ -290,70 +342,106 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
       }
     }
     __builtin_amdgcn_s_setprio(0);
+    bool woven = true;
+    if constexpr (PIPE) {
+      if (active) {
+        if (kv0 + BKV > cur.n_t) {         // ragged last block
+          mask_block(s[0], kv0, cur.n_t, hi);
+          mask_block(s[1], kv0 + 32, cur.n_t, hi);
+        }
+        const float limit = kb == 0 ? __builtin_nanf("") : TAU;      // not a number: in any case
+        woven = !__any(!(__builtin_elementwise_maximum(max_of_block(s[0]), max_of_block(s[1])) <= limit));
+        if (!woven) {
+          // A reference may move: one group of 32 keys after the other, the second's scores again from the reference that the first left.
+          // Same operations in the same order as where no reference moves, and as in the kernel below: same bits.
+          const unsigned va = static_cast<unsigned>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const unsigned char *)st)) + static_cast<unsigned>(v_addr[0][0]);
+          auto group = [&](auto kt_c) __attribute__((always_inline)) {
+            constexpr int kt = decltype(kt_c)::value;
+            if constexpr (kt == 1) {
+#pragma unroll
+              for (int ks = 0; ks < NKS; ++ks) {
+                const bf16x8 kf = *reinterpret_cast<const bf16x8 *>(st + kt * 32 * ROWB + k_row + (((2 * ks + hi) ^ k_swz) << 4));
+                s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], ks == 0 ? minit : s[1], 0, 0, 0);
+              }
+              if (kv0 + BKV > cur.n_t) mask_block(s[1], kv0 + 32, cur.n_t, hi);
+            }
+            move_reference(s[kt], o[0], o[1], minit, lsum, max_of_block(s[kt]), kb == 0 && kt == 0, TAU, c, lane);
+#pragma unroll
+            for (int h2 = 0; h2 < 2; ++h2) {
+              bf16x8 pf;
+#pragma unroll
+              for (int e = 0; e < 8; ++e) pf[e] = static_cast<__bf16>(__builtin_amdgcn_exp2f(QS ? s[kt][8 * h2 + e] : s[kt][8 * h2 + e] * c));
+              lsum.add(ones, pf);
+#pragma unroll
+              for (int d = 0; d < 2; ++d) {
+                const bf16x8 v = v_frag_read<kt * 32 * ROWB>(va ^ (64u * d), h2);
+                o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, pf, o[d], 0, 0, 0);
+              }
+            }
+          };
+          group(std::integral_constant<int, 0>{});
+          group(std::integral_constant<int, 1>{});
+        }
+      }
+    }
     // the query fragments are dead after the last block of a unit: fetch the next unit's
     if (last && has_next) load_q(nxt);
     if (active) {
-      if (kv0 + BKV > cur.n_t) {           // ragged last block: keys past the tile end get -inf
-#pragma unroll
-        for (int kt = 0; kt < NKT; ++kt)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int key = kv0 + kt * 32 + 16 * (r / 8) + 8 * hi + (r % 8);
-            if (key >= cur.n_t) s[kt][r] = -INFINITY;
-          }
-      }
-      float mx = s[0][0];
-#pragma unroll
-      for (int kt = 0; kt < NKT; ++kt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kt][r]);
-      {
-        // Exchange between the two lane halves with v_permlane32_swap, not through LDS:
-        // an LDS lane permute makes the wave wait on the LDS counter, and that wait
-        // also covers the direct-to-LDS loads of the next block just issued (measured:
-        // the prefetch stops being asynchronous).
-        unsigned m_lo, m_up;
-        lane_pair_exchange(__builtin_bit_cast(unsigned, mx), m_lo, m_up);
-        mx = fmaxf(__builtin_bit_cast(float, m_lo), __builtin_bit_cast(float, m_up));   // finite: every block holds a valid key
-      }
-      if (!have_ref || __any(mx > TAU)) {
-        // move this lane's reference up by d (first block: to the block maximum)
-        const float d = have_ref ? fmaxf(mx, 0.f) : mx;
-        const float alpha = have_ref ? __builtin_amdgcn_exp2f(-d * c) : 0.f;
-#pragma unroll
-        for (int kt = 0; kt < NKT; ++kt)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) s[kt][r] -= d;
-#pragma unroll
-        for (int dd = 0; dd < NDT; ++dd)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) o[dd][r] *= alpha;
-        const float ninit = minit[0] - d;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) minit[r] = ninit;
-        lsum.scale(alpha, lane);
-        have_ref = true;
-      }
       if constexpr (!PIPE) {
+        if (kv0 + BKV > cur.n_t) {           // ragged last block: keys past the tile end get -inf
+#pragma unroll
+          for (int kt = 0; kt < NKT; ++kt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              const int key = kv0 + kt * 32 + 16 * (r / 8) + 8 * hi + (r % 8);
+              if (key >= cur.n_t) s[kt][r] = -INFINITY;
+            }
+        }
+        float mx = s[0][0];
+#pragma unroll
+        for (int kt = 0; kt < NKT; ++kt)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kt][r]);
+        {
+          // Exchange between the two lane halves with v_permlane32_swap, not through LDS:
+          // an LDS lane permute makes the wave wait on the LDS counter, and that wait
+          // also covers the direct-to-LDS loads of the next block just issued (measured:
+          // the prefetch stops being asynchronous).
+          unsigned m_lo, m_up;
+          lane_pair_exchange(__builtin_bit_cast(unsigned, mx), m_lo, m_up);
+          mx = fmaxf(__builtin_bit_cast(float, m_lo), __builtin_bit_cast(float, m_up));   // finite: every block holds a valid key
+        }
+        if (!have_ref || __any(mx > TAU)) {
+          // move this lane's reference up by d (first block: to the block maximum)
+          const float d = have_ref ? fmaxf(mx, 0.f) : mx;
+          const float alpha = have_ref ? __builtin_amdgcn_exp2f(-d * c) : 0.f;
+#pragma unroll
+          for (int kt = 0; kt < NKT; ++kt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[kt][r] -= d;
+#pragma unroll
+          for (int dd = 0; dd < NDT; ++dd)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[dd][r] *= alpha;
+          const float ninit = minit[0] - d;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) minit[r] = ninit;
+          lsum.scale(alpha, lane);
+          have_ref = true;
+        }
 #pragma unroll
         for (int kt = 0; kt < NKT; ++kt)
 #pragma unroll
           for (int r = 0; r < 16; ++r)
             s[kt][r] = __builtin_amdgcn_exp2f(QS ? s[kt][r] : s[kt][r] * c);
       }
-
       __builtin_amdgcn_s_setprio(PPV);
       if constexpr (PIPE) {
+        if (woven) {
         // The exponentials and conversions of the second 32-key group are placed between the
         // matrix instructions of the first group's P V product: a wave issues in order, so its own
         // vector work only overlaps its matrix work when the two are interleaved in the stream.
-        const unsigned st_off = static_cast<unsigned>(reinterpret_cast<uintptr_t>(
-            (__attribute__((address_space(3))) const unsigned char *)st));
-        unsigned va[2][2];
-#pragma unroll
-        for (int e = 0; e < 2; ++e)
-#pragma unroll
-          for (int d = 0; d < 2; ++d) va[e][d] = st_off + static_cast<unsigned>(v_addr[e][d]);
+        const unsigned va = static_cast<unsigned>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const unsigned char *)st)) + static_cast<unsigned>(v_addr[0][0]);
         typedef __attribute__((ext_vector_type(2))) uint64_t u64x2;
         // the first group's V reads are issued ahead of its exponentials, which cover their latency
         VFrag64 vf0, vf1;
@@ -399,6 +487,7 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
             const u64x2 both = {vf1.r[h2][d][0], vf1.r[h2][d][1]};
             o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), pf1[h2], o[d], 0, 0, 0);
           }
+        }
         }
       } else if constexpr (DH == 64) {
         // LDS byte addresses of this lane's four fragment pointers in the current stage
@@ -542,8 +631,7 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
 // A block of 32 keys is 8 KiB; four lie in LDS, two of them in flight (five to ten took the same time).  K fragments of block i + 2 are read as soon as
 // block i + 1's last have been used, V's behind the first scores, so only the barrier in the middle (block i + 2 has landed, block i is
 // free) and the rare change of a reference stand between the phases; loads are issued between the scores of phase 1.
-// A query's reference moves only when it meets a logit more than TAU above it, whatever its neighbours do, so that its result
-// depends on neither the work-group's shape nor the queries beside it.
+// Same operations in the same order on every query as in the kernel above, whose launches it shares: same bits.
 // What bounds it: matrix pipe and vector unit are each busy about half of the time at 1.9 GHz, and every part costs its power: without
 // the loads a launch takes 0.89 of its time, without the exponentials 0.95.  403,200 tokens of 16 heads in tiles of 1274 to 1643: 3.06 ms with the kernel
 // above, 2.71 here (815 and 920 TFLOP/s); 42,560 of 8 in tiles of 612 to 720 89.8 us and 83.5.  When it is taken: attention_plan.h.
@@ -662,22 +750,11 @@ __global__ __launch_bounds__(64 * NW, 2) void tiles_attention_pair_bf16_kernel(A
   auto issue_v = [&]() __attribute__((always_inline)) {
     const unsigned at = v_base + v_stage;
     v_stage = after(v_stage);
-    asm volatile(
-        "ds_read_b64_tr_b16 %0, %8\n\t"
-        "ds_read_b64_tr_b16 %1, %8 offset:512\n\t"
-        "ds_read_b64_tr_b16 %2, %9\n\t"
-        "ds_read_b64_tr_b16 %3, %9 offset:512\n\t"
-        "ds_read_b64_tr_b16 %4, %8 offset:2048\n\t"
-        "ds_read_b64_tr_b16 %5, %8 offset:2560\n\t"
-        "ds_read_b64_tr_b16 %6, %9 offset:2048\n\t"
-        "ds_read_b64_tr_b16 %7, %9 offset:2560"
-        : "=&v"(vf.r[0][0][0]), "=&v"(vf.r[0][0][1]), "=&v"(vf.r[0][1][0]), "=&v"(vf.r[0][1][1]),
-          "=&v"(vf.r[1][0][0]), "=&v"(vf.r[1][0][1]), "=&v"(vf.r[1][1][0]), "=&v"(vf.r[1][1][1])
-        : "v"(at), "v"(at ^ 64u));
+    v_frag_issue<0>(vf, at);
   };
 
   const float c = QS ? 1.0f : a.scale_log2;     // MFMA output -> base-2 logit
-  const float TAU = 10.0f / c;                    // in units of the MFMA output
+  const float TAU = kTau / c;                     // in units of the MFMA output
   f32x16 s[2], o[2][2], minit[2];
   bf16x8 p[2][2];
   RowSums lsum[2];
@@ -707,7 +784,6 @@ __global__ __launch_bounds__(64 * NW, 2) void tiles_attention_pair_bf16_kernel(A
     const u64x2 both = {vf.r[h2][d][0], vf.r[h2][d][1]};
     o[g][d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), p[g][h2], o[g][d], 0, 0, 0);
   };
-  auto max3 = [](float x, float y, float z) __attribute__((always_inline)) { return __builtin_elementwise_maximum(__builtin_elementwise_maximum(x, y), z); };
   auto exps = [&](auto g_c, auto r_c) __attribute__((always_inline)) {         // four values
     constexpr int g = decltype(g_c)::value, r = decltype(r_c)::value;
     float e0 = __builtin_amdgcn_exp2f(QS ? s[g][r] : s[g][r] * c), e1 = __builtin_amdgcn_exp2f(QS ? s[g][r + 1] : s[g][r + 1] * c);
@@ -726,32 +802,6 @@ __global__ __launch_bounds__(64 * NW, 2) void tiles_attention_pair_bf16_kernel(A
     lsum[g].add(ones, p[g][h2]);
   };
   auto fence = []() { __builtin_amdgcn_sched_barrier(0); };
-  // moves the reference of the queries that need it (block blk's scores in s[g])
-  auto settle = [&](auto g_c, int blk, float mx) __attribute__((always_inline)) {
-    constexpr int g = decltype(g_c)::value;
-    if (blk * 32 + 32 > n_t) {           // ragged last block: keys past the tile end get -inf
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (blk * 32 + 16 * (r / 8) + 8 * hi + (r % 8) >= n_t) s[g][r] = -INFINITY;
-      mx = s[g][0];
-#pragma unroll
-      for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[g][r]);
-    }
-    unsigned m_lo, m_up;
-    lane_pair_exchange(__builtin_bit_cast(unsigned, mx), m_lo, m_up);
-    mx = fmaxf(__builtin_bit_cast(float, m_lo), __builtin_bit_cast(float, m_up));
-    const float d = blk == 0 || mx > TAU ? mx : 0.f;
-    const float alpha = blk == 0 ? 0.f : __builtin_amdgcn_exp2f(-d * c);
-    const float ninit = minit[g][0] - d;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      s[g][r] -= d;
-      o[g][0][r] *= alpha;
-      o[g][1][r] *= alpha;
-      minit[g][r] = ninit;
-    }
-    lsum[g].scale(alpha, lane);
-  };
   typedef std::integral_constant<int, 0> I0;
   typedef std::integral_constant<int, 1> I1;
   typedef std::integral_constant<int, 2> I2;
@@ -765,8 +815,9 @@ __global__ __launch_bounds__(64 * NW, 2) void tiles_attention_pair_bf16_kernel(A
     constexpr int GM = decltype(gm)::value, GS = 1 - GM;
     constexpr bool QK = decltype(qk)::value, PV = decltype(pv)::value;
     std::integral_constant<int, GS> gs;
-    const f32x16 &x = s[GS];
-    const float limit = blk == 0 || blk * 32 + 32 > n_t ? __builtin_nanf("") : TAU;      // not a number: settle in any case
+    f32x16 &x = s[GS];
+    const float limit = blk == 0 ? __builtin_nanf("") : TAU;      // not a number: in any case
+    if (__builtin_expect(blk * 32 + 32 > n_t, 0)) mask_block(x, blk * 32, n_t, hi);
     if constexpr (QK) score(gm, I0{});
     fence();
     if constexpr (PV && QK && GM == 1) { next_block(); load_keys(); }
@@ -780,7 +831,7 @@ __global__ __launch_bounds__(64 * NW, 2) void tiles_attention_pair_bf16_kernel(A
     m0 = max3(m0, x[10], x[11]); m1 = max3(m1, x[12], x[13]);
     m0 = max3(m0, x[14], x[15]);
     const float mx = __builtin_elementwise_maximum(m0, m1);
-    if (__builtin_expect(__any(!(mx <= limit)), 0)) settle(gs, blk, mx);
+    if (__builtin_expect(__any(!(mx <= limit)), 0)) move_reference(x, o[GS][0], o[GS][1], minit[GS], lsum[GS], mx, blk == 0, TAU, c, lane);
     fence();
     if constexpr (QK) score(gm, I2{});
     fence();

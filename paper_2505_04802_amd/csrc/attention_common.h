@@ -75,6 +75,23 @@ __device__ __forceinline__ void v_frag_issue(VFrag64 &f, const unsigned (&a)[2][
       : "v"(a[0][0]), "v"(a[1][0]), "v"(a[0][1]), "v"(a[1][1]), "n"(OFF), "n"(OFF + 16 * 128));
 }
 
+// The same from one address, where the rows' swizzle does not change with bit 2 of the row and flips bit 2 of the chunk with the feature block
+template <int OFF>
+__device__ __forceinline__ void v_frag_issue(VFrag64 &f, unsigned at) {
+  asm volatile(
+      "ds_read_b64_tr_b16 %0, %8 offset:%10\n\t"
+      "ds_read_b64_tr_b16 %1, %8 offset:%11\n\t"
+      "ds_read_b64_tr_b16 %2, %9 offset:%10\n\t"
+      "ds_read_b64_tr_b16 %3, %9 offset:%11\n\t"
+      "ds_read_b64_tr_b16 %4, %8 offset:%12\n\t"
+      "ds_read_b64_tr_b16 %5, %8 offset:%13\n\t"
+      "ds_read_b64_tr_b16 %6, %9 offset:%12\n\t"
+      "ds_read_b64_tr_b16 %7, %9 offset:%13"
+      : "=&v"(f.r[0][0][0]), "=&v"(f.r[0][0][1]), "=&v"(f.r[0][1][0]), "=&v"(f.r[0][1][1]),
+        "=&v"(f.r[1][0][0]), "=&v"(f.r[1][0][1]), "=&v"(f.r[1][1][0]), "=&v"(f.r[1][1][1])
+      : "v"(at), "v"(at ^ 64u), "n"(OFF), "n"(OFF + 4 * 128), "n"(OFF + 16 * 128), "n"(OFF + 20 * 128));
+}
+
 __device__ __forceinline__ void v_frag_wait(VFrag64 &f) {
   asm volatile("s_waitcnt lgkmcnt(0)"
                : "+v"(f.r[0][0][0]), "+v"(f.r[0][0][1]), "+v"(f.r[0][1][0]), "+v"(f.r[0][1][1]),

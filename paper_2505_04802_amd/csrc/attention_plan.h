@@ -20,7 +20,7 @@ inline bool attn_split_keys(int units, int cus, int tokens) {
 }
 
 // Waves in a work-group of the kernel with two query groups a wave, 0: the kernel with one.
-// u128, u256: tokens of all tiles, samples and heads in blocks of 128 and of 256 queries; cus: compute units.
+// Both give the same bits.  u128, u256: tokens of all tiles, samples and heads in blocks of 128 and of 256 queries; cus: compute units.
 // Where every SIMD has work for two waves and more, two groups a wave are 1.05 to 1.2 times as fast (blocks of 128 queries per compute unit in
 // brackets; one group, two): 1290 tokens, 512 sets of keys (22) 276 and 251 us; 660, 1024 (24) 189 and 159; 2000, 64 (4) 89 and 73; 400, 256 (4) 26.8 and
 // 23.5.  One group a wave keeps three blocks on a compute unit, two groups four and half as many waves to give them.  Up to three blocks all

@@ -89,3 +89,17 @@ def test_stitched_output_is_the_same_bits():
         for l in range(cfg.depth):
             m.block(l, tok)
         assert torch.equal(m.forward(x), m.head(x, tok))
+
+
+@pytest.mark.parametrize("scale", [0.3, 3.0, 9.0])      # no reference moves after the first keys; some do; most do
+def test_the_same_bits_as_with_one_group_a_wave(scale):
+    """A batch takes the kernel with two groups, its samples one by one the kernel with one: what a query gets does not depend on it."""
+    cfg = BASE.with_(batch=4, H=128, W=256, tiles_y=4, tiles_x=4, halo=2, embed_dim=512, heads=8)
+    _, _, _, n_h = O.tiles_partition(cfg.Hp, cfg.Wp, 4, 4, 2)
+    qkv = WL.make_qkv(cfg.batch * n_h, 512, seed=9, bf16=True).reshape(cfg.batch, n_h, 1536).astype(np.float32)
+    qkv[..., :512] *= scale
+    with B.Reslim(cfg, WL.make_weights(cfg)) as m:
+        act = torch.from_numpy(qkv).cuda().to(m.act_dtype)
+        out, lse = m.attention_with_lse(act)
+        parts = [m.attention_with_lse(act[b:b + 1].contiguous()) for b in range(cfg.batch)]
+    assert torch.equal(out, torch.cat([p[0] for p in parts])) and torch.equal(lse, torch.cat([p[1] for p in parts]))
