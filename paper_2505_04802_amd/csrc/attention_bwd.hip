@@ -12,10 +12,10 @@
 //                       -lse_i*sqrt(dh) as 16-byte records (see below);
 //   2. attn_bwd<KV=0>   query-stationary:  dQ;
 //   3. attn_bwd<KV=1>   key-stationary:    dK and dV.
-// Launches 2 and 3 are ONE kernel template.  As in the forward kernel a work unit is
-// 128 "stationary" tokens of one (sample, tile, head), 32 per wave, kept in registers
-// as MFMA B operands; the other side of the tile is streamed through LDS in blocks of
-// BS tokens (global -> LDS directly, two stages).  Every product is computed
+// Launches 2 and 3 are ONE kernel template, attn_bwd_woven at head dimension 64 and attn_bwd above.
+// As in the forward kernel a work unit is 128 "stationary" tokens of one (sample, tile, head), 32
+// per wave, kept in registers as MFMA B operands; the other side of the tile is streamed through
+// LDS in blocks of 32 or BS tokens (global -> LDS directly).  Every product is computed
 // transposed so that a lane owns one stationary token and the streamed index runs
 // over the accumulator registers:
 //     Sx  = Y1 X1^T      (stream x stationary)   Y1 = K | Q,   X1 = Q | K
@@ -37,6 +37,7 @@
 #include <type_traits>
 
 #include "attention_common.h"
+#include "gelu.h"
 
 namespace reslim {
 
@@ -130,10 +131,10 @@ __global__ __launch_bounds__(256, MINW) void attn_bwd_bf16_kernel(AttnBwdArgs a)
   constexpr int STAGE = 2 * TILE_B + AUXB;
   constexpr int LPW = TILE_B / 1024 / NW;
   constexpr int NKT = BS / 32, NKS = DH / 16, NDT = DH / 32 / NSPLIT;   // NDT: 32-feature blocks of the accumulators
-  constexpr bool PP = NKT == 2 && DH >= 128;   // wide heads with 64-token blocks: two groups in flight per wave
-  constexpr bool HAND = DH <= 128;        // transposing reads issued by hand (see attention_common.h); needs a spill-free kernel
+  constexpr bool PP = NKT == 2;           // 64-token blocks: two groups in flight per wave
+  constexpr bool HAND = DH == 128;        // transposing reads issued by hand (see attention_common.h); needs a spill-free kernel
   static_assert(TILE_B % (1024 * NW) == 0 && AUXB % 1024 == 0 && NST * STAGE <= 160 * 1024, "LDS plan");
-  static_assert((NST == 2 || NST == 3) && NKT <= 2, "ring of two or three stages of 32 or 64 tokens");
+  static_assert(DH >= 128 && (NST == 2 || NST == 3) && NKT <= 2, "ring of two or three stages of 32 or 64 tokens");
   extern __shared__ __align__(1024) unsigned char smem[];   // NST * STAGE bytes
 
   const int t = threadIdx.x, lane = t & 63;
@@ -145,7 +146,7 @@ __global__ __launch_bounds__(256, MINW) void attn_bwd_bf16_kernel(AttnBwdArgs a)
   // chunk swizzle of a row, good for both the 16-byte row fragments (16 lanes, 16 rows, one
   // chunk column) and the transposing reads (32 lanes, 4 consecutive rows x 4 chunks)
   auto swz = [](int r) {
-    return CPR == 8 ? ((((r >> 1) & 1) << 2) | (((r >> 2) & 1) << 1) | ((r >> 3) & 1)) : (((r & 3) << 2) | ((r >> 2) & 3));
+    return ((r & 3) << 2) | ((r >> 2) & 3);
   };
 
   // A unit = 128 stationary tokens of one (sample, tile, head); everything is uniform over the
@@ -405,42 +406,27 @@ __global__ __launch_bounds__(256, MINW) void attn_bwd_bf16_kernel(AttnBwdArgs a)
     // that one wave keeps both pipes busy (wide heads run a single wave per SIMD)
     auto scores = [&](auto kt_c, f32x16 &s, f32x16 &dp, auto between) {          // matrix pipe
       constexpr int kt = decltype(kt_c)::value;
-      if constexpr (DH >= 128) {
-        // wide heads: the fragment reads run PF steps ahead of the MFMAs that use them, in a ring
-        // of PF + 1 register sets, and a scheduling barrier per step keeps that order (left to
-        // itself the compiler either waits for every read right before its MFMA or hoists all
-        // reads of the group to its top: 64+ registers of fragments next to the accumulators)
-        constexpr int PF = 2;
-        bf16x8 f1[PF + 1], f2[DP ? PF + 1 : 1];
-        auto fetch = [&](int ks) {
-          const unsigned char *rp = st + kt * 32 * ROWB + y_row + (((2 * ks + hi) ^ y_swz) << 4);
-          f1[ks % (PF + 1)] = *reinterpret_cast<const bf16x8 *>(rp);
-          if constexpr (DP) f2[ks % (PF + 1)] = *reinterpret_cast<const bf16x8 *>(rp + TILE_B);
-        };
+      // the fragment reads run PF steps ahead of the MFMAs that use them, in a ring
+      // of PF + 1 register sets, and a scheduling barrier per step keeps that order (left to
+      // itself the compiler either waits for every read right before its MFMA or hoists all
+      // reads of the group to its top: 64+ registers of fragments next to the accumulators)
+      constexpr int PF = 2;
+      bf16x8 f1[PF + 1], f2[DP ? PF + 1 : 1];
+      auto fetch = [&](int ks) {
+        const unsigned char *rp = st + kt * 32 * ROWB + y_row + (((2 * ks + hi) ^ y_swz) << 4);
+        f1[ks % (PF + 1)] = *reinterpret_cast<const bf16x8 *>(rp);
+        if constexpr (DP) f2[ks % (PF + 1)] = *reinterpret_cast<const bf16x8 *>(rp + TILE_B);
+      };
 #pragma unroll
-        for (int ks = 0; ks < PF; ++ks) fetch(ks);
+      for (int ks = 0; ks < PF; ++ks) fetch(ks);
 #pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) {
-          if (ks + PF < NKS) fetch(ks + PF);
-          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f1[ks % (PF + 1)], x1f[ks], ks == 0 ? sinit : s, 0, 0, 0);
-          if constexpr (DP) dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f2[ks % (PF + 1)], x2f[ks], ks == 0 ? dpinit : dp, 0, 0, 0);
+      for (int ks = 0; ks < NKS; ++ks) {
+        if (ks + PF < NKS) fetch(ks + PF);
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f1[ks % (PF + 1)], x1f[ks], ks == 0 ? sinit : s, 0, 0, 0);
+        if constexpr (DP) dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f2[ks % (PF + 1)], x2f[ks], ks == 0 ? dpinit : dp, 0, 0, 0);
 #pragma unroll
-          for (int i = ks * 16 / NKS; i < (ks + 1) * 16 / NKS; ++i) between(i);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      } else {
-#pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) {
-          const unsigned char *rp = st + kt * 32 * ROWB + y_row + (((2 * ks + hi) ^ y_swz) << 4);
-          const bf16x8 f1 = *reinterpret_cast<const bf16x8 *>(rp);
-          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f1, x1f[ks], ks == 0 ? sinit : s, 0, 0, 0);
-          if constexpr (DP) {
-            const bf16x8 f2 = *reinterpret_cast<const bf16x8 *>(rp + TILE_B);
-            dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f2, x2f[ks], ks == 0 ? dpinit : dp, 0, 0, 0);
-          }
-#pragma unroll
-          for (int i = ks * 16 / NKS; i < (ks + 1) * 16 / NKS; ++i) between(i);
-        }
+        for (int i = ks * 16 / NKS; i < (ks + 1) * 16 / NKS; ++i) between(i);
+        __builtin_amdgcn_sched_barrier(0);
       }
       if constexpr (KV) {
         const bf16x8 fa = *reinterpret_cast<const bf16x8 *>(st + aux_addr + kt * 32 * 16);
@@ -560,20 +546,12 @@ __global__ __launch_bounds__(256, MINW) void attn_bwd_bf16_kernel(AttnBwdArgs a)
         products(std::integral_constant<int, 1>{}, sB, dB, nothing);
       }
     } else {
-      if constexpr (NKT == 2) {
-        if (active) {
-          scores(std::integral_constant<int, 0>{}, sA, dA, nothing);
-          if (ragged) mask(0, sA);
-          probs(sA, dA);
-          products(std::integral_constant<int, 0>{}, sA, dA, nothing);
-        }
-      }
-      if (active) scores(std::integral_constant<int, NKT - 1>{}, sA, dA, nothing);
+      if (active) scores(std::integral_constant<int, 0>{}, sA, dA, nothing);
       if (last && has_next) load_x(nxt);
       if (active) {
-        if (ragged) mask(NKT - 1, sA);
+        if (ragged) mask(0, sA);
         probs(sA, dA);
-        products(std::integral_constant<int, NKT - 1>{}, sA, dA, nothing);
+        products(std::integral_constant<int, 0>{}, sA, dA, nothing);
       }
     }
     if (++buf == NST) buf = 0;
@@ -615,6 +593,444 @@ __global__ __launch_bounds__(256, MINW) void attn_bwd_bf16_kernel(AttnBwdArgs a)
     sb = 0;
     reset();
   }
+}
+
+// ------------------------------------------------------------------ head dimension 64: two groups of streamed tokens in flight
+// A phase of a wave is 32 streamed tokens: the products of the group before (acc += Y^T dS, Y^T P), with the exponentials of this group between
+// their matrix instructions, then the scores of the group after, with the rest of this group's dS and P between theirs.  So
+// neither the vector work nor the LDS reads are in the matrix instructions' way: row fragments are read a phase ahead, each as soon as the one
+// in its place has been used, column fragments half a phase ahead.  The order is pinned as in the forward kernel with two query groups.
+// Seven or eight blocks lie in LDS, one barrier a phase: block i + 2 has landed, block i - 2 is free.  Two work-groups of four waves per
+// compute unit (206 and 238 registers); they start unit after unit, not persistent, so uneven tiles even out.
+// Every sum has the order of the kernel above: the same bits.  That one had scores, exponentials and products one after the other, two or three
+// waves a SIMD: 80,704 tokens of 16 heads in tiles of 1128 to 1323, dQ 749 us and dK, dV 1149 there, 737 and 967 here; 2000 tokens, 16 sets of keys
+// 45.4 and 57.8, 36.4 and 43.7; 30 tokens, 1024 sets 9.7 and 10.0, 8.4 and 8.3.  What bounds it: matrix pipe 45 and 51 % of the cycles, vector unit 47 and
+// 42 %, at 1.85 GHz; the loads are 15 % of the time (eight waves that share them were slower still: 814 and 1057 us), the LDS reads 7 %.
+template <bool KV, bool QS>
+__global__ __launch_bounds__(256, 2) void attn_bwd_woven_bf16_kernel(AttnBwdArgs a) {
+  constexpr int DH = 64, ROWB = DH * 2, TILE = 32 * ROWB, REC = KV ? 2 * 32 * 16 : 0, STAGE = 2 * TILE + REC, NST = KV ? 7 : 8, NKS = DH / 16;
+  constexpr int LOADS = KV ? 3 : 2;                    // direct loads of a wave per block
+  __shared__ __align__(1024) unsigned char smem[NST * STAGE];
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int l32 = lane & 31, hi = lane >> 5;
+  const int logical = xcd_remap_attn(blockIdx.x, a.total);
+  const int xb = logical % a.QB;
+  int rest = logical / a.QB;
+  const int head = rest % a.heads;
+  rest /= a.heads;
+  const int tile = rest % a.T, b = rest / a.T;
+  const int n_t = a.tiles[tile].n_tok, x0 = xb * 128 + wave * 32;
+  if (xb * 128 >= n_t) return;                         // uniform
+  const int64_t row0 = static_cast<int64_t>(b) * a.n_h + a.tiles[tile].tok_off;
+  const int64_t rec0 = (static_cast<int64_t>(b) * a.heads + head) * a.n_h + a.tiles[tile].tok_off;
+  const int ldq = 3 * a.D, ldx2 = KV ? ldq : a.D, ldy2 = KV ? a.D : ldq;
+  const bf16_t *const q = a.qkv + row0 * ldq + head * DH, *const dout = a.dout + row0 * a.D + head * DH;
+  const bool active = x0 < n_t;
+  const int n = (n_t + 31) / 32;                       // blocks of streamed tokens
+
+  // ---- load side.  The buffers cover exactly the rows of a block that exist: the rest of it, and blocks past the last one, are zeros without
+  // an access.  A wave loads eight rows of either operand and a quarter of the records.
+  auto swz = [](int r) { return (((r >> 1) & 1) << 2) | (((r >> 2) & 1) << 1) | ((r >> 3) & 1); };
+  const int l_row = wave * 8 + lane / 8, l_chunk = ((lane % 8) ^ swz(l_row)) * 16;
+  const int off1 = l_row * ldq * 2 + l_chunk, off2 = l_row * ldy2 * 2 + l_chunk, off3 = (wave & 1) * 256 + lane * 4;
+  const bf16_t *y1 = q + (KV ? 0 : a.D), *y2 = KV ? dout : q + 2 * a.D;
+  const u32x4 *rec = a.aux + rec0 + (wave >> 1) * a.aux_stride;
+  int rows_left = n_t;
+  unsigned l_stage = 0;
+  auto after = [](unsigned stage) { return stage == (NST - 1) * STAGE ? 0u : stage + STAGE; };
+  auto buffer = [](const void *p, int bytes) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00020000); };
+  auto to_lds = [&](__amdgpu_buffer_rsrc_t r, unsigned at, int off) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)(smem + at), 16, off, 0, 0, 0);
+  };
+  auto load_rows = [&]() {
+    to_lds(buffer(y1, max((min(rows_left, 32) - 1) * ldq * 2 + ROWB, 0)), l_stage + wave * 1024, off1);
+    y1 += static_cast<size_t>(32) * ldq;
+  };
+  auto load_rest = [&]() {
+    to_lds(buffer(y2, max((min(rows_left, 32) - 1) * ldy2 * 2 + ROWB, 0)), l_stage + TILE + wave * 1024, off2);
+    y2 += static_cast<size_t>(32) * ldy2;
+    if constexpr (KV) {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer(rec, max(min(rows_left, 32) * 16, 0)),
+                                               (__attribute__((address_space(3))) void *)(smem + l_stage + 2 * TILE + wave * 256), 4, off3, 0, 0, 0);
+      rec += 32;
+    }
+    rows_left -= 32;
+    l_stage = after(l_stage);
+  };
+  // all but the youngest `blocks` of this wave's loads are done, then everybody's
+  auto landed = [&](auto blocks) {
+    constexpr int N = LOADS * decltype(blocks)::value;
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | (N >> 4 << 14));
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  typedef std::integral_constant<int, NST - 4> First;
+  typedef std::integral_constant<int, NST - 5> Next;
+
+  // ---- stationary side
+  bf16x8 x1f[NKS], x2f[NKS];
+  f32x16 sinit, dpinit;
+  if (active) {
+    const int xrow = min(x0 + l32, n_t - 1);
+    const bf16_t *p1 = q + (KV ? a.D : 0) + static_cast<size_t>(xrow) * ldq + hi * 8;
+    const bf16_t *p2 = (KV ? q + 2 * a.D : dout) + static_cast<size_t>(xrow) * ldx2 + hi * 8;
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) {
+      x1f[ks] = *reinterpret_cast<const bf16x8 *>(p1 + ks * 16);
+      x2f[ks] = *reinterpret_cast<const bf16x8 *>(p2 + ks * 16);
+    }
+    float si = 0.f, di = 0.f;
+    if constexpr (!KV) {
+      const u32x2 r0 = *reinterpret_cast<const u32x2 *>(a.aux + rec0 + xrow), r1 = *reinterpret_cast<const u32x2 *>(a.aux + rec0 + a.aux_stride + xrow);
+      si = join3_bf16(r0[0], r0[1]);
+      di = join3_bf16(r1[0], r1[1]);
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) { sinit[r] = si; dpinit[r] = di; }
+  }
+  for (int i = 0; i < NST - 2; ++i) {
+    load_rows();
+    load_rest();
+  }
+  landed(First{});                       // blocks 0 and 1
+  if (!active) {                         // loads and barriers only
+    for (int i = 0; i < n; ++i) {
+      landed(Next{});
+      load_rows();
+      load_rest();
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // no load into LDS outlives its work-group
+    return;
+  }
+
+  // ---- read side: rows (a lane's token key_perm(l32), 16-byte chunks) and, through the transposing read, columns
+  const unsigned lds0 = static_cast<unsigned>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const unsigned char *)smem));
+  auto lds = [](unsigned at) { return *reinterpret_cast<__attribute__((address_space(3))) bf16x8 *>(at); };
+  const int yr = key_perm(l32);
+  const unsigned r_base = lds0 + yr * ROWB + ((hi ^ swz(yr)) << 4), rec_base = lds0 + 2 * TILE + hi * 512 + yr * 16;
+  const int vr = 8 * hi + ((lane & 15) >> 2), vo = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+  const unsigned t_base = lds0 + vr * ROWB + (((vo >> 3) ^ swz(vr)) << 4) + ((vo >> 2) & 1) * 8;
+  bf16x8 f1[NKS], f2[NKS], fr;
+  unsigned r_stage = 0, t_stage = 0;
+  auto read_row1 = [&](auto ks_c) __attribute__((always_inline)) { f1[decltype(ks_c)::value] = lds((r_base + r_stage) ^ (decltype(ks_c)::value * 32)); };
+  auto read_row2 = [&](auto ks_c) __attribute__((always_inline)) { f2[decltype(ks_c)::value] = lds(((r_base + r_stage) ^ (decltype(ks_c)::value * 32)) + TILE); };
+  auto read_record = [&]() __attribute__((always_inline)) {
+    if constexpr (KV) fr = lds(rec_base + r_stage);
+    r_stage = after(r_stage);
+  };
+  auto rows_are_there = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) asm volatile("" : "+v"(f1[ks]), "+v"(f2[ks]));
+    if constexpr (KV) asm volatile("" : "+v"(fr));
+  };
+  // columns of 16 streamed tokens: Y1's and, keys stationary, Y2's; [block of 32 features][rows + 0..3 and + 4..7].  Issued in one statement and
+  // waited for in another (see attention_common.h)
+  struct Columns { uint64_t y1[2][2], y2[2][2]; };
+  Columns c0, c1;
+  auto issue_columns = [&](Columns &c, auto h_c) __attribute__((always_inline)) {
+    constexpr int OFF = decltype(h_c)::value * 16 * ROWB;
+    const unsigned at0 = t_base + t_stage, at1 = (at0 + 512) ^ 32;
+    if constexpr (KV) {
+      asm volatile(
+          "ds_read_b64_tr_b16 %0, %8 offset:%12\n\t"
+          "ds_read_b64_tr_b16 %1, %9 offset:%12\n\t"
+          "ds_read_b64_tr_b16 %2, %8 offset:%13\n\t"
+          "ds_read_b64_tr_b16 %3, %9 offset:%13\n\t"
+          "ds_read_b64_tr_b16 %4, %10 offset:%12\n\t"
+          "ds_read_b64_tr_b16 %5, %11 offset:%12\n\t"
+          "ds_read_b64_tr_b16 %6, %10 offset:%13\n\t"
+          "ds_read_b64_tr_b16 %7, %11 offset:%13"
+          : "=&v"(c.y1[0][0]), "=&v"(c.y1[0][1]), "=&v"(c.y2[0][0]), "=&v"(c.y2[0][1]),
+            "=&v"(c.y1[1][0]), "=&v"(c.y1[1][1]), "=&v"(c.y2[1][0]), "=&v"(c.y2[1][1])
+          : "v"(at0), "v"(at1), "v"(at0 ^ 64u), "v"(at1 ^ 64u), "n"(OFF), "n"(OFF + TILE));
+    } else {
+      asm volatile(
+          "ds_read_b64_tr_b16 %0, %4 offset:%8\n\t"
+          "ds_read_b64_tr_b16 %1, %5 offset:%8\n\t"
+          "ds_read_b64_tr_b16 %2, %6 offset:%8\n\t"
+          "ds_read_b64_tr_b16 %3, %7 offset:%8"
+          : "=&v"(c.y1[0][0]), "=&v"(c.y1[0][1]), "=&v"(c.y1[1][0]), "=&v"(c.y1[1][1])
+          : "v"(at0), "v"(at1), "v"(at0 ^ 64u), "v"(at1 ^ 64u), "n"(OFF));
+    }
+  };
+  auto wait_columns = [&](Columns &c) __attribute__((always_inline)) {
+    if constexpr (KV) {
+      asm volatile("s_waitcnt lgkmcnt(0)"
+                   : "+v"(c.y1[0][0]), "+v"(c.y1[0][1]), "+v"(c.y2[0][0]), "+v"(c.y2[0][1]),
+                     "+v"(c.y1[1][0]), "+v"(c.y1[1][1]), "+v"(c.y2[1][0]), "+v"(c.y2[1][1]));
+    } else {
+      asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(c.y1[0][0]), "+v"(c.y1[0][1]), "+v"(c.y1[1][0]), "+v"(c.y1[1][1]));
+    }
+  };
+  bf16x8 ones_s, ones_d;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    ones_s[e] = static_cast<__bf16>(e < 3 && hi == 0 ? 1.0f : 0.0f);
+    ones_d[e] = static_cast<__bf16>(e < 3 && hi == 1 ? 1.0f : 0.0f);
+  }
+
+  f32x16 acc1[2], acc2[KV ? 2 : 1], s[2], dp[2];
+#pragma unroll
+  for (int d = 0; d < 2; ++d)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      acc1[d][r] = 0.f;
+      if constexpr (KV) acc2[d][r] = 0.f;
+    }
+  u32x4 pk_p[2], pk_d[2];                // P and dS of the group before, bf16 pairs
+  auto fence = []() { __builtin_amdgcn_sched_barrier(0); };
+  auto score = [&](auto p_c, auto ks_c) __attribute__((always_inline)) {
+    constexpr int p = decltype(p_c)::value, ks = decltype(ks_c)::value;
+    if constexpr (ks == NKS) {
+      s[p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr, ones_s, s[p], 0, 0, 0);
+    } else if constexpr (ks == 0) {
+      if constexpr (!KV) asm volatile("" : "+v"(sinit));
+      s[p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f1[0], x1f[0], sinit, 0, 0, 0);
+      if constexpr (!KV) asm volatile("" : "+v"(s[p]), "+v"(sinit));
+    } else {
+      s[p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f1[ks], x1f[ks], s[p], 0, 0, 0);
+    }
+  };
+  auto dscore = [&](auto p_c, auto ks_c) __attribute__((always_inline)) {
+    constexpr int p = decltype(p_c)::value, ks = decltype(ks_c)::value;
+    if constexpr (ks == NKS) {
+      dp[p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr, ones_d, dp[p], 0, 0, 0);
+    } else if constexpr (ks == 0) {
+      if constexpr (!KV) asm volatile("" : "+v"(dpinit));
+      dp[p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f2[0], x2f[0], dpinit, 0, 0, 0);
+      if constexpr (!KV) asm volatile("" : "+v"(dp[p]), "+v"(dpinit));
+    } else {
+      dp[p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f2[ks], x2f[ks], dp[p], 0, 0, 0);
+    }
+  };
+  typedef __attribute__((ext_vector_type(2))) uint64_t u64x2;
+  auto product1 = [&](const Columns &c, auto h_c, auto d_c) __attribute__((always_inline)) {
+    constexpr int h2 = decltype(h_c)::value, d = decltype(d_c)::value;
+    const u64x2 y = {c.y1[d][0], c.y1[d][1]};
+    acc1[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, y), __builtin_bit_cast(bf16x8, pk_d[h2]), acc1[d], 0, 0, 0);
+  };
+  auto product2 = [&](const Columns &c, auto h_c, auto d_c) __attribute__((always_inline)) {
+    constexpr int h2 = decltype(h_c)::value, d = decltype(d_c)::value;
+    if constexpr (KV) {
+      const u64x2 y = {c.y2[d][0], c.y2[d][1]};
+      acc2[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, y), __builtin_bit_cast(bf16x8, pk_p[h2]), acc2[d], 0, 0, 0);
+    }
+  };
+  auto exps = [&](auto p_c, auto r_c, auto n_c) __attribute__((always_inline)) {      // P of values r .. r + n - 1
+    constexpr int p = decltype(p_c)::value, r = decltype(r_c)::value, N = decltype(n_c)::value;
+#pragma unroll
+    for (int k = 0; k < N; k += 2) {
+      float e0 = __builtin_amdgcn_exp2f(QS ? s[p][r + k] : s[p][r + k] * a.c), e1 = __builtin_amdgcn_exp2f(QS ? s[p][r + k + 1] : s[p][r + k + 1] * a.c);
+      asm volatile("" : "+v"(e0), "+v"(e1));
+      s[p][r + k] = e0; s[p][r + k + 1] = e1;
+    }
+  };
+  auto finish = [&](auto p_c, auto k_c) __attribute__((always_inline)) {              // dS and the bf16 pair k
+    constexpr int p = decltype(p_c)::value, k = decltype(k_c)::value;
+    uint32_t d = pack2(dp[p][2 * k] * s[p][2 * k], dp[p][2 * k + 1] * s[p][2 * k + 1]);
+    asm volatile("" : "+v"(d));
+    pk_d[k / 4][k % 4] = d;
+    if constexpr (KV) {
+      uint32_t v = pack2(s[p][2 * k], s[p][2 * k + 1]);
+      asm volatile("" : "+v"(v));
+      pk_p[k / 4][k % 4] = v;
+    }
+  };
+  auto mask = [&](auto p_c, int blk) __attribute__((always_inline)) {                 // streamed tokens past the tile end get probability 0
+    constexpr int p = decltype(p_c)::value;
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      if (blk * 32 + 16 * (r / 8) + 8 * hi + (r % 8) >= n_t) s[p][r] = -INFINITY;
+  };
+#define RESLIM_I(n) std::integral_constant<int, n>{}
+  // Phase of block blk, whose scores are in s[P] and dp[P]: first the products of the block before (where pr) with the exponentials between them,
+  // then the scores of the block after (past the last one: of zeros, not used) with the rest of dS between them.
+  auto phase = [&](auto p_c, auto pr, int blk) __attribute__((always_inline)) {
+    constexpr int P = decltype(p_c)::value;
+    constexpr bool PR = decltype(pr)::value;
+    std::integral_constant<int, 1 - P> o_c;
+    landed(Next{});                      // block blk + 2; everybody has left block blk - 2
+    if (__builtin_expect(blk * 32 + 32 > n_t, 0)) mask(p_c, blk);
+    if constexpr (PR) {
+      wait_columns(c0);
+      if constexpr (KV) issue_columns(c1, RESLIM_I(1));
+      else wait_columns(c1);
+      if constexpr (KV) t_stage = after(t_stage);
+    }
+    if constexpr (KV) {
+      fence();
+      if constexpr (PR) product1(c0, RESLIM_I(0), RESLIM_I(0));
+      fence();
+      load_rows();
+      exps(p_c, RESLIM_I(0), RESLIM_I(2));
+      fence();
+      if constexpr (PR) product2(c0, RESLIM_I(0), RESLIM_I(0));
+      fence();
+      load_rest();
+      exps(p_c, RESLIM_I(2), RESLIM_I(2));
+      fence();
+      if constexpr (PR) product1(c0, RESLIM_I(0), RESLIM_I(1));
+      fence();
+      exps(p_c, RESLIM_I(4), RESLIM_I(2));
+      fence();
+      if constexpr (PR) product2(c0, RESLIM_I(0), RESLIM_I(1));
+      fence();
+      exps(p_c, RESLIM_I(6), RESLIM_I(2));
+      if constexpr (PR) wait_columns(c1);
+      fence();
+      if constexpr (PR) product1(c1, RESLIM_I(1), RESLIM_I(0));
+      fence();
+      exps(p_c, RESLIM_I(8), RESLIM_I(2));
+      fence();
+      if constexpr (PR) product2(c1, RESLIM_I(1), RESLIM_I(0));
+      fence();
+      exps(p_c, RESLIM_I(10), RESLIM_I(2));
+      fence();
+      if constexpr (PR) product1(c1, RESLIM_I(1), RESLIM_I(1));
+      fence();
+      exps(p_c, RESLIM_I(12), RESLIM_I(2));
+      fence();
+      if constexpr (PR) product2(c1, RESLIM_I(1), RESLIM_I(1));
+      fence();
+      exps(p_c, RESLIM_I(14), RESLIM_I(2));
+      fence();
+    } else {
+      if constexpr (PR) product1(c0, RESLIM_I(0), RESLIM_I(0));
+      fence();
+      load_rows();
+      exps(p_c, RESLIM_I(0), RESLIM_I(4));
+      fence();
+      if constexpr (PR) product1(c0, RESLIM_I(0), RESLIM_I(1));
+      fence();
+      load_rest();
+      exps(p_c, RESLIM_I(4), RESLIM_I(4));
+      fence();
+      if constexpr (PR) product1(c1, RESLIM_I(1), RESLIM_I(0));
+      fence();
+      exps(p_c, RESLIM_I(8), RESLIM_I(4));
+      fence();
+      if constexpr (PR) product1(c1, RESLIM_I(1), RESLIM_I(1));
+      fence();
+      exps(p_c, RESLIM_I(12), RESLIM_I(4));
+      fence();
+    }
+    rows_are_there();
+    fence();
+    score(o_c, RESLIM_I(0));
+    fence();
+    read_row1(RESLIM_I(0));
+    finish(p_c, RESLIM_I(0));
+    fence();
+    dscore(o_c, RESLIM_I(0));
+    fence();
+    read_row2(RESLIM_I(0));
+    finish(p_c, RESLIM_I(1));
+    fence();
+    score(o_c, RESLIM_I(1));
+    fence();
+    read_row1(RESLIM_I(1));
+    finish(p_c, RESLIM_I(2));
+    fence();
+    dscore(o_c, RESLIM_I(1));
+    fence();
+    read_row2(RESLIM_I(1));
+    finish(p_c, RESLIM_I(3));
+    fence();
+    score(o_c, RESLIM_I(2));
+    fence();
+    read_row1(RESLIM_I(2));
+    finish(p_c, RESLIM_I(4));
+    fence();
+    dscore(o_c, RESLIM_I(2));
+    fence();
+    read_row2(RESLIM_I(2));
+    issue_columns(c0, RESLIM_I(0));
+    if constexpr (!KV) {
+      issue_columns(c1, RESLIM_I(1));
+      t_stage = after(t_stage);
+    }
+    finish(p_c, RESLIM_I(5));
+    fence();
+    score(o_c, RESLIM_I(3));
+    fence();
+    read_row1(RESLIM_I(3));
+    finish(p_c, RESLIM_I(6));
+    fence();
+    dscore(o_c, RESLIM_I(3));
+    fence();
+    read_row2(RESLIM_I(3));
+    finish(p_c, RESLIM_I(7));
+    fence();
+    if constexpr (KV) {
+      score(o_c, RESLIM_I(NKS));
+      dscore(o_c, RESLIM_I(NKS));
+      fence();
+    }
+    read_record();
+    fence();
+  };
+  typedef std::integral_constant<int, 0> Even;
+  typedef std::integral_constant<int, 1> Odd;
+  typedef std::true_type Yes;
+  typedef std::false_type No;
+
+  auto read_rows = [&]() __attribute__((always_inline)) {
+    read_row1(RESLIM_I(0)); read_row2(RESLIM_I(0));
+    read_row1(RESLIM_I(1)); read_row2(RESLIM_I(1));
+    read_row1(RESLIM_I(2)); read_row2(RESLIM_I(2));
+    read_row1(RESLIM_I(3)); read_row2(RESLIM_I(3));
+    read_record();
+  };
+  read_rows();
+  rows_are_there();
+  score(Even{}, RESLIM_I(0)); dscore(Even{}, RESLIM_I(0));
+  score(Even{}, RESLIM_I(1)); dscore(Even{}, RESLIM_I(1));
+  score(Even{}, RESLIM_I(2)); dscore(Even{}, RESLIM_I(2));
+  score(Even{}, RESLIM_I(3)); dscore(Even{}, RESLIM_I(3));
+  if constexpr (KV) { score(Even{}, RESLIM_I(NKS)); dscore(Even{}, RESLIM_I(NKS)); }
+  read_rows();
+  phase(Even{}, No{}, 0);
+  int i = 1;
+#pragma unroll 1
+  for (; i + 1 < n; i += 2) {
+    phase(Odd{}, Yes{}, i);
+    phase(Even{}, Yes{}, i + 1);
+  }
+  if (i < n) phase(Odd{}, Yes{}, i);
+  wait_columns(c0);
+  if constexpr (KV) {
+    issue_columns(c1, RESLIM_I(1));
+    wait_columns(c1);
+  } else {
+    wait_columns(c1);
+  }
+  product1(c0, RESLIM_I(0), RESLIM_I(0)); product2(c0, RESLIM_I(0), RESLIM_I(0));
+  product1(c0, RESLIM_I(0), RESLIM_I(1)); product2(c0, RESLIM_I(0), RESLIM_I(1));
+  product1(c1, RESLIM_I(1), RESLIM_I(0)); product2(c1, RESLIM_I(1), RESLIM_I(0));
+  product1(c1, RESLIM_I(1), RESLIM_I(1)); product2(c1, RESLIM_I(1), RESLIM_I(1));
+#undef RESLIM_I
+  __builtin_amdgcn_s_waitcnt(0x0F70);    // no load into LDS outlives its work-group
+
+  // ---- scale, round and store this lane's row of each gradient
+  const int xrow = x0 + l32;
+  if (xrow >= n_t) return;
+  bf16_t *p1 = a.dqkv + row0 * ldq + head * DH + (KV ? a.D : 0) + static_cast<size_t>(xrow) * ldq + hi * 4, *p2 = p1 + a.D;
+  const float sc1 = KV ? a.sck : a.scq;
+#pragma unroll
+  for (int d = 0; d < 2; ++d)
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4) {
+      // registers 4*r4 .. 4*r4+3 hold features 32d + 8*r4 + 4*hi + (0..3) of this lane's token
+      bf16x4 tmp;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) tmp[e] = static_cast<__bf16>(acc1[d][4 * r4 + e] * sc1);
+      *reinterpret_cast<u32x2 *>(p1 + d * 32 + r4 * 8) = __builtin_bit_cast(u32x2, tmp);
+      if constexpr (KV) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) tmp[e] = static_cast<__bf16>(acc2[d][4 * r4 + e]);
+        *reinterpret_cast<u32x2 *>(p2 + d * 32 + r4 * 8) = __builtin_bit_cast(u32x2, tmp);
+      }
+    }
 }
 
 // ------------------------------------------------------------------ fp32 path
@@ -744,8 +1160,7 @@ static hipError_t launch_bwd_one(const AttnBwdArgs &a0, hipStream_t st) {
 }
 
 // Launch shapes (measured on MI355X; the file is built with MFMA operands in ordinary vector
-// registers, see the build script): dh = 64: 64-token blocks, three stages; the dQ kernel fits 168
-// registers = three work-groups per CU, the dK/dV kernel (197) two.  dh = 128: one work-group per
+// registers, see the build script): dh = 64: attn_bwd_woven.  dh = 128: one work-group per
 // CU, 64-token blocks with two 32-token groups in flight; dQ ~350 registers, dK and dV together
 // ~510, no spills (c4: 7.1 ms; 13.1 ms with 32-token blocks, separate dK and dV passes and
 // accumulator-register MFMAs; 17.4 ms with two spilling work-groups).  dh = 256: dQ unsplit on
@@ -757,8 +1172,10 @@ static hipError_t launch_bwd_all(const AttnBwdArgs &a, int dh, hipStream_t st) {
   hipError_t e;
   switch (dh) {
     case 64:
-      e = launch_bwd_one<64, 64, 0, QS, 3, 3>(a, st);
-      return e != hipSuccess ? e : launch_bwd_one<64, 64, 1, QS, 2, 3>(a, st);
+      attn_bwd_woven_bf16_kernel<false, QS><<<dim3(a.total), dim3(256), 0, st>>>(a);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+      attn_bwd_woven_bf16_kernel<true, QS><<<dim3(a.total), dim3(256), 0, st>>>(a);
+      return hipGetLastError();
     case 128:
       if (!g_bwd_big_ok) return hipErrorInvalidValue;
       e = launch_bwd_one<128, 64, 0, QS, 1, 3>(a, st);
