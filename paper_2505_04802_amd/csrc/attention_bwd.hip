@@ -9,7 +9,9 @@
 //
 // bf16 path = three launches, no atomics, deterministic:
 //   1. attn_bwd_prep    delta_i per head (bandwidth-bound), written together with
-//                       -lse_i*sqrt(dh) as 16-byte records (see below);
+//                       -lse_i*sqrt(dh) as 16-byte records (see below); at head dimension 64
+//                       launch 2 does it, which has every query's dO in registers
+//                       (80,704 tokens of 16 heads: 93 us, 19,584 of 4: 6.6 us);
 //   2. attn_bwd<KV=0>   query-stationary:  dQ;
 //   3. attn_bwd<KV=1>   key-stationary:    dK and dV.
 // Launches 2 and 3 are ONE kernel template, attn_bwd_woven at head dimension 64 and attn_bwd above.
@@ -44,7 +46,10 @@ namespace reslim {
 struct AttnBwdArgs {
   const bf16_t *qkv;     // [B, n_h, 3, heads, dh]
   const bf16_t *dout;    // [B, n_h, D]
-  const u32x4 *aux;      // [2][B * heads * n_h] records: 0: -lse*sqrt(dh), 1: -delta; three bf16 summands + padding
+  u32x4 *aux;            // [2][B * heads * n_h] records: 0: -lse*sqrt(dh), 1: -delta; three bf16 summands + padding
+  const bf16_t *out;     // [B, n_h, D]          (head dimension 64: the query-stationary launch makes the records)
+  const float *lse;      // [B, heads, n_h]
+  float lse_f;           // factor of lse in record 0
   bf16_t *dqkv;          // [B, n_h, 3, heads, dh]
   const tile_desc *tiles;
   int T, heads, D, QB, total;
@@ -681,7 +686,29 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_woven_bf16_kernel(AttnBwdArgs
     }
     float si = 0.f, di = 0.f;
     if constexpr (!KV) {
-      const u32x2 r0 = *reinterpret_cast<const u32x2 *>(a.aux + rec0 + xrow), r1 = *reinterpret_cast<const u32x2 *>(a.aux + rec0 + a.aux_stride + xrow);
+      // delta of the lane's query: its upstream gradient is here, so only the output is read.  Chunks of eight features, then pairs of
+      // chunks, in the order of attn_bwd_prep; a lane has the chunks of its half.  The records are for the key-stationary launch.
+      const bf16_t *po = a.out + (row0 + xrow) * a.D + head * DH + hi * 8;
+      float part[NKS];
+#pragma unroll
+      for (int ks = 0; ks < NKS; ++ks) {
+        const u32x4 o = *reinterpret_cast<const u32x4 *>(po + ks * 16), g = __builtin_bit_cast(u32x4, x2f[ks]);
+        float acc = 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          acc = fmaf(__uint_as_float(o[e] << 16), __uint_as_float(g[e] << 16), acc);
+          acc = fmaf(__uint_as_float(o[e] & 0xffff0000u), __uint_as_float(g[e] & 0xffff0000u), acc);
+        }
+        unsigned lo, up;
+        lane_pair_exchange(__builtin_bit_cast(unsigned, acc), lo, up);
+        part[ks] = __builtin_bit_cast(float, lo) + __builtin_bit_cast(float, up);
+      }
+      const float delta = (part[0] + part[1]) + (part[2] + part[3]);
+      const u32x4 r0 = split3_bf16(-a.lse[rec0 + xrow] * a.lse_f), r1 = split3_bf16(-delta);
+      if (x0 + l32 < n_t) {
+        if (hi == 0) a.aux[rec0 + xrow] = r0;
+        else a.aux[a.aux_stride + rec0 + xrow] = r1;
+      }
       si = join3_bf16(r0[0], r0[1]);
       di = join3_bf16(r1[0], r1[1]);
     }
@@ -1200,7 +1227,9 @@ hipError_t launch_tiles_attention_bwd(const reslim_ctx *c, const void *qkv, cons
     AttnBwdArgs a;
     a.qkv = static_cast<const bf16_t *>(qkv);
     a.dout = static_cast<const bf16_t *>(dout);
-    a.aux = static_cast<const u32x4 *>(ws);
+    a.aux = static_cast<u32x4 *>(ws);
+    a.out = static_cast<const bf16_t *>(out);
+    a.lse = lse;
     a.dqkv = static_cast<bf16_t *>(dqkv);
     a.tiles = sg.d_tiles;
     a.T = sg.T;
@@ -1222,12 +1251,11 @@ hipError_t launch_tiles_attention_bwd(const reslim_ctx *c, const void *qkv, cons
     const unsigned pg = static_cast<unsigned>((n_vec + 255) / 256);
     // record 0 holds -lse in the unit of the MFMA output: -lse*sqrt(dh), or -lse*log2(e) for pre-scaled q
     const float lse_f = q_prescaled ? 1.4426950408889634f : sqrtf(static_cast<float>(dh));
-    u32x4 *aux = static_cast<u32x4 *>(ws);
-    const bf16_t *o = static_cast<const bf16_t *>(out);
+    a.lse_f = lse_f;
     switch (dh) {
-      case 64: attn_bwd_prep_bf16_kernel<64><<<dim3(pg), dim3(256), 0, st>>>(o, a.dout, lse, aux, n_vec, sg.n_h, heads, D, lse_f, recs); break;
-      case 128: attn_bwd_prep_bf16_kernel<128><<<dim3(pg), dim3(256), 0, st>>>(o, a.dout, lse, aux, n_vec, sg.n_h, heads, D, lse_f, recs); break;
-      case 256: attn_bwd_prep_bf16_kernel<256><<<dim3(pg), dim3(256), 0, st>>>(o, a.dout, lse, aux, n_vec, sg.n_h, heads, D, lse_f, recs); break;
+      case 64: break;                      // the query-stationary launch does it
+      case 128: attn_bwd_prep_bf16_kernel<128><<<dim3(pg), dim3(256), 0, st>>>(a.out, a.dout, lse, a.aux, n_vec, sg.n_h, heads, D, lse_f, recs); break;
+      case 256: attn_bwd_prep_bf16_kernel<256><<<dim3(pg), dim3(256), 0, st>>>(a.out, a.dout, lse, a.aux, n_vec, sg.n_h, heads, D, lse_f, recs); break;
       default: return hipErrorInvalidValue;
     }
     hipError_t e = hipGetLastError();
