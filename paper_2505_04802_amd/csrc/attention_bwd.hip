@@ -7,17 +7,15 @@
 // P is never stored by the forward: it is recomputed here from Q, K and the
 // log-sum-exp of every query that the forward returns.
 //
-// bf16 path = three launches, no atomics, deterministic:
-//   1. attn_bwd_prep    delta_i per head (bandwidth-bound), written together with
-//                       -lse_i*sqrt(dh) as 16-byte records (see below); at head dimension 64
-//                       launch 2 does it, which has every query's dO in registers
-//                       (80,704 tokens of 16 heads: 93 us, 19,584 of 4: 6.6 us);
-//   2. attn_bwd<KV=0>   query-stationary:  dQ;
-//   3. attn_bwd<KV=1>   key-stationary:    dK and dV.
-// Launches 2 and 3 are ONE kernel template, attn_bwd_woven at head dimension 64 and attn_bwd above.
+// bf16 path = two launches (three at head dimension 256), no atomics, deterministic:
+//   1. KV=0   query-stationary:  dQ.  It has every query's dO in registers and makes delta_i, written together with -lse_i*sqrt(dh) as
+//             16-byte records (see below).  At head dimension 256 a launch before it does, attn_bwd_prep: two passes over memory
+//             (80,704 tokens of 16 heads of 64 features, when it was a launch there: 93 us, 19,584 of 4: 6.6 us);
+//   2. KV=1   key-stationary:    dK and dV.
+// Both are ONE kernel template: attn_bwd_woven at head dimension 64, attn_bwd_wide at 128, attn_bwd at 256.
 // As in the forward kernel a work unit is 128 "stationary" tokens of one (sample, tile, head), 32
 // per wave, kept in registers as MFMA B operands; the other side of the tile is streamed through
-// LDS in blocks of 32 or BS tokens (global -> LDS directly).  Every product is computed
+// LDS in blocks of 32 tokens (global -> LDS directly).  Every product is computed
 // transposed so that a lane owns one stationary token and the streamed index runs
 // over the accumulator registers:
 //     Sx  = Y1 X1^T      (stream x stationary)   Y1 = K | Q,   X1 = Q | K
@@ -37,6 +35,7 @@
 // with the value split into three bf16 summands (exact to 2^-24), multiplied by an
 // all-ones B operand (lane half 0 feeds Sx, lane half 1 feeds dPx).
 #include <type_traits>
+#include <utility>
 
 #include "attention_common.h"
 #include "gelu.h"
@@ -47,7 +46,7 @@ struct AttnBwdArgs {
   const bf16_t *qkv;     // [B, n_h, 3, heads, dh]
   const bf16_t *dout;    // [B, n_h, D]
   u32x4 *aux;            // [2][B * heads * n_h] records: 0: -lse*sqrt(dh), 1: -delta; three bf16 summands + padding
-  const bf16_t *out;     // [B, n_h, D]          (head dimension 64: the query-stationary launch makes the records)
+  const bf16_t *out;     // [B, n_h, D]          (head dimensions 64 and 128: the query-stationary launch makes the records)
   const float *lse;      // [B, heads, n_h]
   float lse_f;           // factor of lse in record 0
   bf16_t *dqkv;          // [B, n_h, 3, heads, dh]
@@ -104,27 +103,15 @@ __global__ __launch_bounds__(256) void attn_bwd_prep_bf16_kernel(const bf16_t *o
   }
 }
 
-template <int OFF>
-__device__ __forceinline__ uint64_t tr_issue(unsigned addr) {
-  uint64_t r;
-  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(r) : "v"(addr), "n"(OFF));
-  return r;
-}
-
-// MODE: 0 = query-stationary, dQ;  1 = key-stationary, dK and dV;  2 = key-stationary, dV only;
-// 3 = key-stationary, dK only (2 + 3 can replace 1 where the accumulators of both do not fit the
-// register file next to the stationary fragments; no launch shape in use needs them).
+// KV: keys stationary, dK and dV; else queries, dQ.
 // QS: q in qkv already carries the factor log2(e)/sqrt(dh) (as the fused QKV epilogue of the
 // block leaves it): the MFMA output is the base-2 logit itself.
 // NSPLIT: a launch accumulates only DH / NSPLIT of the head's output features (a.part says which)
 // and recomputes the scores for each part; for heads whose full accumulators do not fit the
 // register file next to the stationary fragments (dh = 256).
-template <int DH, int BS, int MODE, bool QS, int MINW, int NST, int NSPLIT = 1>
-__global__ __launch_bounds__(256, MINW) void attn_bwd_bf16_kernel(AttnBwdArgs a) {
-  constexpr bool KV = MODE != 0;          // keys stationary
-  constexpr bool DP = MODE != 2;          // dP = dO V^T is needed
-  constexpr bool A1 = MODE != 2;          // accumulator 1: Y1^T dS  (dQ^T | dK^T)
-  constexpr bool A2 = MODE == 1 || MODE == 2;   // accumulator 2: Y2^T P  (dV^T)
+template <int DH, bool KV, bool QS, int NST, int NSPLIT>
+__global__ __launch_bounds__(256, 1) void attn_bwd_bf16_kernel(AttnBwdArgs a) {
+  constexpr int BS = 32;                  // streamed tokens of a block
   constexpr int NW = 4;
   constexpr int BX = 32 * NW;             // stationary tokens per unit: 32 per wave
   constexpr int ROWB = DH * 2;
@@ -135,11 +122,9 @@ __global__ __launch_bounds__(256, MINW) void attn_bwd_bf16_kernel(AttnBwdArgs a)
   constexpr int AUXL = AUXB / 1024;       // wave-loads of the record block
   constexpr int STAGE = 2 * TILE_B + AUXB;
   constexpr int LPW = TILE_B / 1024 / NW;
-  constexpr int NKT = BS / 32, NKS = DH / 16, NDT = DH / 32 / NSPLIT;   // NDT: 32-feature blocks of the accumulators
-  constexpr bool PP = NKT == 2;           // 64-token blocks: two groups in flight per wave
-  constexpr bool HAND = DH == 128;        // transposing reads issued by hand (see attention_common.h); needs a spill-free kernel
+  constexpr int NKS = DH / 16, NDT = DH / 32 / NSPLIT;   // NDT: 32-feature blocks of the accumulators
   static_assert(TILE_B % (1024 * NW) == 0 && AUXB % 1024 == 0 && NST * STAGE <= 160 * 1024, "LDS plan");
-  static_assert(DH >= 128 && (NST == 2 || NST == 3) && NKT <= 2, "ring of two or three stages of 32 or 64 tokens");
+  static_assert(NST == 3, "ring of three stages");
   extern __shared__ __align__(1024) unsigned char smem[];   // NST * STAGE bytes
 
   const int t = threadIdx.x, lane = t & 63;
@@ -241,7 +226,7 @@ __global__ __launch_bounds__(256, MINW) void attn_bwd_bf16_kernel(AttnBwdArgs a)
       }
     }
   };
-  bf16x8 x1f[NKS], x2f[DP ? NKS : 1];
+  bf16x8 x1f[NKS], x2f[NKS];
   f32x16 sinit, dpinit;
   auto load_x = [&](const Unit &u) {
     const int xrow = min(u.r0 + wave * 32 + l32, u.n_t - 1);
@@ -250,7 +235,7 @@ __global__ __launch_bounds__(256, MINW) void attn_bwd_bf16_kernel(AttnBwdArgs a)
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks) {
       x1f[ks] = *reinterpret_cast<const bf16x8 *>(p1 + ks * 16);
-      if constexpr (DP) x2f[ks] = *reinterpret_cast<const bf16x8 *>(p2 + ks * 16);
+      x2f[ks] = *reinterpret_cast<const bf16x8 *>(p2 + ks * 16);
     }
     float si = 0.f, di = 0.f;
     if constexpr (!KV) {
@@ -290,14 +275,14 @@ __global__ __launch_bounds__(256, MINW) void attn_bwd_bf16_kernel(AttnBwdArgs a)
     ones_d[e] = static_cast<__bf16>(e < 3 && hi == 1 ? 1.0f : 0.0f);
   }
 
-  f32x16 acc1[A1 ? NDT : 1], acc2[A2 ? NDT : 1];
+  f32x16 acc1[NDT], acc2[KV ? NDT : 1];
   auto reset = [&]() {
 #pragma unroll
-    for (int d = 0; d < (A1 ? NDT : 1); ++d)
+    for (int d = 0; d < NDT; ++d)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc1[d][r] = 0.f;
 #pragma unroll
-    for (int d = 0; d < (A2 ? NDT : 1); ++d)
+    for (int d = 0; d < (KV ? NDT : 1); ++d)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc2[d][r] = 0.f;
   };
@@ -313,56 +298,6 @@ __global__ __launch_bounds__(256, MINW) void attn_bwd_bf16_kernel(AttnBwdArgs a)
     }
     return true;
   };
-  // The same in two steps, for the kernels that keep two groups in flight: plan_next() picks the
-  // block and moves the cursor, issue_part(i) sends this wave's i-th pair of direct loads (the
-  // record load rides with pair 0).  A wave's burst of loads stalls it while the CU's load queue
-  // is full; spread between the MFMAs of the first score product they cost nothing.  Blocks that
-  // cross the tile end, and waves without stationary tokens, keep the burst.
-  struct Pending {
-    const unsigned char *g1, *g2;
-    const u32x4 *aux;
-    unsigned char *sb;
-    int lim;
-  } pend;
-  auto plan_next = [&](int buf) -> bool {
-    if (ivb >= a.total) return false;
-    const int s0 = iblk * BS;
-    pend.sb = smem + buf * STAGE;
-    pend.g1 = reinterpret_cast<const unsigned char *>(y1_of(iu) + static_cast<size_t>(s0) * ldq);
-    pend.g2 = reinterpret_cast<const unsigned char *>(y2_of(iu) + static_cast<size_t>(s0) * ldy2);
-    pend.aux = a.aux + iu.aux_off + s0;
-    pend.lim = iu.n_t - 1 - s0;
-    if (++iblk == iu.nsb) {
-      ivb = decode(ivb + G, iu);
-      iblk = 0;
-    }
-    return true;
-  };
-  auto issue_part = [&](int i) {          // only for blocks wholly inside the tile
-    attn_dl_load16(reinterpret_cast<const bf16_t *>(pend.g1 + static_cast<uint32_t>(off1[i])), pend.sb + (wave + NW * i) * 1024);
-    attn_dl_load16(reinterpret_cast<const bf16_t *>(pend.g2 + static_cast<uint32_t>(off2[i])),
-                   pend.sb + TILE_B + (wave + NW * i) * 1024);
-    if constexpr (KV) {
-      if (i == 0 && wave < AUXL)
-        attn_dl_load16(reinterpret_cast<const bf16_t *>(pend.aux + aux_arr * a.aux_stride + aux_row),
-                       pend.sb + 2 * TILE_B + wave * 1024);
-    }
-  };
-  auto issue_planned_burst = [&]() {      // any block: rows past the tile end re-read its last row
-#pragma unroll
-    for (int i = 0; i < LPW; ++i) {
-      const int back = max(ld_row[i] - pend.lim, 0);
-      attn_dl_load16(reinterpret_cast<const bf16_t *>(pend.g1 + static_cast<uint32_t>(off1[i] - back * ldq * 2)),
-                     pend.sb + (wave + NW * i) * 1024);
-      attn_dl_load16(reinterpret_cast<const bf16_t *>(pend.g2 + static_cast<uint32_t>(off2[i] - back * ldy2 * 2)),
-                     pend.sb + TILE_B + (wave + NW * i) * 1024);
-    }
-    if constexpr (KV) {
-      if (wave < AUXL)
-        attn_dl_load16(reinterpret_cast<const bf16_t *>(pend.aux + aux_arr * a.aux_stride + min(aux_row, pend.lim)),
-                       pend.sb + 2 * TILE_B + wave * 1024);
-    }
-  };
   constexpr int NLD = 2 * LPW;            // direct loads of one block per wave (+1 in the waves that fetch records)
   int ahead = 0;                          // blocks in flight beyond the one about to be computed
   issue_next(0);
@@ -373,7 +308,7 @@ __global__ __launch_bounds__(256, MINW) void attn_bwd_bf16_kernel(AttnBwdArgs a)
   for (;;) {
     // block `sb` of `cur` must have landed; younger blocks may stay in flight.  Loads complete in
     // issue order, so "at most `ahead` blocks' worth outstanding" is enough.
-    if (NST == 2 || ahead == 0) {
+    if (ahead == 0) {
       __builtin_amdgcn_s_waitcnt(0x0F70);
     } else if (KV && wave < AUXL) {
       __builtin_amdgcn_s_waitcnt(0x0F70 | ((NLD + 1) & 15) | (((NLD + 1) >> 4) << 14));
@@ -386,41 +321,26 @@ __global__ __launch_bounds__(256, MINW) void attn_bwd_bf16_kernel(AttnBwdArgs a)
     __builtin_amdgcn_s_barrier();           // everybody's part of the block is in LDS; the oldest stage is free
     const bool last = sb + 1 == cur.nsb;
     const bool active = cur.r0 + wave * 32 < cur.n_t;
-    bool spread = false;                    // this wave sends the next block's loads between its MFMAs
     {
       int ibuf = buf + NST - 1;
       if (ibuf >= NST) ibuf -= NST;
-      bool issued;
-      if constexpr (PP) {
-        issued = plan_next(ibuf);
-        spread = issued && active && pend.lim >= BS - 1;
-        if (issued && !spread) issue_planned_burst();
-      } else {
-        issued = issue_next(ibuf);
-      }
-      if (issued) { if (NST == 2) ahead = 0; }   // one computed, one issued: `ahead` unchanged
-      else if (ahead > 0) --ahead;
+      if (!issue_next(ibuf) && ahead > 0) --ahead;      // one computed, one issued: `ahead` unchanged
     }
     const unsigned char *st = smem + buf * STAGE;
     const int s0 = sb * BS;
 
-    // The work on one 32-token group of the streamed block, in three phases.
-    const unsigned st_off = static_cast<unsigned>(reinterpret_cast<uintptr_t>(
-        (__attribute__((address_space(3))) const unsigned char *)st));
-    // `between(i)`, i < 16: vector work of ANOTHER group placed behind the MFMAs of this one, so
-    // that one wave keeps both pipes busy (wide heads run a single wave per SIMD)
-    auto scores = [&](auto kt_c, f32x16 &s, f32x16 &dp, auto between) {          // matrix pipe
-      constexpr int kt = decltype(kt_c)::value;
+    // The work on a block, in three phases.
+    auto scores = [&](f32x16 &s, f32x16 &dp) {                      // matrix pipe
       // the fragment reads run PF steps ahead of the MFMAs that use them, in a ring
       // of PF + 1 register sets, and a scheduling barrier per step keeps that order (left to
       // itself the compiler either waits for every read right before its MFMA or hoists all
       // reads of the group to its top: 64+ registers of fragments next to the accumulators)
       constexpr int PF = 2;
-      bf16x8 f1[PF + 1], f2[DP ? PF + 1 : 1];
+      bf16x8 f1[PF + 1], f2[PF + 1];
       auto fetch = [&](int ks) {
-        const unsigned char *rp = st + kt * 32 * ROWB + y_row + (((2 * ks + hi) ^ y_swz) << 4);
+        const unsigned char *rp = st + y_row + (((2 * ks + hi) ^ y_swz) << 4);
         f1[ks % (PF + 1)] = *reinterpret_cast<const bf16x8 *>(rp);
-        if constexpr (DP) f2[ks % (PF + 1)] = *reinterpret_cast<const bf16x8 *>(rp + TILE_B);
+        f2[ks % (PF + 1)] = *reinterpret_cast<const bf16x8 *>(rp + TILE_B);
       };
 #pragma unroll
       for (int ks = 0; ks < PF; ++ks) fetch(ks);
@@ -428,136 +348,67 @@ __global__ __launch_bounds__(256, MINW) void attn_bwd_bf16_kernel(AttnBwdArgs a)
       for (int ks = 0; ks < NKS; ++ks) {
         if (ks + PF < NKS) fetch(ks + PF);
         s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f1[ks % (PF + 1)], x1f[ks], ks == 0 ? sinit : s, 0, 0, 0);
-        if constexpr (DP) dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f2[ks % (PF + 1)], x2f[ks], ks == 0 ? dpinit : dp, 0, 0, 0);
-#pragma unroll
-        for (int i = ks * 16 / NKS; i < (ks + 1) * 16 / NKS; ++i) between(i);
+        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f2[ks % (PF + 1)], x2f[ks], ks == 0 ? dpinit : dp, 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
       }
       if constexpr (KV) {
-        const bf16x8 fa = *reinterpret_cast<const bf16x8 *>(st + aux_addr + kt * 32 * 16);
+        const bf16x8 fa = *reinterpret_cast<const bf16x8 *>(st + aux_addr);
         s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, ones_s, s, 0, 0, 0);
-        if constexpr (DP) dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, ones_d, dp, 0, 0, 0);
+        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, ones_d, dp, 0, 0, 0);
       }
     };
-    auto mask = [&](int kt, f32x16 &s) {      // ragged end: streamed tokens past the tile end get probability 0
-      if (s0 + kt * 32 + 32 > cur.n_t) {
+    auto mask = [&](f32x16 &s) {              // ragged end: streamed tokens past the tile end get probability 0
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int row = s0 + kt * 32 + 16 * (r / 8) + 8 * hi + (r % 8);
-          if (row >= cur.n_t) s[r] = -INFINITY;
-        }
+      for (int r = 0; r < 16; ++r) {
+        const int row = s0 + 16 * (r / 8) + 8 * hi + (r % 8);
+        if (row >= cur.n_t) s[r] = -INFINITY;
       }
     };
-    auto prob1 = [&](f32x16 &s, f32x16 &dp, int r) {                // vector pipe: s <- P, dp <- dS
-      s[r] = __builtin_amdgcn_exp2f(QS ? s[r] : s[r] * a.c);
-      if constexpr (DP) dp[r] *= s[r];
-    };
-    auto probs = [&](f32x16 &s, f32x16 &dp) {
+    auto probs = [&](f32x16 &s, f32x16 &dp) {                       // vector pipe: s <- P, dp <- dS
 #pragma unroll
-      for (int r = 0; r < 16; ++r) prob1(s, dp, r);
+      for (int r = 0; r < 16; ++r) {
+        s[r] = __builtin_amdgcn_exp2f(QS ? s[r] : s[r] * a.c);
+        dp[r] *= s[r];
+      }
     };
-    auto nothing = [](int) {};
-    auto products = [&](auto kt_c, const f32x16 &s, const f32x16 &dp, auto between) {   // matrix pipe
-      constexpr int kt = decltype(kt_c)::value;
+    auto products = [&](const f32x16 &s, const f32x16 &dp) {        // matrix pipe
       auto step = [&](auto h2_c) {
         constexpr int h2 = decltype(h2_c)::value;
-        constexpr int ROFF = (kt * 32 + h2 * 16) * ROWB;
+        constexpr int ROFF = h2 * 16 * ROWB;
         bf16x8 pf, dsf;
-        typedef __attribute__((ext_vector_type(2))) uint64_t u64x2;
-        if constexpr (HAND) {
-          uint64_t r1[NDT][2], r2[NDT][2];
 #pragma unroll
-          for (int d = 0; d < NDT; ++d)
+        for (int e = 0; e < 8; ++e) {
+          dsf[e] = static_cast<__bf16>(dp[8 * h2 + e]);
+          if constexpr (KV) pf[e] = static_cast<__bf16>(s[8 * h2 + e]);
+        }
+        typedef __attribute__((ext_vector_type(8))) short s16x8;
+        auto tr_frag = [&](int off) {
+          const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3))) *)(st + off));
+          return lo;
+        };
 #pragma unroll
-            for (int e = 0; e < 2; ++e) {
-              if constexpr (A1) r1[d][e] = tr_issue<ROFF>(st_off + static_cast<unsigned>(t_addr[e][d]));
-              if constexpr (A2) r2[d][e] = tr_issue<ROFF + TILE_B>(st_off + static_cast<unsigned>(t_addr[e][d]));
-            }
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            if constexpr (A1) dsf[e] = static_cast<__bf16>(dp[8 * h2 + e]);
-            if constexpr (A2) pf[e] = static_cast<__bf16>(s[8 * h2 + e]);
+        for (int d = 0; d < NDT; ++d) {
+          {
+            const s16x8 both = __builtin_shufflevector(tr_frag(ROFF + t_addr[0][d]), tr_frag(ROFF + t_addr[1][d]), 0, 1, 2, 3, 4, 5, 6, 7);
+            acc1[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), dsf, acc1[d], 0, 0, 0);
           }
-          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-          for (int d = 0; d < NDT; ++d)
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-              if constexpr (A1) asm volatile("" : "+v"(r1[d][e]));
-              if constexpr (A2) asm volatile("" : "+v"(r2[d][e]));
-            }
-#pragma unroll
-          for (int d = 0; d < NDT; ++d) {
-            if constexpr (A1) {
-              const u64x2 b1 = {r1[d][0], r1[d][1]};
-              acc1[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, b1), dsf, acc1[d], 0, 0, 0);
-            }
-            if constexpr (A2) {
-              const u64x2 b2 = {r2[d][0], r2[d][1]};
-              acc2[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, b2), pf, acc2[d], 0, 0, 0);
-            }
-#pragma unroll
-            for (int i = (h2 * NDT + d) * 8 / NDT; i < (h2 * NDT + d + 1) * 8 / NDT; ++i) between(i);
-          }
-        } else {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            if constexpr (A1) dsf[e] = static_cast<__bf16>(dp[8 * h2 + e]);
-            if constexpr (A2) pf[e] = static_cast<__bf16>(s[8 * h2 + e]);
-          }
-          typedef __attribute__((ext_vector_type(8))) short s16x8;
-          auto tr_frag = [&](int off) {
-            const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3))) *)(st + off));
-            return lo;
-          };
-#pragma unroll
-          for (int d = 0; d < NDT; ++d) {
-            if constexpr (A1) {
-              const s16x8 both = __builtin_shufflevector(tr_frag(ROFF + t_addr[0][d]), tr_frag(ROFF + t_addr[1][d]), 0, 1, 2, 3, 4, 5, 6, 7);
-              acc1[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), dsf, acc1[d], 0, 0, 0);
-            }
-            if constexpr (A2) {
-              const s16x8 both = __builtin_shufflevector(tr_frag(ROFF + TILE_B + t_addr[0][d]), tr_frag(ROFF + TILE_B + t_addr[1][d]), 0, 1, 2, 3, 4, 5, 6, 7);
-              acc2[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), pf, acc2[d], 0, 0, 0);
-            }
-#pragma unroll
-            for (int i = (h2 * NDT + d) * 8 / NDT; i < (h2 * NDT + d + 1) * 8 / NDT; ++i) between(i);
+          if constexpr (KV) {
+            const s16x8 both = __builtin_shufflevector(tr_frag(ROFF + TILE_B + t_addr[0][d]), tr_frag(ROFF + TILE_B + t_addr[1][d]), 0, 1, 2, 3, 4, 5, 6, 7);
+            acc2[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), pf, acc2[d], 0, 0, 0);
           }
         }
       };
       step(std::integral_constant<int, 0>{});
       step(std::integral_constant<int, 1>{});
     };
-    // One straight path for every block, one 32-token group after the other; a second group
-    // that lies wholly past the tile end (last block only) is computed and masked to zero rather
-    // than skipped.  The next unit's stationary fragments are fetched at ONE place, after the
-    // last scores that use the current ones.
-    const bool ragged = s0 + BS > cur.n_t;
+    // The next unit's stationary fragments are fetched at ONE place, after the last scores that use the current ones.
     f32x16 sA, dA;
-    if constexpr (PP) {
-      // two groups in flight: the exponentials of one sit between the MFMAs of the other
-      f32x16 sB, dB;
-      if (active) {
-        scores(std::integral_constant<int, 0>{}, sA, dA, [&](int i) {
-          if (spread && i % (16 / LPW) == 0) issue_part(i / (16 / LPW));
-        });
-        if (ragged) mask(0, sA);
-        scores(std::integral_constant<int, 1>{}, sB, dB, [&](int i) { prob1(sA, dA, i); });
-      }
-      if (last && has_next) load_x(nxt);
-      if (active) {
-        if (ragged) mask(1, sB);
-        products(std::integral_constant<int, 0>{}, sA, dA, [&](int i) { prob1(sB, dB, i); });
-        products(std::integral_constant<int, 1>{}, sB, dB, nothing);
-      }
-    } else {
-      if (active) scores(std::integral_constant<int, 0>{}, sA, dA, nothing);
-      if (last && has_next) load_x(nxt);
-      if (active) {
-        if (ragged) mask(0, sA);
-        probs(sA, dA);
-        products(std::integral_constant<int, 0>{}, sA, dA, nothing);
-      }
+    if (active) scores(sA, dA);
+    if (last && has_next) load_x(nxt);
+    if (active) {
+      if (s0 + BS > cur.n_t) mask(sA);
+      probs(sA, dA);
+      products(sA, dA);
     }
     if (++buf == NST) buf = 0;
     if (!last) { ++sb; continue; }
@@ -574,12 +425,10 @@ __global__ __launch_bounds__(256, MINW) void attn_bwd_bf16_kernel(AttnBwdArgs a)
         for (int r4 = 0; r4 < 4; ++r4) {
           // registers 4*r4 .. 4*r4+3 hold features 32d + 8*r4 + 4*hi + (0..3) of this lane's token
           bf16x4 tmp;
-          if constexpr (A1) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) tmp[e] = static_cast<__bf16>(acc1[d][4 * r4 + e] * sc1);
-            *reinterpret_cast<u32x2 *>(p1 + d * 32 + r4 * 8) = __builtin_bit_cast(u32x2, tmp);
-          }
-          if constexpr (A2) {
+          for (int e = 0; e < 4; ++e) tmp[e] = static_cast<__bf16>(acc1[d][4 * r4 + e] * sc1);
+          *reinterpret_cast<u32x2 *>(p1 + d * 32 + r4 * 8) = __builtin_bit_cast(u32x2, tmp);
+          if constexpr (KV) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) tmp[e] = static_cast<__bf16>(acc2[d][4 * r4 + e]);
             *reinterpret_cast<u32x2 *>(p2 + d * 32 + r4 * 8) = __builtin_bit_cast(u32x2, tmp);
@@ -1060,6 +909,494 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_woven_bf16_kernel(AttnBwdArgs
     }
 }
 
+// ------------------------------------------------------------------ head dimension 128: the same weave, one wave a SIMD
+// The phases of attn_bwd_woven, with twice the products for the same exponentials: 24 matrix instructions a phase query-stationary, 34
+// key-stationary.  The accumulators, the stationary rows and a phase's fragments take 383 and 408 registers, so one wave a SIMD and nothing else to fill its
+// gaps: the second half of a block's rows is read during the products, and columns and rows lie in accumulator registers, which the matrix
+// instructions read as well and vector code does not need.  One work-group to a compute unit walks its units; the loads run six blocks ahead across
+// units, and the next unit's stationary rows arrive during a unit's last products.  Every sum has the order of the kernel for head dimension 256: the same bits.
+// 19,840 tokens of 24 heads in tiles of 1128 to 1323: 1564 us with two groups one after the other and three stages of 64 tokens, 1281 us here (dQ 0.56, dK
+// and dV 0.70 ms); 37,536 of 32 in tiles to 2448: 6.69 and 5.39 ms; 2000 tokens, 8 sets of keys 150 and 115 us; 30 tokens, 1024 sets 53 and 48.
+// What bounds it: the matrix pipe is busy 34 and 39 % of the cycles, at 2.0 GHz; waits (LDS, barrier) are 22 and 19 %, issue of everything else 47 %, and a
+// sixth of the time compute units have run out of units.  Exponentials and loads spread evenly over both halves of the phase measured the same.
+template <int N, typename F, int... I>
+__device__ __forceinline__ void each_of(const F &f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+__device__ __forceinline__ int64_t scalar64(int64_t v) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v)), up = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v >> 32));
+  return static_cast<int64_t>(static_cast<uint64_t>(up) << 32 | lo);
+}
+__device__ __forceinline__ void pin2(bf16x8 &x, bf16x8 &y) { asm volatile("" : "+a"(x), "+a"(y)); }
+template <int N, typename F>
+__device__ __forceinline__ void each(const F &f) { each_of<N>(f, std::make_integer_sequence<int, N>{}); }
+
+constexpr int kWideStages = 8;
+constexpr int wide_lds_bytes(bool kv) { return kWideStages * (2 * 32 * 256 + (kv ? 2 * 32 * 16 : 0)); }
+
+template <bool KV, bool QS>
+__global__ __launch_bounds__(256, 1) void attn_bwd_wide_bf16_kernel(AttnBwdArgs a) {
+  constexpr int DH = 128, ROWB = DH * 2, TILE = 32 * ROWB, STAGE = wide_lds_bytes(KV) / kWideStages, NST = kWideStages, NKS = DH / 16, ND = DH / 32;
+  constexpr int LOADS = KV ? 5 : 4;                    // direct loads of a wave per block
+  extern __shared__ __align__(1024) unsigned char smem[];   // wide_lds_bytes(KV)
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int l32 = lane & 31, hi = lane >> 5;
+  const int ldq = 3 * a.D, ldx2 = KV ? ldq : a.D, ldy2 = KV ? a.D : ldq;
+  const int G = gridDim.x;
+  struct Unit {
+    int n_t, x0, head;   // tokens of the tile; first stationary token of the work-group
+    int64_t row0, rec0;  // first row of the tile, first record of its head
+  };
+  auto decode = [&](int vb, Unit &u) __attribute__((always_inline)) -> int {         // first non-empty unit at or after vb (stride G), or >= total
+    while (vb < a.total) {
+      const int logical = xcd_remap_attn(vb, a.total);
+      const int xb = logical % a.QB;
+      int rest = logical / a.QB;
+      u.head = rest % a.heads;
+      rest /= a.heads;
+      const int tile = rest % a.T, b = rest / a.T;
+      // the kernel writes to memory, so these come through vector loads: back to scalar registers, or the buffers' addresses are not
+      u.n_t = __builtin_amdgcn_readfirstlane(a.tiles[tile].n_tok);
+      const int64_t off = scalar64(a.tiles[tile].tok_off);
+      u.x0 = xb * 128;
+      u.row0 = static_cast<int64_t>(b) * a.n_h + off;
+      u.rec0 = (static_cast<int64_t>(b) * a.heads + u.head) * a.n_h + off;
+      if (u.x0 < u.n_t) break;
+      vb += G;
+    }
+    return vb;
+  };
+  auto q_of = [&](const Unit &u) __attribute__((always_inline)) { return a.qkv + u.row0 * ldq + u.head * DH; };
+  auto dout_of = [&](const Unit &u) __attribute__((always_inline)) { return a.dout + u.row0 * a.D + u.head * DH; };
+  Unit cur;
+  int vb = decode(blockIdx.x, cur);
+  if (vb >= a.total) return;                           // uniform
+
+  // ---- load side, ahead of the arithmetic across units.  The buffers cover exactly the rows of a block that exist: the rest of it, and
+  // blocks past the last unit, are zeros without an access.  A wave loads eight rows of either operand and a quarter of the records.
+  auto swz = [](int r) { return ((r & 3) << 2) | ((r >> 2) & 3); };
+  int off1[2], off2[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int row = wave * 8 + i * 4 + lane / 16, chunk = ((lane % 16) ^ swz(row)) * 16;
+    off1[i] = row * ldq * 2 + chunk;
+    off2[i] = row * ldy2 * 2 + chunk;
+  }
+  const int off3 = (wave & 1) * 256 + lane * 4;
+  // at least two, so that a unit's first and last phase are two: a second block of a short tile is of zeros, masked like any row past the end
+  auto blocks_of = [](int n_t) { return max((n_t + 31) / 32, 2); };
+  int lvb = vb, rows_left = 0, blocks_left = 0;
+  const bf16_t *y1 = nullptr, *y2 = nullptr;
+  const u32x4 *rec = nullptr;
+  unsigned l_stage = 0;
+  auto after = [](unsigned stage) { return stage == (NST - 1) * STAGE ? 0u : stage + STAGE; };
+  auto buffer = [](const void *p, int bytes) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00020000); };
+  auto to_lds = [&](__amdgpu_buffer_rsrc_t r, unsigned at, int off) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)(smem + at), 16, off, 0, 0, 0);
+  };
+  auto load_from = [&](const Unit &u) __attribute__((always_inline)) {
+    y1 = q_of(u) + (KV ? 0 : a.D);
+    y2 = KV ? dout_of(u) : q_of(u) + 2 * a.D;
+    rec = a.aux + u.rec0 + (wave >> 1) * a.aux_stride;
+    rows_left = u.n_t;
+    blocks_left = blocks_of(u.n_t);
+  };
+  auto load_rows = [&]() __attribute__((always_inline)) {
+    const auto r = buffer(y1, max((min(rows_left, 32) - 1) * ldq * 2 + ROWB, 0));
+    to_lds(r, l_stage + wave * 2048, off1[0]);
+    to_lds(r, l_stage + wave * 2048 + 1024, off1[1]);
+    y1 += static_cast<size_t>(32) * ldq;
+  };
+  auto load_rest = [&]() __attribute__((always_inline)) {
+    const auto r = buffer(y2, max((min(rows_left, 32) - 1) * ldy2 * 2 + ROWB, 0));
+    to_lds(r, l_stage + TILE + wave * 2048, off2[0]);
+    to_lds(r, l_stage + TILE + wave * 2048 + 1024, off2[1]);
+    y2 += static_cast<size_t>(32) * ldy2;
+    if constexpr (KV) {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer(rec, max(min(rows_left, 32) * 16, 0)),
+                                               (__attribute__((address_space(3))) void *)(smem + l_stage + 2 * TILE + wave * 256), 4, off3, 0, 0, 0);
+      rec += 32;
+    }
+    rows_left -= 32;
+    --blocks_left;
+    l_stage = after(l_stage);
+  };
+  auto next_to_load = [&]() __attribute__((always_inline)) {   // before a block's loads: the next unit, where this one has no block left
+    if (blocks_left <= 0 && lvb < a.total) {
+      Unit u;
+      lvb = decode(lvb + G, u);
+      if (lvb < a.total) load_from(u);
+    }
+  };
+  // all but the youngest `blocks` of this wave's loads are done, then everybody's
+  auto landed = [&](auto blocks) __attribute__((always_inline)) {
+    constexpr int N = LOADS * decltype(blocks)::value;
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | (N >> 4 << 14));
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  typedef std::integral_constant<int, NST - 4> First;
+  typedef std::integral_constant<int, NST - 5> Next;
+
+  // ---- stationary side: fetch() starts the loads of a unit's, settle() needs them done
+  bf16x8 x1f[NKS], x2f[NKS];
+  u32x4 o_row[KV ? 1 : NKS];
+  float lse_x = 0.f;
+  f32x16 sinit, dpinit;
+  auto fetch = [&](const Unit &u) __attribute__((always_inline)) {
+    const int xrow = min(u.x0 + wave * 32 + l32, u.n_t - 1);
+    const bf16_t *p1 = q_of(u) + (KV ? a.D : 0) + static_cast<size_t>(xrow) * ldq + hi * 8;
+    const bf16_t *p2 = (KV ? q_of(u) + 2 * a.D : dout_of(u)) + static_cast<size_t>(xrow) * ldx2 + hi * 8;
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) {
+      x1f[ks] = *reinterpret_cast<const bf16x8 *>(p1 + ks * 16);
+      x2f[ks] = *reinterpret_cast<const bf16x8 *>(p2 + ks * 16);
+    }
+    if constexpr (!KV) {
+      const bf16_t *po = a.out + (u.row0 + xrow) * a.D + u.head * DH + hi * 8;
+#pragma unroll
+      for (int ks = 0; ks < NKS; ++ks) o_row[ks] = *reinterpret_cast<const u32x4 *>(po + ks * 16);
+      lse_x = a.lse[u.rec0 + xrow];
+    }
+  };
+  auto settle = [&](const Unit &u) __attribute__((always_inline)) {
+    float si = 0.f, di = 0.f;
+    if constexpr (!KV) {
+      // delta of the lane's query: chunks of eight features, then pairs of chunks, in the order of attn_bwd_prep; a lane has the chunks
+      // of its half.  The records are for the key-stationary launch.
+      float part[NKS];
+#pragma unroll
+      for (int ks = 0; ks < NKS; ++ks) {
+        const u32x4 o = o_row[ks], g = __builtin_bit_cast(u32x4, x2f[ks]);
+        float acc = 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          acc = fmaf(__uint_as_float(o[e] << 16), __uint_as_float(g[e] << 16), acc);
+          acc = fmaf(__uint_as_float(o[e] & 0xffff0000u), __uint_as_float(g[e] & 0xffff0000u), acc);
+        }
+        unsigned lo, up;
+        lane_pair_exchange(__builtin_bit_cast(unsigned, acc), lo, up);
+        part[ks] = __builtin_bit_cast(float, lo) + __builtin_bit_cast(float, up);
+      }
+      const float delta = ((part[0] + part[1]) + (part[2] + part[3])) + ((part[4] + part[5]) + (part[6] + part[7]));
+      const u32x4 r0 = split3_bf16(-lse_x * a.lse_f), r1 = split3_bf16(-delta);
+      const int xrow = u.x0 + wave * 32 + l32;
+      if (xrow < u.n_t) {
+        if (hi == 0) a.aux[u.rec0 + xrow] = r0;
+        else a.aux[a.aux_stride + u.rec0 + xrow] = r1;
+      }
+      si = join3_bf16(r0[0], r0[1]);
+      di = join3_bf16(r1[0], r1[1]);
+    }
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) pin2(x1f[ks], x2f[ks]);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) { sinit[r] = si; dpinit[r] = di; }
+  };
+
+  // ---- read side: rows (a lane's token key_perm(l32), 16-byte chunks) and, through the transposing read, columns
+  const unsigned lds0 = static_cast<unsigned>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const unsigned char *)smem));
+  auto lds = [](unsigned at) __attribute__((always_inline)) { return *reinterpret_cast<__attribute__((address_space(3))) bf16x8 *>(at); };
+  const int yr = key_perm(l32);
+  const unsigned r_base = lds0 + yr * ROWB + ((hi ^ swz(yr)) << 4), rec_base = lds0 + 2 * TILE + hi * 512 + yr * 16;
+  const int vr = 8 * hi + ((lane & 15) >> 2), vo = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+  const unsigned t_base = lds0 + vr * ROWB + (((vo >> 3) ^ swz(vr)) << 4) + ((vo >> 2) & 1) * 8;
+  bf16x8 f1[NKS], f2[NKS], fr;
+  unsigned r_stage = 0, t_stage = 0;
+  auto read_row1 = [&](auto ks_c) __attribute__((always_inline)) { f1[decltype(ks_c)::value] = lds((r_base + r_stage) ^ (decltype(ks_c)::value * 32)); };
+  auto read_row2 = [&](auto ks_c) __attribute__((always_inline)) { f2[decltype(ks_c)::value] = lds(((r_base + r_stage) ^ (decltype(ks_c)::value * 32)) + TILE); };
+  auto read_record = [&]() __attribute__((always_inline)) {
+    if constexpr (KV) {
+      fr = lds(rec_base + r_stage);
+    }
+  };
+  auto half_is_there = [&](auto h_c) __attribute__((always_inline)) {
+    constexpr int h = decltype(h_c)::value;
+#pragma unroll
+    for (int ks = h * NKS / 2; ks < (h + 1) * NKS / 2; ++ks) pin2(f1[ks], f2[ks]);
+  };
+  // columns of 16 streamed tokens of one operand: [block of 32 features][rows + 0..3 and + 4..7].  Issued in one statement and waited for in another
+  // (see attention_common.h)
+  typedef uint64_t Columns[ND][2];
+  Columns c1[2], c2[KV ? 2 : 1];
+  auto issue_columns = [&](Columns &c, auto off_c) __attribute__((always_inline)) {
+    const unsigned at0 = t_base + t_stage, at1 = (at0 + 1024) ^ 16;
+    asm volatile(
+        "ds_read_b64_tr_b16 %0, %8 offset:%16\n\t"
+        "ds_read_b64_tr_b16 %1, %9 offset:%16\n\t"
+        "ds_read_b64_tr_b16 %2, %10 offset:%16\n\t"
+        "ds_read_b64_tr_b16 %3, %11 offset:%16\n\t"
+        "ds_read_b64_tr_b16 %4, %12 offset:%16\n\t"
+        "ds_read_b64_tr_b16 %5, %13 offset:%16\n\t"
+        "ds_read_b64_tr_b16 %6, %14 offset:%16\n\t"
+        "ds_read_b64_tr_b16 %7, %15 offset:%16"
+        : "=&a"(c[0][0]), "=&a"(c[0][1]), "=&a"(c[1][0]), "=&a"(c[1][1]), "=&a"(c[2][0]), "=&a"(c[2][1]), "=&a"(c[3][0]), "=&a"(c[3][1])
+        : "v"(at0), "v"(at1), "v"(at0 ^ 64u), "v"(at1 ^ 64u), "v"(at0 ^ 128u), "v"(at1 ^ 128u), "v"(at0 ^ 192u), "v"(at1 ^ 192u),
+          "n"(decltype(off_c)::value));
+  };
+  auto wait_columns = [&](Columns &c) __attribute__((always_inline)) {
+    asm volatile("s_waitcnt lgkmcnt(0)"
+                 : "+a"(c[0][0]), "+a"(c[0][1]), "+a"(c[1][0]), "+a"(c[1][1]), "+a"(c[2][0]), "+a"(c[2][1]), "+a"(c[3][0]), "+a"(c[3][1]));
+  };
+  auto issue1 = [&](auto h_c) __attribute__((always_inline)) { issue_columns(c1[decltype(h_c)::value], std::integral_constant<int, decltype(h_c)::value * 16 * ROWB>{}); };
+  auto issue2 = [&](auto h_c) __attribute__((always_inline)) {
+    if constexpr (KV) issue_columns(c2[decltype(h_c)::value], std::integral_constant<int, decltype(h_c)::value * 16 * ROWB + TILE>{});
+  };
+  auto wait_half = [&](auto h_c) __attribute__((always_inline)) {
+    wait_columns(c1[decltype(h_c)::value]);
+    if constexpr (KV) wait_columns(c2[decltype(h_c)::value]);
+  };
+  bf16x8 ones_s, ones_d;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    ones_s[e] = static_cast<__bf16>(e < 3 && hi == 0 ? 1.0f : 0.0f);
+    ones_d[e] = static_cast<__bf16>(e < 3 && hi == 1 ? 1.0f : 0.0f);
+  }
+
+  asm volatile("" : "+a"(ones_s), "+a"(ones_d));
+
+  f32x16 acc1[ND], acc2[KV ? ND : 1], s[2], dp[2];
+  u32x4 pk_p[2], pk_d[2];                // P and dS of the group before, bf16 pairs
+  int n_t = 0;
+  auto fence = []() { __builtin_amdgcn_sched_barrier(0); };
+  auto score = [&](auto p_c, auto ks_c) __attribute__((always_inline)) {
+    constexpr int p = decltype(p_c)::value, ks = decltype(ks_c)::value;
+    if constexpr (ks == NKS) {
+      s[p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr, ones_s, s[p], 0, 0, 0);
+    } else if constexpr (ks == 0) {
+      if constexpr (!KV) asm volatile("" : "+v"(sinit));
+      s[p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f1[0], x1f[0], sinit, 0, 0, 0);
+      if constexpr (!KV) asm volatile("" : "+v"(s[p]), "+v"(sinit));
+    } else {
+      s[p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f1[ks], x1f[ks], s[p], 0, 0, 0);
+    }
+  };
+  auto dscore = [&](auto p_c, auto ks_c) __attribute__((always_inline)) {
+    constexpr int p = decltype(p_c)::value, ks = decltype(ks_c)::value;
+    if constexpr (ks == NKS) {
+      dp[p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr, ones_d, dp[p], 0, 0, 0);
+    } else if constexpr (ks == 0) {
+      if constexpr (!KV) asm volatile("" : "+v"(dpinit));
+      dp[p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f2[0], x2f[0], dpinit, 0, 0, 0);
+      if constexpr (!KV) asm volatile("" : "+v"(dp[p]), "+v"(dpinit));
+    } else {
+      dp[p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f2[ks], x2f[ks], dp[p], 0, 0, 0);
+    }
+  };
+  typedef __attribute__((ext_vector_type(2))) uint64_t u64x2;
+  // product j of a group: 16 streamed tokens h2, 32 features d; keys stationary dK and dV in turn
+  constexpr int NP = KV ? 4 * ND : 2 * ND;
+  auto product = [&](auto j_c) __attribute__((always_inline)) {
+    constexpr int h2 = decltype(j_c)::value / (NP / 2), i = decltype(j_c)::value % (NP / 2), d = KV ? i / 2 : i;
+    if constexpr (!KV || i % 2 == 0) {
+      const u64x2 y = {c1[h2][d][0], c1[h2][d][1]};
+      acc1[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, y), __builtin_bit_cast(bf16x8, pk_d[h2]), acc1[d], 0, 0, 0);
+    } else {
+      const u64x2 y = {c2[h2][d][0], c2[h2][d][1]};
+      acc2[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, y), __builtin_bit_cast(bf16x8, pk_p[h2]), acc2[d], 0, 0, 0);
+    }
+  };
+  auto exp_of = [&](auto p_c, auto r_c) __attribute__((always_inline)) {              // P
+    constexpr int p = decltype(p_c)::value, r = decltype(r_c)::value;
+    float e = __builtin_amdgcn_exp2f(QS ? s[p][r] : s[p][r] * a.c);
+    asm volatile("" : "+v"(e));
+    s[p][r] = e;
+  };
+  auto finish = [&](auto p_c, auto k_c) __attribute__((always_inline)) {              // dS and the bf16 pair k
+    constexpr int p = decltype(p_c)::value, k = decltype(k_c)::value;
+    uint32_t d = pack2(dp[p][2 * k] * s[p][2 * k], dp[p][2 * k + 1] * s[p][2 * k + 1]);
+    asm volatile("" : "+v"(d));
+    pk_d[k / 4][k % 4] = d;
+    if constexpr (KV) {
+      uint32_t v = pack2(s[p][2 * k], s[p][2 * k + 1]);
+      asm volatile("" : "+v"(v));
+      pk_p[k / 4][k % 4] = v;
+    }
+  };
+  auto mask = [&](auto p_c, int blk) __attribute__((always_inline)) {                 // streamed tokens past the tile end get probability 0
+    constexpr int p = decltype(p_c)::value;
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      if (blk * 32 + 16 * (r / 8) + 8 * hi + (r % 8) >= n_t) s[p][r] = -INFINITY;
+  };
+  typedef std::integral_constant<int, 0> Even;
+  typedef std::integral_constant<int, 1> Odd;
+  typedef std::true_type Yes;
+  typedef std::false_type No;
+  // First half of the phase of block blk, whose scores are in s[P] and dp[P]: the products of the block before (where pr) with the exponentials and the second
+  // half of the rows of block blk + 1 between them.
+  auto products = [&](auto p_c, auto pr, int blk) __attribute__((always_inline)) {
+    constexpr bool PR = decltype(pr)::value;
+    next_to_load();
+    landed(Next{});                      // block blk + 2; everybody has left block blk - 2
+    if (__builtin_expect(blk * 32 + 32 > n_t, 0)) mask(p_c, blk);
+    if constexpr (PR) {
+      wait_half(Even{});
+      if constexpr (KV) {
+        issue1(Odd{});
+        issue2(Odd{});
+        t_stage = after(t_stage);
+      } else {
+        wait_half(Odd{});
+      }
+    }
+    fence();
+    each<NP>([&](auto j_c) __attribute__((always_inline)) {
+      constexpr int j = decltype(j_c)::value, E = 16 / NP, R = NP - 8;       // E exponentials an instruction; rows from instruction R on
+      if constexpr (PR) {
+        if constexpr (KV && j == NP / 2) wait_half(Odd{});
+        product(j_c);
+        fence();
+      }
+      if constexpr (j == 0) load_rows();
+      if constexpr (j == 1) load_rest();
+      each<E>([&](auto e_c) __attribute__((always_inline)) { exp_of(p_c, std::integral_constant<int, j * E + decltype(e_c)::value>{}); });
+      if constexpr (j >= R && (j - R) % 2 == 0) read_row1(std::integral_constant<int, NKS / 2 + (j - R) / 2>{});
+      if constexpr (j >= R && (j - R) % 2 == 1) read_row2(std::integral_constant<int, NKS / 2 + (j - R) / 2>{});
+      fence();
+    });
+    read_record();
+    r_stage = after(r_stage);
+    fence();
+  };
+  // Second half: the scores of the block after (where sc) with the rest of dS (where fin) and the first half of the rows of the block after that between
+  // them, and the columns of this block.
+  auto scores = [&](auto p_c, auto fin, auto sc) __attribute__((always_inline)) {
+    constexpr int P = decltype(p_c)::value;
+    constexpr bool FIN = decltype(fin)::value, SC = decltype(sc)::value;
+    std::integral_constant<int, 1 - P> o_c;
+    if constexpr (SC) half_is_there(Even{});
+    fence();
+    each<NKS>([&](auto ks_c) __attribute__((always_inline)) {
+      constexpr int ks = decltype(ks_c)::value;
+      if constexpr (SC) {
+        if constexpr (ks == NKS / 2) half_is_there(Odd{});
+        fence();
+        score(o_c, ks_c);
+        fence();
+        if constexpr (ks < NKS / 2) read_row1(ks_c);
+      }
+      if constexpr (FIN) {
+        if constexpr (ks == (SC ? NKS / 2 + KV : 0)) issue1(Even{});
+        finish(p_c, ks_c);
+        fence();
+      }
+      if constexpr (SC) {
+        dscore(o_c, ks_c);
+        fence();
+        if constexpr (ks < NKS / 2) read_row2(ks_c);
+      }
+      if constexpr (FIN) {
+        if constexpr (ks == (SC ? NKS / 2 + 2 : 0)) {
+          if constexpr (KV) {
+            issue2(Even{});
+          } else {
+            issue1(Odd{});
+            t_stage = after(t_stage);
+          }
+        }
+        fence();
+      }
+    });
+    if constexpr (SC && KV) {
+      score(o_c, std::integral_constant<int, NKS>{});
+      dscore(o_c, std::integral_constant<int, NKS>{});
+    }
+    fence();
+  };
+
+  load_from(cur);
+  for (int i = 0; i < NST - 2; ++i) {
+    next_to_load();
+    load_rows();
+    load_rest();
+  }
+  fetch(cur);
+  __builtin_amdgcn_s_waitcnt(0x0F70);
+  landed(First{});                       // blocks 0 and 1
+  unsigned stage0 = 0;                   // of the unit's first block
+  for (;;) {
+    n_t = cur.n_t;
+    const int n = blocks_of(n_t), x0 = cur.x0 + wave * 32;
+    if (x0 < n_t) {
+      settle(cur);
+      r_stage = t_stage = stage0;
+      each<NKS>([&](auto ks_c) __attribute__((always_inline)) { read_row1(ks_c); read_row2(ks_c); });
+      read_record();
+      r_stage = after(r_stage);
+#pragma unroll
+      for (int d = 0; d < ND; ++d)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          acc1[d][r] = 0.f;
+          if constexpr (KV) acc2[d][r] = 0.f;
+        }
+      scores(Odd{}, No{}, Yes{});
+      // Phases 0 .. n - 1.  Scores change between s[0], dp[0] and s[1], dp[1]; the last phase, which has none to compute, is always one with s[1].
+      products(Even{}, No{}, 0);
+      scores(Even{}, Yes{}, Yes{});
+      int i = 1;
+#pragma unroll 1
+      for (; i + 2 < n; i += 2) {
+        products(Odd{}, Yes{}, i);
+        scores(Odd{}, Yes{}, Yes{});
+        products(Even{}, Yes{}, i + 1);
+        scores(Even{}, Yes{}, Yes{});
+      }
+      if (i + 1 < n) {
+        products(Odd{}, Yes{}, i);
+        scores(Odd{}, Yes{}, Yes{});
+        s[1] = s[0];
+        dp[1] = dp[0];
+      }
+      products(Odd{}, Yes{}, n - 1);
+      scores(Odd{}, Yes{}, No{});
+      if constexpr (KV) {
+        issue1(Odd{});
+        issue2(Odd{});
+      }
+      wait_half(Even{});
+      wait_half(Odd{});
+    } else {                             // loads and barriers only
+      for (int i = 0; i < n; ++i) {
+        next_to_load();
+        landed(Next{});
+        load_rows();
+        load_rest();
+      }
+    }
+    Unit nxt;
+    vb = decode(vb + G, nxt);
+    const bool more = vb < a.total;
+    if (more) fetch(nxt);                // while the last products are computed and this lane's row of each gradient is scaled, rounded and stored
+    const int xrow = x0 + l32;
+    if (x0 < n_t) each<NP>([&](auto j_c) __attribute__((always_inline)) { product(j_c); });
+    if (xrow < n_t) {
+      bf16_t *p1 = a.dqkv + cur.row0 * ldq + cur.head * DH + (KV ? a.D : 0) + static_cast<size_t>(xrow) * ldq + hi * 4, *p2 = p1 + a.D;
+      const float sc1 = KV ? a.sck : a.scq;
+#pragma unroll
+      for (int d = 0; d < ND; ++d)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+          // registers 4*r4 .. 4*r4+3 hold features 32d + 8*r4 + 4*hi + (0..3) of this lane's token
+          bf16x4 tmp;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) tmp[e] = static_cast<__bf16>(acc1[d][4 * r4 + e] * sc1);
+          *reinterpret_cast<u32x2 *>(p1 + d * 32 + r4 * 8) = __builtin_bit_cast(u32x2, tmp);
+          if constexpr (KV) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) tmp[e] = static_cast<__bf16>(acc2[d][4 * r4 + e]);
+            *reinterpret_cast<u32x2 *>(p2 + d * 32 + r4 * 8) = __builtin_bit_cast(u32x2, tmp);
+          }
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // the next unit's rows are there; after the last unit no load into LDS outlives its work-group
+    if (!more) return;
+    stage0 = (stage0 / STAGE + n) % NST * STAGE;
+    cur = nxt;
+  }
+}
+
 // ------------------------------------------------------------------ fp32 path
 __global__ __launch_bounds__(256) void attn_bwd_delta_f32_kernel(const float *out, const float *dout, float *delta,
                                                                  int64_t n, int64_t n_h, int heads, int dh) {
@@ -1136,8 +1473,8 @@ __global__ __launch_bounds__(128) void attn_bwd_f32_kernel(const float *qkv, con
   }
 }
 
-template <int DH, int BS, int NST>
-constexpr int bwd_lds_bytes(bool kv) { return NST * (2 * BS * DH * 2 + (kv ? 2 * BS * 16 : 0)); }
+template <int DH, int NST>
+constexpr int bwd_lds_bytes(bool kv) { return NST * (2 * 32 * DH * 2 + (kv ? 2 * 32 * 16 : 0)); }
 
 static int g_bwd_cus = 0;
 static bool g_bwd_big_ok = false;
@@ -1152,12 +1489,14 @@ hipError_t attention_bwd_init() {
   g_bwd_big_ok = true;
   struct Big { const void *fn; int bytes; };
   const Big big[] = {
-#define RESLIM_BIG(DH, BS, MODE, NST, NSPLIT)                                                                       \
-  {reinterpret_cast<const void *>(&attn_bwd_bf16_kernel<DH, BS, MODE, false, 1, NST, NSPLIT>), bwd_lds_bytes<DH, BS, NST>(MODE != 0)}, \
-  {reinterpret_cast<const void *>(&attn_bwd_bf16_kernel<DH, BS, MODE, true, 1, NST, NSPLIT>), bwd_lds_bytes<DH, BS, NST>(MODE != 0)},
-      RESLIM_BIG(128, 64, 0, 3, 1) RESLIM_BIG(128, 64, 3, 3, 1) RESLIM_BIG(128, 64, 1, 3, 1)
-      RESLIM_BIG(256, 32, 0, 3, 1) RESLIM_BIG(256, 32, 1, 3, 2)
-#undef RESLIM_BIG
+      {reinterpret_cast<const void *>(&attn_bwd_wide_bf16_kernel<false, false>), wide_lds_bytes(false)},
+      {reinterpret_cast<const void *>(&attn_bwd_wide_bf16_kernel<false, true>), wide_lds_bytes(false)},
+      {reinterpret_cast<const void *>(&attn_bwd_wide_bf16_kernel<true, false>), wide_lds_bytes(true)},
+      {reinterpret_cast<const void *>(&attn_bwd_wide_bf16_kernel<true, true>), wide_lds_bytes(true)},
+      {reinterpret_cast<const void *>(&attn_bwd_bf16_kernel<256, false, false, 3, 1>), bwd_lds_bytes<256, 3>(false)},
+      {reinterpret_cast<const void *>(&attn_bwd_bf16_kernel<256, false, true, 3, 1>), bwd_lds_bytes<256, 3>(false)},
+      {reinterpret_cast<const void *>(&attn_bwd_bf16_kernel<256, true, false, 3, 2>), bwd_lds_bytes<256, 3>(true)},
+      {reinterpret_cast<const void *>(&attn_bwd_bf16_kernel<256, true, true, 3, 2>), bwd_lds_bytes<256, 3>(true)},
   };
   for (const Big &k : big) {
     e = hipFuncSetAttribute(k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, k.bytes);
@@ -1174,12 +1513,12 @@ size_t tiles_attention_bwd_ws_bytes(const reslim_ctx *c, int batch, const SeqGeo
   return c->cfg.dtype == RESLIM_BF16 ? align256(recs * 32) : align256(recs * 4);
 }
 
-template <int DH, int BS, int MODE, bool QS, int MINW, int NST, int NSPLIT = 1>
+template <int DH, bool KV, bool QS, int NST, int NSPLIT>
 static hipError_t launch_bwd_one(const AttnBwdArgs &a0, hipStream_t st) {
-  const int g = a0.total < MINW * g_bwd_cus ? a0.total : MINW * g_bwd_cus;    // persistent grid
+  const int g = a0.total < g_bwd_cus ? a0.total : g_bwd_cus;    // persistent grid
   AttnBwdArgs a = a0;
   for (a.part = 0; a.part < NSPLIT; ++a.part) {
-    attn_bwd_bf16_kernel<DH, BS, MODE, QS, MINW, NST, NSPLIT><<<dim3(g), dim3(256), bwd_lds_bytes<DH, BS, NST>(MODE != 0), st>>>(a);
+    attn_bwd_bf16_kernel<DH, KV, QS, NST, NSPLIT><<<dim3(g), dim3(256), bwd_lds_bytes<DH, NST>(KV), st>>>(a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -1187,11 +1526,8 @@ static hipError_t launch_bwd_one(const AttnBwdArgs &a0, hipStream_t st) {
 }
 
 // Launch shapes (measured on MI355X; the file is built with MFMA operands in ordinary vector
-// registers, see the build script): dh = 64: attn_bwd_woven.  dh = 128: one work-group per
-// CU, 64-token blocks with two 32-token groups in flight; dQ ~350 registers, dK and dV together
-// ~510, no spills (c4: 7.1 ms; 13.1 ms with 32-token blocks, separate dK and dV passes and
-// accumulator-register MFMAs; 17.4 ms with two spilling work-groups).  dh = 256: dQ unsplit on
-// 32-token blocks (15 registers spilled, still faster than two spill-free half passes), dK and dV
+// registers, see the build script): dh = 64: attn_bwd_woven.  dh = 128: attn_bwd_wide.
+// dh = 256: dQ unsplit on 32-token blocks (15 registers spilled, still faster than two spill-free half passes), dK and dV
 // together, once per half of the head's features (505 registers, no spills).  The 10B model's
 // block: 6.6 ms, against 40.5 ms for unsplit dQ and dK/dV passes that spilled 130 .. 145 registers.
 template <bool QS>
@@ -1205,12 +1541,14 @@ static hipError_t launch_bwd_all(const AttnBwdArgs &a, int dh, hipStream_t st) {
       return hipGetLastError();
     case 128:
       if (!g_bwd_big_ok) return hipErrorInvalidValue;
-      e = launch_bwd_one<128, 64, 0, QS, 1, 3>(a, st);
-      return e != hipSuccess ? e : launch_bwd_one<128, 64, 1, QS, 1, 3>(a, st);
+      attn_bwd_wide_bf16_kernel<false, QS><<<dim3(min(a.total, g_bwd_cus)), dim3(256), wide_lds_bytes(false), st>>>(a);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+      attn_bwd_wide_bf16_kernel<true, QS><<<dim3(min(a.total, g_bwd_cus)), dim3(256), wide_lds_bytes(true), st>>>(a);
+      return hipGetLastError();
     case 256:
       if (!g_bwd_big_ok) return hipErrorInvalidValue;
-      e = launch_bwd_one<256, 32, 0, QS, 1, 3, 1>(a, st);
-      return e != hipSuccess ? e : launch_bwd_one<256, 32, 1, QS, 1, 3, 2>(a, st);
+      e = launch_bwd_one<256, false, QS, 3, 1>(a, st);
+      return e != hipSuccess ? e : launch_bwd_one<256, true, QS, 3, 2>(a, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1253,8 +1591,7 @@ hipError_t launch_tiles_attention_bwd(const reslim_ctx *c, const void *qkv, cons
     const float lse_f = q_prescaled ? 1.4426950408889634f : sqrtf(static_cast<float>(dh));
     a.lse_f = lse_f;
     switch (dh) {
-      case 64: break;                      // the query-stationary launch does it
-      case 128: attn_bwd_prep_bf16_kernel<128><<<dim3(pg), dim3(256), 0, st>>>(a.out, a.dout, lse, a.aux, n_vec, sg.n_h, heads, D, lse_f, recs); break;
+      case 64: case 128: break;            // the query-stationary launch does it
       case 256: attn_bwd_prep_bf16_kernel<256><<<dim3(pg), dim3(256), 0, st>>>(a.out, a.dout, lse, a.aux, n_vec, sg.n_h, heads, D, lse_f, recs); break;
       default: return hipErrorInvalidValue;
     }
