@@ -52,6 +52,7 @@ struct AttnBwdArgs {
   bf16_t *dqkv;          // [B, n_h, 3, heads, dh]
   const tile_desc *tiles;
   int T, heads, D, QB, total;
+  int per;               // head dimension 128: blocks of 128 tokens of one sample and head, 0: `total` counts slots of QB a tile
   int part;              // which 1/NSPLIT of the head's features this launch accumulates and writes
   int64_t n_h;
   int64_t aux_stride;    // records per array
@@ -915,10 +916,10 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_woven_bf16_kernel(AttnBwdArgs
 // gaps: the second half of a block's rows is read during the products, and columns and rows lie in accumulator registers, which the matrix
 // instructions read as well and vector code does not need.  One work-group to a compute unit walks its units; the loads run six blocks ahead across
 // units, and the next unit's stationary rows arrive during a unit's last products.  Every sum has the order of the kernel for head dimension 256: the same bits.
-// 19,840 tokens of 24 heads in tiles of 1128 to 1323: 1564 us with two groups one after the other and three stages of 64 tokens, 1281 us here (dQ 0.56, dK
-// and dV 0.70 ms); 37,536 of 32 in tiles to 2448: 6.69 and 5.39 ms; 2000 tokens, 8 sets of keys 150 and 115 us; 30 tokens, 1024 sets 53 and 48.
-// What bounds it: the matrix pipe is busy 34 and 39 % of the cycles, at 2.0 GHz; waits (LDS, barrier) are 22 and 19 %, issue of everything else 47 %, and a
-// sixth of the time compute units have run out of units.  Exponentials and loads spread evenly over both halves of the phase measured the same.
+// 19,840 tokens of 24 heads in tiles of 1128 to 1323: 1564 us with two groups one after the other and three stages of 64 tokens, 1201 us here;
+// 37,536 of 32 in tiles to 2448: 6.69 and 5.05 ms; 2000 tokens, 8 sets of keys 150 and 115 us; 30 tokens, 1024 sets 53 and 48.
+// What bounds it: the matrix pipe is busy 34 and 39 % of the cycles, at 2.0 GHz; waits (LDS, barrier) are 22 and 19 %, issue of everything else 47 %.
+// Exponentials and loads spread evenly over both halves of the phase measured the same.
 template <int N, typename F, int... I>
 __device__ __forceinline__ void each_of(const F &f, std::integer_sequence<int, I...>) {
   (f(std::integral_constant<int, I>{}), ...);
@@ -947,18 +948,37 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_wide_bf16_kernel(AttnBwdArgs 
     int n_t, x0, head;   // tokens of the tile; first stationary token of the work-group
     int64_t row0, rec0;  // first row of the tile, first record of its head
   };
-  auto decode = [&](int vb, Unit &u) __attribute__((always_inline)) -> int {         // first non-empty unit at or after vb (stride G), or >= total
+  // Unit `vb` of the launch: of the blocks of 128 tokens that exist, over samples, heads and tiles; every wave finds the tile with a running sum
+  // over the tiles, a lane each.  Where that does not pay (a.per == 0, see the launch) of the slots of as many blocks as the longest tile
+  // has, empty ones skipped, stride G.
+  auto decode = [&](int vb, Unit &u) __attribute__((always_inline)) -> int {         // vb, or the next slot that has a block; >= total: none
+    int b = 0, tile = 0;
     while (vb < a.total) {
       const int logical = xcd_remap_attn(vb, a.total);
-      const int xb = logical % a.QB;
-      int rest = logical / a.QB;
-      u.head = rest % a.heads;
-      rest /= a.heads;
-      const int tile = rest % a.T, b = rest / a.T;
+      if (a.per) {
+        int at = logical % a.per, rest = logical / a.per;
+        u.head = rest % a.heads;
+        b = rest / a.heads;
+        const int own = lane < a.T ? (a.tiles[lane].n_tok + 127) / 128 : 0;
+        int upto = own;
+#pragma unroll
+        for (int w = 1; w < 64; w <<= 1) {
+          const int v = __shfl_up(upto, w);
+          upto += lane >= w ? v : 0;
+        }
+        tile = __builtin_ctzll(__ballot(upto > at));
+        u.x0 = (at - __builtin_amdgcn_readlane(upto - own, tile)) * 128;
+      } else {
+        int rest = logical / a.QB;
+        u.x0 = logical % a.QB * 128;
+        u.head = rest % a.heads;
+        rest /= a.heads;
+        tile = rest % a.T;
+        b = rest / a.T;
+      }
       // the kernel writes to memory, so these come through vector loads: back to scalar registers, or the buffers' addresses are not
       u.n_t = __builtin_amdgcn_readfirstlane(a.tiles[tile].n_tok);
       const int64_t off = scalar64(a.tiles[tile].tok_off);
-      u.x0 = xb * 128;
       u.row0 = static_cast<int64_t>(b) * a.n_h + off;
       u.rec0 = (static_cast<int64_t>(b) * a.heads + u.head) * a.n_h + off;
       if (u.x0 < u.n_t) break;
@@ -1585,6 +1605,14 @@ hipError_t launch_tiles_attention_bwd(const reslim_ctx *c, const void *qkv, cons
     const int64_t total = static_cast<int64_t>(batch) * sg.T * heads * a.QB;
     if (total > INT32_MAX || g_bwd_cus <= 0) return hipErrorInvalidValue;
     a.total = static_cast<int>(total);
+    // One work-group to a compute unit at head dimension 128: a work-group with one slot more that has a block, where others skip empty ones,
+    // is waited for.  Blocks that exist are numbered instead where a fiftieth of the slots and more are empty and there are more slots than
+    // compute units (16 tiles of 1128 to 1323 tokens, 24 heads: 1296 and 1201 us; of 2244 to 2448, 32 heads: 5.22 and 5.05 ms).  Finding the tile
+    // takes 0.8 us a unit, more than it gives for tiles of one to three blocks (30 tokens, 1024 sets of keys: 48 and 54 us) or without empty slots
+    // (1290 tokens, 16 sets: 84 and 86; 300, 256: 96 and 100), and needs a lane to a tile.
+    const int64_t slots = static_cast<int64_t>(sg.T) * a.QB;
+    a.per = dh == 128 && sg.T <= 64 && a.QB > 3 && total > g_bwd_cus && 50 * (slots - sg.blocks128) >= slots ? static_cast<int>(sg.blocks128) : 0;
+    if (a.per) a.total = batch * heads * a.per;
     const int64_t n_vec = static_cast<int64_t>(batch) * sg.n_h * D / 8;
     const unsigned pg = static_cast<unsigned>((n_vec + 255) / 256);
     // record 0 holds -lse in the unit of the MFMA output: -lse*sqrt(dh), or -lse*log2(e) for pre-scaled q
