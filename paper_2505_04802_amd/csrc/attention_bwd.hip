@@ -918,7 +918,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_woven_bf16_kernel(AttnBwdArgs
 // units, and the next unit's stationary rows arrive during a unit's last products.  Every sum has the order of the kernel for head dimension 256: the same bits.
 // 19,840 tokens of 24 heads in tiles of 1128 to 1323: 1564 us with two groups one after the other and three stages of 64 tokens, 1201 us here;
 // 37,536 of 32 in tiles to 2448: 6.69 and 5.05 ms; 2000 tokens, 8 sets of keys 150 and 115 us; 30 tokens, 1024 sets 53 and 48.
-// What bounds it: the matrix pipe is busy 34 and 39 % of the cycles, at 2.0 GHz; waits (LDS, barrier) are 22 and 19 %, issue of everything else 47 %.
+// What bounds it: the matrix pipe is busy 39 and 44 % of the cycles, at 1.94 GHz; a wave issues 47 % of the time, waits for LDS, loads and the barrier 22 and 21 %, and for
+// a busy unit the rest.
 // Exponentials and loads spread evenly over both halves of the phase measured the same.
 template <int N, typename F, int... I>
 __device__ __forceinline__ void each_of(const F &f, std::integer_sequence<int, I...>) {
