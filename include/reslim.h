@@ -578,11 +578,11 @@ int reslim_debug_copy(const void *src, void *dst, size_t bytes, void *hip_stream
  * other thread is inside the library and restore -1 afterwards. */
 void reslim_debug_set_gemm_tile(int choice);
 
-/* Tuning hook for benchmarks and tests: launch shape of the bf16 tile-attention kernel at
- * head dimension 64 (0, the default = 64-key blocks, three work-groups per compute unit, or,
- * for few queries, the keys split over the waves of a work-group; 1 = 128-key blocks, two
- * work-groups per compute unit).  Process-wide and not thread-safe,
- * like the hook above. */
+/* Tuning hook for benchmarks and tests: the bf16 tile-attention kernel at head dimension 64 (0,
+ * the default = by the sizes of the launch; 1 = 128-key blocks, two work-groups per compute unit;
+ * 2 = 64-key blocks, one group of 32 queries a wave; 3 and 4 = two groups a wave, two and four
+ * waves to a work-group).  2 to 4 give the same bits.  Process-wide and not thread-safe, like the
+ * hook above. */
 void reslim_debug_set_attention_variant(int variant);
 
 #ifdef __cplusplus

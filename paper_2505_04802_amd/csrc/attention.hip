@@ -1251,7 +1251,7 @@ __global__ __launch_bounds__(256) void tiles_attention_f32_kernel(AttnArgs a, in
   }
 }
 
-// at dh = 64, 0: what attention_plan.h names (default); 1: 128-key blocks, two work-groups per CU
+// at dh = 64, 0: what attention_plan.h names (default); 1: 128-key blocks, two work-groups per CU; 2: one query group a wave; 3, 4: two groups, work-groups of two, four waves
 static int g_attn_variant = 0;
 static int g_attn_cus = 0;
 
@@ -1342,12 +1342,12 @@ hipError_t launch_tiles_attention(const reslim_ctx *c, const void *qkv, void *ou
       else if (stitched) tiles_attention_split_bf16_kernel<64, false, true><<<grid, blk, 0, st>>>(a);
       else if (q_prescaled) tiles_attention_split_bf16_kernel<64, true, false><<<grid, blk, 0, st>>>(a);
       else tiles_attention_split_bf16_kernel<64, false, false><<<grid, blk, 0, st>>>(a);
-    } else if (const int nw = c->dh == 64 && g_attn_variant == 0 ? attn_pair_waves(sets * sg.blocks128, sets * sg.blocks256, g_attn_cus) : 0) {
+    } else if (const int nw = c->dh != 64 ? 0 : g_attn_variant == 0 ? attn_pair_waves(sets * sg.blocks128, sets * sg.blocks256, g_attn_cus) : g_attn_variant == 3 ? 2 : g_attn_variant == 4 ? 4 : 0) {
       a.QB = (sg.max_n_tok + 64 * nw - 1) / (64 * nw);
       a.total = static_cast<int>(sets * sg.T * a.QB);
       if (nw == 2) launch_pair<2>(a, q_prescaled, stitched, st);
       else launch_pair<4>(a, q_prescaled, stitched, st);
-    } else if (c->dh == 64 && g_attn_variant == 0) launch_bf16_variant<64, 64, 3, 2, 1>(a, q_prescaled, stitched, pg3, st);
+    } else if (c->dh == 64 && g_attn_variant != 1) launch_bf16_variant<64, 64, 3, 2, 1>(a, q_prescaled, stitched, pg3, st);
     else if (c->dh == 64) launch_bf16_variant<64, 128, 2>(a, q_prescaled, stitched, pg2, st);
     else if (c->dh == 128) launch_bf16_variant<128, 64, 2>(a, q_prescaled, stitched, pg2, st);
     else if (c->dh == 256) {
@@ -1377,5 +1377,6 @@ hipError_t launch_tiles_attention(const reslim_ctx *c, const void *qkv, void *ou
 
 }  // namespace reslim
 
-// tuning hook for dh = 64: 0 = the kernel that attention_plan.h names (default), 1 = 128-key blocks, one query group a wave, two work-groups per CU
+// tuning hook for dh = 64: 0 = the kernel that attention_plan.h names (default), 1 = 128-key blocks, one query group a wave, two work-groups per CU, 2 = 64-key
+// blocks, one query group a wave, 3 and 4 = two query groups a wave, two and four waves to a work-group
 extern "C" void reslim_debug_set_attention_variant(int v) { reslim::g_attn_variant = v; }

@@ -85,3 +85,14 @@ def test_two_query_groups_where_they_gain(plan):
         got = {0: one, 2: two_by_two, 4: two_by_four}[plan.pair_waves(*blocks, 256)]
         assert got <= 1.1 * min(one, two_by_two, two_by_four), (tokens, sets, got)
     assert plan.pair_waves(0, 0, 256) == 0 and plan.pair_waves(2 ** 31 - 1, 2 ** 30, 256) == 4 and plan.pair_waves(2 ** 31, 2 ** 31, 256) == 2
+
+
+def test_the_gpu_tests_run_the_kernels_they_name(plan):
+    """The lists of test_gpu_attention_pair.py by the kernel with two groups that the default takes on a chip of 256 compute units."""
+    from oracle import reslim_oracle as O
+    from test_gpu_attention_pair import FOUR, TWO
+    for cfgs, waves in ((FOUR, 4), (TWO, 2)):
+        for c in cfgs:
+            tiles = O.tiles_partition(c.Hp, c.Wp, c.tiles_y, c.tiles_x, c.halo)[0]
+            blocks = [c.batch * c.heads * sum(-(-int(t["n_tok"]) // n) for t in tiles) for n in (128, 256)]
+            assert plan.pair_waves(*blocks, 256) == waves, c.name

@@ -20,14 +20,14 @@ def tiled(h, w, ty, tx, **other):
     return BASE.with_(name=f"{h}x{w}_{ty}x{tx}_{'_'.join(map(str, other.values()))}", H=2 * h, W=2 * w, tiles_y=ty, tiles_x=tx, **other)
 
 
-# at 16 heads 49 to 64 blocks of 128 queries in all, tiles of 129 to 256 tokens or near a multiple of 256: four waves in a work-group
+# 768 blocks of 128 queries and more, in tiles that fill blocks of 256 as well, or leave a tenth of the waves idle at most: four waves in a work-group
 FOUR = [tiled(3, 43 * 25, 1, 25),                           # 129: no query for the fourth wave, one for the third
         tiled(8, 20 * 25, 1, 25),                           # 160: five whole blocks of keys, none in the third wave's second group
         tiled(7, 23 * 25, 1, 25),                           # 161: a last block of one key
         tiled(15, 15 * 25 + 9, 1, 25),                      # 225 and 240: one query in the last group
         tiled(16, 16 * 13, 1, 13, batch=2),                 # 256
         tiled(60, 84, 2, 3, batch=3, halo=2)]               # 32 by 30 to 32
-# at 64 heads 128 blocks and more, at least a twentieth fewer waves than with four: two
+# 8192 blocks and more, a twentieth fewer waves than with four at least: two (tests/test_attention_plan_cpu.py holds both lists against the rule)
 TWO = [tiled(n, 128, 1, 128, embed_dim=4096, heads=64) for n in (1, 33, 65)] + [tiled(257, 43, 1, 43, embed_dim=4096, heads=64)]
 
 
@@ -41,6 +41,13 @@ def qkv_of(cfg, n_h, kind):
         x[:, tok % 37 == 36, D:2 * D] = 3.0
     if kind == "low":              # every logit is about -100 in base 2: a zero would be all there is
         x[..., :D], x[..., D:2 * D] = 3.0, -3.0 + 0.25 * np.sign(x[..., D:2 * D])
+    if kind == "stairs":           # queries that meet a logit 11 above their last largest (base 2) every 64 keys: in the first 32 of them, in the others, in both
+        f = np.arange(D) % 64
+        x[..., :D][..., f < 2] = x[..., D:2 * D][..., f < 2] = 0.0
+        for first, key, queries in ((0, 8, (1, 3)), (1, 40, (2, 3))):
+            x[:, np.ix_(np.isin(tok % 5, queries), f == first)[0], np.flatnonzero(f == first)] = 8.0
+            at = tok[tok % 64 == key]
+            x[:, at[:, None], D + np.flatnonzero(f == first)] = (8.0 * (1 + at // 64))[None, :, None]
     return x
 
 
@@ -103,3 +110,45 @@ def test_the_same_bits_as_with_one_group_a_wave(scale):
         out, lse = m.attention_with_lse(act)
         parts = [m.attention_with_lse(act[b:b + 1].contiguous()) for b in range(cfg.batch)]
     assert torch.equal(out, torch.cat([p[0] for p in parts])) and torch.equal(lse, torch.cat([p[1] for p in parts]))
+
+
+SHORT = [tiled(n, 3 * 16, 1, 48) for n in (1, 31, 32, 33, 63, 64, 65, 96, 97, 128)]
+EDGES = SHORT + [tiled(n, 25, 1, 25) for n in (129, 160, 161, 255, 256, 257)] + [FOUR[-1]]
+
+
+@pytest.mark.parametrize("kind", ["normal", "moving", "low", "stairs"])
+@pytest.mark.parametrize("cfg", EDGES, ids=lambda c: c.name)
+def test_the_same_bits_in_every_kernel(cfg, kind):
+    """One query group a wave and two, in work-groups of two waves and of four: by the rule, launches of one size or another get them."""
+    print(f"attention kernels beside each other {cfg.name} {kind}", flush=True)
+    _, _, _, n_h = O.tiles_partition(cfg.Hp, cfg.Wp, cfg.tiles_y, cfg.tiles_x, cfg.halo)
+    with B.Reslim(cfg, WL.make_weights(cfg)) as m:
+        act = torch.from_numpy(qkv_of(cfg, n_h, kind).astype(np.float32)).cuda().to(m.act_dtype)
+        try:
+            got = []
+            for variant in (2, 3, 4):
+                B.reslim_debug_set_attention_variant(variant)
+                got.append(m.attention_with_lse(act))
+        finally:
+            B.reslim_debug_set_attention_variant(0)
+    assert all(torch.isfinite(t.float()).all() for t in got[0])
+    for other in got[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(got[0], other))
+
+
+@pytest.mark.parametrize("std", [0.02, 0.3])
+@pytest.mark.parametrize("cfg", [FOUR[-1].with_(depth=2, embed_dim=256, heads=4, batch=2), tiled(9, 42, 1, 3, halo=2, embed_dim=128, heads=2).with_(depth=2)],
+                         ids=lambda c: c.name)
+def test_a_forward_is_the_same_bits_with_every_kernel(cfg, std):
+    """q scaled by the QKV epilogue; the last block's output stitched."""
+    print(f"forward with each attention kernel {cfg.name} {std}", flush=True)
+    w, x = WL.make_weights(cfg, std=std), torch.from_numpy(WL.make_fields(cfg)).cuda()
+    with B.Reslim(cfg, w) as m:
+        try:
+            got = []
+            for variant in (2, 3, 4):
+                B.reslim_debug_set_attention_variant(variant)
+                got.append(m.forward(x).clone())
+        finally:
+            B.reslim_debug_set_attention_variant(0)
+    assert torch.isfinite(got[0]).all() and torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
