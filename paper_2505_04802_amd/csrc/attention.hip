@@ -78,9 +78,9 @@ struct RowSums {
   }
   __device__ __forceinline__ void reset() { v = f32x4{0.f, 0.f, 0.f, 0.f}; }
   __device__ __forceinline__ void add(const bf16x8 &ones, const bf16x8 &p) { v = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, p, v, 0, 0, 0); }
-  __device__ __forceinline__ void scale(float alpha, int lane) {
+  __device__ __forceinline__ void scale(float alpha) {
     v[0] *= alpha;
-    v[1] *= __shfl(alpha, (lane & 15) + 16);
+    v[1] *= of_next_16_lanes(alpha);
   }
   __device__ __forceinline__ float total(int lane) const {
     const float lo = __shfl(v[0], lane & 15), up = __shfl(v[1], lane & 15);
@@ -119,25 +119,19 @@ __device__ __forceinline__ void move_reference(f32x16 &s, f32x16 &o0, f32x16 &o1
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     s[r] -= d;
-    o0[r] *= alpha;
-    o1[r] *= alpha;
     minit[r] = ninit;
   }
-  lsum.scale(alpha, lane);
+  if (first) return;                     // uniform: nothing summed yet
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    o0[r] *= alpha;
+    o1[r] *= alpha;
+  }
+  lsum.scale(alpha);
 }
 
-// one V^T fragment of a 32-key group (32 features, the 16 keys of half h2), read and waited for in one statement; addresses as in v_frag_issue(f, at)
-template <int OFF>
-__device__ __forceinline__ bf16x8 v_frag_read(unsigned at, int h2) {
-  uint64_t lo, up;
-  if (h2 == 0)
-    asm volatile("ds_read_b64_tr_b16 %0, %2 offset:%3\n\tds_read_b64_tr_b16 %1, %2 offset:%4\n\ts_waitcnt lgkmcnt(0)"
-                 : "=&v"(lo), "=&v"(up) : "v"(at), "n"(OFF), "n"(OFF + 4 * 128));
-  else
-    asm volatile("ds_read_b64_tr_b16 %0, %2 offset:%3\n\tds_read_b64_tr_b16 %1, %2 offset:%4\n\ts_waitcnt lgkmcnt(0)"
-                 : "=&v"(lo), "=&v"(up) : "v"(at), "n"(OFF + 16 * 128), "n"(OFF + 20 * 128));
-  typedef __attribute__((ext_vector_type(2))) uint64_t u64x2;
-  return __builtin_bit_cast(bf16x8, u64x2{lo, up});
+__device__ __forceinline__ unsigned lds_addr(const unsigned char *p) {
+  return static_cast<unsigned>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const unsigned char *)p));
 }
 
 template <int DH, int BKV, bool QS, int MINW = 2, bool ST = false, int PQK = 1, int PPV = 1>
@@ -301,6 +295,25 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
     const bool active = cur.q0 + wave * 32 < cur.n_t && wave_owns;   // wave-uniform
 
     f32x16 s[NKT];
+    const unsigned k_at = lds_addr(st) + k_row + ((hi ^ k_swz) << 4);
+    // scores of 32 or 64 keys at head dimension 64, every fragment requested ahead of the products (from one address: four would be four registers more)
+    auto score_groups = [&](auto first_c, auto count_c) __attribute__((always_inline)) {
+      constexpr int FIRST = decltype(first_c)::value, COUNT = decltype(count_c)::value;
+      bf16x8 kf[COUNT][NKS];
+#pragma unroll
+      for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+        for (int i = 0; i < COUNT; ++i) kf[i][ks] = *reinterpret_cast<__attribute__((address_space(3))) bf16x8 *>((k_at ^ (ks * 32)) + (FIRST + i) * 32 * ROWB);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+        for (int i = 0; i < COUNT; ++i) s[FIRST + i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i][ks], qf[ks], ks == 0 ? minit : s[FIRST + i], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    typedef std::integral_constant<int, 0> I0;
+    typedef std::integral_constant<int, 1> I1;
+    typedef std::integral_constant<int, 2> I2;
     if (active) {
       // The MFMA phases run at raised wave priority, the softmax arithmetic at the default one: a
       // wave whose operands are ready gets the matrix pipe ahead of the vector work of the other
@@ -310,7 +323,14 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
       // 3 / 1, 3.50 with 2 / 2, 3.62 with the P V phase at the default level, 3.76 with none).
       __builtin_amdgcn_s_setprio(PQK);
       // feature step outermost: consecutive MFMAs belong to different accumulator chains
-      if constexpr (DH <= 128) {
+      if constexpr (PIPE) {
+        if (kb == 0) {
+          score_groups(I0{}, I1{});                // the second group's follow from the reference that these set
+          asm volatile("" : "=v"(s[1]));           // (any value: without one the registers would be kept from the block before)
+        } else {
+          score_groups(I0{}, I2{});
+        }
+      } else if constexpr (DH <= 128) {
 #pragma unroll
         for (int ks = 0; ks < NKS; ++ks) {
 #pragma unroll
@@ -345,41 +365,52 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
     bool woven = true;
     if constexpr (PIPE) {
       if (active) {
-        if (kv0 + BKV > cur.n_t) {         // ragged last block
-          mask_block(s[0], kv0, cur.n_t, hi);
-          mask_block(s[1], kv0 + 32, cur.n_t, hi);
+        // A reference moves at a group of 32 keys, by the group's own logits, and the scores behind it start from where it went: at a tile's first
+        // block those of the second group are computed behind the move, later (rare) once more.  A lane's products wait for the first move
+        // of every tile, so what it costs is the smallest launches' time: 1 token, 256 sets of keys 4.05 us (4.80 with both groups' scores before the move, the second's
+        // again and each V fragment waited for by itself), 100 tokens, 1024 sets 15.2 (16.1).  Logits of a standard deviation of 3, 200 tokens, 256 sets
+        // 11.1 us (12.8; of 0.3 10.9), 1290 tokens, 64 sets 42.8 (45.5; 40.8); of 9, where nearly every block of a wave moves some query, 51.5 (55.3).
+        const bool ragged = kv0 + BKV > cur.n_t;
+        bool move = kb == 0;               // at the first group; woven: not at the second
+        if (ragged) mask_block(s[0], kv0, cur.n_t, hi);
+        if (kb != 0) {
+          if (ragged) mask_block(s[1], kv0 + 32, cur.n_t, hi);
+          const float m0 = max_of_block(s[0]);
+          woven = !__any(!(__builtin_elementwise_maximum(m0, max_of_block(s[1])) <= TAU));
+          move = !woven && __any(!(m0 <= TAU));
         }
-        const float limit = kb == 0 ? __builtin_nanf("") : TAU;      // not a number: in any case
-        woven = !__any(!(__builtin_elementwise_maximum(max_of_block(s[0]), max_of_block(s[1])) <= limit));
+        if (move) {
+          move_reference(s[0], o[0], o[1], minit, lsum, max_of_block(s[0]), kb == 0, TAU, c, lane);
+          score_groups(I1{}, I1{});
+          if (ragged) mask_block(s[1], kv0 + 32, cur.n_t, hi);
+          woven = !__any(!(max_of_block(s[1]) <= TAU));
+        }
         if (!woven) {
-          // A reference may move: one group of 32 keys after the other, the second's scores again from the reference that the first left.
-          // Same operations in the same order as where no reference moves, and as in the kernel below: same bits.
-          const unsigned va = static_cast<unsigned>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const unsigned char *)st)) + static_cast<unsigned>(v_addr[0][0]);
+          // One group after the other.  Same operations in the same order as below, and as in the kernel with two query groups: same bits.
+          const unsigned va = lds_addr(st) + static_cast<unsigned>(v_addr[0][0]);
           auto group = [&](auto kt_c) __attribute__((always_inline)) {
             constexpr int kt = decltype(kt_c)::value;
-            if constexpr (kt == 1) {
+            VFrag64 vf;
+            v_frag_issue<kt * 32 * ROWB>(vf, va);
+            bf16x8 pf[2];
 #pragma unroll
-              for (int ks = 0; ks < NKS; ++ks) {
-                const bf16x8 kf = *reinterpret_cast<const bf16x8 *>(st + kt * 32 * ROWB + k_row + (((2 * ks + hi) ^ k_swz) << 4));
-                s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], ks == 0 ? minit : s[1], 0, 0, 0);
-              }
-              if (kv0 + BKV > cur.n_t) mask_block(s[1], kv0 + 32, cur.n_t, hi);
-            }
-            move_reference(s[kt], o[0], o[1], minit, lsum, max_of_block(s[kt]), kb == 0 && kt == 0, TAU, c, lane);
+            for (int h2 = 0; h2 < 2; ++h2)
+#pragma unroll
+              for (int e = 0; e < 8; ++e) pf[h2][e] = static_cast<__bf16>(__builtin_amdgcn_exp2f(QS ? s[kt][8 * h2 + e] : s[kt][8 * h2 + e] * c));
+            v_frag_wait(vf);
 #pragma unroll
             for (int h2 = 0; h2 < 2; ++h2) {
-              bf16x8 pf;
-#pragma unroll
-              for (int e = 0; e < 8; ++e) pf[e] = static_cast<__bf16>(__builtin_amdgcn_exp2f(QS ? s[kt][8 * h2 + e] : s[kt][8 * h2 + e] * c));
-              lsum.add(ones, pf);
+              lsum.add(ones, pf[h2]);
 #pragma unroll
               for (int d = 0; d < 2; ++d) {
-                const bf16x8 v = v_frag_read<kt * 32 * ROWB>(va ^ (64u * d), h2);
-                o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, pf, o[d], 0, 0, 0);
+                typedef __attribute__((ext_vector_type(2))) uint64_t u64x2;
+                const u64x2 both = {vf.r[h2][d][0], vf.r[h2][d][1]};
+                o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), pf[h2], o[d], 0, 0, 0);
               }
             }
           };
           group(std::integral_constant<int, 0>{});
+          move_reference(s[1], o[0], o[1], minit, lsum, max_of_block(s[1]), false, TAU, c, lane);
           group(std::integral_constant<int, 1>{});
         }
       }
@@ -426,7 +457,7 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
           const float ninit = minit[0] - d;
 #pragma unroll
           for (int r = 0; r < 16; ++r) minit[r] = ninit;
-          lsum.scale(alpha, lane);
+          lsum.scale(alpha);
           have_ref = true;
         }
 #pragma unroll
@@ -441,7 +472,7 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
         // The exponentials and conversions of the second 32-key group are placed between the
         // matrix instructions of the first group's P V product: a wave issues in order, so its own
         // vector work only overlaps its matrix work when the two are interleaved in the stream.
-        const unsigned va = static_cast<unsigned>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const unsigned char *)st)) + static_cast<unsigned>(v_addr[0][0]);
+        const unsigned va = lds_addr(st) + static_cast<unsigned>(v_addr[0][0]);
         typedef __attribute__((ext_vector_type(2))) uint64_t u64x2;
         // the first group's V reads are issued ahead of its exponentials, which cover their latency
         VFrag64 vf0, vf1;

@@ -111,4 +111,12 @@ __device__ __forceinline__ void lane_pair_exchange(unsigned v, unsigned &from_lo
   asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(from_lower), "+v"(from_upper));
 }
 
+// Lanes 0 to 15 get the value of lanes 16 to 31, lanes 32 to 47 that of 48 to 63; the others keep their own.  Of two copies, v_permlane16_swap
+// exchanges the odd rows of 16 lanes of the first with the even rows of the second.
+__device__ __forceinline__ float of_next_16_lanes(float v) {
+  unsigned first = __builtin_bit_cast(unsigned, v), second = first;
+  asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 1" : "+v"(first), "+v"(second));
+  return __builtin_bit_cast(float, second);
+}
+
 }  // namespace reslim
