@@ -67,6 +67,7 @@ namespace reslim {
 // on the vector unit, looks cheaper and is not: it does not run beside matrix instructions (two waves a SIMD, each one matrix instruction
 // and then eight others: 65 ns with v_dot2c, 39 with conversions or multiplications, 33 with none).  With it a launch of 9.5M-model tiles
 // took 43.8 us, 40.5 now; 37,520 tokens of 32 heads of 128 features 1924 us, 1710 now.
+// The zeros that keep two queries apart do so only while probabilities are finite, see reference_move.
 struct RowSums {
   typedef __attribute__((ext_vector_type(4))) float f32x4;
   f32x4 v;
@@ -90,10 +91,50 @@ struct RowSums {
 
 // Head dimension 64, 32 keys of 32 queries before their exponentials (register r: key 16 (r / 8) + 8 hi + r % 8).  A query's reference is the
 // largest logit of its first 32 keys; it moves to any later 32 keys' largest logit more than kTau above it: by the query's own logits
-// alone, so that what it gets depends neither on its neighbours nor on the shape of the launch.  (Starting from zero needs no first move,
+// alone, so that what it gets depends neither on its neighbours nor, between the kernels with one query group a wave and with two, on the shape of the launch
+// (the kernel that splits the keys over the waves has a reference a wave and sums in another order).  (Starting from zero needs no first move,
 // but then the largest probability is not the 1 that rounding to bf16 leaves as it is: 2.02e-3 of the result in place of 2.00e-3 with logits
 // of a standard deviation of 3.)
 constexpr float kTau = 10.0f;            // in base-2 logits
+
+// How a block of keys moves the references, in every bf16 kernel but the one that splits the keys over the waves.  mx: largest logit above the
+// reference, of this lane's half of the keys; init: minus the reference.  limit: what logits are compared with; not a number while a query of the wave
+// has met no finite logit, which keeps the reference 0 and no weight until it does (first: none has).
+// A query with a logit that is +inf or not a number is lost: with the reference +inf its probabilities are 0 from here on, and 0 / 0 at the end is its row.
+// They must not be what they are: times 0 they would be in the sums of the query 16 away (RowSums).
+// alone: a query moves by its own logits; else, where one moves, all do that have a logit above their reference.
+struct RefMove { float d, alpha, init; bool lost, any_lost; };
+__device__ __forceinline__ RefMove reference_move(float mx, float init, const RowSums &lsum, bool first, bool alone, float &limit, float tau, float c, int lane) {
+  // The two lane halves exchange with v_permlane32_swap, not through LDS: an LDS lane permute makes the wave wait on the LDS counter,
+  // and that wait also covers the direct-to-LDS loads just issued (measured: the prefetch stops being asynchronous).
+  unsigned m_lo, m_up;
+  lane_pair_exchange(__builtin_bit_cast(unsigned, mx), m_lo, m_up);
+  mx = __builtin_elementwise_maximum(__builtin_bit_cast(float, m_lo), __builtin_bit_cast(float, m_up));
+  RefMove m;
+  m.lost = !(mx < INFINITY);
+  m.any_lost = __any(m.lost);
+  bool none = false;
+  if (limit != limit) {
+    none = first || lsum.total(lane) == 0.f;
+    limit = __any(none && mx == -INFINITY && init > -INFINITY) ? __builtin_nanf("") : tau;
+  }
+  const float from = none ? -INFINITY : alone || !__any(mx > tau && !m.lost && !none) ? tau : 0.f;
+  m.d = mx > from ? mx : 0.f;
+  m.alpha = none ? 0.f : __builtin_amdgcn_exp2f(-m.d * c);
+  m.init = init - m.d;
+  if (__builtin_expect(m.any_lost, 0) && m.lost) {
+    m.alpha = 0.f;
+    m.init = -INFINITY;
+  }
+  return m;
+}
+// the scores of a lost query: everything behind them is 0
+__device__ __forceinline__ void drop_lost(f32x16 &s, const RefMove &m) {
+  if (__builtin_expect(m.any_lost, 0)) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = m.lost ? -INFINITY : s[r];
+  }
+}
 __device__ __forceinline__ void mask_block(f32x16 &s, int key0, int n_t, int hi) {      // keys past the tile end get -inf
 #pragma unroll
   for (int r = 0; r < 16; ++r)
@@ -107,27 +148,21 @@ __device__ __forceinline__ float max_of_block(const f32x16 &s) {      // of this
   m0 = max3(m0, s[14], s[15]);
   return __builtin_elementwise_maximum(m0, m1);
 }
-__device__ __forceinline__ void move_reference(f32x16 &s, f32x16 &o0, f32x16 &o1, f32x16 &minit, RowSums &lsum, float mx, bool first, float tau, float c, int lane) {
-  // The two lane halves exchange with v_permlane32_swap, not through LDS: an LDS lane permute makes the wave wait on the LDS counter,
-  // and that wait also covers the direct-to-LDS loads just issued (measured: the prefetch stops being asynchronous).
-  unsigned m_lo, m_up;
-  lane_pair_exchange(__builtin_bit_cast(unsigned, mx), m_lo, m_up);
-  mx = fmaxf(__builtin_bit_cast(float, m_lo), __builtin_bit_cast(float, m_up));
-  const float d = first || mx > tau ? mx : 0.f;
-  const float alpha = first ? 0.f : __builtin_amdgcn_exp2f(-d * c);
-  const float ninit = minit[0] - d;
+__device__ __forceinline__ void move_reference(f32x16 &s, f32x16 &o0, f32x16 &o1, f32x16 &minit, RowSums &lsum, float mx, bool first, float &limit, float tau, float c, int lane) {
+  const RefMove m = reference_move(mx, minit[0], lsum, first, true, limit, tau, c, lane);
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
-    s[r] -= d;
-    minit[r] = ninit;
+    s[r] -= m.d;
+    minit[r] = m.init;
   }
+  drop_lost(s, m);
   if (first) return;                     // uniform: nothing summed yet
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
-    o0[r] *= alpha;
-    o1[r] *= alpha;
+    o0[r] *= m.alpha;
+    o1[r] *= m.alpha;
   }
-  lsum.scale(alpha);
+  lsum.scale(m.alpha);
 }
 
 __device__ __forceinline__ unsigned lds_addr(const unsigned char *p) {
@@ -268,7 +303,7 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
   const bf16x8 ones = RowSums::ones(lane);
   const float c = QS ? 1.0f : a.scale_log2;     // MFMA output -> base-2 logit
   const float TAU = kTau / c;                     // in units of the MFMA output
-  bool have_ref = false;
+  float limit;                                    // TAU, or not a number (reference_move)
   auto reset = [&]() {
 #pragma unroll
     for (int d = 0; d < NDT; ++d)
@@ -277,7 +312,7 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
 #pragma unroll
     for (int r = 0; r < 16; ++r) minit[r] = 0.f;
     lsum.reset();
-    have_ref = false;
+    limit = __builtin_nanf("");
   };
   reset();
   load_q(cur);
@@ -376,14 +411,14 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
         if (kb != 0) {
           if (ragged) mask_block(s[1], kv0 + 32, cur.n_t, hi);
           const float m0 = max_of_block(s[0]);
-          woven = !__any(!(__builtin_elementwise_maximum(m0, max_of_block(s[1])) <= TAU));
-          move = !woven && __any(!(m0 <= TAU));
+          woven = !__any(!(__builtin_elementwise_maximum(m0, max_of_block(s[1])) <= limit));
+          move = !woven && __any(!(m0 <= limit));
         }
         if (move) {
-          move_reference(s[0], o[0], o[1], minit, lsum, max_of_block(s[0]), kb == 0, TAU, c, lane);
+          move_reference(s[0], o[0], o[1], minit, lsum, max_of_block(s[0]), kb == 0, limit, TAU, c, lane);
           score_groups(I1{}, I1{});
           if (ragged) mask_block(s[1], kv0 + 32, cur.n_t, hi);
-          woven = !__any(!(max_of_block(s[1]) <= TAU));
+          woven = !__any(!(max_of_block(s[1]) <= limit));
         }
         if (!woven) {
           // One group after the other.  Same operations in the same order as below, and as in the kernel with two query groups: same bits.
@@ -410,7 +445,7 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
             }
           };
           group(std::integral_constant<int, 0>{});
-          move_reference(s[1], o[0], o[1], minit, lsum, max_of_block(s[1]), false, TAU, c, lane);
+          move_reference(s[1], o[0], o[1], minit, lsum, max_of_block(s[1]), false, limit, TAU, c, lane);
           group(std::integral_constant<int, 1>{});
         }
       }
@@ -428,37 +463,24 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
               if (key >= cur.n_t) s[kt][r] = -INFINITY;
             }
         }
-        float mx = s[0][0];
+        float mx = max_of_block(s[0]);
 #pragma unroll
-        for (int kt = 0; kt < NKT; ++kt)
+        for (int kt = 1; kt < NKT; ++kt) mx = __builtin_elementwise_maximum(mx, max_of_block(s[kt]));
+        if (__any(!(mx <= limit))) {
+          const RefMove m = reference_move(mx, minit[0], lsum, kb == 0, false, limit, TAU, c, lane);
 #pragma unroll
-          for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kt][r]);
-        {
-          // Exchange between the two lane halves with v_permlane32_swap, not through LDS:
-          // an LDS lane permute makes the wave wait on the LDS counter, and that wait
-          // also covers the direct-to-LDS loads of the next block just issued (measured:
-          // the prefetch stops being asynchronous).
-          unsigned m_lo, m_up;
-          lane_pair_exchange(__builtin_bit_cast(unsigned, mx), m_lo, m_up);
-          mx = fmaxf(__builtin_bit_cast(float, m_lo), __builtin_bit_cast(float, m_up));   // finite: every block holds a valid key
-        }
-        if (!have_ref || __any(mx > TAU)) {
-          // move this lane's reference up by d (first block: to the block maximum)
-          const float d = have_ref ? fmaxf(mx, 0.f) : mx;
-          const float alpha = have_ref ? __builtin_amdgcn_exp2f(-d * c) : 0.f;
+          for (int kt = 0; kt < NKT; ++kt) {
 #pragma unroll
-          for (int kt = 0; kt < NKT; ++kt)
+            for (int r = 0; r < 16; ++r) s[kt][r] -= m.d;
+            drop_lost(s[kt], m);
+          }
 #pragma unroll
-            for (int r = 0; r < 16; ++r) s[kt][r] -= d;
+          for (int r = 0; r < 16; ++r) minit[r] = m.init;
 #pragma unroll
           for (int dd = 0; dd < NDT; ++dd)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) o[dd][r] *= alpha;
-          const float ninit = minit[0] - d;
-#pragma unroll
-          for (int r = 0; r < 16; ++r) minit[r] = ninit;
-          lsum.scale(alpha);
-          have_ref = true;
+            for (int r = 0; r < 16; ++r) o[dd][r] *= m.alpha;
+          lsum.scale(m.alpha);
         }
 #pragma unroll
         for (int kt = 0; kt < NKT; ++kt)
@@ -786,6 +808,7 @@ __global__ __launch_bounds__(64 * NW, 2) void tiles_attention_pair_bf16_kernel(A
 
   const float c = QS ? 1.0f : a.scale_log2;     // MFMA output -> base-2 logit
   const float TAU = kTau / c;                     // in units of the MFMA output
+  float limit[2] = {__builtin_nanf(""), __builtin_nanf("")};      // TAU, or not a number (reference_move)
   f32x16 s[2], o[2][2], minit[2];
   bf16x8 p[2][2];
   RowSums lsum[2];
@@ -847,7 +870,6 @@ __global__ __launch_bounds__(64 * NW, 2) void tiles_attention_pair_bf16_kernel(A
     constexpr bool QK = decltype(qk)::value, PV = decltype(pv)::value;
     std::integral_constant<int, GS> gs;
     f32x16 &x = s[GS];
-    const float limit = blk == 0 ? __builtin_nanf("") : TAU;      // not a number: in any case
     if (__builtin_expect(blk * 32 + 32 > n_t, 0)) mask_block(x, blk * 32, n_t, hi);
     if constexpr (QK) score(gm, I0{});
     fence();
@@ -862,7 +884,7 @@ __global__ __launch_bounds__(64 * NW, 2) void tiles_attention_pair_bf16_kernel(A
     m0 = max3(m0, x[10], x[11]); m1 = max3(m1, x[12], x[13]);
     m0 = max3(m0, x[14], x[15]);
     const float mx = __builtin_elementwise_maximum(m0, m1);
-    if (__builtin_expect(__any(!(mx <= limit)), 0)) move_reference(x, o[GS][0], o[GS][1], minit[GS], lsum[GS], mx, blk == 0, TAU, c, lane);
+    if (__builtin_expect(__any(!(mx <= limit[GS])), 0)) move_reference(x, o[GS][0], o[GS][1], minit[GS], lsum[GS], mx, blk == 0, limit[GS], TAU, c, lane);
     fence();
     if constexpr (QK) score(gm, I2{});
     fence();
