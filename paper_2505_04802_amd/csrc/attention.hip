@@ -1389,13 +1389,15 @@ hipError_t launch_tiles_attention(const reslim_ctx *c, const void *qkv, void *ou
     if (g_attn_cus <= 0) return hipErrorInvalidValue;
     const int pg2 = a.total < 2 * g_attn_cus ? a.total : 2 * g_attn_cus;   // persistent grids
     const int pg3 = a.total < 3 * g_attn_cus ? a.total : 3 * g_attn_cus;
+    const int nw = c->dh != 64 ? 0 : g_attn_variant == 0 ? attn_pair_waves(sets * sg.blocks128, sets * sg.blocks256, g_attn_cus) : g_attn_variant == 3 ? 2 : g_attn_variant == 4 ? 4 : 0;
+    const bool pair_fits = nw > 0 && sets * sg.T * ((sg.max_n_tok + 64 * nw - 1) / (64 * nw)) <= most_work_groups(64 * nw);
     if (c->dh == 64 && g_attn_variant == 0 && attn_split_keys(a.total, g_attn_cus, sg.max_n_tok)) {
       const dim3 grid(4 * a.total), blk(256);
       if (stitched && q_prescaled) tiles_attention_split_bf16_kernel<64, true, true><<<grid, blk, 0, st>>>(a);
       else if (stitched) tiles_attention_split_bf16_kernel<64, false, true><<<grid, blk, 0, st>>>(a);
       else if (q_prescaled) tiles_attention_split_bf16_kernel<64, true, false><<<grid, blk, 0, st>>>(a);
       else tiles_attention_split_bf16_kernel<64, false, false><<<grid, blk, 0, st>>>(a);
-    } else if (const int nw = c->dh != 64 ? 0 : g_attn_variant == 0 ? attn_pair_waves(sets * sg.blocks128, sets * sg.blocks256, g_attn_cus) : g_attn_variant == 3 ? 2 : g_attn_variant == 4 ? 4 : 0) {
+    } else if (pair_fits) {
       a.QB = (sg.max_n_tok + 64 * nw - 1) / (64 * nw);
       a.total = static_cast<int>(sets * sg.T * a.QB);
       if (nw == 2) launch_pair<2>(a, q_prescaled, stitched, st);

@@ -34,10 +34,12 @@
 // per-register subtractions: the streamed block carries, per query, a 16-byte record
 // with the value split into three bf16 summands (exact to 2^-24), multiplied by an
 // all-ones B operand (lane half 0 feeds Sx, lane half 1 feeds dPx).
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
 #include "attention_common.h"
+#include "attention_plan.h"
 #include "gelu.h"
 
 namespace reslim {
@@ -52,6 +54,7 @@ struct AttnBwdArgs {
   bf16_t *dqkv;          // [B, n_h, 3, heads, dh]
   const tile_desc *tiles;
   int T, heads, D, QB, total;
+  int first;             // head dimension 64: slot of the launch's first work-group
   int per;               // head dimension 128: blocks of 128 tokens of one sample and head, 0: `total` counts slots of QB a tile
   int part;              // which 1/NSPLIT of the head's features this launch accumulates and writes
   int64_t n_h;
@@ -468,7 +471,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_woven_bf16_kernel(AttnBwdArgs
   __shared__ __align__(1024) unsigned char smem[NST * STAGE];
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int l32 = lane & 31, hi = lane >> 5;
-  const int logical = xcd_remap_attn(blockIdx.x, a.total);
+  const int logical = a.first + xcd_remap_attn(blockIdx.x, gridDim.x);
   const int xb = logical % a.QB;
   int rest = logical / a.QB;
   const int head = rest % a.heads;
@@ -1546,6 +1549,19 @@ static hipError_t launch_bwd_one(const AttnBwdArgs &a0, hipStream_t st) {
   return hipSuccess;
 }
 
+template <bool KV, bool QS>
+static hipError_t launch_bwd_woven(const AttnBwdArgs &a0, hipStream_t st) {
+  AttnBwdArgs a = a0;
+  constexpr int64_t most = most_work_groups(256);
+  for (int64_t first = 0; first < a.total; first += most) {
+    a.first = static_cast<int>(first);
+    attn_bwd_woven_bf16_kernel<KV, QS><<<dim3(static_cast<unsigned>(std::min(most, a.total - first))), dim3(256), 0, st>>>(a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 // Launch shapes (measured on MI355X; the file is built with MFMA operands in ordinary vector
 // registers, see the build script): dh = 64: attn_bwd_woven.  dh = 128: attn_bwd_wide.
 // dh = 256: dQ unsplit on 32-token blocks (15 registers spilled, still faster than two spill-free half passes), dK and dV
@@ -1556,10 +1572,8 @@ static hipError_t launch_bwd_all(const AttnBwdArgs &a, int dh, hipStream_t st) {
   hipError_t e;
   switch (dh) {
     case 64:
-      attn_bwd_woven_bf16_kernel<false, QS><<<dim3(a.total), dim3(256), 0, st>>>(a);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-      attn_bwd_woven_bf16_kernel<true, QS><<<dim3(a.total), dim3(256), 0, st>>>(a);
-      return hipGetLastError();
+      if ((e = launch_bwd_woven<false, QS>(a, st)) != hipSuccess) return e;
+      return launch_bwd_woven<true, QS>(a, st);
     case 128:
       if (!g_bwd_big_ok) return hipErrorInvalidValue;
       attn_bwd_wide_bf16_kernel<false, QS><<<dim3(min(a.total, g_bwd_cus)), dim3(256), wide_lds_bytes(false), st>>>(a);
@@ -1595,6 +1609,7 @@ hipError_t launch_tiles_attention_bwd(const reslim_ctx *c, const void *qkv, cons
     a.heads = heads;
     a.D = D;
     a.n_h = sg.n_h;
+    a.first = a.part = 0;
     a.aux_stride = recs;
     // With q pre-scaled by log2(e)/sqrt(dh) the MFMA output is the base-2 logit; the gradient with
     // respect to the UNSCALED q keeps the factor 1/sqrt(dh), the one of k becomes ln 2 (k meets the

@@ -6,6 +6,10 @@
 
 namespace reslim {
 
+// Work-groups that one launch may have: a dimension of a grid takes fewer than 2^32 threads.  More slots than that are many short tiles, or sequences of which
+// one is long: the forward takes its persistent kernel, the gradient several launches.
+constexpr int64_t most_work_groups(int threads) { return 0xffffffffLL / threads; }
+
 // units: of 128 queries, over the whole launch; cus: compute units; tokens: of the longest tile.
 // The split kernel has four work-groups to a unit, two at a time on a compute unit.  Up to half as many units as compute units
 // they all run at once, and it is 1.2 to 2.6 times as fast from 512 tokens on (512 tokens, 128 units: 12.0 us without the split,

@@ -54,10 +54,12 @@ def plan(tmp_path_factory):
     d = tmp_path_factory.mktemp("attention")
     src, so = d / "plan.cpp", d / "plan.so"
     src.write_text('#include "attention_plan.h"\nextern "C" int ask(int units, int cus, int tokens) { return reslim::attn_split_keys(units, cus, tokens); }\n'
-                   'extern "C" int pair_waves(long long a, long long b, int cus) { return reslim::attn_pair_waves(a, b, cus); }\n')
+                   'extern "C" int pair_waves(long long a, long long b, int cus) { return reslim::attn_pair_waves(a, b, cus); }\n'
+                   'extern "C" long long most(int threads) { return reslim::most_work_groups(threads); }\n')
     cxx = shutil.which("g++") or shutil.which("clang++") or "/opt/rocm/llvm/bin/clang++"
     subprocess.run([cxx, "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, str(src), "-o", str(so)], check=True)
     lib = ctypes.CDLL(str(so))
+    lib.most.restype = ctypes.c_longlong
     lib.pair_waves.argtypes = [ctypes.c_longlong, ctypes.c_longlong, ctypes.c_int]
     return lib
 
@@ -85,6 +87,11 @@ def test_two_query_groups_where_they_gain(plan):
         got = {0: one, 2: two_by_two, 4: two_by_four}[plan.pair_waves(*blocks, 256)]
         assert got <= 1.1 * min(one, two_by_two, two_by_four), (tokens, sets, got)
     assert plan.pair_waves(0, 0, 256) == 0 and plan.pair_waves(2 ** 31 - 1, 2 ** 30, 256) == 4 and plan.pair_waves(2 ** 31, 2 ** 31, 256) == 2
+
+
+def test_a_launch_has_fewer_threads_than_2_to_the_32(plan):
+    for threads in (128, 256):
+        assert plan.most(threads) * threads < 2 ** 32 <= (plan.most(threads) + 1) * threads
 
 
 def test_the_gpu_tests_run_the_kernels_they_name(plan):
