@@ -152,3 +152,19 @@ def test_a_forward_is_the_same_bits_with_every_kernel(cfg, std):
         finally:
             B.reslim_debug_set_attention_variant(0)
     assert torch.isfinite(got[0]).all() and torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
+
+
+@pytest.mark.parametrize("dh", [128, 256])
+@pytest.mark.parametrize("n", [1, 8, 31, 33, 40, 64, 65, 100, 129])
+def test_wide_heads_in_short_tiles(n, dh):
+    """Blocks of keys that the tile ends in (rows past its end are its last row again), beside whole ones; logits so low that anything else there would be all there is."""
+    print(f"attention at head dimension {dh}, tiles of {n} tokens", flush=True)
+    cfg = tiled(n, 4, 1, 4, embed_dim=2 * dh, heads=2)
+    tiles, _, _, n_h = O.tiles_partition(cfg.Hp, cfg.Wp, 1, 4, 0)
+    for kind in ("normal", "low"):
+        qkv = qkv_of(cfg, n_h, kind)
+        with B.Reslim(cfg, WL.make_weights(cfg)) as m:
+            out = m.attention(torch.from_numpy(qkv.astype(np.float32)).cuda().to(m.act_dtype)).float().cpu().numpy()
+        ref = O.tiles_attention(qkv, tiles, 2)
+        elem = 0.05 + 2.0 ** -8 * np.abs(ref).max() / np.sqrt((ref ** 2).mean())      # as above
+        assert_parity(out, ref, 2e-2, "attention", print, k_elem=elem)
