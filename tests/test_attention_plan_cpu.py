@@ -85,7 +85,8 @@ def test_two_query_groups_where_they_gain(plan):
     for tokens, sets, one, two_by_two, two_by_four in PAIRS:
         blocks = [sets * -(-tokens // n) for n in (128, 256)]
         got = {0: one, 2: two_by_two, 4: two_by_four}[plan.pair_waves(*blocks, 256)]
-        assert got <= 1.1 * min(one, two_by_two, two_by_four), (tokens, sets, got)
+        # two groups only where they gain (two runs differ by up to 2 %); with one group, and with the other size of work-group, up to a tenth is left
+        assert got <= 1.01 * one and got <= 1.1 * min(one, two_by_two, two_by_four), (tokens, sets, got)
     assert plan.pair_waves(0, 0, 256) == 0 and plan.pair_waves(2 ** 31 - 1, 2 ** 30, 256) == 4 and plan.pair_waves(2 ** 31, 2 ** 31, 256) == 2
 
 
