@@ -7,12 +7,12 @@
 // P is never stored by the forward: it is recomputed here from Q, K and the
 // log-sum-exp of every query that the forward returns.
 //
-// bf16 path = two launches (three at head dimension 256), no atomics, deterministic:
+// bf16 path = two launches (four at head dimension 256), no atomics, deterministic:
 //   1. KV=0   query-stationary:  dQ.  It has every query's dO in registers and makes delta_i, written together with -lse_i*sqrt(dh) as
 //             16-byte records (see below).  At head dimension 256 a launch before it does, attn_bwd_prep: two passes over memory
 //             (80,704 tokens of 16 heads of 64 features, when it was a launch there: 93 us, 19,584 of 4: 6.6 us);
-//   2. KV=1   key-stationary:    dK and dV.
-// Both are ONE kernel template: attn_bwd_woven at head dimension 64, attn_bwd_wide at 128, attn_bwd at 256.
+//   2. KV=1   key-stationary:    dK and dV (at head dimension 256 in two launches, half of the head's features each).
+// Each head dimension has one kernel template for both: attn_bwd_woven at 64, attn_bwd_wide at 128, attn_bwd at 256.
 // As in the forward kernel a work unit is 128 "stationary" tokens of one (sample, tile, head), 32
 // per wave, kept in registers as MFMA B operands; the other side of the tile is streamed through
 // LDS in blocks of 32 tokens (global -> LDS directly).  Every product is computed
@@ -77,12 +77,11 @@ __device__ __forceinline__ float join3_bf16(uint32_t w0, uint32_t w1) {
          bf16_to_f32(static_cast<bf16_t>(w1 & 0xffffu));
 }
 
-// delta[b, head, tok] = sum over the head's features of dO * O; one thread per 8 features
-template <int DH>
+// head dimension 256: delta[b, head, tok] = sum over the head's features of dO * O; one thread per 8 features
 __global__ __launch_bounds__(256) void attn_bwd_prep_bf16_kernel(const bf16_t *out, const bf16_t *dout, const float *lse,
                                                                  u32x4 *aux, int64_t n_vec, int64_t n_h, int heads,
                                                                  int D, float lse_factor, int64_t aux_stride) {
-  constexpr int LPH = DH / 8;   // lanes per head
+  constexpr int LPH = 256 / 8;  // lanes per head
   const int64_t idx = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
   const bool live = idx < n_vec;
   const int64_t i = live ? idx : 0;
@@ -107,15 +106,21 @@ __global__ __launch_bounds__(256) void attn_bwd_prep_bf16_kernel(const bf16_t *o
   }
 }
 
+// Head dimension 256.
 // KV: keys stationary, dK and dV; else queries, dQ.
 // QS: q in qkv already carries the factor log2(e)/sqrt(dh) (as the fused QKV epilogue of the
 // block leaves it): the MFMA output is the base-2 logit itself.
-// NSPLIT: a launch accumulates only DH / NSPLIT of the head's output features (a.part says which)
-// and recomputes the scores for each part; for heads whose full accumulators do not fit the
-// register file next to the stationary fragments (dh = 256).
-template <int DH, bool KV, bool QS, int NST, int NSPLIT>
+// NSPLIT: a launch accumulates only 1 / NSPLIT of the head's output features (a.part says which)
+// and recomputes the scores for each part: the accumulators of dK and dV do not fit the
+// register file next to the stationary fragments.
+constexpr int kBwd256Stages = 3;
+constexpr int bwd256_lds_bytes(bool kv) { return kBwd256Stages * (2 * 32 * 512 + (kv ? 2 * 32 * 16 : 0)); }
+
+template <bool KV, bool QS, int NSPLIT>
 __global__ __launch_bounds__(256, 1) void attn_bwd_bf16_kernel(AttnBwdArgs a) {
+  constexpr int DH = 256;
   constexpr int BS = 32;                  // streamed tokens of a block
+  constexpr int NST = kBwd256Stages;      // ring of stages
   constexpr int NW = 4;
   constexpr int BX = 32 * NW;             // stationary tokens per unit: 32 per wave
   constexpr int ROWB = DH * 2;
@@ -127,8 +132,7 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_bf16_kernel(AttnBwdArgs a) {
   constexpr int STAGE = 2 * TILE_B + AUXB;
   constexpr int LPW = TILE_B / 1024 / NW;
   constexpr int NKS = DH / 16, NDT = DH / 32 / NSPLIT;   // NDT: 32-feature blocks of the accumulators
-  static_assert(TILE_B % (1024 * NW) == 0 && AUXB % 1024 == 0 && NST * STAGE <= 160 * 1024, "LDS plan");
-  static_assert(NST == 3, "ring of three stages");
+  static_assert(TILE_B % (1024 * NW) == 0 && AUXB % 1024 == 0 && NST * STAGE == bwd256_lds_bytes(KV), "LDS plan");
   extern __shared__ __align__(1024) unsigned char smem[];   // NST * STAGE bytes
 
   const int t = threadIdx.x, lane = t & 63;
@@ -918,7 +922,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_woven_bf16_kernel(AttnBwdArgs
 
 // ------------------------------------------------------------------ head dimension 128: the same weave, one wave a SIMD
 // The phases of attn_bwd_woven, with twice the products for the same exponentials: 24 matrix instructions a phase query-stationary, 34
-// key-stationary.  The accumulators, the stationary rows and a phase's fragments take 383 and 408 registers, so one wave a SIMD and nothing else to fill its
+// key-stationary.  The accumulators, the stationary rows and a phase's fragments take 398 and 419 registers, so one wave a SIMD and nothing else to fill its
 // gaps: the second half of a block's rows is read during the products, and columns and rows lie in accumulator registers, which the matrix
 // instructions read as well and vector code does not need.  One work-group to a compute unit walks its units; the loads run six blocks ahead across
 // units, and the next unit's stationary rows arrive during a unit's last products.  Every sum has the order of the kernel for head dimension 256: the same bits.
@@ -1500,9 +1504,6 @@ __global__ __launch_bounds__(128) void attn_bwd_f32_kernel(const float *qkv, con
   }
 }
 
-template <int DH, int NST>
-constexpr int bwd_lds_bytes(bool kv) { return NST * (2 * 32 * DH * 2 + (kv ? 2 * 32 * 16 : 0)); }
-
 static int g_bwd_cus = 0;
 static bool g_bwd_big_ok = false;
 
@@ -1520,10 +1521,10 @@ hipError_t attention_bwd_init() {
       {reinterpret_cast<const void *>(&attn_bwd_wide_bf16_kernel<false, true>), wide_lds_bytes(false)},
       {reinterpret_cast<const void *>(&attn_bwd_wide_bf16_kernel<true, false>), wide_lds_bytes(true)},
       {reinterpret_cast<const void *>(&attn_bwd_wide_bf16_kernel<true, true>), wide_lds_bytes(true)},
-      {reinterpret_cast<const void *>(&attn_bwd_bf16_kernel<256, false, false, 3, 1>), bwd_lds_bytes<256, 3>(false)},
-      {reinterpret_cast<const void *>(&attn_bwd_bf16_kernel<256, false, true, 3, 1>), bwd_lds_bytes<256, 3>(false)},
-      {reinterpret_cast<const void *>(&attn_bwd_bf16_kernel<256, true, false, 3, 2>), bwd_lds_bytes<256, 3>(true)},
-      {reinterpret_cast<const void *>(&attn_bwd_bf16_kernel<256, true, true, 3, 2>), bwd_lds_bytes<256, 3>(true)},
+      {reinterpret_cast<const void *>(&attn_bwd_bf16_kernel<false, false, 1>), bwd256_lds_bytes(false)},
+      {reinterpret_cast<const void *>(&attn_bwd_bf16_kernel<false, true, 1>), bwd256_lds_bytes(false)},
+      {reinterpret_cast<const void *>(&attn_bwd_bf16_kernel<true, false, 2>), bwd256_lds_bytes(true)},
+      {reinterpret_cast<const void *>(&attn_bwd_bf16_kernel<true, true, 2>), bwd256_lds_bytes(true)},
   };
   for (const Big &k : big) {
     e = hipFuncSetAttribute(k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, k.bytes);
@@ -1540,12 +1541,12 @@ size_t tiles_attention_bwd_ws_bytes(const reslim_ctx *c, int batch, const SeqGeo
   return c->cfg.dtype == RESLIM_BF16 ? align256(recs * 32) : align256(recs * 4);
 }
 
-template <int DH, bool KV, bool QS, int NST, int NSPLIT>
-static hipError_t launch_bwd_one(const AttnBwdArgs &a0, hipStream_t st) {
+template <bool KV, bool QS, int NSPLIT>
+static hipError_t launch_bwd_256(const AttnBwdArgs &a0, hipStream_t st) {
   const int g = a0.total < g_bwd_cus ? a0.total : g_bwd_cus;    // persistent grid
   AttnBwdArgs a = a0;
   for (a.part = 0; a.part < NSPLIT; ++a.part) {
-    attn_bwd_bf16_kernel<DH, KV, QS, NST, NSPLIT><<<dim3(g), dim3(256), bwd_lds_bytes<DH, NST>(KV), st>>>(a);
+    attn_bwd_bf16_kernel<KV, QS, NSPLIT><<<dim3(g), dim3(256), bwd256_lds_bytes(KV), st>>>(a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -1585,8 +1586,8 @@ static hipError_t launch_bwd_all(const AttnBwdArgs &a, int dh, hipStream_t st) {
       return hipGetLastError();
     case 256:
       if (!g_bwd_big_ok) return hipErrorInvalidValue;
-      e = launch_bwd_one<256, false, QS, 3, 1>(a, st);
-      return e != hipSuccess ? e : launch_bwd_one<256, true, QS, 3, 2>(a, st);
+      e = launch_bwd_256<false, QS, 1>(a, st);
+      return e != hipSuccess ? e : launch_bwd_256<true, QS, 2>(a, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1632,18 +1633,15 @@ hipError_t launch_tiles_attention_bwd(const reslim_ctx *c, const void *qkv, cons
     const int64_t slots = static_cast<int64_t>(sg.T) * a.QB;
     a.per = dh == 128 && sg.T <= 64 && a.QB > 3 && total > g_bwd_cus && 50 * (slots - sg.blocks128) >= slots ? static_cast<int>(sg.blocks128) : 0;
     if (a.per) a.total = batch * heads * a.per;
-    const int64_t n_vec = static_cast<int64_t>(batch) * sg.n_h * D / 8;
-    const unsigned pg = static_cast<unsigned>((n_vec + 255) / 256);
     // record 0 holds -lse in the unit of the MFMA output: -lse*sqrt(dh), or -lse*log2(e) for pre-scaled q
     const float lse_f = q_prescaled ? 1.4426950408889634f : sqrtf(static_cast<float>(dh));
     a.lse_f = lse_f;
-    switch (dh) {
-      case 64: case 128: break;            // the query-stationary launch does it
-      case 256: attn_bwd_prep_bf16_kernel<256><<<dim3(pg), dim3(256), 0, st>>>(a.out, a.dout, lse, a.aux, n_vec, sg.n_h, heads, D, lse_f, recs); break;
-      default: return hipErrorInvalidValue;
+    if (dh == 256) {                       // at 64 and 128 the query-stationary launch does it
+      const int64_t n_vec = static_cast<int64_t>(batch) * sg.n_h * D / 8;
+      attn_bwd_prep_bf16_kernel<<<dim3(static_cast<unsigned>((n_vec + 255) / 256)), dim3(256), 0, st>>>(a.out, a.dout, lse, a.aux, n_vec, sg.n_h, heads, D, lse_f, recs);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
     }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
     return q_prescaled ? launch_bwd_all<true>(a, dh, st) : launch_bwd_all<false>(a, dh, st);
   }
   float *delta = static_cast<float *>(ws);
