@@ -66,7 +66,7 @@ namespace reslim {
 // It takes the matrix unit for half as long as one instruction of the P V product.  v_dot2c_f32_bf16, two probabilities an instruction
 // on the vector unit, looks cheaper and is not: it does not run beside matrix instructions (two waves a SIMD, each one matrix instruction
 // and then eight others: 65 ns with v_dot2c, 39 with conversions or multiplications, 33 with none).  With it a launch of 9.5M-model tiles
-// took 43.8 us, 40.5 now; 37,520 tokens of 32 heads of 128 features 1924 us, 1710 now.
+// took 43.8 us, 40.5 with this; 37,520 tokens of 32 heads of 128 features 1924 us and 1710.
 // The zeros that keep two queries apart do so only while probabilities are finite, see reference_move.
 struct RowSums {
   typedef __attribute__((ext_vector_type(4))) float f32x4;
@@ -984,8 +984,9 @@ __global__ __launch_bounds__(64 * NW, 2) void tiles_attention_pair_bf16_kernel(A
 // feeds K and V from L2 (every 32 queries read all of them) and the chain of a wave's blocks; so it is for few queries only, see attention_plan.h.
 //
 // A wave's K and V tiles (32 keys, 4 KiB each) go through a ring of its own of five tiles in the order K0 V0 K1 V1 ...: when
-// tile i has been read its place takes tile i + 5, so two blocks are in flight and two work-groups fit a compute unit.  Fragments,
-// swizzles, the running reference and the row sums are those of the kernel above.
+// tile i has been read its place takes tile i + 5, so two blocks are in flight and two work-groups fit a compute unit.  Fragments and
+// swizzles are those of the kernels above.  A reference is of a wave's keys and moves for all of its queries at once, and the row sums are a lane's own, so the
+// last bits are not those of the kernels above; a wave whose first 32 keys all have logits of -inf for a query leaves that query not a number.
 template <int DH, bool QS, bool ST>
 __global__ __launch_bounds__(256, 2) void tiles_attention_split_bf16_kernel(AttnArgs a) {
   static_assert(DH == 64, "fragment tables below");
