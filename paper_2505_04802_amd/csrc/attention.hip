@@ -90,9 +90,11 @@ struct RowSums {
 };
 
 // Head dimension 64, 32 keys of 32 queries before their exponentials (register r: key 16 (r / 8) + 8 hi + r % 8).  A query's reference is the
-// largest logit of its first 32 keys; it moves to any later 32 keys' largest logit more than kTau above it: by the query's own logits
-// alone, so that what it gets depends neither on its neighbours nor, between the kernels with one query group a wave and with two, on the shape of the launch
-// (the kernel that splits the keys over the waves has a reference a wave and sums in another order).  (Starting from zero needs no first move,
+// largest logit of its first 32 keys.  Where a later 32 keys have one more than kTau above some query's reference, every one of the 32 queries moves to the largest
+// that it meets there: that makes the next moves rarer and leaves the largest probability at 1 more often than moves by a query's own logits alone (logits of a standard
+// deviation of 9, 1290 tokens: 50.2 us at 64 sets of keys and 325 at 512, error 1.683e-3; alone 51.5, 341 and 1.691e-3).  The 32 are the same in the kernel with one
+// query group a wave and with two, so what a query gets does not depend on the shape of the launch between these (the kernel that splits the keys over the waves has a
+// reference a wave and sums in another order).  (Starting from zero needs no first move,
 // but then the largest probability is not the 1 that rounding to bf16 leaves as it is: 2.02e-3 of the result in place of 2.00e-3 with logits
 // of a standard deviation of 3.)
 constexpr float kTau = 10.0f;            // in base-2 logits
@@ -101,10 +103,9 @@ constexpr float kTau = 10.0f;            // in base-2 logits
 // reference, of this lane's half of the keys; init: minus the reference.  limit: what logits are compared with; not a number while a query of the wave
 // has met no finite logit, which keeps the reference 0 and no weight until it does (first: none has).
 // A query with a logit that is +inf or not a number is lost: with the reference +inf its probabilities are 0 from here on, and 0 / 0 at the end is its row.
-// They must not be what they are: times 0 they would be in the sums of the query 16 away (RowSums).
-// alone: a query moves by its own logits; else, where one moves, all do that have a logit above their reference.
+// They must not be what they are: times 0 they would be in the sums of the query 16 away (RowSums).  Nor does it move the others' references.
 struct RefMove { float d, alpha, init; bool lost, any_lost; };
-__device__ __forceinline__ RefMove reference_move(float mx, float init, const RowSums &lsum, bool first, bool alone, float &limit, float tau, float c, int lane) {
+__device__ __forceinline__ RefMove reference_move(float mx, float init, const RowSums &lsum, bool first, float &limit, float tau, float c, int lane) {
   // The two lane halves exchange with v_permlane32_swap, not through LDS: an LDS lane permute makes the wave wait on the LDS counter,
   // and that wait also covers the direct-to-LDS loads just issued (measured: the prefetch stops being asynchronous).
   unsigned m_lo, m_up;
@@ -118,7 +119,7 @@ __device__ __forceinline__ RefMove reference_move(float mx, float init, const Ro
     none = first || lsum.total(lane) == 0.f;
     limit = __any(none && mx == -INFINITY && init > -INFINITY) ? __builtin_nanf("") : tau;
   }
-  const float from = none ? -INFINITY : alone || !__any(mx > tau && !m.lost && !none) ? tau : 0.f;
+  const float from = none ? -INFINITY : __any(mx > tau && !m.lost && !none) ? 0.f : tau;
   m.d = mx > from ? mx : 0.f;
   m.alpha = none ? 0.f : __builtin_amdgcn_exp2f(-m.d * c);
   m.init = init - m.d;
@@ -149,7 +150,7 @@ __device__ __forceinline__ float max_of_block(const f32x16 &s) {      // of this
   return __builtin_elementwise_maximum(m0, m1);
 }
 __device__ __forceinline__ void move_reference(f32x16 &s, f32x16 &o0, f32x16 &o1, f32x16 &minit, RowSums &lsum, float mx, bool first, float &limit, float tau, float c, int lane) {
-  const RefMove m = reference_move(mx, minit[0], lsum, first, true, limit, tau, c, lane);
+  const RefMove m = reference_move(mx, minit[0], lsum, first, limit, tau, c, lane);
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     s[r] -= m.d;
@@ -412,7 +413,7 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
         // block those of the second group are computed behind the move, later (rare) once more.  A lane's products wait for the first move
         // of every tile, so what it costs is the smallest launches' time: 1 token, 256 sets of keys 4.05 us (4.80 with both groups' scores before the move, the second's
         // again and each V fragment waited for by itself), 100 tokens, 1024 sets 15.2 (16.1).  Logits of a standard deviation of 3, 200 tokens, 256 sets
-        // 11.1 us (12.8; of 0.3 10.9), 1290 tokens, 64 sets 42.8 (45.5; 40.8); of 9, where nearly every block of a wave moves some query, 51.5 (55.3).
+        // 11.1 us (12.8; of 0.3 10.9), 1290 tokens, 64 sets 42.8 (45.5; 40.8); of 9, where most blocks of a wave move some query, 50.2 (55.3).
         const bool ragged = kv0 + BKV > cur.n_t;
         bool move = kb == 0;               // at the first group; woven: not at the second
         if (ragged) mask_block(s[0], kv0, cur.n_t, hi);
@@ -475,7 +476,7 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
 #pragma unroll
         for (int kt = 1; kt < NKT; ++kt) mx = __builtin_elementwise_maximum(mx, max_of_block(s[kt]));
         if (__any(!(mx <= limit))) {
-          const RefMove m = reference_move(mx, minit[0], lsum, kb == 0, false, limit, TAU, c, lane);
+          const RefMove m = reference_move(mx, minit[0], lsum, kb == 0, limit, TAU, c, lane);
 #pragma unroll
           for (int kt = 0; kt < NKT; ++kt) {
 #pragma unroll
