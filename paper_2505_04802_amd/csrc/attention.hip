@@ -90,13 +90,13 @@ struct RowSums {
 };
 
 // Head dimension 64, 32 keys of 32 queries before their exponentials (register r: key 16 (r / 8) + 8 hi + r % 8).  A query's reference is the
-// largest logit of its first 32 keys.  Where a later 32 keys have one more than kTau above some query's reference, every one of the 32 queries moves to the largest
-// that it meets there: that makes the next moves rarer and leaves the largest probability at 1 more often than moves by a query's own logits alone (logits of a standard
-// deviation of 9, 1290 tokens: 50.2 us at 64 sets of keys and 325 at 512, error 1.683e-3; alone 51.5, 341 and 1.691e-3).  The 32 are the same in the kernel with one
+// largest logit of its tile's first 64 keys; of the first 32 it would be the 1 that rounding to bf16 leaves as it is for fewer queries (error of the output with logits of
+// a standard deviation of 1, 64 tokens 2.08e-3 and 2.14e-3, 1290 tokens 2.317e-3 and 2.321e-3; from zero, without a first move, 1 % more with logits of 3).
+// Where a later 32 keys have a logit more than kTau above some query's reference, every one of the 32 queries moves to the largest that it meets there: that
+// makes the next moves rarer and leaves the largest probability at 1 more often than moves by a query's own logits alone (logits of a standard
+// deviation of 9, 1290 tokens: 325 us at 512 sets of keys, error 1.683e-3; alone 341 and 1.691e-3).  The 32 are the same in the kernel with one
 // query group a wave and with two, so what a query gets does not depend on the shape of the launch between these (the kernel that splits the keys over the waves has a
-// reference a wave and sums in another order).  (Starting from zero needs no first move,
-// but then the largest probability is not the 1 that rounding to bf16 leaves as it is: 2.02e-3 of the result in place of 2.00e-3 with logits
-// of a standard deviation of 3.)
+// reference a wave and sums in another order).
 constexpr float kTau = 10.0f;            // in base-2 logits
 
 // How a block of keys moves the references, in every bf16 kernel but the one that splits the keys over the waves.  mx: largest logit above the
@@ -149,20 +149,29 @@ __device__ __forceinline__ float max_of_block(const f32x16 &s) {      // of this
   m0 = max3(m0, s[14], s[15]);
   return __builtin_elementwise_maximum(m0, m1);
 }
-__device__ __forceinline__ void move_reference(f32x16 &s, f32x16 &o0, f32x16 &o1, f32x16 &minit, RowSums &lsum, float mx, bool first, float &limit, float tau, float c, int lane) {
-  const RefMove m = reference_move(mx, minit[0], lsum, first, limit, tau, c, lane);
+// A tile's first 64 keys, scores from zero
+__device__ __forceinline__ void first_reference(f32x16 &s0, f32x16 &s1, f32x16 &minit, const RowSums &lsum, float &limit, float tau, float c, int lane) {
+  const RefMove m = reference_move(__builtin_elementwise_maximum(max_of_block(s0), max_of_block(s1)), minit[0], lsum, true, limit, tau, c, lane);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    s0[r] -= m.d;
+    s1[r] -= m.d;
+    minit[r] = m.init;
+  }
+  drop_lost(s0, m);
+  drop_lost(s1, m);
+}
+// 32 later ones
+__device__ __forceinline__ void move_reference(f32x16 &s, f32x16 &o0, f32x16 &o1, f32x16 &minit, RowSums &lsum, float mx, float &limit, float tau, float c, int lane) {
+  const RefMove m = reference_move(mx, minit[0], lsum, false, limit, tau, c, lane);
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     s[r] -= m.d;
     minit[r] = m.init;
-  }
-  drop_lost(s, m);
-  if (first) return;                     // uniform: nothing summed yet
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
     o0[r] *= m.alpha;
     o1[r] *= m.alpha;
   }
+  drop_lost(s, m);
   lsum.scale(m.alpha);
 }
 
@@ -368,12 +377,7 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
       __builtin_amdgcn_s_setprio(PQK);
       // feature step outermost: consecutive MFMAs belong to different accumulator chains
       if constexpr (PIPE) {
-        if (kb == 0) {
-          score_groups(I0{}, I1{});                // the second group's follow from the reference that these set
-          asm volatile("" : "=v"(s[1]));           // (any value: without one the registers would be kept from the block before)
-        } else {
-          score_groups(I0{}, I2{});
-        }
+        score_groups(I0{}, I2{});
       } else if constexpr (DH <= 128) {
 #pragma unroll
         for (int ks = 0; ks < NKS; ++ks) {
@@ -409,25 +413,40 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
     bool woven = true;
     if constexpr (PIPE) {
       if (active) {
-        // A reference moves at a group of 32 keys, by the group's own logits, and the scores behind it start from where it went: at a tile's first
-        // block those of the second group are computed behind the move, later (rare) once more.  A lane's products wait for the first move
-        // of every tile, so what it costs is the smallest launches' time: 1 token, 256 sets of keys 4.05 us (4.80 with both groups' scores before the move, the second's
-        // again and each V fragment waited for by itself), 100 tokens, 1024 sets 15.2 (16.1).  Logits of a standard deviation of 3, 200 tokens, 256 sets
-        // 11.1 us (12.8; of 0.3 10.9), 1290 tokens, 64 sets 42.8 (45.5; 40.8); of 9, where most blocks of a wave move some query, 50.2 (55.3).
+        // The first block's 64 keys give the references; later ones move at a group of 32 keys, by the group's logits, and the scores behind start from where they went:
+        // where they move at the first group the second's are computed once more.  One branch for both, which the first block of every tile takes, so what it costs is
+        // the smallest launches' time (1 token, 256 sets of keys 4.16 us; 4.80 with the first 32 keys' references, the second group's scores again and each V fragment waited for by
+        // itself).  Logits of a standard deviation of 0.3, 3 and 9: 400 tokens, 64 sets 11.4, 11.7 and 14.2 us, 1290 tokens 40.1, 41.7 and 49.3.
         const bool ragged = kv0 + BKV > cur.n_t;
-        bool move = kb == 0;               // at the first group; woven: not at the second
-        if (ragged) mask_block(s[0], kv0, cur.n_t, hi);
-        if (kb != 0) {
-          if (ragged) mask_block(s[1], kv0 + 32, cur.n_t, hi);
-          const float m0 = max_of_block(s[0]);
-          woven = !__any(!(__builtin_elementwise_maximum(m0, max_of_block(s[1])) <= limit));
-          move = !woven && __any(!(m0 <= limit));
+        if (ragged) {
+          mask_block(s[0], kv0, cur.n_t, hi);
+          mask_block(s[1], kv0 + 32, cur.n_t, hi);
         }
-        if (move) {
-          move_reference(s[0], o[0], o[1], minit, lsum, max_of_block(s[0]), kb == 0, limit, TAU, c, lane);
-          score_groups(I1{}, I1{});
-          if (ragged) mask_block(s[1], kv0 + 32, cur.n_t, hi);
-          woven = !__any(!(max_of_block(s[1]) <= limit));
+        const float m0 = max_of_block(s[0]), m01 = __builtin_elementwise_maximum(m0, max_of_block(s[1]));
+        if (__any(!(m01 <= limit))) {
+          const bool first = kb == 0;
+          woven = first;
+          if (first || __any(!(m0 <= limit))) {
+            const RefMove m = reference_move(first ? m01 : m0, minit[0], lsum, first, limit, TAU, c, lane);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              s[0][r] -= m.d;
+              o[0][r] *= m.alpha;
+              o[1][r] *= m.alpha;
+              minit[r] = m.init;
+            }
+            lsum.scale(m.alpha);
+            drop_lost(s[0], m);
+            if (first) {
+#pragma unroll
+              for (int r = 0; r < 16; ++r) s[1][r] -= m.d;
+              drop_lost(s[1], m);
+            } else {
+              score_groups(I1{}, I1{});
+              if (ragged) mask_block(s[1], kv0 + 32, cur.n_t, hi);
+              woven = !__any(!(max_of_block(s[1]) <= limit));      // no reference moves at the second group
+            }
+          }
         }
         if (!woven) {
           // One group after the other.  Same operations in the same order as below, and as in the kernel with two query groups: same bits.
@@ -454,7 +473,7 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
             }
           };
           group(std::integral_constant<int, 0>{});
-          move_reference(s[1], o[0], o[1], minit, lsum, max_of_block(s[1]), false, limit, TAU, c, lane);
+          move_reference(s[1], o[0], o[1], minit, lsum, max_of_block(s[1]), limit, TAU, c, lane);
           group(std::integral_constant<int, 1>{});
         }
       }
@@ -690,6 +709,7 @@ __global__ __launch_bounds__(256, MINW) void tiles_attention_bf16_kernel(AttnArg
 // wave has two groups of 32 queries, A and B, and every phase of 32 keys weaves the matrix instructions of one (scores of the next
 // block, P V of the last) with the softmax of the other:
 //   phase 0: S_A(i + 1), O_A += V(i) P_A(i)  beside the softmax of S_B(i);   phase 1: S_B(i + 1), O_B += V(i) P_B(i)  beside that of S_A(i + 1)
+// The first two blocks' scores come first: their largest is the reference.
 // Fragments of K and V are read from LDS once for both.  Order within a phase is pinned, one matrix instruction and what fits beside it
 // at a time (scheduling barriers; the empty statements keep the compiler from sinking vector work out of its place).
 // A block of 32 keys is 8 KiB; four lie in LDS, two of them in flight (five to ten took the same time).  K fragments of block i + 2 are read as soon as
@@ -874,28 +894,28 @@ __global__ __launch_bounds__(64 * NW, 2) void tiles_attention_pair_bf16_kernel(A
   typedef std::integral_constant<int, 4> I4;
   typedef std::integral_constant<int, 8> I8;
   typedef std::integral_constant<int, 12> I12;
-  // One phase: matrix instructions of group gm (scores of a block where qk, P V of the block before where pv) with the softmax of block
-  // blk of the other group between them.
-  auto phase = [&](auto gm, auto qk, auto pv, int blk) __attribute__((always_inline)) {
+  // One phase: matrix instructions of group gm (scores of a block where qk is 2, P V of the block before where pv) with the softmax of block
+  // blk of the other group between them; with qk of 1 and 2 the loads that go with it.  known: the references are what these scores gave.
+  auto phase = [&](auto gm, auto qk, auto pv, auto known, int blk) __attribute__((always_inline)) {
     constexpr int GM = decltype(gm)::value, GS = 1 - GM;
-    constexpr bool QK = decltype(qk)::value, PV = decltype(pv)::value;
+    constexpr bool QK = decltype(qk)::value == 2, LD = decltype(qk)::value >= 1 && GM == 1, PV = decltype(pv)::value, NEW = !decltype(known)::value;
     std::integral_constant<int, GS> gs;
     f32x16 &x = s[GS];
-    if (__builtin_expect(blk * 32 + 32 > n_t, 0)) mask_block(x, blk * 32, n_t, hi);
+    if (NEW && __builtin_expect(blk * 32 + 32 > n_t, 0)) mask_block(x, blk * 32, n_t, hi);
     if constexpr (QK) score(gm, I0{});
     fence();
-    if constexpr (PV && QK && GM == 1) { next_block(); load_keys(); }
+    if constexpr (LD) { next_block(); load_keys(); }
     if constexpr (PV && GM == 0) issue_v();
     float m0 = max3(x[0], x[1], x[2]), m1 = max3(x[3], x[4], x[5]);
     m0 = max3(m0, x[6], x[7]); m1 = max3(m1, x[8], x[9]);
     fence();
     if constexpr (QK) score(gm, I1{});
     fence();
-    if constexpr (PV && QK && GM == 1) load_values();
+    if constexpr (LD) load_values();
     m0 = max3(m0, x[10], x[11]); m1 = max3(m1, x[12], x[13]);
     m0 = max3(m0, x[14], x[15]);
     const float mx = __builtin_elementwise_maximum(m0, m1);
-    if (__builtin_expect(__any(!(mx <= limit[GS])), 0)) move_reference(x, o[GS][0], o[GS][1], minit[GS], lsum[GS], mx, blk == 0, limit[GS], TAU, c, lane);
+    if (NEW && __builtin_expect(__any(!(mx <= limit[GS])), 0)) move_reference(x, o[GS][0], o[GS][1], minit[GS], lsum[GS], mx, limit[GS], TAU, c, lane);
     fence();
     if constexpr (QK) score(gm, I2{});
     fence();
@@ -903,7 +923,7 @@ __global__ __launch_bounds__(64 * NW, 2) void tiles_attention_pair_bf16_kernel(A
     fence();
     if constexpr (QK) score(gm, I3{});
     fence();
-    if constexpr (QK && GM == 1) read_k();       // of the block after; past the last one zeros
+    if constexpr (LD) read_k();                  // of the block after; past the last one zeros
     exps(gs, I4{});
     if constexpr (PV && GM == 0) v_frag_wait(vf);
     fence();
@@ -930,16 +950,42 @@ __global__ __launch_bounds__(64 * NW, 2) void tiles_attention_pair_bf16_kernel(A
   typedef std::true_type Yes;
   typedef std::false_type No;
 
+  // The first two blocks' scores, from zero, give the references; the second's stay where the outputs will be.
+  f32x16 second[2];
+  auto scores = [&](f32x16 &x, int g) __attribute__((always_inline)) {
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], q[g][ks], ks == 0 ? minit[g] : x, 0, 0, 0);
+  };
   read_k();
-  score(I0{}, I0{}); score(I0{}, I1{}); score(I0{}, I2{}); score(I0{}, I3{});
-  phase(I1{}, Yes{}, No{}, 0);
-#pragma unroll 1
-  for (int i = 0; i + 1 < nkb; ++i) {
-    phase(I0{}, Yes{}, Yes{}, i);
-    landed();                            // block i + 2; everybody has left block i, whose place takes block i + NST
-    phase(I1{}, Yes{}, Yes{}, i + 1);
+  scores(s[0], 0);
+  scores(s[1], 1);
+  read_k();
+  scores(second[0], 0);
+  scores(second[1], 1);
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    if (n_t < 32) mask_block(s[g], 0, n_t, hi);
+    if (n_t < 64) mask_block(second[g], 32, n_t, hi);
+    first_reference(s[g], second[g], minit[g], lsum[g], limit[g], TAU, c, lane);
   }
-  phase(I0{}, No{}, Yes{}, nkb - 1);
+  typedef std::integral_constant<int, 0> None;
+  typedef std::integral_constant<int, 1> Loads;
+  typedef std::integral_constant<int, 2> Scores;
+  phase(I1{}, None{}, No{}, Yes{}, 0);
+  if (nkb > 1) {
+    s[0] = second[0];
+    phase(I0{}, None{}, Yes{}, Yes{}, 0);
+    s[1] = second[1];
+    landed();                            // block 2; everybody has left block 0, whose place takes block NST
+    phase(I1{}, Loads{}, Yes{}, Yes{}, 1);
+  }
+#pragma unroll 1
+  for (int i = 1; i + 1 < nkb; ++i) {
+    phase(I0{}, Scores{}, Yes{}, No{}, i);
+    landed();                            // block i + 2; everybody has left block i, whose place takes block i + NST
+    phase(I1{}, Scores{}, Yes{}, No{}, i + 1);
+  }
+  phase(I0{}, None{}, Yes{}, No{}, nkb - 1);
   value(I1{}, I0{}); value(I1{}, I1{}); value(I1{}, I2{}); value(I1{}, I3{});
   add_up(I1{}, I0{});
   add_up(I1{}, I1{});
@@ -1401,7 +1447,7 @@ hipError_t launch_tiles_attention(const reslim_ctx *c, const void *qkv, void *ou
     if (g_attn_cus <= 0) return hipErrorInvalidValue;
     const int pg2 = a.total < 2 * g_attn_cus ? a.total : 2 * g_attn_cus;   // persistent grids
     const int pg3 = a.total < 3 * g_attn_cus ? a.total : 3 * g_attn_cus;
-    const int nw = c->dh != 64 ? 0 : g_attn_variant == 0 ? attn_pair_waves(sets * sg.blocks128, sets * sg.blocks256, g_attn_cus) : g_attn_variant == 3 ? 2 : g_attn_variant == 4 ? 4 : 0;
+    const int nw = c->dh != 64 ? 0 : g_attn_variant == 0 ? attn_pair_waves(sets * sg.blocks128, sets * sg.blocks256, g_attn_cus, sg.max_n_tok) : g_attn_variant == 3 ? 2 : g_attn_variant == 4 ? 4 : 0;
     const bool pair_fits = nw > 0 && sets * sg.T * ((sg.max_n_tok + 64 * nw - 1) / (64 * nw)) <= most_work_groups(64 * nw);
     if (c->dh == 64 && g_attn_variant == 0 && attn_split_keys(a.total, g_attn_cus, sg.max_n_tok)) {
       const dim3 grid(4 * a.total), blk(256);

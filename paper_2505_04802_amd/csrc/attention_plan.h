@@ -24,7 +24,7 @@ inline bool attn_split_keys(int units, int cus, int tokens) {
 }
 
 // Waves in a work-group of the kernel with two query groups a wave, 0: the kernel with one.
-// Both give the same bits.  u128, u256: tokens of all tiles, samples and heads in blocks of 128 and of 256 queries; cus: compute units.
+// Both give the same bits.  u128, u256: tokens of all tiles, samples and heads in blocks of 128 and of 256 queries; cus: compute units; tokens: of the longest tile.
 // Where every SIMD has work for two waves and more, two groups a wave are 1.05 to 1.2 times as fast (blocks of 128 queries per compute unit in
 // brackets; one group, two): 1290 tokens, 512 sets of keys (22) 276 and 251 us; 660, 1024 (24) 189 and 159; 2000, 64 (4) 89 and 73; 400, 256 (4) 26.8 and
 // 23.5.  One group a wave keeps three blocks on a compute unit, two groups four and half as many waves to give them.  Up to three blocks all
@@ -36,7 +36,10 @@ inline bool attn_split_keys(int units, int cus, int tokens) {
 // third more: 49 and 65; 1290, 256, a tenth more: 143 and 132).  Two waves leave fewer idle and are twice as many work-groups to start: for
 // launches of 32 blocks a compute unit and more, where that leaves a twentieth fewer waves (tiles of 1274 to 1643 tokens, 203 blocks: 2.77 ms
 // with four, 2.71 with two; 520 tokens, 40 blocks 249 us with one group, 226 with two waves of two; 1290 tokens, 11 blocks 132 with four, 139).
-inline int attn_pair_waves(int64_t u128, int64_t u256, int cus) {
+// Up to 40 tokens the second group has no or few queries and a tile is over with the first two blocks of keys (16,384 sets: 33 tokens 83.7 us with one group, 88.8 with
+// two, 40 tokens 102.7 and 102.1, 48 118.9 and 109.9; 8192 sets of 48 46.1 and 48.4, of 64 56.3 and 53.3).
+inline int attn_pair_waves(int64_t u128, int64_t u256, int cus, int tokens) {
+  if (tokens <= 40) return 0;
   if (u128 <= 3LL * cus || (u128 > 4LL * cus && 2 * u128 <= 9LL * cus)) return 0;
   if (u128 >= 32LL * cus && 20 * u128 <= 19 * 2 * u256) return 2;
   return 10 * 2 * u256 <= 11 * u128 ? 4 : 0;

@@ -46,7 +46,11 @@ PAIRS = [(130, 384, 10.7, 11.9, 11.3), (130, 512, 15.1, 14.4, 12.5), (130, 1024,
          192, 225.2, 204.8, 194.4), (2000, 256, 284.5, 261.0, 248.4), (2000, 384, 428.1, 397.7, 377.7), (2000, 512, 565.6, 522.0, 492.8),
          (2000, 1024, 1108.0, 1020.7, 983.3), (4200, 16, 98.8, 116.5, 115.7), (4200, 32, 182.7, 182.1, 177.2), (4200, 64, 306.3, 299.1,
          288.0), (4200, 96, 438.0, 415.2, 396.4), (4200, 128, 578.3, 534.3, 509.8), (4200, 192, 836.4, 785.1, 761.1), (4200, 256, 1123.9,
-         1037.0, 998.7), (16200, 16, 1028.8, 931.2, 877.9)]
+         1037.0, 998.7), (16200, 16, 1028.8, 931.2, 877.9),
+         # launches in a graph
+         (1, 16384, 58.4, 58.5, 62.8), (16, 16384, 63.6, 66.0, 86.6), (32, 16384, 70.7, 68.8, 93.6), (33, 16384, 83.7, 88.8, 139.4), (33, 8192, 40.5, 43.9, 69.1),
+         (33, 32768, 172.1, 183.3, 288.9), (40, 16384, 102.7, 102.1, 149.9), (48, 16384, 118.9, 109.9, 152.3), (64, 16384, 155.4, 134.7, 152.4), (65, 16384, 172.3,
+         143.1, 183.0), (100, 16384, 233.4, 204.1, 232.4)]
 
 
 @pytest.fixture(scope="module")
@@ -54,13 +58,13 @@ def plan(tmp_path_factory):
     d = tmp_path_factory.mktemp("attention")
     src, so = d / "plan.cpp", d / "plan.so"
     src.write_text('#include "attention_plan.h"\nextern "C" int ask(int units, int cus, int tokens) { return reslim::attn_split_keys(units, cus, tokens); }\n'
-                   'extern "C" int pair_waves(long long a, long long b, int cus) { return reslim::attn_pair_waves(a, b, cus); }\n'
+                   'extern "C" int pair_waves(long long a, long long b, int cus, int tokens) { return reslim::attn_pair_waves(a, b, cus, tokens); }\n'
                    'extern "C" long long most(int threads) { return reslim::most_work_groups(threads); }\n')
     cxx = shutil.which("g++") or shutil.which("clang++") or "/opt/rocm/llvm/bin/clang++"
     subprocess.run([cxx, "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, str(src), "-o", str(so)], check=True)
     lib = ctypes.CDLL(str(so))
     lib.most.restype = ctypes.c_longlong
-    lib.pair_waves.argtypes = [ctypes.c_longlong, ctypes.c_longlong, ctypes.c_int]
+    lib.pair_waves.argtypes = [ctypes.c_longlong, ctypes.c_longlong, ctypes.c_int, ctypes.c_int]
     return lib
 
 
@@ -84,10 +88,10 @@ def test_only_where_it_was_measured(splits):
 def test_two_query_groups_where_they_gain(plan):
     for tokens, sets, one, two_by_two, two_by_four in PAIRS:
         blocks = [sets * -(-tokens // n) for n in (128, 256)]
-        got = {0: one, 2: two_by_two, 4: two_by_four}[plan.pair_waves(*blocks, 256)]
+        got = {0: one, 2: two_by_two, 4: two_by_four}[plan.pair_waves(*blocks, 256, tokens)]
         # two groups only where they gain (two runs differ by up to 2 %); with one group, and with the other size of work-group, up to a tenth is left
         assert got <= 1.01 * one and got <= 1.1 * min(one, two_by_two, two_by_four), (tokens, sets, got)
-    assert plan.pair_waves(0, 0, 256) == 0 and plan.pair_waves(2 ** 31 - 1, 2 ** 30, 256) == 4 and plan.pair_waves(2 ** 31, 2 ** 31, 256) == 2
+    assert plan.pair_waves(0, 0, 256, 0) == 0 and plan.pair_waves(2 ** 31 - 1, 2 ** 30, 256, 300) == 4 and plan.pair_waves(2 ** 31, 2 ** 31, 256, 100) == 2
 
 
 def test_a_launch_has_fewer_threads_than_2_to_the_32(plan):
@@ -103,4 +107,5 @@ def test_the_gpu_tests_run_the_kernels_they_name(plan):
         for c in cfgs:
             tiles = O.tiles_partition(c.Hp, c.Wp, c.tiles_y, c.tiles_x, c.halo)[0]
             blocks = [c.batch * c.heads * sum(-(-int(t["n_tok"]) // n) for t in tiles) for n in (128, 256)]
-            assert plan.pair_waves(*blocks, 256) == waves, c.name
+            longest = max(int(t["n_tok"]) for t in tiles)
+            assert plan.pair_waves(*blocks, 256, longest) == (waves if longest > 40 else 0), c.name

@@ -23,8 +23,13 @@ def test_tiles_of_one_token(batch):
         d_out = torch.empty((batch, m.n_h, D), dtype=m.act_dtype, device="cuda").normal_(generator=g)
         out = torch.empty_like(d_out)
         lse = torch.empty((batch, CFG.heads, m.n_h), dtype=torch.float32, device="cuda")
-        B.tiles_attention_fwd_lse(m.ctx, qkv, out, lse, batch)
-        assert torch.equal(out, qkv[..., 2 * D:])
+        for variant in (0, 3, 4):                    # by the rule; two query groups a wave, in work-groups of two waves and of four
+            B.reslim_debug_set_attention_variant(variant)
+            try:
+                B.tiles_attention_fwd_lse(m.ctx, qkv, out.zero_(), lse, batch)
+            finally:
+                B.reslim_debug_set_attention_variant(0)
+            assert torch.equal(out, qkv[..., 2 * D:]), variant
         d_qkv = torch.empty_like(qkv)
         ws = torch.empty(B.tiles_attention_bwd_workspace_bytes(m.ctx, batch), dtype=torch.uint8, device="cuda")
         B.tiles_attention_bwd(m.ctx, qkv, out, lse, d_out, d_qkv, batch, ws)

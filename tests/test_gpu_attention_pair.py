@@ -27,7 +27,7 @@ FOUR = [tiled(3, 43 * 25, 1, 25),                           # 129: no query for 
         tiled(15, 15 * 25 + 9, 1, 25),                      # 225 and 240: one query in the last group
         tiled(16, 16 * 13, 1, 13, batch=2),                 # 256
         tiled(60, 84, 2, 3, batch=3, halo=2)]               # 32 by 30 to 32
-# 8192 blocks and more, a twentieth fewer waves than with four at least: two (tests/test_attention_plan_cpu.py holds both lists against the rule)
+# 8192 blocks and more, a twentieth fewer waves than with four at least: two, where a tile has more than 40 tokens (tests/test_attention_plan_cpu.py holds both lists against the rule)
 TWO = [tiled(n, 128, 1, 128, embed_dim=4096, heads=64) for n in (1, 33, 65)] + [tiled(257, 43, 1, 43, embed_dim=4096, heads=64)]
 
 
