@@ -1,6 +1,6 @@
 """Tile attention with a query that is not finite (csrc/attention.hip): its own row is not a number, every other row keeps its bits, in every
 bf16 kernel.  A query that shares a column of the row sums' matrix instruction with it (16 further on) is the one that would show.  And a query whose
-first 32 logits overflow to -inf: it gets the softmax over the other keys."""
+first 32 or 64 logits overflow to -inf: it gets the softmax over the other keys."""
 import numpy as np
 import pytest
 import torch
@@ -59,13 +59,14 @@ def test_a_query_that_is_not_finite_keeps_to_itself(cfg, variant, kind):
         assert np.array_equal(out[~own], clean[0][~own]) and np.array_equal(lse[~own_lse], clean[1][~own_lse]), query
 
 
+@pytest.mark.parametrize("dead", [32, 64])
 @pytest.mark.parametrize("cfg,variant", [k for k in KERNELS if k[0].name != "keys_split"], ids=lambda v: getattr(v, "name", None))
-def test_first_keys_that_overflow_downwards_have_no_weight(cfg, variant):
+def test_first_keys_that_overflow_downwards_have_no_weight(cfg, variant, dead):
     """The kernel that splits the keys gives each wave a reference of its own and needs a finite logit among a wave's first 32 keys."""
-    print(f"attention, first keys at -inf: {cfg.name}", flush=True)
+    print(f"attention, first {dead} keys at -inf: {cfg.name}", flush=True)
     qkv, D, dh, n = inputs(cfg), cfg.embed_dim, cfg.embed_dim // cfg.heads, cfg.Hp * (cfg.Wp // cfg.tiles_x)
     qkv[..., dh] = qkv[..., D + dh] = 0.0                      # feature 0 of head 1 decides alone
-    qkv[0, :32, D + dh] = -3e38
+    qkv[0, :dead, D + dh] = -3e38
     calm = qkv.copy()
     qkv[0, QUERIES[0], dh] = 3e38
     clean, (out, lse) = run(cfg, variant, calm, qkv)
@@ -73,9 +74,9 @@ def test_first_keys_that_overflow_downwards_have_no_weight(cfg, variant):
     own[0, QUERIES[0], dh:2 * dh] = own_lse[0, 1, QUERIES[0]] = True
     assert np.array_equal(out[~own], clean[0][~own]) and np.array_equal(lse[~own_lse], clean[1][~own_lse])
     q, k, v = (qkv[0, :n, i * D + dh:i * D + 2 * dh].astype(np.float64) for i in range(3))
-    logits = k[32:] @ q[QUERIES[0]] / np.sqrt(dh)
+    logits = k[dead:] @ q[QUERIES[0]] / np.sqrt(dh)
     p = np.exp(logits - logits.max())
-    want = p @ v[32:] / p.sum()
+    want = p @ v[dead:] / p.sum()
     # probabilities and the output are rounded to bf16: 2^-9 of each at most, of a row whose probabilities are positive
     assert np.abs(out[own] - want).max() <= 2.0 ** -8 * np.abs(v).max()
     assert abs(lse[own_lse][0] - (np.log(p.sum()) + logits.max())) <= 2.0 ** -8
